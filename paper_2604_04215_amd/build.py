@@ -19,6 +19,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE,
          # are only registers while every index into them is a compile-time constant
          "-mllvm", "-pragma-unroll-threshold=200000",
          "-Wno-unused-command-line-argument"]
+# The backward kernels run one wavefront per SIMD with more than 256 registers.  There the compiler would put every matrix
+# result into accumulation registers (and copy the scores back before each exponential) and split the accumulators at the
+# loop head into single registers (and gather them again before each product).
+SOURCE_FLAGS = {"attn_bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm", "-amdgpu-codegenprepare-break-large-phis=false"]}
 
 
 def build_lib(verbose: bool = False, save_temps: str | None = None) -> str:
@@ -29,7 +33,7 @@ def build_lib(verbose: bool = False, save_temps: str | None = None) -> str:
     procs = []
     for src in SOURCES + PEAKS_SOURCES:
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
-        cmd = [hipcc, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *FLAGS, *SOURCE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
         if save_temps:
             cmd.append("-save-temps=obj")
         procs.append((src, obj, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))

@@ -5,7 +5,7 @@
 //   dV = P^T dO,  dP = dO V^T,  dS = P * (dP - delta),  dQ = scale dS K,  dK = scale dS^T Q.
 // P is recomputed from Q, K and the forward pass's log-sum-exp; nothing of size Lq x Lk is stored.
 //
-// Three kernels, no atomics, every output element written exactly once (deterministic):
+// No atomics, every output element written exactly once (deterministic):
 //   * attn_bwd_delta_kernel : delta per (sequence, head, query row).
 //   * attn_bwd_dq_kernel    : a workgroup owns 128 rows (query, head in group) of one (sequence, KV head) and
 //                             walks the key tiles of all segments, like the forward kernel.  Per 32-key tile and
@@ -13,13 +13,12 @@
 //                             keys of ONE query row and LSE / delta are per-lane scalars), dS^T in registers is
 //                             already the B operand of dQ^T += K^T dS^T; K^T fragments come from LDS through the
 //                             transposing 64-bit LDS read.
-//   * attn_bwd_dkv_kernel   : the mirror image, run once for dV and once for dK.  A workgroup owns 128 keys of
-//                             ONE segment of one (sequence, KV head), each wavefront 32 of them, and walks the
-//                             32-row tiles of (query, head in group) rows that can see them: S = Q K^T and
-//                             dP = dO V^T (rows are the MFMA rows, a lane holds 16 rows of ONE key), P and dS in
-//                             registers are the B operands of dV^T += dO^T P and dK^T += Q^T dS; the sum over the
-//                             heads of a group happens in the accumulators because the rows of all its heads pass
-//                             through the same workgroup.
+//   * attn_bwd_dkv_kernel   : the mirror image.  A workgroup owns 64 or 128 keys of ONE segment of one (sequence, KV
+//                             head) and walks the 32-row tiles of (query, head in group) rows that can see them:
+//                             S = Q K^T and dP = dO V^T (rows are the MFMA rows, a lane holds 16 rows of ONE key), P
+//                             and dS in registers are the B operands of dV^T += dO^T P and dK^T += Q^T dS; the sum
+//                             over the heads of a group happens in the accumulators because the rows of all its
+//                             heads pass through the same workgroup.
 #include "common.hpp"
 
 namespace dlm {
@@ -63,7 +62,7 @@ __device__ __forceinline__ int64_t stat_index(const BwdParams& p, int b, int h, 
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// delta[b, h, i] = sum_c dO * O.  D / 8 lanes per row, 16-byte loads.
+// -delta[b, h, i] = -sum_c dO * O, as the other kernels add it.  D / 8 lanes per row, 16-byte loads.
 template <int D>
 __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdParams p) {
     constexpr int LPR = D / 8;             // lanes per row
@@ -92,7 +91,7 @@ __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdParams p) {
     }
 #pragma unroll
     for (int off = LPR / 2; off >= 1; off >>= 1) acc += shfl_xor(acc, off);
-    if (i < sl && c == 0) p.delta[stat_index(p, b, h, i, s0)] = acc;
+    if (i < sl && c == 0) p.delta[stat_index(p, b, h, i, s0)] = -acc;
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -192,7 +191,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(BwdParams p, GridRe
         const int64_t si = stat_index(p, b, h, qi, s0);
         const float l = p.lse[si];
         if (l > -INFINITY) lse2 = l * 1.4426950408889634f;
-        delta = p.delta[si];
+        delta = -p.delta[si];
     }
     const int qlim = BC ? ((p.q_pos0 + qi) / p.bs + 1) * p.bs : 0;
     int qlim_min = 0x7fffffff, qlim_max = 0;
@@ -351,27 +350,97 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(BwdParams p, GridRe
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// DK = false: dV of the workgroup's keys (S -> P, dV^T += dO^T P).  DK = true: dK (S, dP -> dS, dK^T += Q^T dS).
-// Two passes instead of one: a pass that holds both accumulators (2 x 64 registers at d = 128) next to the K and
-// V fragments leaves one wavefront per SIMD or spills, and either way every tile waits out the full memory
-// latency; apart, the passes keep two to three workgroups per CU with nothing spilled.  Price: S is formed twice.
-template <int D, bool BC, bool DK>
-__global__ __launch_bounds__(256, DK ? 2 : 3) void attn_bwd_dkv_kernel(BwdParams p, int sidx, int n_slabs, int pair, GridRemap rm) {
-    constexpr int KP = D * 2 + 16;
-    constexpr int TP = D * 2 + 64;
-    constexpr int C8 = D / 8;
-    constexpr int NLD = (32 * C8) / 256;
-    // images: Q rows (both passes); DK: Q transposing + dO rows; DV: dO transposing
-    constexpr int IMG_BYTES = DK ? (2 * 32 * KP + 32 * TP) : (32 * KP + 32 * TP);
-    __shared__ __attribute__((aligned(16))) unsigned char smem[IMG_BYTES + 3 * 32 * 4];
-    unsigned char* Qrow = smem;
-    unsigned char* Xtr = smem + 32 * KP;              // Q^T source (DK) or dO^T source (DV)
-    unsigned char* Grow = smem + 32 * KP + 32 * TP;   // dO rows (DK only)
-    float* s_lse2 = reinterpret_cast<float*>(smem + IMG_BYTES);
-    float* s_delta = s_lse2 + 32;
-    int* s_qlim = reinterpret_cast<int*>(s_delta + 32);
+// A 32-row tile image as the transposing and the row reads both want it: requests of 1024 bytes (4 rows at d = 128, 8 at
+// d = 64) sit 1040 bytes apart, and inside a request piece c (16 bytes) of row r is stored in place c ^ bw_swz(r).  Row
+// reads (16 rows, one piece each) and transposing reads (4 rows x 64 bytes) then touch every bank once, and
+// global_load_lds, whose lanes fill 16-byte places in order, can write it.  The exclusive-or moves only 64-byte (d = 128)
+// or 32-byte (d = 64) steps, so 4 lane addresses serve all row reads of a tile and 4 or 2 all transposing ones.
+constexpr int BW_GP = 1040;
+template <int D>
+__device__ __forceinline__ int bw_swz(int row) {
+    return D == 128 ? (row & 3) << 2 : (((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1);
+}
 
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+// i * stride, without the 64-bit product: a stride outside 32 bits leaves room for fewer than 2^23 rows in any memory, so
+// its upper part takes a 24-bit product
+__device__ __forceinline__ int64_t bw_offset(int i, int64_t stride) {
+    const int32_t lo = (int32_t)stride;
+    const int hi = (int)((stride - lo) >> 32);
+    return (int64_t)i * lo + ((int64_t)__mul24(i, hi) << 32);
+}
+
+// Memory to LDS, 16 or 4 bytes a lane, to consecutive places from a wave-uniform address on.  Asm, so that the compiler, which
+// cannot tell the ring's stages apart, does not wait for every request in flight before each transposing read; the
+// waits that are needed stand in the loop.  No registers are written.
+__device__ __forceinline__ void bw_load_lds16(const void* src, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory");
+}
+// the same 16 bytes a lane at offset + delta of two operands (base0, base1: wave-uniform), to dst and dst + gap
+__device__ __forceinline__ void bw_load_lds16_pair(const void* base0, const void* base1, uint32_t offset, uint32_t delta, uint32_t dst, uint32_t gap) {
+    uint32_t o;
+    asm volatile("s_mov_b32 m0, %3\n\tv_add_u32 %0, %2, %1\n\tglobal_load_lds_dwordx4 %0, %4\n\ts_add_u32 m0, %3, %6\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %5"
+                 : "=&v"(o) : "v"(offset), "s"(__builtin_amdgcn_readfirstlane(delta)), "s"(__builtin_amdgcn_readfirstlane(dst)), "s"(base0), "s"(base1), "s"(gap) : "memory", "scc");
+}
+__device__ __forceinline__ void bw_load_lds16(const void* base, uint32_t offset, uint32_t dst) {   // base: wave-uniform
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory");
+}
+__device__ __forceinline__ void bw_load_lds4(const void* src, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory");
+}
+
+// c += a * b with c in accumulation registers.  Written as asm because the compiler gives all matrix results of a
+// function one register class: in accumulation registers the scores would be copied back before every exponential.
+// fresh (a constant): b may just have been written by a vector instruction, which the product has to stay two wait states behind.
+__device__ __forceinline__ void bw_mfma_acc(f32x16& c, bf16x8 a, bf16x8 b, bool fresh) {
+    if (fresh) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+
+// c = a * b (the first product of a chain: no register is zeroed for it).  The next reader of c is another product with one
+// in between, or far behind.
+__device__ __forceinline__ void bw_mfma_zero(f32x16& c, bf16x8 a, bf16x8 b) {
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+}
+
+// dK and dV of one segment in one pass.  A wavefront owns 64 keys (two MFMA column tiles, K and V fragments and both
+// accumulators in registers) and walks 32-row tiles of (query, head in group) rows; NWK wavefronts side by side share
+// the tiles through LDS, NWR groups of them take every NWR-th tile and are summed through LDS at the end.
+//
+// What bounds it: every MFMA's A operand (Q, dO rows, dO^T, Q^T) comes from LDS, 32 KB per wavefront and tile.  With 32
+// keys a wavefront that is one 1 KB fragment per MFMA, all that the LDS delivers at full MFMA rate; 64 keys use each
+// fragment twice.  That takes the whole register file (one wavefront per SIMD), so nothing may wait in turn:
+//   * S is formed once for dV and dK (two passes, one for each, formed it twice: 5 products instead of 4);
+//   * the exponentials sit between the MFMAs of dP and of the first half of dV, dS between those of the second half of
+//     dV and the first of dK (vector and matrix instructions of one wavefront overlap, of different ones do not);
+//   * tiles go from memory to LDS without registers (global_load_lds) through a ring of four, two tiles ahead, and the
+//     next tile's first fragments are read before this tile's last MFMAs: the barrier sits between;
+//   * one wavefront issues one instruction at a time: 4.0 vector and 1.9 scalar instructions per MFMA, after 7.5 and 1.7 with
+//     LDS addresses, row divisions and statistics formed per read (2.6 -> 1.9 ms below).
+// Measured (8 x 4096 tokens, 32 / 8 heads of 128, blocks of 4): 1.86 - 1.95 ms = 1.17 PFLOP/s of products, two passes with 32
+// keys a wavefront 4.28 ms; 128 packed sequences of 64 k tokens, 32 heads: 1.73 ms, before 2.86.  MFMA pipes busy 0.52 at
+// 2.2 GHz: with all loads, waits and vector work taken out the loop still runs at 1.35 PFLOP/s, the power limit on such data.
+template <int D, bool BC, int NWK, int NWR>
+__global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdParams p, int sidx, int n_slabs, int pair, GridRemap rm) {
+    constexpr int NS = 4, FD = D == 128 ? 2 : 4;       // ring stages; fragments read ahead (at d = 128 all that registers allow)
+    constexpr int AHEAD = NWK == 1 ? 3 : 2;            // tiles requested ahead: a ring that is the wavefront's own needs no slack
+    constexpr int P = D * 2, C8 = D / 8;
+    constexpr int RPI = 64 / C8, IPW = 32 / RPI / NWK; // rows per request, requests per wavefront, operand and tile
+    constexpr int IMG = 32 / RPI * BW_GP;              // one operand's tile image
+    constexpr int STAGE = 2 * IMG;                     // Q, dO
+    constexpr int LOADS = 2 * IPW + 1;                 // ... with the statistics
+    constexpr int KS = 64 * NWK;                       // keys per workgroup
+    constexpr int OPB = D * 2 + 16;                    // output staging row pitch (bytes)
+    constexpr int RING = NWR * NS * STAGE;
+    constexpr int MERGE = NWR > 1 ? NWK * 64 * D * 4 : 0;
+    constexpr int STORE = NWK * 32 * OPB;
+    constexpr int BODY = RING > MERGE ? (RING > STORE ? RING : STORE) : (MERGE > STORE ? MERGE : STORE);
+    static_assert(BODY + NWK * NWR * NS * 256 <= 160 * 1024, "LDS");
+    static_assert(IPW >= 1, "at least one request per wavefront");
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[BODY + NWK * NWR * NS * 256];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = w % NWK, wr = w / NWK;
     const int n = lane & 31, hi = lane >> 5;
     int b = blockIdx.z, kvh = blockIdx.y, bx = blockIdx.x;
     if (rm.nx > 0) {
@@ -404,6 +473,42 @@ __global__ __launch_bounds__(256, DK ? 2 : 3) void attn_bwd_dkv_kernel(BwdParams
         do_off = s0 * p.do_st;
         kv_off = s0 * sst;
     }
+    const int hoff = (BC && srule == DLM_SEG_EARLIER_BLOCKS) ? p.bs : 0;
+    const bool same = BC && srule == DLM_SEG_SAME_BLOCK;
+    const int g = p.g;
+    // Row r of the group is query r / g, head r % g.  Inside a tile that starts at (query i0, head h0) row l is (h0 + l) / g queries
+    // on; (h0 + l + 1/2) / g is at least 1 / 2g from a whole number, so the product with the reciprocal truncates to the
+    // quotient (at most 32, errors below 2^-17 where g < 2^15 and below 2^-22, quotient 0 or 1, above).
+    const float inv_g = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(1.0f / (float)g)));
+    const uint16_t* const qb = p.q + q_off + (int64_t)(kvh * g) * p.q_sh;
+    const uint16_t* const gb = p.dout + do_off + (int64_t)(kvh * g) * p.do_sh;
+    // statistics: lanes 0..31 fetch LSE, lanes 32..63 delta of the tile's rows
+    const float* const stp = (hi ? p.delta : p.lse) + stat_index(p, b, kvh * g, 0, s0);
+    const int st_h = p.cu ? p.total : p.Lq;            // statistics of the next head
+    const int stat_base = BODY + w * NS * 256;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+
+    // lane parts of the LDS addresses: row reads (row n, piece 2 c + hi) and transposing reads (row 16 j + 8 q + 4 hi + s16 / 4,
+    // piece 4 dt + 2 blk + ...); the step-dependent part is an exclusive-or above bit 5 or 6
+    constexpr int RSH = D == 128 ? 6 : 5, RDIV = D == 128 ? 2 : 1;
+    const int row_base = n / RPI * BW_GP + n % RPI * P + hi * 16;
+    const int row_x = bw_swz<D>(n) >> 1 << 5 & (D == 128 ? 0xc0 : 0x60);
+    const int s16 = lane & 15, blk = (lane >> 4) & 1;
+    const int tr_base = (D == 128 ? hi * BW_GP + (s16 >> 2) * P : (4 * hi + (s16 >> 2)) * P) +
+                        (((2 * blk + ((s16 & 3) >> 1)) ^ (D == 128 ? 0 : 2 * hi)) << 4) + 8 * (s16 & 1);
+    const int tr_x = (D == 128 ? s16 >> 2 : s16 >> 3) << 6;
+    // requests with 32-bit offsets from a wave-uniform query: strides of less than 2^24 bytes, all of a group's heads within 2^30
+    const bool small = p.q_st >= 0 && p.q_sh >= 0 && p.do_st >= 0 && p.do_sh >= 0 && p.q_st < (1 << 23) && p.q_sh < (1 << 23) &&
+                       p.do_st < (1 << 23) && p.do_sh < (1 << 23) && g * p.q_sh < (1 << 29) && g * p.do_sh < (1 << 29);
+    // The usual case: 1, 2, 4 .. 32 heads a group and Q and dO laid out alike.  A tile then holds whole queries, so row l of any
+    // tile is at the same place relative to its first row: one lane offset, and a wave-uniform step from request to request.
+    // (Per row this is 1 vector instruction for both operands instead of some 20.)
+    const bool regular = small && (32 % g) == 0 && p.q_st == p.do_st && p.q_sh == p.do_sh;
+    const int gsh = 31 - __builtin_clz(g);
+    const int qst2 = (int)p.q_st * 2, qsh2 = (int)p.q_sh * 2;
+    const uint32_t voff = regular ? __umul24((lane / C8) >> gsh, qst2) + __umul24((lane / C8) & (g - 1), qsh2) + ((lane % C8) ^ bw_swz<D>(lane / C8)) * 16 : 0;
+    const float* const sptr = stp + (int64_t)(n & (g - 1)) * st_h + (n >> gsh);
+
     // Under a block-causal mask the work of a key slab shrinks with its index (later keys are seen by fewer rows).
     // pair != 0: a workgroup takes slab x and then slab n_slabs - 1 - x, so every workgroup does the same amount
     // of work and the workgroups of one (sequence, KV head) stay in step on the same Q / dO tiles (L2 reuse).
@@ -418,136 +523,42 @@ __global__ __launch_bounds__(256, DK ? 2 : 3) void attn_bwd_dkv_kernel(BwdParams
         const int oct = bx >> 3;
         if ((oct & 1) && (oct * 8 + 7 < n_slabs)) slab = oct * 8 + 7 - (bx & 7);
     }
-    const int j0 = slab * 128;                        // first key of this pass inside the segment
+    const int j0 = slab * KS;                         // first key of this pass inside the segment
     if (j0 >= slen) continue;
+    const int jw = j0 + wk * 64;                      // first key of this wavefront (past the end: nothing to multiply)
 
-    // ---- this lane's key: K (and V) fragments (B operands) ----------------------------------------------------
-    const int j = j0 + w * 32 + n;
-    const bool kvalid = j < slen;
-    bf16x8 kf[D / 16], vf[DK ? D / 16 : 1];
-    {
-        const uint16_t* kp = sk + kv_off + kvh * ssh + (int64_t)min(j, slen - 1) * sst;
-        const uint16_t* vp = sv + kv_off + kvh * ssh + (int64_t)min(j, slen - 1) * sst;
+    // ---- this lane's two keys: K and V fragments (B operands).  A key past the end repeats the last one; its column
+    // of the accumulators is never stored. --------------------------------------------------------------------------
+    bf16x8 kf[2][D / 16], vf[2][D / 16];
+    int r_clear_lo = 0, r_clear_hi = R;               // rows that see every key of the wavefront
+    int r_first = 0;                                  // no row before it sees any
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int j = jw + 32 * s + n;
+        const int64_t ko = kv_off + kvh * ssh + (int64_t)min(j, slen - 1) * sst;
 #pragma unroll
         for (int c = 0; c < D / 16; ++c) {
-            u32x4 a = {0, 0, 0, 0}, d = {0, 0, 0, 0};
-            if (kvalid) {
-                a = *reinterpret_cast<const u32x4*>(kp + 16 * c + 8 * hi);
-                if (DK) d = *reinterpret_cast<const u32x4*>(vp + 16 * c + 8 * hi);
-            }
-            kf[c] = bw_as_bf16x8(a);
-            if (DK) vf[c] = bw_as_bf16x8(d);
+            kf[s][c] = bw_as_bf16x8(*reinterpret_cast<const u32x4*>(sk + ko + 16 * c + 8 * hi));
+            vf[s][c] = bw_as_bf16x8(*reinterpret_cast<const u32x4*>(sv + ko + 16 * c + 8 * hi));
         }
     }
-    const int kpos = spos + j;
-    const int hoff = (BC && srule == DLM_SEG_EARLIER_BLOCKS) ? p.bs : 0;
-    const bool same = BC && srule == DLM_SEG_SAME_BLOCK;
-
     // ---- rows that can see some key of this workgroup: tiles [rt_begin, rt_end) -----------------------------
     int rt_begin = 0, rt_end = (R + 31) >> 5;
     if (BC) {
-        const int kp_first = spos + j0, kp_last = spos + min(j0 + 127, slen - 1);
+        const int kp_first = spos + j0, kp_last = spos + min(j0 + KS - 1, slen - 1);
         const int i_begin = max(0, ((kp_first + hoff) / p.bs) * p.bs - p.q_pos0);
-        rt_begin = min(rt_end, (i_begin * p.g) >> 5);
+        rt_begin = min(rt_end, (int)(((int64_t)i_begin * g) >> 5));
         if (same) {
             const int i_end = max(0, min(Lq, (kp_last / p.bs + 1) * p.bs - p.q_pos0));
-            rt_end = min(rt_end, (i_end * p.g + 31) >> 5);
+            rt_end = max(rt_begin, min(rt_end, (i_end * g + 31) >> 5));
         }
+        const int kw_first = spos + jw, kw_last = spos + jw + 63;
+        r_clear_lo = min(max((kw_last + hoff) / p.bs * p.bs - p.q_pos0, 0), Lq) * g;
+        if (same) r_clear_hi = min(max((kw_first + p.bs) / p.bs * p.bs - p.q_pos0, 0), Lq) * g;
+        r_first = min(max((kw_first + hoff) / p.bs * p.bs - p.q_pos0, 0), Lq) * g;
     }
-
-    f32x16 acc[D / 32];   // dK^T or dV^T: lane = key, registers = 16 of the 32 head-dim entries of tile dt
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
-
-    // staging: thread -> NLD chunks of the 32-row tile; rows are (query, head) pairs gathered from Q / dO
-    u32x4 qreg[NLD], greg[NLD];
-    float st_lse2 = INFINITY, st_delta = 0.f;
-    int st_qlim = 0;
-    // Fast path for a full tile when the group size divides 32 (so a tile holds whole queries) and Q and dO share
-    // their strides: row r of tile rt is query rt * (32 / g) + r / g, head r % g, i.e. a wave-uniform tile base plus
-    // an offset that is fixed per thread: no division and no 64-bit per-thread arithmetic per tile.
-    const bool rows_fast = (32 % p.g == 0) && p.q_st == p.do_st && p.q_sh == p.do_sh && p.q_st >= 0 && p.q_sh >= 0 &&
-                           p.q_st < (1 << 25) && p.q_sh < (1 << 25);
-    const int qpt = 32 / max(p.g, 1);                 // queries per tile (fast path)
-    const int bs_shift = (BC && (p.bs & (p.bs - 1)) == 0) ? __builtin_ctz(p.bs) : -1;
-    uint32_t roff[NLD];
-#pragma unroll
-    for (int q = 0; q < NLD; ++q) {
-        const int cidx = tid + q * 256;
-        const int row = cidx / C8, c = cidx - row * C8;
-        roff[q] = (uint32_t)((row / p.g) * (int)p.q_st + (row % p.g) * (int)p.q_sh + c * 8);
-    }
-    const int st_r = tid & 31;
-    const int st_i = st_r / p.g, st_h = kvh * p.g + st_r % p.g;     // this thread's statistics row inside a tile
-    const int64_t st_base = stat_index(p, b, st_h, st_i, s0);       // ... of tile 0; tile rt is qpt entries further
-#define BW_FETCH_ROWS(rt)                                                                                \
-    {                                                                                                    \
-        if (rows_fast && (rt) * 32 + 32 <= R) {                                                          \
-            const int64_t tb_ = (int64_t)((rt) * qpt) * p.q_st + (int64_t)(kvh * p.g) * p.q_sh;          \
-            const uint16_t* qb_ = p.q + q_off + tb_;                                                     \
-            const uint16_t* gb_ = p.dout + do_off + tb_;                                                 \
-            _Pragma("unroll") for (int q = 0; q < NLD; ++q) {                                            \
-                qreg[q] = *reinterpret_cast<const u32x4*>(qb_ + roff[q]);                                \
-                greg[q] = *reinterpret_cast<const u32x4*>(gb_ + roff[q]);                                \
-            }                                                                                            \
-            const int64_t si = st_base + (rt) * qpt;                                                     \
-            const float l = p.lse[si];                                                                   \
-            const float dl_ = DK ? p.delta[si] : 0.f;                                                    \
-            st_lse2 = (l > -INFINITY) ? l * 1.4426950408889634f : INFINITY;                              \
-            st_delta = dl_;                                                                              \
-            const int qp_ = p.q_pos0 + (rt) * qpt + st_i;                                                \
-            st_qlim = BC ? (bs_shift >= 0 ? (((qp_ >> bs_shift) + 1) << bs_shift) : (qp_ / p.bs + 1) * p.bs) : 0; \
-        } else {                                                                                         \
-        _Pragma("unroll") for (int q = 0; q < NLD; ++q) {                                                \
-            const int cidx = tid + q * 256;                                                              \
-            const int row = cidx / C8, c = cidx - row * C8;                                              \
-            const int rr = min((rt) * 32 + row, R - 1);                                                  \
-            const int ii = rr / p.g, hh = kvh * p.g + (rr - ii * p.g);                                   \
-            qreg[q] = *reinterpret_cast<const u32x4*>(p.q + q_off + ii * p.q_st + (int64_t)hh * p.q_sh + c * 8);      \
-            greg[q] = *reinterpret_cast<const u32x4*>(p.dout + do_off + ii * p.do_st + (int64_t)hh * p.do_sh + c * 8); \
-        }                                                                                                \
-        /* per-row statistics: every thread loads (row = tid mod 32, clamped) so that no load sits under a   */ \
-        /* condition (the load counter stays exact and the prefetch really overlaps the tile's arithmetic)  */ \
-        {                                                                                                \
-            const int rr = (rt) * 32 + (tid & 31);                                                       \
-            const int rc_ = min(rr, R - 1);                                                              \
-            const int ii = rc_ / p.g, hh = kvh * p.g + (rc_ - ii * p.g);                                 \
-            const int64_t si = stat_index(p, b, hh, ii, s0);                                             \
-            const float l = p.lse[si];                                                                   \
-            const float dl_ = DK ? p.delta[si] : 0.f;                                                    \
-            const bool ok_ = rr < R;                                                                     \
-            st_lse2 = (ok_ && l > -INFINITY) ? l * 1.4426950408889634f : INFINITY;                       \
-            st_delta = ok_ ? dl_ : 0.f;                                                                  \
-            /* an absent row: its probabilities are 0 through lse2; INT_MAX forces the masked path */    \
-            st_qlim = ok_ ? (BC ? ((p.q_pos0 + ii) / p.bs + 1) * p.bs : 0) : 0x7fffffff;                 \
-        }                                                                                                \
-        }                                                                                                \
-    }
-#define BW_STORE_ROWS(rt)                                                                                \
-    {                                                                                                    \
-        const bool full_ = (rt) * 32 + 32 <= R;                                                          \
-        _Pragma("unroll") for (int q = 0; q < NLD; ++q) {                                                \
-            const int cidx = tid + q * 256;                                                              \
-            const int row = cidx / C8, c = cidx - row * C8;                                              \
-            const bool live = full_ || ((rt) * 32 + row < R);                                            \
-            const u32x4 z = {0, 0, 0, 0};                                                                \
-            const u32x4 qq = live ? qreg[q] : z, gg = live ? greg[q] : z;                                \
-            *reinterpret_cast<u32x4*>(Qrow + row * KP + c * 16) = qq;                                    \
-            if (DK) {                                                                                    \
-                *reinterpret_cast<u32x4*>(Xtr + row * TP + c * 16) = qq;                                 \
-                *reinterpret_cast<u32x4*>(Grow + row * KP + c * 16) = gg;                                \
-            } else {                                                                                     \
-                *reinterpret_cast<u32x4*>(Xtr + row * TP + c * 16) = gg;                                 \
-            }                                                                                            \
-        }                                                                                                \
-        if (tid < 32) {                                                                                  \
-            s_lse2[tid] = st_lse2;                                                                       \
-            if (DK) s_delta[tid] = st_delta;                                                             \
-            s_qlim[tid] = st_qlim;                                                                       \
-        }                                                                                                \
-    }
+    const int n_rt = rt_end - rt_begin;
+    const int n_it = (n_rt + NWR - 1) / NWR;
 
     // Row tiles are walked from the last one down: under a block-causal mask the workgroups of one (sequence,
     // KV head) differ in where their range BEGINS, so this way they all start on the same tile and stay in step.
@@ -555,114 +566,339 @@ __global__ __launch_bounds__(256, DK ? 2 : 3) void attn_bwd_dkv_kernel(BwdParams
     // after n - x steps, slab n - 1 - x begins at tile n - 1 - x), so at any time all the workgroups of the group
     // that are in their second pass are on one tile again, whatever their x.
     const bool up = pair && pass;
-    if (rt_begin < rt_end) BW_FETCH_ROWS(up ? rt_begin : rt_end - 1);
-    for (int it = 0; it < rt_end - rt_begin; ++it) {
-        const int rt = up ? rt_begin + it : rt_end - 1 - it;
-        BW_STORE_ROWS(rt);
-        __syncthreads();
-        BW_FETCH_ROWS(up ? min(rt + 1, rt_end - 1) : max(rt - 1, rt_begin));     // unconditional (clamped) prefetch of the next tile
-        f32x16 S, dP;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            S[i] = 0.f;
-            dP[i] = 0.f;
-        }
-#pragma unroll
-        for (int c = 0; c < D / 16; ++c) {
-            const bf16x8 qa = *reinterpret_cast<const bf16x8*>(Qrow + n * KP + (16 * c + 8 * hi) * 2);
-            S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kf[c], S, 0, 0, 0);      // S[row, key]: lane = key
-            if (DK) {
-                const bf16x8 ga = *reinterpret_cast<const bf16x8*>(Grow + n * KP + (16 * c + 8 * hi) * 2);
-                dP = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, vf[c], dP, 0, 0, 0);
-            }
-        }
-        // Masking is needed only where some (row, key) pair of this tile is hidden: rows' block ends are monotone,
-        // so the first and the last row bound them (an absent last row carries INT_MAX: masked path for "own block").
-        bool masked = !(j0 + w * 32 + 31 < slen);
-        if (BC) {
-            const int ql_first = s_qlim[0], ql_last = s_qlim[31];
-            const int kp0 = spos + j0 + w * 32;
-            masked = masked || !(kp0 + 31 + hoff < ql_first) || (same && !(ql_last <= kp0 + p.bs));
-        }
-        uint32_t pk[8];   // P (DV pass) or dS (DK pass) as bf16 pairs: the B operand of the second product
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-            // registers 4 g4 .. 4 g4 + 3 hold rows 8 g4 + 4 hi + 0..3 of the tile
-            const f32x4 l2 = *reinterpret_cast<const f32x4*>(s_lse2 + 8 * g4 + 4 * hi);
-            float pe[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) pe[e] = fast_exp2(fmaf(S[4 * g4 + e], p.scale_log2, -l2[e]));
-            if (masked) {
-                i32x4 ql = {0, 0, 0, 0};
-                if (BC) ql = *reinterpret_cast<const i32x4*>(s_qlim + 8 * g4 + 4 * hi);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    bool vis = kvalid;
-                    if (BC) vis = vis && (ql[e] > kpos + hoff) && (!same || ql[e] <= kpos + p.bs);
-                    pe[e] = vis ? pe[e] : 0.f;
-                }
-            }
-            if (DK) {
-                const f32x4 dl = *reinterpret_cast<const f32x4*>(s_delta + 8 * g4 + 4 * hi);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) pe[e] = pe[e] * (dP[4 * g4 + e] - dl[e]);
-            }
-            pk[2 * g4] = pack_bf16x2(pe[0], pe[1]);
-            pk[2 * g4 + 1] = pack_bf16x2(pe[2], pe[3]);
-        }
-        bf16x8 bf[2];
-        {
-            u32x4 a = {pk[0], pk[1], pk[2], pk[3]}, c4 = {pk[4], pk[5], pk[6], pk[7]};
-            bf[0] = bw_as_bf16x8(a);
-            bf[1] = bw_as_bf16x8(c4);
-        }
-        const int s16 = lane & 15, blk = (lane >> 4) & 1;
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt) {
-#pragma unroll
-            for (int j2 = 0; j2 < 2; ++j2) {
-                union { s16x4 h[2]; bf16x8 v; } xt;
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const int rrow = 16 * j2 + 8 * q + 4 * hi + (s16 >> 2);
-                    const int dcol = 32 * dt + 16 * blk + 4 * (s16 & 3);
-                    xt.h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(Xtr + rrow * TP + dcol * 2));
-                }
-                // DV: dV^T += dO^T P;  DK: dK^T += Q^T dS
-                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xt.v, bf[j2], acc[dt], 0, 0, 0);
-            }
-        }
-        __syncthreads();
-    }
-#undef BW_FETCH_ROWS
-#undef BW_STORE_ROWS
+    int rt = up ? rt_begin + wr : rt_end - 1 - wr;    // this wavefront's tile
+    const int rt_step = up ? NWR : -NWR;
 
-    if (kvalid) {
-        uint16_t* op = (DK ? sdk : sdv) + kv_off + kvh * ssh + (int64_t)j * sst;
-        const float f = DK ? p.scale : 1.0f;
+    // next tile to request: first row = query i0, head h0 (kept without divisions); queries are clamped to the sequence,
+    // so a request past either end of the walk reads rows that exist and that nobody multiplies
+    int i0, h0;
+    {
+        const int r = rt * 32;
+        i0 = __builtin_amdgcn_readfirstlane(r >= 0 ? r / g : -((-r + g - 1) / g));
+        h0 = __builtin_amdgcn_readfirstlane(r - i0 * g);
+    }
+    const int di = 32 * NWR / g, dh = 32 * NWR - di * g;
+    int ist = 0;                                      // ring stage it goes to
+    // regular tiles: its first row of Q and of dO, and the step to the next tile's; whole: all 32 rows exist
+    const int qpt = regular ? 32 >> gsh : 0;
+    const uint16_t *qt = qb + (regular ? i0 * p.q_st : 0), *gt = gb + (regular ? i0 * p.q_st : 0);
+    const int64_t dqt = regular ? (up ? di : -di) * p.q_st : 0;
+    bool whole = regular && i0 >= 0 && i0 + qpt <= Lq;
+#define BW_ROW(l, i_, h_)                                                                                \
+    const int t_ = h0 + (l);                                                                             \
+    const int dv_ = (int)(((float)t_ + 0.5f) * inv_g);                                                   \
+    const int h_ = t_ - dv_ * g;                                                                         \
+    const int i_ = min(max(i0 + dv_, 0), Lq - 1);
+    // request x of a tile: x < IPW a group of Q rows and the same dO rows, x == IPW the statistics.  The lane number is made
+    // opaque, so that the offsets are formed anew for each tile instead of being kept in registers the loop does not have.
+#define BW_REQUEST(x)                                                                                    \
+    {                                                                                                    \
+        if ((x) < IPW) {                                                                                 \
+            const int q_ = wk * IPW + (x);                                                               \
+            const uint32_t dst_ = lds0 + (wr * NS + ist) * STAGE + q_ * BW_GP;                           \
+            if (whole) {                                                                                 \
+                bw_load_lds16_pair(qt, gt, voff, ((q_ * RPI) >> gsh) * qst2 + ((q_ * RPI) & (g - 1)) * qsh2, dst_, IMG); \
+            } else {                                                                                     \
+            unsigned lo_ = lane;                                                                         \
+            asm volatile("" : "+v"(lo_));                                                                \
+            const int c16 = ((int)(lo_ % C8) ^ bw_swz<D>(lo_ / C8)) * 16;                                \
+            BW_ROW(q_ * RPI + (int)(lo_ / C8), i_, h_)                                                   \
+            if (small) {                                                                                 \
+                const int ic_ = min(max(i0, 0), Lq - 1);                                                 \
+                const uint32_t oq_ = __umul24(i_ - ic_, (int)p.q_st * 2) + __umul24(h_, (int)p.q_sh * 2) + c16;   \
+                const uint32_t og_ = __umul24(i_ - ic_, (int)p.do_st * 2) + __umul24(h_, (int)p.do_sh * 2) + c16; \
+                bw_load_lds16(qb + ic_ * p.q_st, oq_, dst_);                                             \
+                bw_load_lds16(gb + ic_ * p.do_st, og_, dst_ + IMG);                                      \
+            } else {                                                                                     \
+                bw_load_lds16(qb + bw_offset(i_, p.q_st) + bw_offset(h_, p.q_sh) + c16 / 2, dst_);       \
+                bw_load_lds16(gb + bw_offset(i_, p.do_st) + bw_offset(h_, p.do_sh) + c16 / 2, dst_ + IMG); \
+            }                                                                                            \
+            }                                                                                            \
+        } else if (whole) {                                                                              \
+            bw_load_lds4(sptr + i0, lds0 + stat_base + ist * 256);                                       \
+        } else {                                                                                         \
+            unsigned lo_ = lane;                                                                         \
+            asm volatile("" : "+v"(lo_));                                                                \
+            BW_ROW((int)(lo_ & 31), i_, h_)                                                              \
+            bw_load_lds4(stp + (int64_t)h_ * st_h + i_, lds0 + stat_base + ist * 256);              \
+        }                                                                                                \
+    }
+#define BW_ADVANCE()                                                                                     \
+    {                                                                                                    \
+        ist = ist + 1 == NS ? 0 : ist + 1;                                                               \
+        if (up) { i0 += di; h0 += dh; if (h0 >= g) { h0 -= g; ++i0; } }                                  \
+        else { i0 -= di; h0 -= dh; if (h0 < 0) { h0 += g; --i0; } }                                      \
+        qt += dqt;                                                                                       \
+        gt += dqt;                                                                                       \
+        whole = regular && i0 >= 0 && i0 + qpt <= Lq;                                                    \
+    }
+    // fragment of step s (0 .. 4 * PH - 1): Q rows, dO rows, dO^T, Q^T; the transposed ones in the order keys 0..15, 16..31
+    constexpr int PH = D / 16;                        // steps per product
+    union Frag { s16x4 h[2]; bf16x8 v; };
+#define BW_ROW_ADDR(a, sb) _Pragma("unroll") for (int k = 0; k < 4; ++k) a[k] = (row_x ^ (k << RSH)) + ((sb) + row_base);
+#define BW_TR_ADDR(a, sb) _Pragma("unroll") for (int k = 0; k < D / 32; ++k) a[k] = (tr_x ^ (k << 6)) + ((sb) + tr_base);
+#define BW_READ(f, ra, ta, s)                                                                            \
+    {                                                                                                    \
+        if ((s) < 2 * PH) {                                                                              \
+            const int c_ = (s) % PH;                                                                     \
+            f.v = *reinterpret_cast<const bf16x8*>(smem + ra[c_ / RDIV] + (c_ % RDIV) * 32 + ((s) < PH ? 0 : IMG)); \
+        } else {                                                                                         \
+            const int j2_ = ((s) % PH) / (D / 32), dt_ = (s) % (D / 32);                                 \
+            _Pragma("unroll") for (int q = 0; q < 2; ++q)                                                \
+                f.h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(smem + ta[dt_] +           \
+                             (2 * j2_ + q) * (8 / RPI) * BW_GP + ((s) < 3 * PH ? IMG : 0)));             \
+        }                                                                                                \
+    }
+
+    f32x16 av[2][D / 32], ak[2][D / 32];   // dV^T, dK^T: lane = key, registers = 16 of the 32 head-dim entries of tile dt
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                u32x2 a;
-                a[0] = pack_bf16x2(acc[dt][4 * q4] * f, acc[dt][4 * q4 + 1] * f);
-                a[1] = pack_bf16x2(acc[dt][4 * q4 + 2] * f, acc[dt][4 * q4 + 3] * f);
-                *reinterpret_cast<u32x2*>(op + 32 * dt + 8 * q4 + 4 * hi) = a;
+            for (int i = 0; i < 16; ++i) av[s][dt][i] = ak[s][dt][i] = 0.f;
+
+    Frag fr[FD];
+    int st = 0;                                       // ring stage of this iteration's tile
+    if (n_it > 0) {
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a) {
+#pragma unroll
+            for (int x = 0; x <= IPW; ++x) BW_REQUEST(x);
+            BW_ADVANCE();
+        }
+    }
+    // K, V and the first tiles: a full wait, after which the compiler counts no load of its own inside the loop
+    __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
+    if (n_it > 0) {
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int s = 0; s < FD; ++s) {
+            int ra[4], ta[D / 32];
+            BW_ROW_ADDR(ra, wr * NS * STAGE)
+            BW_READ(fr[s], ra, ta, s);
+        }
+    }
+    for (int it = 0; it < n_it; ++it) {
+        const int sb = (wr * NS + st) * STAGE;
+        const int stn = st + 1 == NS ? 0 : st + 1;
+        const int sbn = (wr * NS + stn) * STAGE;
+        const bool work = jw < slen && it * NWR + wr < n_rt && rt * 32 + 32 > r_first;
+        int ra[4], ta[D / 32];                        // LDS addresses of the row and the transposing reads
+        if (work) {
+            BW_ROW_ADDR(ra, sb)
+            float* const stat = reinterpret_cast<float*>(smem + stat_base + st * 256);
+            f32x16 S[2], dP[2];
+            uint32_t pk[2][8];                        // P, then dS, as bf16 pairs: the B operands of the last two products
+            f32x4 l2, sr;                             // statistics in use and the next four
+            const float own_lse = stat[n];            // of row n: for the check below
+#pragma unroll
+            for (int c = 0; c < PH; ++c) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {         // S[row, key]: lane = key
+                    if (c == 0) bw_mfma_zero(S[s], fr[0].v, kf[s][0]);
+                    else S[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[c % FD].v, kf[s][c], S[s], 0, 0, 0);
+                }
+                BW_READ(fr[c % FD], ra, ta, c + FD);
+                // the tile after the next goes into the stage that the tile before the last one has left
+#pragma unroll
+                for (int x = 0; x <= IPW; ++x)
+                    if (x * PH / (IPW + 1) == c) BW_REQUEST(x);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // Hidden scores become -inf (probability 0), on the tiles that hold some: rows outside [r_clear_lo, r_clear_hi) miss
+            // a key of this wavefront, rows from R on do not exist
+            if (__any(own_lse == -INFINITY)) {        // rows that saw no key take +inf, which makes their probabilities 0
+                if (hi == 0 && own_lse == -INFINITY) stat[n] = INFINITY;
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // one wavefront's LDS operations complete in order
+            }
+            if (rt * 32 < r_clear_lo || rt * 32 + 32 > r_clear_hi) {
+                int lo = lane;
+                asm volatile("" : "+v"(lo));          // formed here, on these few tiles, not kept in registers over the loop
+                const int rbase = rt * 32 + 4 * (lo >> 5);
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    int rlo = 0, rhi = R;             // rows that see the lane's key
+                    if (BC) {
+                        const int kpos = spos + jw + 32 * s + (lo & 31);
+                        rlo = min(max((kpos + hoff) / p.bs * p.bs - p.q_pos0, 0), Lq) * g;
+                        if (same) rhi = min(max((kpos + p.bs) / p.bs * p.bs - p.q_pos0, 0), Lq) * g;
+                    }
+                    const unsigned span = (unsigned)max(rhi - rlo, 0);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        if ((unsigned)(rbase + 8 * (i >> 2) + (i & 3) - rlo) >= span) S[s][i] = -INFINITY;
+                }
+            }
+            constexpr int MP = 2 * PH;                // MFMAs per product
+            sr = *reinterpret_cast<const f32x4*>(stat + 4 * hi);
+            // dP starts from -delta (what the workspace holds): dS = P * (dP - delta) is one multiplication
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    const f32x4 d4 = *reinterpret_cast<const f32x4*>(stat + 32 + 8 * g4 + 4 * hi);
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) dP[s][4 * g4 + x] = d4[x];
+                }
+#pragma unroll
+            for (int m = MP; m < 4 * MP; ++m) {
+                const int step = m >> 1, s = m & 1, c = step % PH;
+                const int j2 = c / (D / 32), dt = c % (D / 32);
+                if (m == 7 * MP / 2) {
+                    // the next tile has landed (the one behind it may be in flight), and every wavefront has left the tile
+                    // before this one: its stage takes the next requests
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * LOADS) : "memory");
+                    if (NWK > 1) __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                }
+                if (step < 2 * PH) {
+                    dP[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[step % FD].v, vf[s][c], dP[s], 0, 0, 0);
+                } else {
+                    const u32x4 bp = {pk[s][4 * j2], pk[s][4 * j2 + 1], pk[s][4 * j2 + 2], pk[s][4 * j2 + 3]};
+                    if (step < 3 * PH) bw_mfma_acc(av[s][dt], fr[step % FD].v, bw_as_bf16x8(bp), dt == 0);
+                    else bw_mfma_acc(ak[s][dt], fr[step % FD].v, bw_as_bf16x8(bp), dt == 0);
+                }
+                if (s == 1) {
+                    if (step + FD == 2 * PH) BW_TR_ADDR(ta, sb)
+                    if (step + FD == 4 * PH) BW_ROW_ADDR(ra, sbn)
+                    BW_READ(fr[step % FD], ra, ta, (step + FD) % (4 * PH));
+                }
+                // half-unit u: rows 8 * (u / 4) + 4 * hi + 2 * (u % 2) + {0, 1}, key tile (u / 2) % 2
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    const int g4 = u >> 2, ks = (u >> 1) & 1, e = 4 * g4 + 2 * (u & 1);
+                    if (MP + 2 + u * (3 * MP / 2 - 3) / 16 == m) {
+                        if ((u & 3) == 0) {
+#pragma unroll
+                            for (int x = 0; x < 4; ++x) l2[x] = sr[x] * -1.4426950408889634f;
+                            if (g4 < 3) sr = *reinterpret_cast<const f32x4*>(stat + 8 * g4 + 8 + 4 * hi);
+                        }
+#pragma unroll
+                        for (int x = 0; x < 2; ++x) S[ks][e + x] = fast_exp2(fmaf(S[ks][e + x], p.scale_log2, l2[2 * (u & 1) + x]));
+                        pk[ks][e >> 1] = pack_bf16x2(S[ks][e], S[ks][e + 1]);
+                    }
+                    if (5 * MP / 2 + u * MP / 16 == m) {
+                        pk[ks][e >> 1] = pack_bf16x2(S[ks][e] * dP[ks][e], S[ks][e + 1] * dP[ks][e + 1]);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+#pragma unroll
+            for (int x = 0; x <= IPW; ++x) BW_REQUEST(x);
+            BW_ROW_ADDR(ra, sbn)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * LOADS) : "memory");
+            if (NWK > 1) __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int s = 0; s < FD; ++s) BW_READ(fr[s], ra, ta, s);
+        }
+        BW_ADVANCE();
+        st = stn;
+        rt += rt_step;
+    }
+#undef BW_READ
+#undef BW_ROW_ADDR
+#undef BW_TR_ADDR
+#undef BW_ADVANCE
+#undef BW_REQUEST
+#undef BW_ROW
+    // the requests past the end, before the ring is reused; and the wait states between the last product and a read of its result
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    __syncthreads();
+
+    int le = lane;
+    asm volatile("" : "+v"(le));                      // its offsets are formed here, not kept over the loop
+    const int ne = le & 31, he = le >> 5;
+    // ---- sum over the row groups, register for register --------------------------------------------------------------
+    if (NWR > 1) {
+        f32x4* mb = reinterpret_cast<f32x4*>(smem) + wk * (64 * D / 4) + le;
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+            for (int src = 1; src < NWR; ++src) {
+                if (wr == src) {
+#pragma unroll
+                    for (int x = 0; x < 2 * (D / 32) * 4; ++x) {
+                        const f32x16& a = o ? ak[x / (D / 8)][x / 4 % (D / 32)] : av[x / (D / 8)][x / 4 % (D / 32)];
+                        mb[x * 64] = f32x4{a[4 * (x & 3)], a[4 * (x & 3) + 1], a[4 * (x & 3) + 2], a[4 * (x & 3) + 3]};
+                    }
+                }
+                __syncthreads();
+                if (wr == 0) {
+#pragma unroll
+                    for (int x = 0; x < 2 * (D / 32) * 4; ++x) {
+                        f32x16& a = o ? ak[x / (D / 8)][x / 4 % (D / 32)] : av[x / (D / 8)][x / 4 % (D / 32)];
+                        const f32x4 v = mb[x * 64];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) a[4 * (x & 3) + e] += v[e];
+                    }
+                }
+                __syncthreads();
+            }
+    }
+    // ---- store: 32 keys at a time through a private LDS region, whole rows, 16 bytes per lane ------------------------
+    if (wr == 0) {
+        unsigned char* ob = smem + wk * (32 * OPB);
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const float f = o ? p.scale : 1.0f;
+#pragma unroll
+                for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        const f32x16& a = o ? ak[s][dt] : av[s][dt];
+                        u32x2 v;
+                        v[0] = pack_bf16x2(a[4 * q4] * f, a[4 * q4 + 1] * f);
+                        v[1] = pack_bf16x2(a[4 * q4 + 2] * f, a[4 * q4 + 3] * f);
+                        *reinterpret_cast<u32x2*>(ob + ne * OPB + (32 * dt + 8 * q4 + 4 * he) * 2) = v;
+                    }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // one wavefront's LDS operations complete in order
+                uint16_t* op = (o ? sdk : sdv) + kv_off + kvh * ssh;
+#pragma unroll
+                for (int q = 0; q < (32 * C8) / 64; ++q) {
+                    const int id = q * 64 + le;
+                    const int row = id / C8, c = id - row * C8;
+                    const int j = jw + 32 * s + row;
+                    const u32x4 v = *reinterpret_cast<const u32x4*>(ob + row * OPB + c * 16);
+                    if (j < slen) *reinterpret_cast<u32x4*>(op + (int64_t)j * sst + 8 * c) = v;
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
     }
     __syncthreads();   // the LDS images are reused by the next pass
     }
 }
 
+template <int D, bool BC, int NWK, int NWR>
+static int launch_dkv(const BwdParams& p, int s, hipStream_t st) {
+    const int n_slabs = (p.seg[s].len + 64 * NWK - 1) / (64 * NWK);
+    // equal-work pairing where the mask makes slabs unequal (not for "own block only": every slab sees one block's rows) and
+    // half as many workgroups still fill the chip
+    const int pair = (BC && p.seg[s].rule != DLM_SEG_SAME_BLOCK && n_slabs >= 4 && (int64_t)n_slabs * p.B * p.Hkv >= 1024) ? 1 : 0;
+    dim3 grid(pair ? (n_slabs + 1) / 2 : n_slabs, p.Hkv, p.B);
+    GridRemap rm = no_remap();
+    if ((g_attn_remap & 4) && grid.x >= 2) {
+        const int64_t n_wg = set_remap(rm, (int64_t)p.B * p.Hkv, (int)grid.x, false);
+        if (n_wg > 0) grid = dim3((unsigned)n_wg);
+        else rm = no_remap();
+    }
+    hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, BC, NWK, NWR>), grid, dim3(64 * NWK * NWR), 0, st, p, s, n_slabs, pair, rm);
+    return check_hip(hipGetLastError(), "attn_bwd_dkv_kernel launch");
+}
+
 template <int D, bool BC>
 static int launch_bwd(const BwdParams& p, hipStream_t st) {
     constexpr int RPB = 256 / (D / 8);
+    int rc;
+    dim3 grid((p.R + 127) / 128, p.Hkv, p.B);
     const int rows = p.Lq * p.Hq;
     hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((rows + RPB - 1) / RPB, 1, p.B), dim3(256), 0, st, p);
-    int rc = check_hip(hipGetLastError(), "attn_bwd_delta_kernel launch");
-    if (rc != DLM_OK) return rc;
+    if ((rc = check_hip(hipGetLastError(), "attn_bwd_delta_kernel launch")) != DLM_OK) return rc;
     if (p.dq) {
-        dim3 grid((p.R + 127) / 128, p.Hkv, p.B);
         GridRemap rm = no_remap();
         if ((g_attn_remap & 1) && grid.x >= 2) {
             const int64_t n_wg = set_remap(rm, (int64_t)p.B * p.Hkv, (int)grid.x, BC && (g_attn_remap & 2));
@@ -670,26 +906,20 @@ static int launch_bwd(const BwdParams& p, hipStream_t st) {
             else rm = no_remap();
         }
         hipLaunchKernelGGL((attn_bwd_dq_kernel<D, BC>), grid, dim3(256), 0, st, p, rm);
-        rc = check_hip(hipGetLastError(), "attn_bwd_dq_kernel launch");
-        if (rc != DLM_OK) return rc;
+        if ((rc = check_hip(hipGetLastError(), "attn_bwd dQ kernel launch")) != DLM_OK) return rc;
     }
     for (int s = 0; s < 3; ++s) {
         if (!p.seg[s].dk || p.seg[s].len == 0) continue;
-        const int n_slabs = (p.seg[s].len + 127) / 128;
-        // equal-work pairing where the mask makes slabs unequal (not for "own block only": every slab sees one block's rows)
-        const int pair = (BC && p.seg[s].rule != DLM_SEG_SAME_BLOCK && n_slabs >= 4) ? 1 : 0;
-        dim3 grid(pair ? (n_slabs + 1) / 2 : n_slabs, p.Hkv, p.B);
-        GridRemap rm = no_remap();
-        if ((g_attn_remap & 4) && grid.x >= 2) {
-            const int64_t n_wg = set_remap(rm, (int64_t)p.B * p.Hkv, (int)grid.x, false);
-            if (n_wg > 0) grid = dim3((unsigned)n_wg);
-            else rm = no_remap();
-        }
-        hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, BC, false>), grid, dim3(256), 0, st, p, s, n_slabs, pair, rm);
-        rc = check_hip(hipGetLastError(), "attn_bwd_dkv_kernel (dV pass) launch");
-        if (rc != DLM_OK) return rc;
-        hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, BC, true>), grid, dim3(256), 0, st, p, s, n_slabs, pair, rm);
-        rc = check_hip(hipGetLastError(), "attn_bwd_dkv_kernel (dK pass) launch");
+        // Key-split: two wavefronts of 64 keys, 512 such workgroups at a time.  With at most half of them, or with up to twice
+        // as many that each walk many rows (sequences of unequal length, a causal mask: the longest decide), four wavefronts
+        // share a slab's row tiles instead, for a sum through LDS at the end.  Whole backward pass, us, key- / row-split:
+        // 256 workgroups 4757 / 3097, 64 721 / 327, 32 372 / 274; 320 with 4200 rows 328 / 244, 640 with 4800 426 / 366, with
+        // 600 rows 87 / 103; 1024 with 4096 rows 1671 / 1757.
+        const int64_t n_wg = (int64_t)((p.seg[s].len + 127) / 128) * p.Hkv * p.B;
+        const bool split = n_wg <= 256 || (n_wg < 1024 && p.R >= 2048);
+        if (!split) rc = launch_dkv<D, BC, 2, 1>(p, s, st);
+        else if constexpr (D == 64) rc = launch_dkv<D, BC, 1, 4>(p, s, st);
+        else rc = launch_dkv<D, BC, 2, 2>(p, s, st);
         if (rc != DLM_OK) return rc;
     }
     return DLM_OK;
