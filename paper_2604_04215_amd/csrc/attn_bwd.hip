@@ -746,7 +746,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
             for (int m = MP; m < 4 * MP; ++m) {
                 const int step = m >> 1, s = m & 1, c = step % PH;
                 const int j2 = c / (D / 32), dt = c % (D / 32);
-                if (m == 7 * MP / 2) {
+                if (m == 2 * (4 * PH - FD)) {         // before its first fragment is read
                     // the next tile has landed (the one behind it may be in flight), and every wavefront has left the tile
                     // before this one: its stage takes the next requests
                     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * LOADS) : "memory");
