@@ -6,13 +6,13 @@
 // P is recomputed from Q, K and the forward pass's log-sum-exp; nothing of size Lq x Lk is stored.
 //
 // No atomics, every output element written exactly once (deterministic):
-//   * attn_bwd_delta_kernel : delta per (sequence, head, query row).
+//   * attn_bwd_delta_kernel : delta per (sequence, head, query row), where the dQ kernel below does not form it.
 //   * attn_bwd_dq_kernel    : a workgroup owns 128 rows (query, head in group) of one (sequence, KV head) and
 //                             walks the key tiles of all segments, like the forward kernel.  Per 32-key tile and
 //                             wavefront: S^T = K Q^T and dP^T = V dO^T (keys are the MFMA rows, so a lane holds 16
 //                             keys of ONE query row and LSE / delta are per-lane scalars), dS^T in registers is
 //                             already the B operand of dQ^T += K^T dS^T; K^T fragments come from LDS through the
-//                             transposing 64-bit LDS read.
+//                             transposing 64-bit LDS read.  attn_bwd_dq64_kernel: the same with 64 rows a wavefront.
 //   * attn_bwd_dkv_kernel   : the mirror image.  A workgroup owns 64 or 128 keys of ONE segment of one (sequence, KV
 //                             head) and walks the 32-row tiles of (query, head in group) rows that can see them:
 //                             S = Q K^T and dP = dO V^T (rows are the MFMA rows, a lane holds 16 rows of ONE key), P
@@ -873,6 +873,388 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     }
 }
 
+// dQ with 64 rows a wavefront (two MFMA column tiles), for launches that fill the chip with such wavefronts: as in the dK / dV
+// kernel every K and V fragment read from LDS then feeds two products (with 32 rows the LDS delivers no faster than the
+// matrix pipes consume), and the one wavefront a SIMD holds weaves its vector work between the products: the scores of
+// the NEXT key tile are formed between dP and dQ of this one, so that the exponentials run beside dP and those scores,
+// and dS beside the scores and the first half of dQ.  K / V tiles come by global_load_lds through a ring of four, two tiles
+// ahead.  delta = rowsum(dO * O) is formed here, from the dO fragments the kernel holds anyway, and left for the dK / dV
+// kernels.
+// Measured (8 x 4096 tokens, 32 / 8 heads of 128, blocks of 4): 1.53 ms = 1.09 PFLOP/s of products, 32 rows a wavefront 1.82
+// ms and 0.10 for delta by itself.
+template <bool BC>
+__global__ __launch_bounds__(128, 1) void attn_bwd_dq64_kernel(BwdParams p, GridRemap rm) {
+    constexpr int D = 128, NWQ = 2;                    // head size, wavefronts
+    constexpr int NS = 4, FD = 4;
+    constexpr int P = D * 2, C8 = D / 8;
+    constexpr int RPI = 64 / C8, IPW = 32 / RPI / NWQ;
+    constexpr int IMG = 32 / RPI * BW_GP;
+    constexpr int STAGE = 2 * IMG;                     // K, V
+    constexpr int LOADS = 2 * IPW;
+    constexpr int OPB = D * 2 + 16;                    // output staging row pitch (bytes)
+    constexpr int RING = NS * STAGE, STORE = NWQ * 32 * (OPB + 8);
+    static_assert(IPW >= 1 && RING >= STORE, "ring");
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[RING];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, hi = lane >> 5;
+    int b = blockIdx.z, kvh = blockIdx.y, bx0 = blockIdx.x;
+    if (rm.nx > 0) {
+        int grp;
+        if (!remap_decode(rm, p.B * p.Hkv, grp, bx0)) return;
+        kvh = grp % p.Hkv;
+        b = grp / p.Hkv;
+    }
+    const int r0 = bx0 * (64 * NWQ);
+
+    int len0 = p.seg[0].len, len1 = p.seg[1].len, len2 = p.seg[2].len;
+    int R = p.R, s0 = 0;
+    int64_t q_off = b * p.q_sb, o_off = b * p.o_sb, do_off = b * p.do_sb, dq_off = b * p.dq_sb, kv1_off = b * p.seg[1].sb;
+    if (p.cu) {
+        s0 = min(max(p.cu[b], 0), p.total);
+        const int sl = max(min(min(p.cu[b + 1], p.total) - s0, p.Lq), 0);
+        R = p.g * sl;
+        if (r0 >= R) return;
+        len1 = min(len1, sl);
+        q_off = s0 * p.q_st;
+        o_off = s0 * p.o_st;
+        do_off = s0 * p.do_st;
+        dq_off = s0 * p.dq_st;
+        kv1_off = s0 * p.seg[1].st;
+    }
+    int F0 = 0, F1 = 0, F2 = 0, ho0 = 0, ho1 = 0, ho2 = 0;
+    bool same0 = false, same1 = false, same2 = false;
+    if (BC) {
+        const int rows_end = min(r0 + 64 * NWQ, R);
+        const int lim = ((p.q_pos0 + (rows_end - 1) / p.g) / p.bs + 1) * p.bs;
+        const int first = ((p.q_pos0 + r0 / p.g) / p.bs) * p.bs;
+        ho0 = (p.seg[0].rule == DLM_SEG_EARLIER_BLOCKS) ? p.bs : 0;
+        ho1 = (p.seg[1].rule == DLM_SEG_EARLIER_BLOCKS) ? p.bs : 0;
+        ho2 = (p.seg[2].rule == DLM_SEG_EARLIER_BLOCKS) ? p.bs : 0;
+        same0 = p.seg[0].rule == DLM_SEG_SAME_BLOCK;
+        same1 = p.seg[1].rule == DLM_SEG_SAME_BLOCK;
+        same2 = p.seg[2].rule == DLM_SEG_SAME_BLOCK;
+        len0 = max(0, min(len0, lim - ho0 - p.seg[0].pos0));
+        len1 = max(0, min(len1, lim - ho1 - p.seg[1].pos0));
+        len2 = max(0, min(len2, lim - ho2 - p.seg[2].pos0));
+        if (same0) F0 = min(max(first - p.seg[0].pos0, 0) >> 5, (len0 + 31) >> 5);
+        if (same1) F1 = min(max(first - p.seg[1].pos0, 0) >> 5, (len1 + 31) >> 5);
+        if (same2) F2 = min(max(first - p.seg[2].pos0, 0) >> 5, (len2 + 31) >> 5);
+    }
+    const int T0 = ((len0 + 31) >> 5) - F0, T1 = ((len1 + 31) >> 5) - F1, T2 = ((len2 + 31) >> 5) - F2;
+    const int T = T0 + T1 + T2;
+
+    const uint16_t* kb0 = p.seg[0].k + b * p.seg[0].sb + kvh * p.seg[0].sh;
+    const uint16_t* vb0 = p.seg[0].v + b * p.seg[0].sb + kvh * p.seg[0].sh;
+    const uint16_t* kb1 = p.seg[1].k + kv1_off + kvh * p.seg[1].sh;
+    const uint16_t* vb1 = p.seg[1].v + kv1_off + kvh * p.seg[1].sh;
+    const uint16_t* kb2 = p.seg[2].k + b * p.seg[2].sb + kvh * p.seg[2].sh;
+    const uint16_t* vb2 = p.seg[2].v + b * p.seg[2].sb + kvh * p.seg[2].sh;
+    const int64_t st0 = p.seg[0].st, st1 = p.seg[1].st, st2 = p.seg[2].st;
+    const int sp0 = __builtin_amdgcn_readfirstlane(p.seg[0].pos0), sp1 = __builtin_amdgcn_readfirstlane(p.seg[1].pos0),
+              sp2 = __builtin_amdgcn_readfirstlane(p.seg[2].pos0);
+
+    // ---- lane parts of the LDS addresses, as in the dK / dV kernel --------------------------------------------
+    constexpr int RSH = 6, RDIV = 2;
+    const int row_base = n / RPI * BW_GP + n % RPI * P + hi * 16;
+    const int row_x = (n & 3) << 6;
+    const int s16 = lane & 15, blk = (lane >> 4) & 1;
+    const int tr_base = hi * BW_GP + (s16 >> 2) * P + ((2 * blk + ((s16 & 3) >> 1)) << 4) + 8 * (s16 & 1);
+    const int tr_x = (s16 >> 2) << 6;
+    const int c16 = ((lane % C8) ^ bw_swz<D>(lane / C8)) * 16;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+
+    // Walk over the key tiles of all segments, twice: the tile to request (rk, rv: its first K and V row, rleft: rows from there to
+    // the segment's end) and the tile to multiply (cpos: position of its first key, cleft).  Past the last tile the request
+    // stays on it, for a stage nobody reads.
+    int rseg = -1, rleft = 0, cseg = -1, cleft = 0, cpos = 0, choff = 0;
+    bool csame = false;
+    const uint16_t *rk = nullptr, *rv = nullptr;
+    int64_t rst = 0;
+    uint32_t voff = 0;                                // this lane's offset inside a request of the segment
+#define DQ_REQ_SEG()                                                                                     \
+    {                                                                                                    \
+        ++rseg;                                                                                          \
+        if (rseg == 0 && T0 == 0) ++rseg;                                                                \
+        if (rseg == 1 && T1 == 0) ++rseg;                                                                \
+        const int F_ = rseg == 0 ? F0 : (rseg == 1 ? F1 : F2);                                           \
+        rst = rseg == 0 ? st0 : (rseg == 1 ? st1 : st2);                                                 \
+        rk = (rseg == 0 ? kb0 : (rseg == 1 ? kb1 : kb2)) + (int64_t)(F_ * 32) * rst;                     \
+        rv = (rseg == 0 ? vb0 : (rseg == 1 ? vb1 : vb2)) + (int64_t)(F_ * 32) * rst;                     \
+        rleft = (rseg == 0 ? len0 : (rseg == 1 ? len1 : len2)) - F_ * 32;                                \
+        voff = __umul24(lane / C8, (int)rst * 2) + c16;                                                  \
+    }
+    const int last_seg = T2 > 0 ? 2 : (T1 > 0 ? 1 : 0);
+#define DQ_REQ_NEXT()                                                                                    \
+    if (rleft > 32) {                                                                                    \
+        rleft -= 32;                                                                                     \
+        rk += 32 * rst;                                                                                  \
+        rv += 32 * rst;                                                                                  \
+    } else if (rseg != last_seg) DQ_REQ_SEG()
+#define DQ_CUR_SEG()                                                                                     \
+    {                                                                                                    \
+        ++cseg;                                                                                          \
+        if (cseg == 0 && T0 == 0) ++cseg;                                                                \
+        if (cseg == 1 && T1 == 0) ++cseg;                                                                \
+        const int F_ = cseg == 0 ? F0 : (cseg == 1 ? F1 : F2);                                           \
+        cpos = (cseg == 0 ? sp0 : (cseg == 1 ? sp1 : sp2)) + F_ * 32;                                    \
+        cleft = (cseg == 0 ? len0 : (cseg == 1 ? len1 : len2)) - F_ * 32;                                \
+        choff = cseg == 0 ? ho0 : (cseg == 1 ? ho1 : ho2);                                               \
+        csame = cseg == 0 ? same0 : (cseg == 1 ? same1 : same2);                                         \
+    }
+    // request x of the tile: rows of K and the same rows of V; rows past the segment's end repeat its last row, their scores are
+    // hidden below.  (Strides of 2^24 bytes and more take 64-bit products.)
+#define DQ_REQUEST(stage, x)                                                                             \
+    {                                                                                                    \
+        const int q_ = w * IPW + (x);                                                                    \
+        const uint32_t dst_ = lds0 + (stage) * STAGE + q_ * BW_GP;                                       \
+        if (rleft >= 32 && rst < (1 << 23)) {                                                            \
+            bw_load_lds16_pair(rk, rv, voff, q_ * RPI * ((int)rst * 2), dst_, IMG);                      \
+        } else {                                                                                         \
+            const int64_t off_ = min(q_ * RPI + lane / C8, rleft - 1) * rst + c16 / 2;                   \
+            bw_load_lds16(rk + off_, dst_);                                                              \
+            bw_load_lds16(rv + off_, dst_ + IMG);                                                        \
+        }                                                                                                \
+    }
+
+    if (T > 0) {
+        DQ_REQ_SEG()
+        DQ_CUR_SEG()
+#pragma unroll
+        for (int t = 0; t < NS - 1; ++t) {
+#pragma unroll
+            for (int x = 0; x < IPW; ++x) DQ_REQUEST(t, x);
+            DQ_REQ_NEXT()
+        }
+    }
+
+    // ---- this lane's two query rows: Q and dO fragments (B operands), LSE and delta ---------------------------
+    bf16x8 qf[2][D / 16], dof[2][D / 16];
+    float nlse2[2], ndelta[2];            // -LSE in log2 units (-inf: no probability at all), -delta
+    int qlim[2];
+    int qlim_min = 0x7fffffff, qlim_max = 0;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int r = r0 + w * 64 + s * 32 + n;
+        const bool valid = r < R;
+        const int qi = valid ? r / p.g : 0;
+        const int h = kvh * p.g + (valid ? r - qi * p.g : 0);
+        const uint16_t* qp = p.q + q_off + qi * p.q_st + (int64_t)h * p.q_sh;
+        const uint16_t* dp = p.dout + do_off + qi * p.do_st + (int64_t)h * p.do_sh;
+        const uint16_t* op = p.o + o_off + qi * p.o_st + (int64_t)h * p.o_sh;
+        float acc = 0.f;
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) {
+            u32x4 a = {0, 0, 0, 0}, d = {0, 0, 0, 0}, o = {0, 0, 0, 0};
+            if (valid) {
+                a = *reinterpret_cast<const u32x4*>(qp + 16 * c + 8 * hi);
+                d = *reinterpret_cast<const u32x4*>(dp + 16 * c + 8 * hi);
+                o = *reinterpret_cast<const u32x4*>(op + 16 * c + 8 * hi);
+            }
+            qf[s][c] = bw_as_bf16x8(a);
+            dof[s][c] = bw_as_bf16x8(d);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc += bf16_bits_to_f32(o[e] & 0xffffu) * bf16_bits_to_f32(d[e] & 0xffffu);
+                acc += bf16_bits_to_f32(o[e] >> 16) * bf16_bits_to_f32(d[e] >> 16);
+            }
+        }
+        acc += shfl_xor(acc, 32);
+        ndelta[s] = -acc;
+        nlse2[s] = -INFINITY;
+        if (valid) {
+            const int64_t si = stat_index(p, b, h, qi, s0);
+            const float l = p.lse[si];
+            if (l > -INFINITY) nlse2[s] = l * -1.4426950408889634f;
+            if (hi == 0) p.delta[si] = -acc;
+        }
+        qlim[s] = BC ? ((p.q_pos0 + qi) / p.bs + 1) * p.bs : 0;
+        if (BC) {
+            qlim_min = min(qlim_min, qlim[s]);
+            qlim_max = max(qlim_max, qlim[s]);
+        }
+    }
+    if (BC) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            qlim_min = min(qlim_min, shfl_xor(qlim_min, off));
+            qlim_max = max(qlim_max, shfl_xor(qlim_max, off));
+        }
+        qlim_min = __builtin_amdgcn_readfirstlane(qlim_min);
+        qlim_max = __builtin_amdgcn_readfirstlane(qlim_max);
+    }
+
+    constexpr int PH = D / 16, MP = 2 * PH;           // steps and MFMAs per product
+    union Frag { s16x4 h[2]; bf16x8 v; };
+    f32x16 dq[2][D / 32];
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) dq[s][dt][i] = 0.f;
+
+#define DQ_ROW_ADDR(a, sb) _Pragma("unroll") for (int k = 0; k < 4; ++k) a[k] = (row_x ^ (k << RSH)) + ((sb) + row_base);
+#define DQ_TR_ADDR(a, sb) _Pragma("unroll") for (int k = 0; k < D / 32; ++k) a[k] = (tr_x ^ (k << 6)) + ((sb) + tr_base);
+    // fragment of step s: V rows of this tile, K rows of the next one (va, ka: row addresses), K^T of this one
+#define DQ_READ(f, va, ka, ta, s)                                                                        \
+    {                                                                                                    \
+        const int c_ = (s) % PH;                                                                         \
+        if ((s) < PH) f.v = *reinterpret_cast<const bf16x8*>(smem + va[c_ / RDIV] + (c_ % RDIV) * 32 + IMG); \
+        else if ((s) < 2 * PH) f.v = *reinterpret_cast<const bf16x8*>(smem + ka[c_ / RDIV] + (c_ % RDIV) * 32); \
+        else {                                                                                           \
+            const int j2_ = c_ / (D / 32), dt_ = c_ % (D / 32);                                          \
+            _Pragma("unroll") for (int q = 0; q < 2; ++q)                                                \
+                f.h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(smem + ta[dt_] + (2 * j2_ + q) * (8 / RPI) * BW_GP)); \
+        }                                                                                                \
+    }
+    // Q, dO, O and the first tiles: a full wait, after which the compiler counts no load of its own inside the loop
+    __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
+    if (T > 0) {
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        f32x16 SS[2][2];
+        int va[4], ka[4], ta[D / 32];
+        Frag fr[FD];
+        DQ_ROW_ADDR(ka, 0)
+        {   // scores of tile 0, not overlapped with anything
+            Frag f;
+#pragma unroll
+            for (int c = 0; c < PH; ++c) {
+                DQ_READ(f, va, ka, ta, PH + c)
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    if (c == 0) bw_mfma_zero(SS[0][s], f.v, qf[s][0]);
+                    else SS[0][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[s][c], SS[0][s], 0, 0, 0);
+                }
+            }
+        }
+        DQ_ROW_ADDR(va, 0)
+#pragma unroll
+        for (int s = 0; s < FD; ++s) DQ_READ(fr[s], va, ka, ta, s)
+        // one tile: SS[v] holds its scores, SS[1 - v] takes the next tile's (two tiles a turn: no copies)
+        for (int t0 = 0; t0 < T; t0 += 2)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int t = t0 + v;
+            if (t >= T) break;
+            const int sb = (t & (NS - 1)) * STAGE, sbn = ((t + 1) & (NS - 1)) * STAGE;
+            if (cleft < 32 || (BC && (cpos + 31 >= qlim_min - choff || (csame && cpos < qlim_max - p.bs)))) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    int hi_r = cpos + cleft;
+                    int lo_r = -(1 << 30);
+                    if (BC) {
+                        hi_r = min(hi_r, qlim[s] - choff);
+                        if (csame) lo_r = qlim[s] - p.bs;
+                    }
+                    const unsigned span = (unsigned)max(hi_r - lo_r, 0);
+                    const unsigned off0 = (unsigned)(cpos + 4 * hi - lo_r);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        if (off0 + (unsigned)(8 * (i >> 2) + (i & 3)) >= span) SS[v][s][i] = -INFINITY;
+                }
+            }
+            if (cleft > 32) {
+                cleft -= 32;
+                cpos += 32;
+            } else if (cseg != last_seg) DQ_CUR_SEG()
+            f32x16 dP[2];
+            uint32_t pk[2][8];                        // dS as bf16 pairs: the B operand of the last product
+            DQ_ROW_ADDR(va, sb)
+#pragma unroll
+            for (int m = 0; m < 3 * MP; ++m) {
+                const int step = m >> 1, s = m & 1, c = step % PH;
+                if (m == MP - 2 * FD) {
+                    // the next tile has landed (the one behind it may be in flight), and every wavefront has left the tile
+                    // before this one: its stage takes the requests below
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    DQ_ROW_ADDR(ka, sbn)
+                }
+                if (step < PH) {
+                    if (c == 0) bw_mfma_zero(dP[s], fr[step % FD].v, dof[s][0]);
+                    else dP[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[step % FD].v, dof[s][c], dP[s], 0, 0, 0);
+                } else if (step < 2 * PH) {
+                    if (c == 0) bw_mfma_zero(SS[1 - v][s], fr[step % FD].v, qf[s][0]);
+                    else SS[1 - v][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[step % FD].v, qf[s][c], SS[1 - v][s], 0, 0, 0);
+                } else {
+                    const int j2 = c / (D / 32), dt = c % (D / 32);
+                    const u32x4 bp = {pk[s][4 * j2], pk[s][4 * j2 + 1], pk[s][4 * j2 + 2], pk[s][4 * j2 + 3]};
+                    bw_mfma_acc(dq[s][dt], fr[step % FD].v, bw_as_bf16x8(bp), dt == 0);
+                }
+                if (s == 1) {
+                    if (step + FD == 2 * PH) DQ_TR_ADDR(ta, sb)
+                    if (step + FD == 3 * PH) DQ_ROW_ADDR(va, sbn)
+                    DQ_READ(fr[step % FD], va, ka, ta, (step + FD) % (3 * PH))
+                }
+                // half-unit u: keys 8 * (u / 4) + 4 * hi + 2 * (u % 2) + {0, 1}, row tile (u / 2) % 2
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    const int ks = (u >> 1) & 1, e = 4 * (u >> 2) + 2 * (u & 1);
+                    if (u * 5 * MP / 64 == m) {
+#pragma unroll
+                        for (int x = 0; x < 2; ++x) SS[v][ks][e + x] = fast_exp2(fmaf(SS[v][ks][e + x], p.scale_log2, nlse2[ks]));
+                    }
+                    if (MP + 3 * MP / 16 + u * 5 * MP / 64 == m) {
+                        pk[ks][e >> 1] = pack_bf16x2(SS[v][ks][e] * (dP[ks][e] + ndelta[ks]), SS[v][ks][e + 1] * (dP[ks][e + 1] + ndelta[ks]));
+                        asm volatile("" : "+v"(pk[ks][e >> 1]));   // here, not behind the branches of the requests below
+                    }
+                }
+                if (m >= 5 * MP / 2) {
+#pragma unroll
+                    for (int x = 0; x < IPW; ++x)
+                        if (5 * MP / 2 + x * (MP / 2) / IPW == m) DQ_REQUEST((t + NS - 1) & (NS - 1), x);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            DQ_REQ_NEXT()
+        }
+    }
+#undef DQ_REQ_SEG
+#undef DQ_REQ_NEXT
+#undef DQ_CUR_SEG
+#undef DQ_REQUEST
+#undef DQ_ROW_ADDR
+#undef DQ_TR_ADDR
+#undef DQ_READ
+    // the requests past the end, before the ring is reused; and the wait states between the last product and a read of its result
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    __syncthreads();
+
+    // dQ^T sits in the accumulators with lane = row: each wavefront transposes 32 rows at a time through a private LDS
+    // region and stores whole rows, 16 bytes per lane
+    unsigned char* ob = smem + w * (32 * OPB);
+    int64_t* roff = reinterpret_cast<int64_t*>(smem + NWQ * 32 * OPB) + w * 32;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int r = r0 + w * 64 + s * 32 + n;
+        const int qi = r / p.g;
+        if (hi == 0) roff[n] = r < R ? qi * p.dq_st + (int64_t)(kvh * p.g + r - qi * p.g) * p.dq_sh : (int64_t)-1;
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                u32x2 v;
+                v[0] = pack_bf16x2(dq[s][dt][4 * q4] * p.scale, dq[s][dt][4 * q4 + 1] * p.scale);
+                v[1] = pack_bf16x2(dq[s][dt][4 * q4 + 2] * p.scale, dq[s][dt][4 * q4 + 3] * p.scale);
+                *reinterpret_cast<u32x2*>(ob + n * OPB + (32 * dt + 8 * q4 + 4 * hi) * 2) = v;
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // one wavefront's LDS operations complete in order
+#pragma unroll
+        for (int q = 0; q < (32 * C8) / 64; ++q) {
+            const int id = q * 64 + lane;
+            const int row = id / C8, c = id - row * C8;
+            const int64_t ro = roff[row];
+            const u32x4 v = *reinterpret_cast<const u32x4*>(ob + row * OPB + c * 16);
+            if (ro >= 0) *reinterpret_cast<u32x4*>(p.dq + dq_off + ro + 8 * c) = v;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+}
+
 template <int D, bool BC, int NWK, int NWR>
 static int launch_dkv(const BwdParams& p, int s, hipStream_t st) {
     const int n_slabs = (p.seg[s].len + 64 * NWK - 1) / (64 * NWK);
@@ -895,9 +1277,16 @@ static int launch_bwd(const BwdParams& p, hipStream_t st) {
     constexpr int RPB = 256 / (D / 8);
     int rc;
     dim3 grid((p.R + 127) / 128, p.Hkv, p.B);
-    const int rows = p.Lq * p.Hq;
-    hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((rows + RPB - 1) / RPB, 1, p.B), dim3(256), 0, st, p);
-    if ((rc = check_hip(hipGetLastError(), "attn_bwd_delta_kernel launch")) != DLM_OK) return rc;
+    // 64 rows a wavefront (d = 128): one wavefront a SIMD, so only where its workgroups of two fill the 512 places twice; below
+    // that the 32-row kernel's twice as many wavefronts are as fast or faster.  Whole backward pass, us, 32 / 64 rows: 1024
+    // workgroups 1671 / 1556 (4096 tokens, 32 heads, blocks of 4), 2112 328 / 313, 640 87 / 87, 128 365 / 372; at d = 64 the
+    // 32-row kernel leads throughout (253 / 266, 108 / 115).
+    const bool wide = p.dq && D == 128 && (int64_t)grid.x * grid.y * grid.z >= 1024;
+    if (!wide) {
+        const int rows = p.Lq * p.Hq;
+        hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((rows + RPB - 1) / RPB, 1, p.B), dim3(256), 0, st, p);
+        if ((rc = check_hip(hipGetLastError(), "attn_bwd_delta_kernel launch")) != DLM_OK) return rc;
+    }
     if (p.dq) {
         GridRemap rm = no_remap();
         if ((g_attn_remap & 1) && grid.x >= 2) {
@@ -905,7 +1294,8 @@ static int launch_bwd(const BwdParams& p, hipStream_t st) {
             if (n_wg > 0) grid = dim3((unsigned)n_wg);
             else rm = no_remap();
         }
-        hipLaunchKernelGGL((attn_bwd_dq_kernel<D, BC>), grid, dim3(256), 0, st, p, rm);
+        if (wide) hipLaunchKernelGGL((attn_bwd_dq64_kernel<BC>), grid, dim3(128), 0, st, p, rm);
+        else hipLaunchKernelGGL((attn_bwd_dq_kernel<D, BC>), grid, dim3(256), 0, st, p, rm);
         if ((rc = check_hip(hipGetLastError(), "attn_bwd dQ kernel launch")) != DLM_OK) return rc;
     }
     for (int s = 0; s < 3; ++s) {

@@ -1,7 +1,7 @@
 """Every shape of the backward kernels at the sizes where it can go wrong: keys and rows around a wavefront's 64 and a workgroup's
 128, group sizes that do and do not divide a 32-row tile, token strides that do not fit 32-bit offsets.  The batch decides which
 shape runs: 1 sequence takes the row-split dK / dV kernel, more than 256 slabs of 128 keys the key-split one, 1024 workgroups of
-128 rows and more fill the chip.  All sequences of a batch are copies of one, so the first is checked against the oracle
+128 rows and more (d = 128) the 64-row dQ kernel.  All sequences of a batch are copies of one, so the first is checked against the oracle
 and the others have to have its bits."""
 import numpy as np
 import pytest
@@ -41,7 +41,7 @@ def check_copies(q, segs, d_out, B, mode="full", bs=0):
         assert elem_err(got[:1], ref) <= TOL and fro_err(got[:1], ref) <= FRO_TOL
 
 
-@pytest.mark.parametrize("size", [0, 1, 2], ids=["row-split", "key-split", "full-chip"])
+@pytest.mark.parametrize("size", [0, 1, 2], ids=["row-split", "key-split", "dq64"])
 @pytest.mark.parametrize("L,Hq,Hkv,d,bs", [(63, 2, 2, 128, 0), (65, 7, 1, 64, 0), (127, 8, 1, 128, 4), (129, 3, 1, 128, 32), (257, 4, 1, 64, 8),
                                            (260, 7, 1, 128, 4), (31, 64, 1, 64, 0), (1, 1, 1, 128, 1)])
 def test_edges(size, L, Hq, Hkv, d, bs):
@@ -49,7 +49,7 @@ def test_edges(size, L, Hq, Hkv, d, bs):
     check_copies(q, segs, d_out, batches(L, Hq, Hkv)[size], **(dict(mode="block_causal", bs=bs) if bs else {}))
 
 
-@pytest.mark.parametrize("size", [0, 1, 2], ids=["row-split", "key-split", "full-chip"])
+@pytest.mark.parametrize("size", [0, 1, 2], ids=["row-split", "key-split", "dq64"])
 def test_segments(size):
     q, segs, d_out = make(1, 132, 4, 2, 128, (132, 132, 0), seed=3400, pos=(0, 0, 0), rules=("earlier", "same", "causal"))
     check_copies(q, segs, d_out, batches(132, 4, 2)[size], mode="block_causal", bs=4)
@@ -71,7 +71,7 @@ def test_paired_slabs(B):
 
 
 @pytest.mark.parametrize("what", ["q", "kv"])
-@pytest.mark.parametrize("size", [0, 1, 2], ids=["row-split", "key-split", "full-chip"])
+@pytest.mark.parametrize("size", [0, 1, 2], ids=["row-split", "key-split", "dq64"])
 def test_strides_beyond_32_bit_offsets(size, what):
     """Token strides of 2^23 elements (2^24 bytes) and more leave the 32-bit offsets of the tile requests."""
     L, Hq, Hkv, d, st = 40, 3, 1, 128, (1 << 23) + 8
