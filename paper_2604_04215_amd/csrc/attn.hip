@@ -831,6 +831,9 @@ _Pragma("unroll") \
 // Combines the nsplit partial results of every (sequence, head, query row) in a fixed order (split 0, 1, ...): with
 // M = max_s m_s and w_s = 2^(m_s - M), out = sum_s w_s o_s / sum_s w_s l_s and lse = (M + log2 sum_s w_s l_s) ln 2.
 // D / 4 threads per row (16 bytes of fp32 in, 8 bytes of bf16 out each), 256 / (D / 4) rows per workgroup.
+// A few microseconds of memory latency and nothing else: four splits' loads go out together.  Whole call, us, before / after
+// (loads of one split at a time): 1 x 32 / 8 heads x 8192 keys (16 splits) 30.0 / 26.7, 1 x 28 / 4 x 4096 24.7 / 21.5, 1 x 4 heads
+// of 64 x 2048 15.2 / 11.8, 4 x 32 / 8 x 4096 (4 splits) 26.8 / 25.7.
 template <int D>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
     constexpr int TPR = D / 4, RPW = 256 / TPR;
@@ -841,18 +844,36 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
     const int grp = (int)(row / p.R), r = (int)(row - (int64_t)grp * p.R);
     const int b = grp / p.Hkv, kvh = grp - b * p.Hkv;
     if (p.seq_active && p.seq_active[b] == 0) return;
+    // (past the last split it is loaded again and not used)
     float M = -INFINITY;
-    for (int s = 0; s < p.nsplit; ++s) M = fmaxf(M, p.part_ml[(s * rows_total + row) * 2]);
+    for (int s0 = 0; s0 < p.nsplit; s0 += 4) {
+        float ms[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ms[u] = p.part_ml[(min(s0 + u, p.nsplit - 1) * rows_total + row) * 2];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) M = fmaxf(M, ms[u]);
+    }
     float den = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < p.nsplit; ++s) {
-        const float ms = p.part_ml[(s * rows_total + row) * 2];
-        const float ls = p.part_ml[(s * rows_total + row) * 2 + 1];
-        const float wgt = (ms == -INFINITY) ? 0.f : fast_exp2(ms - M);
-        const f32x4 o = *reinterpret_cast<const f32x4*>(p.part_o + (s * rows_total + row) * D + 4 * c4);
-        den += wgt * ls;
+    for (int s0 = 0; s0 < p.nsplit; s0 += 4) {
+        float ms[4], ls[4];
+        f32x4 o[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] += wgt * o[e];
+        for (int u = 0; u < 4; ++u) {
+            const int64_t at = min(s0 + u, p.nsplit - 1) * rows_total + row;
+            ms[u] = p.part_ml[at * 2];
+            ls[u] = p.part_ml[at * 2 + 1];
+            o[u] = *reinterpret_cast<const f32x4*>(p.part_o + at * D + 4 * c4);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (s0 + u < p.nsplit) {
+                const float wgt = (ms[u] == -INFINITY) ? 0.f : fast_exp2(ms[u] - M);
+                den += wgt * ls[u];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] += wgt * o[u][e];
+            }
+        }
     }
     const float inv = den > 0.f ? 1.f / den : 0.f;
     const int i = r / p.g, hg = r - i * p.g;
