@@ -1075,6 +1075,20 @@ __global__ __launch_bounds__(256) void lmhead_reduce_kernel(LmParams p) {
     int M = p.M;
     int n_vt = p.n_vt;
     const f32x4* part2 = p.part2;
+    const bool ent = p.conf_mode == DLM_CONF_NEG_ENTROPY;
+    const bool second = p.sample || ent;
+    // The kernel is a chain of trips to memory.  The row's place in the output is fetched at once, and so are its partials where
+    // there are few (n_vt <= 256, one a thread) and no second layout: the row lies inside the workspace whatever the device's
+    // count says.  With many partials the rows past the count would cost more bandwidth than the trip saved.  V = 2048: 4.2 ->
+    // 2.8 us a launch; V = 126464 (494 partials) unchanged at 4.8.
+    const int place = (p.out_scatter && p.row_idx) ? p.row_idx[r] : r;
+    const bool early = n_vt <= 256 && p.alt_cap == 0;
+    f32x4 v0 = {-INFINITY, 0.f, -INFINITY, __int_as_float(0x7fffffff)};
+    f32x4 g0 = {-INFINITY, -INFINITY, __int_as_float(0x7fffffff), 0.f};
+    if (early && tid < n_vt) {
+        v0 = p.part[(int64_t)r * n_vt + tid];
+        if (second) g0 = part2[(int64_t)r * n_vt + tid];
+    }
     if (p.m_dev) {
         const int md = max(*p.m_dev, 0);
         M = min(M, md);
@@ -1084,14 +1098,18 @@ __global__ __launch_bounds__(256) void lmhead_reduce_kernel(LmParams p) {
         }
     }
     if (r >= M) return;
-    const bool ent = p.conf_mode == DLM_CONF_NEG_ENTROPY;
-    const bool second = p.sample || ent;
     const f32x4* row = p.part + (int64_t)r * n_vt;
     const f32x4* row2 = part2 + (int64_t)r * n_vt;
     Red tot{-INFINITY, 0.f, -INFINITY, 0x7fffffff};
     Smp sm{-INFINITY, -INFINITY, 0x7fffffff};
     float uent = 0.f;
-    for (int t0 = 0; t0 < n_vt; t0 += 1024) {
+    if (early) {
+        const Red o{v0[0], v0[1], v0[2], __float_as_int(v0[3])};
+        if (ent) uent = u_merge(tot, uent, o, g0[3]);
+        tot = red_merge(tot, o);
+        if (p.sample) sm = smp_merge(sm, Smp{g0[0], g0[1], __float_as_int(g0[2])});
+    }
+    for (int t0 = early ? n_vt : 0; t0 < n_vt; t0 += 1024) {
         f32x4 v[4], g[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
@@ -1113,6 +1131,7 @@ __global__ __launch_bounds__(256) void lmhead_reduce_kernel(LmParams p) {
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
+        if (off >= n_vt) continue;     // the other side holds no partial: merging it changes nothing
         const Red o = red_shfl_xor(tot, off);
         if (ent) uent = u_merge(tot, uent, o, shfl_xor(uent, off));
         tot = red_merge(tot, o);
@@ -1138,7 +1157,7 @@ __global__ __launch_bounds__(256) void lmhead_reduce_kernel(LmParams p) {
             tot = red_merge(tot, ro);
             sm = smp_merge(sm, Smp{g[0], g[1], __float_as_int(g[2])});
         }
-        const int64_t oidx = (p.out_scatter && p.row_idx) ? (int64_t)p.row_idx[r] : (int64_t)r;
+        const int64_t oidx = place;
         float conf;
         if (p.conf_mode == DLM_CONF_MARGIN) {
             // p(top-1) - p(top-2) = (1 - exp(z2nd - zmax)) / sum_v exp(z_v - zmax)
