@@ -375,7 +375,8 @@ __device__ __forceinline__ int64_t bw_offset(int i, int64_t stride) {
 __device__ __forceinline__ void bw_load_lds16(const void* src, uint32_t dst) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory");
 }
-// the same 16 bytes a lane at offset + delta of two operands (base0, base1: wave-uniform), to dst and dst + gap
+// the same 16 bytes a lane at offset + delta of two operands (base0, base1: wave-uniform and computed by scalar instructions: a
+// lane read just before would need wait states that the compiler does not see a need for), to dst and dst + gap
 __device__ __forceinline__ void bw_load_lds16_pair(const void* base0, const void* base1, uint32_t offset, uint32_t delta, uint32_t dst, uint32_t gap) {
     uint32_t o;
     asm volatile("s_mov_b32 m0, %3\n\tv_add_u32 %0, %2, %1\n\tglobal_load_lds_dwordx4 %0, %4\n\ts_add_u32 m0, %3, %6\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %5"
@@ -397,9 +398,9 @@ __device__ __forceinline__ void bw_mfma_acc(f32x16& c, bf16x8 a, bf16x8 b, bool 
 }
 
 // c = a * b (the first product of a chain: no register is zeroed for it).  The next reader of c is another product with one
-// in between, or far behind.
+// in between, or far behind; s_nop as above, should the compiler have to move an operand into place.
 __device__ __forceinline__ void bw_mfma_zero(f32x16& c, bf16x8 a, bf16x8 b) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
 }
 
 // dK and dV of one segment in one pass.  A wavefront owns 64 keys (two MFMA column tiles, K and V fragments and both
