@@ -372,18 +372,23 @@ __device__ __forceinline__ int64_t bw_offset(int i, int64_t stride) {
 // Memory to LDS, 16 or 4 bytes a lane, to consecutive places from a wave-uniform address on.  Asm, so that the compiler, which
 // cannot tell the ring's stages apart, does not wait for every request in flight before each transposing read; the
 // waits that are needed stand in the loop.  No registers are written.
+// Where the compiler takes a scalar operand from (it may be restored from a spill by a lane read right in front of the block) is not
+// known here, and a vector instruction has to stay two wait states behind a lane read of its scalar, a memory address
+// five.  So scalar operands are read by scalar instructions alone, for which the hardware waits, and addresses are what those wrote.
 __device__ __forceinline__ void bw_load_lds16(const void* src, uint32_t dst) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory");
 }
-// the same 16 bytes a lane at offset + delta of two operands (base0, base1: wave-uniform and computed by scalar instructions: a
-// lane read just before would need wait states that the compiler does not see a need for), to dst and dst + gap
-__device__ __forceinline__ void bw_load_lds16_pair(const void* base0, const void* base1, uint32_t offset, uint32_t delta, uint32_t dst, uint32_t gap) {
-    uint32_t o;
-    asm volatile("s_mov_b32 m0, %3\n\tv_add_u32 %0, %2, %1\n\tglobal_load_lds_dwordx4 %0, %4\n\ts_add_u32 m0, %3, %6\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %5"
-                 : "=&v"(o) : "v"(offset), "s"(__builtin_amdgcn_readfirstlane(delta)), "s"(__builtin_amdgcn_readfirstlane(dst)), "s"(base0), "s"(base1), "s"(gap) : "memory", "scc");
+// the same 16 bytes a lane at offset + delta of two operands (base0, base1: wave-uniform), to dst and dst + GAP
+template <int GAP>
+__device__ __forceinline__ void bw_load_lds16_pair(const void* base0, const void* base1, uint32_t offset, uint32_t delta, uint32_t dst) {
+    uint64_t a;
+    asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %1, %0\n\ts_add_u32 m0, %2, %5\n\ts_mov_b64 %0, %4\n\tglobal_load_lds_dwordx4 %1, %0"
+                 : "=&s"(a) : "v"(offset), "s"(__builtin_amdgcn_readfirstlane(dst)), "s"((uintptr_t)base0 + delta), "s"((uintptr_t)base1 + delta), "n"(GAP) : "memory", "scc");
 }
 __device__ __forceinline__ void bw_load_lds16(const void* base, uint32_t offset, uint32_t dst) {   // base: wave-uniform
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory");
+    uint64_t a;
+    asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %1, %0"
+                 : "=&s"(a) : "v"(offset), "s"(__builtin_amdgcn_readfirstlane(dst)), "s"(base) : "memory");
 }
 __device__ __forceinline__ void bw_load_lds4(const void* src, uint32_t dst) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(__builtin_amdgcn_readfirstlane(dst)) : "memory");
@@ -598,7 +603,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
             const int q_ = wk * IPW + (x);                                                               \
             const uint32_t dst_ = lds0 + (wr * NS + ist) * STAGE + q_ * BW_GP;                           \
             if (whole) {                                                                                 \
-                bw_load_lds16_pair(qt, gt, voff, ((q_ * RPI) >> gsh) * qst2 + ((q_ * RPI) & (g - 1)) * qsh2, dst_, IMG); \
+                bw_load_lds16_pair<IMG>(qt, gt, voff, ((q_ * RPI) >> gsh) * qst2 + ((q_ * RPI) & (g - 1)) * qsh2, dst_); \
             } else {                                                                                     \
             unsigned lo_ = lane;                                                                         \
             asm volatile("" : "+v"(lo_));                                                                \
@@ -1011,7 +1016,7 @@ __global__ __launch_bounds__(128, 1) void attn_bwd_dq64_kernel(BwdParams p, Grid
         const int q_ = w * IPW + (x);                                                                    \
         const uint32_t dst_ = lds0 + (stage) * STAGE + q_ * BW_GP;                                       \
         if (rleft >= 32 && rst < (1 << 23)) {                                                            \
-            bw_load_lds16_pair(rk, rv, voff, q_ * RPI * ((int)rst * 2), dst_, IMG);                      \
+            bw_load_lds16_pair<IMG>(rk, rv, voff, q_ * RPI * ((int)rst * 2), dst_);                      \
         } else {                                                                                         \
             const int64_t off_ = min(q_ * RPI + lane / C8, rleft - 1) * rst + c16 / 2;                   \
             bw_load_lds16(rk + off_, dst_);                                                              \
