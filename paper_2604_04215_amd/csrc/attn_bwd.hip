@@ -482,10 +482,10 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     const int hoff = (BC && srule == DLM_SEG_EARLIER_BLOCKS) ? p.bs : 0;
     const bool same = BC && srule == DLM_SEG_SAME_BLOCK;
     const int g = p.g;
-    // Row r of the group is query r / g, head r % g.  Inside a tile that starts at (query i0, head h0) row l is (h0 + l) / g queries
-    // on; (h0 + l + 1/2) / g is at least 1 / 2g from a whole number, so the product with the reciprocal truncates to the
-    // quotient (at most 32, errors below 2^-17 where g < 2^15 and below 2^-22, quotient 0 or 1, above).
-    const float inv_g = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(1.0f / (float)g)));
+    // Row r of the group is query r / g, head r % g.  Inside a tile that starts at (query i0, head h0) row l is on query i0 + 1 + u / g
+    // rounded down, u = h0 + l - g: on i0 where u < 0, and otherwise u < 31, where u * ceil(2^16 / g) / 2^16 rounds down to the same (the
+    // excess is below 31 / 2^16, u / g at least 1 / 31 short of the next whole number, or g > 31 and both are 0).
+    const int mul_g = (65536 + g - 1) / g;
     const uint16_t* const qb = p.q + q_off + (int64_t)(kvh * g) * p.q_sh;
     const uint16_t* const gb = p.dout + do_off + (int64_t)(kvh * g) * p.do_sh;
     // statistics: lanes 0..31 fetch LSE, lanes 32..63 delta of the tile's rows
@@ -591,10 +591,10 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     const int64_t dqt = regular ? (up ? di : -di) * p.q_st : 0;
     bool whole = regular && i0 >= 0 && i0 + qpt <= Lq;
 #define BW_ROW(l, i_, h_)                                                                                \
-    const int t_ = h0 + (l);                                                                             \
-    const int dv_ = (int)(((float)t_ + 0.5f) * inv_g);                                                   \
-    const int h_ = t_ - dv_ * g;                                                                         \
-    const int i_ = min(max(i0 + dv_, 0), Lq - 1);
+    const int u_ = h0 - g + (l);                                                                         \
+    const int dv_ = __mul24(max(u_, -1), mul_g) >> 16;                                                   \
+    const int h_ = u_ - dv_ * g;                                                                         \
+    const int i_ = min(max(i0 + 1 + dv_, 0), Lq - 1);
     // request x of a tile: x < IPW a group of Q rows and the same dO rows, x == IPW the statistics.  The lane number is made
     // opaque, so that the offsets are formed anew for each tile instead of being kept in registers the loop does not have.
 #define BW_REQUEST(x)                                                                                    \

@@ -97,3 +97,26 @@ def test_strides_beyond_32_bit_offsets(size, what):
         h = bf16_host(got.contiguous())
         assert (h == h[:1]).all()
         assert elem_err(h[:1], ref) <= TOL and fro_err(h[:1], ref) <= FRO_TOL
+
+
+def test_millions_of_heads_a_group():
+    """7 715 248 query heads on one KV head: the place of a row inside its group needs more than the 24 bits of an fp32 quotient.  Only
+    heads at a group's two ends have an upstream gradient, so the oracle needs those alone; the last tile of a query's heads runs into the
+    next query's."""
+    g, L, d = 7715248, 2, 64
+    q, segs, d_out = make(1, L, 4, 1, d, (0, L, 0), seed=3800)
+    heads = torch.tensor([0, 1, g - 2, g - 1], device=DEV)
+    gen = torch.Generator(device=DEV).manual_seed(3800)
+    qd = torch.randn((1, L, g, d), generator=gen, device=DEV, dtype=torch.bfloat16)
+    dod = torch.zeros_like(qd)
+    qd[:, :, heads], dod[:, :, heads] = bf16_dev(q), bf16_dev(d_out)
+    kd, vd = bf16_dev(segs[1].k), bf16_dev(segs[1].v)
+    out, dq, dk, dv = (torch.empty_like(x) for x in (qd, qd, kd, vd))
+    lse = torch.empty((1, g, L), dtype=torch.float32, device=DEV)
+    dlm.block_attn(qd, out, block=(kd, vd, 0), lse=lse)
+    ws = torch.empty(dlm.block_attn_bwd_workspace_bytes(L, g), dtype=torch.uint8, device=DEV)
+    dlm.block_attn_bwd(qd, out, dod, lse, dq, block=(kd, vd, 0), d_block=(dk, dv), workspace=ws)
+    rq, [(rk, rv)] = obw.attention_backward(q, [segs[1]], d_out)
+    assert int(torch.count_nonzero(dq)) == int(torch.count_nonzero(dq[:, :, heads]))
+    for got, ref in ((dq[:, :, heads], rq), (dk, rk), (dv, rv)):
+        assert elem_err(bf16_host(got), ref) <= TOL and fro_err(bf16_host(got), ref) <= FRO_TOL
