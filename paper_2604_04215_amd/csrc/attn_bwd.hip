@@ -715,8 +715,8 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
             }
             // Hidden scores become -inf (probability 0), on the tiles that hold some: rows outside [r_clear_lo, r_clear_hi) miss
             // a key of this wavefront, rows from R on do not exist
-            if (__any(own_lse == -INFINITY)) {        // rows that saw no key take +inf, which makes their probabilities 0
-                if (hi == 0 && own_lse == -INFINITY) stat[n] = INFINITY;
+            if (__any(!(own_lse > -INFINITY))) {      // rows that saw no key (or have no LSE: NaN) take +inf: probabilities 0
+                if (hi == 0 && !(own_lse > -INFINITY)) stat[n] = INFINITY;
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // one wavefront's LDS operations complete in order
             }
             if (rt * 32 < r_clear_lo || rt * 32 + 32 > r_clear_hi) {

@@ -120,3 +120,29 @@ def test_millions_of_heads_a_group():
     assert int(torch.count_nonzero(dq)) == int(torch.count_nonzero(dq[:, :, heads]))
     for got, ref in ((dq[:, :, heads], rq), (dk, rk), (dv, rv)):
         assert elem_err(bf16_host(got), ref) <= TOL and fro_err(bf16_host(got), ref) <= FRO_TOL
+
+
+@pytest.mark.parametrize("value", [float("-inf"), float("nan")])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("size", [0, 1, 2], ids=["row-split", "key-split", "dq64"])
+def test_rows_without_a_log_sum_exp(size, d, value):
+    """A row whose log-sum-exp is -inf (it saw no key) or NaN has no probabilities in any of the kernels: as if its upstream
+    gradient were 0."""
+    L, Hq, Hkv = 70, 4, 1
+    B = batches(L, Hq, Hkv)[size]
+    q, segs, d_out = make(1, L, Hq, Hkv, d, (0, L, 0), seed=3900)
+    rep = lambda x: bf16_dev(np.repeat(x, B, axis=0))
+    qd, kd, vd, dod = rep(q), rep(segs[1].k), rep(segs[1].v), rep(d_out)
+    out, dq, dk, dv = (torch.empty_like(x) for x in (qd, qd, kd, vd))
+    lse = torch.empty((B, Hq, L), dtype=torch.float32, device=DEV)
+    dlm.block_attn(qd, out, block=(kd, vd, 0), lse=lse)
+    for i, h in ((0, 0), (33, 1), (40, 3), (L - 1, 2)):
+        lse[:, h, i] = value
+        d_out[:, i, h] = 0
+    ws = torch.empty(dlm.block_attn_bwd_workspace_bytes(B * L, Hq), dtype=torch.uint8, device=DEV)
+    dlm.block_attn_bwd(qd, out, dod, lse, dq, block=(kd, vd, 0), d_block=(dk, dv), workspace=ws)
+    rq, [(rk, rv)] = obw.attention_backward(q, [segs[1]], d_out)
+    for got, ref in ((dq, rq), (dk, rk), (dv, rv)):
+        h = bf16_host(got)
+        assert (h == h[:1]).all()
+        assert elem_err(h[:1], ref) <= TOL and fro_err(h[:1], ref) <= FRO_TOL
