@@ -1308,11 +1308,13 @@ static int launch_bwd(const BwdParams& p, hipStream_t st) {
         if (!p.seg[s].dk || p.seg[s].len == 0) continue;
         // Key-split: two wavefronts of 64 keys, 512 such workgroups at a time.  With at most half of them, or with up to twice
         // as many that each walk many rows (sequences of unequal length, a causal mask: the longest decide), four wavefronts
-        // share a slab's row tiles instead, for a sum through LDS at the end.  Whole backward pass, us, key- / row-split:
-        // 256 workgroups 4757 / 3097, 64 721 / 327, 32 372 / 274; 320 with 4200 rows 328 / 244, 640 with 4800 426 / 366, with
-        // 600 rows 87 / 103; 1024 with 4096 rows 1671 / 1757.
+        // share a slab's row tiles instead, for a sum through LDS at the end, which few rows do not earn back, the fewer the
+        // more workgroups take turns on a CU.  Whole backward pass, us, key- / row-split: 256 workgroups 4757 / 3097, 64 721 / 327;
+        // 320 with 4200 rows 328 / 244, 640 with 4800 426 / 366, with 600 rows 87 / 103; 1024 with 4096 rows 1671 / 1757.  dK and dV
+        // alone, d = 64 and d = 128: 32 workgroups with 60 rows 10.9 / 15.8 and 14.8 / 18.9, 292 rows 20.8 / 20.1 and 29.5 / 27.9; 256
+        // with 292 rows 25.4 / 40.5 and 38.8 / 38.8, 512 rows 35.0 / 46.0 and 53.7 / 49.1, 1024 rows 52.8 / 55.7 and 77.5 / 63.4.
         const int64_t n_wg = (int64_t)((p.seg[s].len + 127) / 128) * p.Hkv * p.B;
-        const bool split = n_wg <= 256 || (n_wg < 1024 && p.R >= 2048);
+        const bool split = n_wg < 1024 && p.R >= (n_wg <= 128 ? 256 : n_wg <= 256 ? 512 : 2048);
         if (!split) rc = launch_dkv<D, BC, 2, 1>(p, s, st);
         else if constexpr (D == 64) rc = launch_dkv<D, BC, 1, 4>(p, s, st);
         else rc = launch_dkv<D, BC, 2, 2>(p, s, st);

@@ -1,7 +1,7 @@
 """Every shape of the backward kernels at the sizes where it can go wrong: keys and rows around a wavefront's 64 and a workgroup's
 128, group sizes that do and do not divide a 32-row tile, token strides that do not fit 32-bit offsets.  The batch decides which
-shape runs: 1 sequence takes the row-split dK / dV kernel, more than 256 slabs of 128 keys the key-split one, 1024 workgroups of
-128 rows and more (d = 128) the 64-row dQ kernel.  All sequences of a batch are copies of one, so the first is checked against the oracle
+shape runs: 1 sequence with 256 rows a KV head and more takes the row-split dK / dV kernel, fewer rows or more than 256 slabs of 128
+keys the key-split one, 1024 workgroups of 128 rows and more (d = 128) the 64-row dQ kernel.  All sequences of a batch are copies of one, so the first is checked against the oracle
 and the others have to have its bits."""
 import numpy as np
 import pytest
@@ -90,6 +90,15 @@ def test_segments(size):
     check_copies(q, segs, d_out, batches(40, 8, 2)[size])
 
 
+@pytest.mark.parametrize("L,Hq,Hkv", [(256, 1, 1), (255, 1, 1), (86, 6, 2), (85, 6, 2)])
+@pytest.mark.parametrize("d,bs", [(64, 0), (64, 4), (128, 0), (128, 32)])
+def test_around_the_fewest_rows_of_a_row_split(L, Hq, Hkv, d, bs):
+    """256 rows a KV head and the next fewer, with few, 128 and 129 slabs of 128 keys (where 512 rows would be needed)."""
+    for B in (1, 128 // ((L + 127) // 128 * Hkv), 128 // ((L + 127) // 128 * Hkv) + 1):
+        q, segs, d_out = make(1, L, Hq, Hkv, d, (0, L, 0), seed=3550 + L)
+        check_copies(q, segs, d_out, B, **(dict(mode="block_causal", bs=bs) if bs else {}))
+
+
 @pytest.mark.parametrize("B", [16, 32], ids=["row-split", "key-split"])
 def test_paired_slabs(B):
     """33 slabs of 64 keys (17 of 128), 1024 of them and more: the launch pairs the slabs of a block-causal segment.  The gradients
@@ -104,10 +113,10 @@ def test_paired_slabs(B):
 
 
 @pytest.mark.parametrize("what", ["q", "kv"])
-@pytest.mark.parametrize("size", [0, 1, 2], ids=["row-split", "key-split", "dq64"])
-def test_strides_beyond_32_bit_offsets(size, what):
+@pytest.mark.parametrize("size,Hq", [(0, 7), (0, 3), (1, 3), (2, 3)], ids=["row-split", "key-split-1", "key-split", "dq64"])
+def test_strides_beyond_32_bit_offsets(size, Hq, what):
     """Token strides of 2^23 elements (2^24 bytes) and more leave the 32-bit offsets of the tile requests."""
-    L, Hq, Hkv, d, st = 40, 3, 1, 128, (1 << 23) + 8
+    L, Hkv, d, st = 40, 1, 128, (1 << 23) + 8
     B = batches(L, Hq, Hkv)[size]
     q, segs, d_out = make(1, L, Hq, Hkv, d, (0, L, 0), seed=3700)
 
