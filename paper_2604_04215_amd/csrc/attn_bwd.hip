@@ -1286,8 +1286,14 @@ static int launch_bwd(const BwdParams& p, hipStream_t st) {
     // 64 rows a wavefront (d = 128): one wavefront a SIMD, so only where its workgroups of two fill the 512 places twice; below
     // that the 32-row kernel's twice as many wavefronts are as fast or faster.  Whole backward pass, us, 32 / 64 rows: 1024
     // workgroups 1671 / 1556 (4096 tokens, 32 heads, blocks of 4), 2112 328 / 313, 640 87 / 87, 128 365 / 372; at d = 64 the
-    // 32-row kernel leads throughout (253 / 266, 108 / 115).
-    const bool wide = p.dq && D == 128 && (int64_t)grid.x * grid.y * grid.z >= 1024;
+    // 32-row kernel leads throughout (253 / 266, 108 / 115).  And only where the rows see enough keys: nothing covers the start and
+    // end of a workgroup that has its SIMDs to itself.  dQ and delta alone, 2048 workgroups, all keys seen: 73 keys 57 / 68, 152 71 / 83,
+    // 256 119 / 123 and 108 / 108, 4096 workgroups with 256 keys 239 / 234, 512 331 / 311; under a block-causal mask, where half of
+    // the keys are seen, 152 keys 73 / 87, 256 117 / 126, 512 306 / 301.
+    int64_t keys = 0;
+    for (int s = 0; s < 3; ++s)
+        if (p.seg[s].rule != DLM_SEG_SAME_BLOCK) keys += p.seg[s].len;
+    const bool wide = p.dq && D == 128 && (int64_t)grid.x * grid.y * grid.z >= 1024 && keys >= (BC ? 384 : 256);
     if (!wide) {
         const int rows = p.Lq * p.Hq;
         hipLaunchKernelGGL((attn_bwd_delta_kernel<D>), dim3((rows + RPB - 1) / RPB, 1, p.B), dim3(256), 0, st, p);

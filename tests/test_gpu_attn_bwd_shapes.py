@@ -1,8 +1,9 @@
 """Every shape of the backward kernels at the sizes where it can go wrong: keys and rows around a wavefront's 64 and a workgroup's
 128, group sizes that do and do not divide a 32-row tile, token strides that do not fit 32-bit offsets.  The batch decides which
 shape runs: 1 sequence with 256 rows a KV head and more takes the row-split dK / dV kernel, fewer rows or more than 256 slabs of 128
-keys the key-split one, 1024 workgroups of 128 rows and more (d = 128) the 64-row dQ kernel.  All sequences of a batch are copies of one, so the first is checked against the oracle
-and the others have to have its bits."""
+keys the key-split one; 1024 workgroups of 128 rows and more with 256 keys and more (384 under a block-causal mask), d = 128, the 64-row
+dQ kernel.  All sequences of a batch are copies of one, so the first is checked against the oracle and the others have to have
+its bits."""
 import numpy as np
 import pytest
 import torch
@@ -22,18 +23,18 @@ def batches(L, Hq, Hkv):
     return [1, 256 // slabs + 1, (1024 + rows - 1) // rows]
 
 
-def error_bounds(q, segs, d_out, mode="full", bs=0):
+def error_bounds(q, segs, d_out, mode="full", bs=0, q_pos0=0):
     """Per element of (dQ, dK and dV of each segment): 6 standard deviations of the error that the roundings to bf16 leave (8 significant
     bits: independent, uniform within 2^-8 of the value or less, so of deviation u = 2^-8 / sqrt 3 or less), to first order:
       forward   O: the probabilities of its product and the result, u^2 (sum_j P^2 V^2 + O^2), so for delta = sum_c dO O
                 the sum of that times dO^2
       backward  dV: P in the product; dK, dQ: dS in the product, and delta, which shifts all dS of a row by P times its error; the results
-    The 32-bit sums, exponentials and log-sum-exps are off by some 1e-6 and do not show.  The largest error seen is 0.56 of this."""
+    The 32-bit sums, exponentials and log-sum-exps are off by some 1e-6 and do not show.  The largest error seen is 0.6 of this."""
     u = 2.0 ** -8 / 3 ** 0.5
     (B, Lq, Hq, d), f64 = q.shape, synth.bf16_bits_to_f64
     segs = [x for x in segs if x is not None]
     k, v = (np.concatenate([f64(x.k if what == "k" else x.v) for x in segs], axis=2)[0] for what in "kv")
-    g, scale, vis = Hq // k.shape[0], d ** -0.5, obw.visibility(Lq, segs, mask_mode=mode, bs=bs, q_pos0=0)
+    g, scale, vis = Hq // k.shape[0], d ** -0.5, obw.visibility(Lq, segs, mask_mode=mode, bs=bs, q_pos0=q_pos0)
     e_q, e_k, e_v = np.zeros((Lq, Hq, d)), np.zeros(k.shape), np.zeros(k.shape)
     grad_k, grad_v = np.zeros(k.shape), np.zeros(k.shape)
     for h in range(Hq):
@@ -64,12 +65,13 @@ def assert_close(got_u16, ref, bound):
     assert worst <= 1.0 and fro_err(got_u16, ref) <= FRO_TOL, (worst, fro_err(got_u16, ref))
 
 
-def check_copies(q, segs, d_out, B, mode="full", bs=0):
+def check_copies(q, segs, d_out, B, **mask):
     rep = lambda x: np.repeat(x, B, axis=0)
-    dq, grads = run_bwd(rep(q), [None if s is None else KV(rep(s.k), rep(s.v), s.pos0, s.rule) for s in segs], rep(d_out), mode=mode, bs=bs)
-    rdq, rg = obw.attention_backward(q, [s for s in segs if s is not None], d_out, mask_mode=mode, bs=bs)
+    dq, grads = run_bwd(rep(q), [None if s is None else KV(rep(s.k), rep(s.v), s.pos0, s.rule) for s in segs], rep(d_out), **mask)
+    rdq, rg = obw.attention_backward(q, [s for s in segs if s is not None], d_out, mask_mode=mask.get("mode", "full"),
+                                     **{x: mask[x] for x in mask if x != "mode"})
     pairs = [(dq, rdq)] + [(got, ref) for g, r in zip([g for g in grads if g is not None], rg) for got, ref in zip(g, r)]
-    for (got, ref), bound in zip(pairs, error_bounds(q, segs, d_out, mode, bs)):
+    for (got, ref), bound in zip(pairs, error_bounds(q, segs, d_out, **mask)):
         assert (got == got[:1]).all()
         assert_close(got[:1], ref, bound)
 
@@ -88,6 +90,26 @@ def test_segments(size):
     check_copies(q, segs, d_out, batches(132, 4, 2)[size], mode="block_causal", bs=4)
     q, segs, d_out = make(1, 40, 8, 2, 128, (33, 40, 70), seed=3500)
     check_copies(q, segs, d_out, batches(40, 8, 2)[size])
+
+
+@pytest.mark.parametrize("L,Hq,Hkv,bs", [(255, 1, 1, 0), (256, 2, 1, 0), (257, 1, 1, 0), (319, 3, 1, 0), (383, 7, 1, 4), (384, 2, 2, 32),
+                                         (415, 7, 1, 4), (450, 3, 1, 32)])
+def test_dq64_edges(L, Hq, Hkv, bs):
+    q, segs, d_out = make(1, L, Hq, Hkv, 128, (0, L, 0), seed=3250 + L)
+    check_copies(q, segs, d_out, batches(L, Hq, Hkv)[2], **(dict(mode="block_causal", bs=bs) if bs else {}))
+
+
+@pytest.mark.parametrize("lens,mask", [
+    ((150, 40, 70), {}), ((0, 40, 230), {}), ((300, 0, 0), {}), ((31, 40, 200), {}),
+    ((400, 40, 0), dict(mode="block_causal", bs=16, q_pos0=400)), ((385, 40, 64), dict(mode="block_causal", bs=7, q_pos0=385))])
+def test_dq64_segments(lens, mask):
+    q, segs, d_out = make(1, 40, 8, 2, 128, lens, seed=3260 + lens[0])
+    check_copies(q, segs, d_out, batches(40, 8, 2)[2], **mask)
+
+
+def test_dq64_block_diffusion():
+    q, segs, d_out = make(1, 388, 4, 2, 128, (388, 388, 0), seed=3270, pos=(0, 0, 0), rules=("earlier", "same", "causal"))
+    check_copies(q, segs, d_out, batches(388, 4, 2)[2], mode="block_causal", bs=4)
 
 
 @pytest.mark.parametrize("L,Hq,Hkv", [(256, 1, 1), (255, 1, 1), (86, 6, 2), (85, 6, 2)])
@@ -113,12 +135,14 @@ def test_paired_slabs(B):
 
 
 @pytest.mark.parametrize("what", ["q", "kv"])
-@pytest.mark.parametrize("size,Hq", [(0, 7), (0, 3), (1, 3), (2, 3)], ids=["row-split", "key-split-1", "key-split", "dq64"])
-def test_strides_beyond_32_bit_offsets(size, Hq, what):
-    """Token strides of 2^23 elements (2^24 bytes) and more leave the 32-bit offsets of the tile requests."""
+@pytest.mark.parametrize("size,Hq,P", [(0, 7, 0), (0, 3, 0), (1, 3, 0), (2, 3, 0), (2, 3, 256)], ids=["row-split", "key-split-1", "key-split", "dq32", "dq64"])
+def test_strides_beyond_32_bit_offsets(size, Hq, P, what):
+    """Token strides of 2^23 elements (2^24 bytes) and more leave the 32-bit offsets of the tile requests (a prefix of P keys has
+    none of them: it only makes enough keys)."""
     L, Hkv, d, st = 40, 1, 128, (1 << 23) + 8
     B = batches(L, Hq, Hkv)[size]
-    q, segs, d_out = make(1, L, Hq, Hkv, d, (0, L, 0), seed=3700)
+    q, segs, d_out = make(1, L, Hq, Hkv, d, (P, L, 0), seed=3700)
+    prefix = tuple(bf16_dev(np.repeat(x, B, axis=0)) for x in (segs[0].k, segs[0].v)) + (0,) if P else None
 
     def spread(x):        # [1, L, H, d] -> B copies with token stride st, side by side inside it
         H = x.shape[2]
@@ -130,12 +154,13 @@ def test_strides_beyond_32_bit_offsets(size, Hq, what):
     kd, vd, dk, dv = (wide_kv(bf16_dev(x)) for x in (segs[1].k, segs[1].v, segs[1].k, segs[1].v))
     out = torch.empty((B, L, Hq, d), dtype=torch.bfloat16, device=DEV)
     lse = torch.empty((B, Hq, L), dtype=torch.float32, device=DEV)
-    dlm.block_attn(qd, out, block=(kd, vd, 0), lse=lse)
+    dlm.block_attn(qd, out, prefix=prefix, block=(kd, vd, P), lse=lse)
     dq = torch.empty_like(out)
     ws = torch.empty(dlm.block_attn_bwd_workspace_bytes(B * L, Hq), dtype=torch.uint8, device=DEV)
-    dlm.block_attn_bwd(qd, out, dod, lse, dq, block=(kd, vd, 0), d_block=(dk, dv), workspace=ws)
-    rq, [(rk, rv)] = obw.attention_backward(q, [segs[1]], d_out)
-    for got, ref, bound in zip((dq, dk, dv), (rq, rk, rv), error_bounds(q, [segs[1]], d_out)):
+    dlm.block_attn_bwd(qd, out, dod, lse, dq, prefix=prefix, block=(kd, vd, P), d_block=(dk, dv), workspace=ws)
+    rq, grads = obw.attention_backward(q, segs, d_out)
+    bounds = error_bounds(q, segs, d_out)
+    for got, ref, bound in zip((dq, dk, dv), (rq, *grads[-1]), (bounds[0], *bounds[-2:])):
         h = bf16_host(got.contiguous())
         assert (h == h[:1]).all()
         assert_close(h[:1], ref, bound)
@@ -170,7 +195,7 @@ def test_millions_of_heads_a_group():
 def test_rows_without_a_log_sum_exp(size, d, value):
     """A row whose log-sum-exp is -inf (it saw no key) or NaN has no probabilities in any of the kernels: as if its upstream
     gradient were 0."""
-    L, Hq, Hkv = 70, 4, 1
+    L, Hq, Hkv = 260, 4, 1
     B = batches(L, Hq, Hkv)[size]
     q, segs, d_out = make(1, L, Hq, Hkv, d, (0, L, 0), seed=3900)
     rep = lambda x: bf16_dev(np.repeat(x, B, axis=0))
