@@ -191,7 +191,7 @@ def test_full_size_training_shape_sampled_against_oracle():
 @pytest.mark.parametrize("B,Hkv,g,L", [(1, 1, 2, 600), (1, 3, 4, 300), (4, 2, 2, 520)])
 def test_xcd_grouped_grids_give_the_plain_grids_bits(B, Hkv, g, L):
     """Group counts 1, 3, 8: the 1-D grids of the dQ and dK / dV passes against the plain ones, bit for bit, and the
-    oracle's gradients; 520 and 600 keys make 5 slabs, so block-causal slabs are paired (second one walked upwards)."""
+    oracle's gradients."""
     for mode, bs in (("full", 0), ("block_causal", 8)):
         q, segs, d_out = make(B, L, Hkv * g, Hkv, 64, (0, L, 0), seed=1200 + L)
         res = []

@@ -12,7 +12,7 @@ from oracle import KV
 from oracle import backward as obw
 from paper_2604_04215_amd import binding as dlm
 from paper_2604_04215_amd import synth
-from gpu_util import DEV, bf16_dev, bf16_host
+from gpu_util import DEV, GuardedWorkspace, bf16_dev, bf16_host, dev, rnd
 from test_gpu_attn_bwd import FRO_TOL, fro_err, make, run_bwd
 
 pytestmark = pytest.mark.gpu
@@ -123,15 +123,127 @@ def test_around_the_fewest_rows_of_a_row_split(L, Hq, Hkv, d, bs):
 
 @pytest.mark.parametrize("B", [16, 32], ids=["row-split", "key-split"])
 def test_paired_slabs(B):
-    """33 slabs of 64 keys (17 of 128), 1024 of them and more: the launch pairs the slabs of a block-causal segment.  The gradients
-    against the same sequence by itself (no pairs): two bf16 results whose sums over rows differ in order."""
+    """33 slabs of 64 keys (17 of 128), 1024 of them and more: the launch pairs the slabs of a block-causal segment."""
     q, segs, d_out = make(1, 2100, 2, 2, 64, (0, 2100, 0), seed=3600)
+    check_copies(q, segs, d_out, B, mode="block_causal", bs=32)
+
+
+@pytest.mark.parametrize("L,g,bs,rules", [(388, 4, 4, None), (520, 7, 8, None), (642, 4, 32, None), (388, 4, 4, ("earlier", "same", "causal")),
+                                          (516, 7, 4, ("earlier", "same", "causal"))])
+def test_paired_slabs_at_128(L, g, bs, rules):
+    """4, 5 and 6 slabs of 128 keys (odd: the middle one has no partner), 1024 of them and more; the grouped 1-D grid and the plain one
+    give the same bits."""
+    q, segs, d_out = make(1, L, g, 1, 128, (L, L, 0) if rules else (0, L, 0), seed=3650 + L, **(dict(pos=(0, 0, 0), rules=rules) if rules else {}))
+    B = 1024 // ((L + 127) // 128) + 1
+    check_copies(q, segs, d_out, B, mode="block_causal", bs=bs)
     rep = lambda x: np.repeat(x, B, axis=0)
-    dq, grads = run_bwd(rep(q), [None, KV(rep(segs[1].k), rep(segs[1].v), 0), None], rep(d_out), mode="block_causal", bs=32)
-    dq1, grads1 = run_bwd(q, segs, d_out, mode="block_causal", bs=32)
-    for a, r in ((dq, dq1), (grads[1][0], grads1[1][0]), (grads[1][1], grads1[1][1])):
-        assert (a == a[:1]).all()
-        assert fro_err(a[:1], synth.bf16_bits_to_f64(r).reshape(r.shape)) <= FRO_TOL
+    res = []
+    try:
+        for remap in (7, 0):
+            dlm.set_option("attn_remap", remap)
+            res.append(run_bwd(rep(q), [None if x is None else KV(rep(x.k), rep(x.v), x.pos0, x.rule) for x in segs], rep(d_out), mode="block_causal", bs=bs))
+    finally:
+        dlm.set_option("attn_remap", 7)
+    for (x, y) in zip(res[0][1], res[1][1]):
+        assert x is y is None or all(np.array_equal(a, r) for a, r in zip(x, y))
+    assert np.array_equal(res[0][0], res[1][0])
+
+
+@pytest.mark.parametrize("size", [0, 1, 2], ids=["row-split", "key-split", "dq64"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_rows_that_see_no_key(size, d):
+    """The earlier blocks alone: the first block's rows see nothing."""
+    q, segs, d_out = make(1, 388, 4, 1, d, (388, 0, 0), seed=3690, pos=(0, 0, 0), rules=("earlier", "same", "causal"))
+    check_copies(q, segs, d_out, batches(388, 4, 1)[size], mode="block_causal", bs=4)
+
+
+class Backwards:
+    """The tokens of x [B, L, H, d] as the binding sees a tensor, last one first in memory: a negative token stride."""
+    def __init__(self, x):
+        self.flipped = x.flip(1).contiguous()
+        self.shape, self.dtype, self.is_cuda = x.shape, x.dtype, x.is_cuda
+        self.dim, self.numel = x.dim, x.numel
+
+    def stride(self, i):
+        st = self.flipped.stride(i)
+        return -st if i == 1 else st
+
+    def data_ptr(self):
+        return self.flipped[:, -1].data_ptr()
+
+
+@pytest.mark.parametrize("size", [0, 1, 2], ids=["row-split", "key-split", "dq64"])
+@pytest.mark.parametrize("layout", ["heads first", "heads first, backwards", "backwards"])
+@pytest.mark.parametrize("g,d,bs", [(4, 128, 0), (7, 128, 4), (4, 64, 4), (7, 64, 0)])
+def test_layouts(size, layout, g, d, bs):
+    """Q and dO laid out differently (with 4 heads a group a tile still holds whole queries) and tokens backwards in memory."""
+    L = 386
+    B = batches(L, g, 1)[size]
+    mask = dict(mask_mode=dlm.MASK_BLOCK_CAUSAL, block_size=bs) if bs else {}
+    q, segs, d_out = make(1, L, g, 1, d, (0, L, 0), seed=3720 + L)
+    rep = lambda x: bf16_dev(np.repeat(x, B, axis=0))
+    qd, kd, vd, dod = rep(q), rep(segs[1].k), rep(segs[1].v), rep(d_out)
+    out, dk, dv = (torch.empty_like(x) for x in (qd, kd, vd))
+    lse = torch.empty((B, g, L), dtype=torch.float32, device=DEV)
+    dlm.block_attn(qd, out, block=(kd, vd, 0), lse=lse, **mask)
+    dq = torch.empty_like(qd)
+    if "heads first" in layout:
+        dod = dod.transpose(1, 2).contiguous().transpose(1, 2)
+    if "backwards" in layout:
+        qd, out = Backwards(qd), Backwards(out)
+        dod = dod if "heads first" in layout else Backwards(dod)
+    ws = torch.empty(dlm.block_attn_bwd_workspace_bytes(B * L, g), dtype=torch.uint8, device=DEV)
+    dlm.block_attn_bwd(qd, out, dod, lse, dq, block=(kd, vd, 0), d_block=(dk, dv), workspace=ws, **mask)
+    oracle_mask = dict(mode="block_causal", bs=bs) if bs else {}
+    rq, [(rk, rv)] = obw.attention_backward(q, [segs[1]], d_out, mask_mode=oracle_mask.get("mode", "full"), bs=bs)
+    for got, ref, bound in zip((dq, dk, dv), (rq, rk, rv), error_bounds(q, segs, d_out, **oracle_mask)):
+        h = bf16_host(got)
+        assert (h == h[:1]).all()
+        assert_close(h[:1], ref, bound)
+
+
+PACKED = (400, 1, 65, 0, 129, 63, 257, 33)
+
+
+@pytest.mark.parametrize("groups", [10, 19], ids=["single", "paired"])
+@pytest.mark.parametrize("g,bs", [(2, 0), (7, 0), (2, 4), (7, 32)])
+def test_packed(groups, g, bs):
+    """Unequal sequences, many enough for the 64-row dQ and the key-split dK / dV kernels (80 of them: 1120 workgroups of 128 rows, 640
+    slabs) and, under the block-causal mask, for paired slabs (152: 1216).  The lengths come in groups of 8, the same 8
+    sequences each time and in another order."""
+    Hkv, d = 2, 128
+    Hq = g * Hkv
+    starts = np.concatenate([[0], np.cumsum(PACKED)])
+    n = int(starts[-1])
+    q, k, v, d_out = rnd(41, (n, Hq, d)), rnd(42, (n, Hkv, d)), rnd(43, (n, Hkv, d)), rnd(44, (n, Hq, d))
+    which = np.concatenate([np.roll(np.arange(8), i) for i in range(groups)])
+    lens = np.array(PACKED)[which]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    take = np.concatenate([np.arange(starts[s], starts[s + 1]) for s in which])
+    qd, kd, vd, dod = (bf16_dev(x[take]) for x in (q, k, v, d_out))
+    T = len(take)
+    mask = dict(mask_mode=dlm.MASK_BLOCK_CAUSAL, block_size=bs) if bs else {}
+    out, (dq, dk, dv) = torch.empty_like(qd), (torch.full_like(x, float("nan")) for x in (qd, kd, vd))
+    lse = torch.empty((Hq, T), dtype=torch.float32, device=DEV)
+    dlm.varlen_attn(qd, kd, vd, out, dev(cu), max(PACKED), lse=lse, **mask)
+    gw = GuardedWorkspace(dlm.block_attn_bwd_workspace_bytes(T, Hq))
+    dlm.block_attn_bwd(qd, out, dod, lse, dq, block=(kd, vd), d_block=(dk, dv), cu_seqlens=dev(cu), max_seqlen=max(PACKED), workspace=gw.ws, **mask)
+    gw.check()
+    got = [bf16_host(x) for x in (dq, dk, dv)]
+    oracle_mask = dict(mode="block_causal", bs=bs) if bs else {}
+    heads_first = lambda x: np.ascontiguousarray(x.transpose(1, 0, 2))[None]
+    for s in range(8):
+        if PACKED[s] == 0:
+            continue
+        own = slice(starts[s], starts[s + 1])
+        q1, seg, do1 = q[own][None], KV(heads_first(k[own]), heads_first(v[own]), 0), d_out[own][None]
+        rq, [(rk, rv)] = obw.attention_backward(q1, [seg], do1, mask_mode=oracle_mask.get("mode", "full"), bs=bs)
+        bounds = error_bounds(q1, [seg], do1, **oracle_mask)
+        at = [i for i in range(len(which)) if which[i] == s]
+        for x, ref, bound, kv in zip(got, (rq, rk, rv), bounds, (False, True, True)):
+            first = x[cu[at[0]]:cu[at[0] + 1]]
+            assert all(np.array_equal(x[cu[i]:cu[i + 1]], first) for i in at)
+            assert_close(heads_first(first) if kv else first[None], ref, bound)
 
 
 @pytest.mark.parametrize("what", ["q", "kv"])
