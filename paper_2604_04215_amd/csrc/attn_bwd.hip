@@ -420,8 +420,10 @@ __device__ __forceinline__ void bw_mfma_zero(f32x16& c, bf16x8 a, bf16x8 b) {
 //     dV and the first of dK (vector and matrix instructions of one wavefront overlap, of different ones do not);
 //   * tiles go from memory to LDS without registers (global_load_lds) through a ring of four, two tiles ahead, and the
 //     next tile's first fragments are read before this tile's last MFMAs: the barrier sits between;
-//   * one wavefront issues one instruction at a time: 4.0 vector and 1.9 scalar instructions per MFMA, after 7.5 and 1.7 with
-//     LDS addresses, row divisions and statistics formed per read (2.6 -> 1.9 ms below).
+//   * one wavefront issues one instruction at a time: 3.9 vector and 2.3 scalar instructions per MFMA, after 7.5 and 1.7 with
+//     LDS addresses, row divisions and statistics formed per read (2.6 -> 1.9 ms below).  At d = 128 the compiler still spills: 18
+//     or 50 vector registers outside the tile loop (with the full mask one of them comes back once a tile), and 52 - 65 scalars to
+//     lanes of vector registers, some 20 of which the loop reads back a tile, most for request paths the launch does not take.
 // Measured (8 x 4096 tokens, 32 / 8 heads of 128, blocks of 4): 1.86 - 1.95 ms = 1.17 PFLOP/s of products, two passes with 32
 // keys a wavefront 4.28 ms; 128 packed sequences of 64 k tokens, 32 heads: 1.73 ms, before 2.86.  MFMA pipes busy 0.52 at
 // 2.2 GHz: with all loads, waits and vector work taken out the loop still runs at 1.35 PFLOP/s, the power limit on such data.

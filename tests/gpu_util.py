@@ -24,7 +24,7 @@ def attn_rel_err(got_u16: np.ndarray, ref: np.ndarray) -> float:
     """max |got - ref| / max(|ref|, rms of the reference row over head_dim): the 2e-2 criterion.
 
     Why the floor is the row rms: the kernel rounds every probability p_j to bf16 (relative error
-    <= 2^-9) before the second product and rounds the output to bf16, so an output element carries an
+    <= 2^-8) before the second product and rounds the output to bf16, so an output element carries an
     absolute error of about 2^-9 * sqrt(sum_j p_j^2 v_jc^2), which scales with the row's typical
     magnitude and not with the element's own value; an element that happens to be near zero has no
     meaningful relative error of its own."""

@@ -3,7 +3,7 @@
 The forward results the gradient kernels consume (O and LSE) come from dlm_block_attn itself, as in training.
 Two bounds per gradient tensor:
   * element-wise, the forward pass's metric |got - ref| / max(|ref|, rms of the reference row over head_dim),
-    at 4e-2: besides the bf16 rounding of dS (2^-9) and of the result, delta = rowsum(dO * O) is formed from the
+    at 4e-2: besides the bf16 rounding of dS (up to 2^-8) and of the result, delta = rowsum(dO * O) is formed from the
     bf16 forward output, and for a row that sees only a few keys that error (about sqrt(d) * 2^-9 * |O|) shifts
     every dS of the row the same way; a float64 emulation of exactly these roundings gives 2.3e-2 on the worst
     case here (block size 7, first block), of which 1.4e-2 is the delta term;
