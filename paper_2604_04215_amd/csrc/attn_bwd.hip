@@ -429,8 +429,9 @@ __device__ __forceinline__ void bw_mfma_zero(f32x16& c, bf16x8 a, bf16x8 b) {
 // 2.2 GHz: with all loads, waits and vector work taken out the loop still runs at 1.35 PFLOP/s, the power limit on such data.
 template <int D, bool BC, int NWK, int NWR>
 __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdParams p, int sidx, int n_slabs, int pair, GridRemap rm) {
-    constexpr int NS = 4, FD = D == 128 ? 2 : 4;       // ring stages; fragments read ahead (at d = 128 all that registers allow)
-    constexpr int AHEAD = NWK == 1 ? 3 : 2;            // tiles requested ahead: a ring that is the wavefront's own needs no slack
+    constexpr int NS = D == 128 && NWK * NWR == 1 ? 2 : 4;   // ring stages: four such rings fit a CU, one a SIMD
+    constexpr int FD = D == 128 ? 2 : 4;               // fragments read ahead (at d = 128 all that registers allow)
+    constexpr int AHEAD = NWK == 1 ? NS - 1 : 2;       // tiles requested ahead: a ring that is the wavefront's own needs no slack
     constexpr int P = D * 2, C8 = D / 8;
     constexpr int RPI = 64 / C8, IPW = 32 / RPI / NWK; // rows per request, requests per wavefront, operand and tile
     constexpr int IMG = 32 / RPI * BW_GP;              // one operand's tile image
@@ -1323,7 +1324,13 @@ static int launch_bwd(const BwdParams& p, hipStream_t st) {
         // with 292 rows 25.4 / 40.5 and 38.8 / 38.8, 512 rows 35.0 / 46.0 and 53.7 / 49.1, 1024 rows 52.8 / 55.7 and 77.5 / 63.4.
         const int64_t n_wg = (int64_t)((p.seg[s].len + 127) / 128) * p.Hkv * p.B;
         const bool split = n_wg < 1024 && p.R >= (n_wg <= 128 ? 256 : n_wg <= 256 ? 512 : 2048);
-        if (!split) rc = launch_dkv<D, BC, 2, 1>(p, s, st);
+        // One wavefront a workgroup where a second one would have no keys: four such workgroups fit a CU, at d = 128 with a ring of
+        // two tiles, which is slower over many tiles while two wavefronts a workgroup fit the chip at once.  dK and dV alone, us, two /
+        // one: 4096 workgroups with 8 keys and rows 56 / 36 (d = 64) and 86 / 48 (d = 128), 64 keys and 448 rows 293 / 236 and 489 /
+        // 426; 512 with 64 keys and 448 rows, d = 128, 63 / 65.
+        const bool one = p.seg[s].len <= 64 && (D == 64 || n_wg > 512 || p.R <= 128);
+        if (!split && one) rc = launch_dkv<D, BC, 1, 1>(p, s, st);
+        else if (!split) rc = launch_dkv<D, BC, 2, 1>(p, s, st);
         else if constexpr (D == 64) rc = launch_dkv<D, BC, 1, 4>(p, s, st);
         else rc = launch_dkv<D, BC, 2, 2>(p, s, st);
         if (rc != DLM_OK) return rc;

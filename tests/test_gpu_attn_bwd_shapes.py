@@ -1,9 +1,9 @@
 """Every shape of the backward kernels at the sizes where it can go wrong: keys and rows around a wavefront's 64 and a workgroup's
 128, group sizes that do and do not divide a 32-row tile, token strides that do not fit 32-bit offsets.  The batch decides which
 shape runs: 1 sequence with 256 rows a KV head and more takes the row-split dK / dV kernel, fewer rows or more than 256 slabs of 128
-keys the key-split one; 1024 workgroups of 128 rows and more with 256 keys and more (384 under a block-causal mask), d = 128, the 64-row
-dQ kernel.  All sequences of a batch are copies of one, so the first is checked against the oracle and the others have to have
-its bits."""
+keys the key-split one, with at most 64 keys one wavefront a workgroup of it; 1024 workgroups of 128 rows and more with 256 keys and
+more (384 under a block-causal mask), d = 128, the 64-row dQ kernel.  All sequences of a batch are copies of one, so the first is
+checked against the oracle and the others have to have its bits."""
 import numpy as np
 import pytest
 import torch
@@ -110,6 +110,22 @@ def test_dq64_segments(lens, mask):
 def test_dq64_block_diffusion():
     q, segs, d_out = make(1, 388, 4, 2, 128, (388, 388, 0), seed=3270, pos=(0, 0, 0), rules=("earlier", "same", "causal"))
     check_copies(q, segs, d_out, batches(388, 4, 2)[2], mode="block_causal", bs=4)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L,Hq,Hkv,bs", [(1, 1, 1, 0), (31, 2, 2, 0), (33, 3, 1, 4), (63, 8, 1, 0), (64, 7, 1, 32), (64, 1, 1, 4), (65, 2, 1, 0)])
+def test_at_most_64_keys(d, L, Hq, Hkv, bs):
+    """513 (sequence, KV head) pairs and more: one wavefront a workgroup up to 64 keys; 1 to 16 tiles of 32 rows."""
+    q, segs, d_out = make(1, L, Hq, Hkv, d, (0, L, 0), seed=3300 + L)
+    check_copies(q, segs, d_out, 513 // Hkv + 1, **(dict(mode="block_causal", bs=bs) if bs else {}))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_at_most_64_keys_a_segment(d):
+    q, segs, d_out = make(1, 60, 4, 1, d, (60, 60, 0), seed=3310, pos=(0, 0, 0), rules=("earlier", "same", "causal"))
+    check_copies(q, segs, d_out, 520, mode="block_causal", bs=4)
+    q, segs, d_out = make(1, 40, 4, 1, d, (33, 40, 70), seed=3320)
+    check_copies(q, segs, d_out, 520)
 
 
 @pytest.mark.parametrize("L,Hq,Hkv", [(256, 1, 1), (255, 1, 1), (86, 6, 2), (85, 6, 2)])
