@@ -1068,6 +1068,11 @@ __global__ __launch_bounds__(64 * WV * WH) void lmhead_pair_kernel(LmParams p) {
 // One workgroup per row: merge the per-vocabulary-tile partials (contiguous per row) in a fixed order: every thread
 // takes the tiles t = tid, tid + 256, ... (all loads issued before the first merge), then a fixed tree over the
 // lanes and the four wavefronts.  The merge is associative and its tie rule (lowest index) does not depend on order.
+// The kernel is a chain of trips to memory.  AHEAD: the row's place in the output is fetched beside the device's count, and so are
+// its partials where there are few (n_vt <= 256, one a thread) and no second layout: the row lies inside the workspace
+// whatever the count says.  With many partials the rows past the count would cost more bandwidth than the trip saved.  V = 2048:
+// 4.2 -> 3.3 us a launch, 361 -> 350 a block of 15 steps; V = 126464 (494 partials) unchanged at 4.8.
+template <bool AHEAD>
 __global__ __launch_bounds__(256) void lmhead_reduce_kernel(LmParams p) {
     __shared__ f32x4 s_red[4], s_smp[4];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -1077,18 +1082,17 @@ __global__ __launch_bounds__(256) void lmhead_reduce_kernel(LmParams p) {
     const f32x4* part2 = p.part2;
     const bool ent = p.conf_mode == DLM_CONF_NEG_ENTROPY;
     const bool second = p.sample || ent;
-    // The kernel is a chain of trips to memory.  The row's place in the output is fetched at once, and so are its partials where
-    // there are few (n_vt <= 256, one a thread) and no second layout: the row lies inside the workspace whatever the device's
-    // count says.  With many partials the rows past the count would cost more bandwidth than the trip saved.  V = 2048: 4.2 ->
-    // 3.3 us a launch, 361 -> 350 a block of 15 steps; V = 126464 (494 partials) unchanged at 4.8.
-    const int place = (p.out_scatter && p.row_idx) ? p.row_idx[r] : r;
-    const bool early = n_vt <= 256 && p.alt_cap == 0;
+    const bool scatter = p.out_scatter && p.row_idx;
+    const bool few = n_vt <= 256 && p.alt_cap == 0;
+    int place = AHEAD && scatter ? p.row_idx[r] : r;
     f32x4 v0 = {-INFINITY, 0.f, -INFINITY, __int_as_float(0x7fffffff)};
     f32x4 g0 = {-INFINITY, -INFINITY, __int_as_float(0x7fffffff), 0.f};
-    if (early && tid < n_vt) {
+    if (AHEAD && few && tid < n_vt) {
         v0 = p.part[(int64_t)r * n_vt + tid];
         if (second) g0 = part2[(int64_t)r * n_vt + tid];
     }
+    // (without AHEAD the arguments at least come with the count, not in a trip of their own behind it)
+    if (!AHEAD) asm volatile("" ::"s"(n_vt), "s"(part2), "s"(p.part), "s"(p.row_idx), "s"(p.out_scatter), "s"(p.sample), "s"(p.conf_mode));
     if (p.m_dev) {
         const int md = max(*p.m_dev, 0);
         M = min(M, md);
@@ -1098,18 +1102,27 @@ __global__ __launch_bounds__(256) void lmhead_reduce_kernel(LmParams p) {
         }
     }
     if (r >= M) return;
+    if (!AHEAD) {
+        int zero = 0;
+        asm volatile("" : "+v"(zero));       // by a vector load, which does not hold up the scalar ones
+        if (scatter) place = p.row_idx[r + zero];
+        if (few && tid < n_vt) {
+            v0 = p.part[(int64_t)r * n_vt + tid];
+            if (second) g0 = part2[(int64_t)r * n_vt + tid];
+        }
+    }
     const f32x4* row = p.part + (int64_t)r * n_vt;
     const f32x4* row2 = part2 + (int64_t)r * n_vt;
     Red tot{-INFINITY, 0.f, -INFINITY, 0x7fffffff};
     Smp sm{-INFINITY, -INFINITY, 0x7fffffff};
     float uent = 0.f;
-    if (early) {
+    if (few) {
         const Red o{v0[0], v0[1], v0[2], __float_as_int(v0[3])};
         if (ent) uent = u_merge(tot, uent, o, g0[3]);
         tot = red_merge(tot, o);
         if (p.sample) sm = smp_merge(sm, Smp{g0[0], g0[1], __float_as_int(g0[2])});
     }
-    for (int t0 = early ? n_vt : 0; t0 < n_vt; t0 += 1024) {
+    for (int t0 = few ? n_vt : 0; t0 < n_vt; t0 += 1024) {
         f32x4 v[4], g[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
@@ -1410,7 +1423,11 @@ static int lmhead_enqueue(const dlm_lmhead_args* a, void* workspace, void* strea
     }
     rc = launch_lm_shape(v_safe, p, a->M, st);
     if (rc != DLM_OK) return rc;
-    hipLaunchKernelGGL(lmhead_reduce_kernel, dim3(a->M), dim3(256), 0, st, p);
+    // Many rows of which the device counts few: what a workgroup past the count loads before it ends is all that shows.  Whole call, us,
+    // Dh = 256, with / without AHEAD: 65536 rows, V = 2048, 1 counted 36.3 / 27.7, 8192 counted 63.7 / 57.0, all 240 / 245; V = 60000, 1
+    // counted 166 / 142; 8192 rows, V = 2048, 1 counted 13.9 / 12.9, 4096 counted 27.5 / 28.4; 4097 rows, 512 counted 23.2 / 23.7.
+    if (a->M <= 4096 || !p.m_dev) hipLaunchKernelGGL(lmhead_reduce_kernel<true>, dim3(a->M), dim3(256), 0, st, p);
+    else hipLaunchKernelGGL(lmhead_reduce_kernel<false>, dim3(a->M), dim3(256), 0, st, p);
     return check_hip(hipGetLastError(), "lmhead_reduce_kernel launch");
 }
 

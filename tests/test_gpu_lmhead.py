@@ -195,6 +195,23 @@ def test_device_row_count_below_the_bound_in_row_split_shapes(bound, variant):
         dlm.set_option("lmhead_variant", -1)
 
 
+@pytest.mark.parametrize("M", [4096, 4097])
+@pytest.mark.parametrize("V,counted", [(300, 1), (300, 50), (300, -1), (33000, 1), (33000, 50)])
+def test_many_rows_of_which_the_device_counts_few(M, V, counted):
+    """More than 4096 rows with a device count take the reduction that looks at the count first; up to 256 partials a row (V = 300) and
+    more; rows gathered and scattered, those past the count untouched."""
+    m, Dh = M if counted < 0 else counted, 64
+    h, w = rnd(1500 + M, (M, Dh)), rnd(1501 + V, (V, Dh), Dh ** -0.25)
+    idx = np.random.default_rng(15).permutation(M).astype(np.int32)
+    got = run_lm(h, w, row_idx=idx, m_dev=m, forbid=V - 1, scatter=True)
+    ref = oracle.lmhead(h, w, row_idx=idx[:m], forbid_token=V - 1)
+    if m >= 20:
+        compare(got, ref, sel=idx[:m])
+    else:
+        assert np.abs(got["conf"][idx[:m]].astype(np.float64) - ref["conf"]).max() <= CONF_TOL and np.abs(got["lse"][idx[:m]] - ref["lse"]).max() <= Z_TOL
+    assert np.all(np.isnan(got["conf"][idx[m:]])) and np.all(got["tok"][idx[m:]] == -7)
+
+
 def test_non_temporal_w_stream_changes_nothing():
     """One row chunk: W is fetched with non-temporal loads unless the option turns that off; same bits either way."""
     h, w = rnd(71, (150, 256)), rnd(72, (3000, 256), 0.25)
