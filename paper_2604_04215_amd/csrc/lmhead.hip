@@ -184,6 +184,7 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
     f32x4* redbuf2 = redbuf + WV * MB;               // [WV][MB] of the second partial (sampling and / or entropy)
     const bool ent = p.conf_mode == DLM_CONF_NEG_ENTROPY;
     const bool second = p.sample || ent;
+    const bool runner = p.z2nd || p.conf_mode == DLM_CONF_MARGIN;
     constexpr int TVWG = 32 * TVW * WV;
     // does this workgroup's vocabulary tile hold a token that must be masked (past V, or the forbidden one)?
     const bool edge = (v0 + TVWG > p.V) || (p.forbid >= v0 && p.forbid < v0 + TVWG);
@@ -199,7 +200,20 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
             oidx = (p.out_scatter && p.row_idx) ? (int64_t)p.row_idx[r] : (int64_t)r;
             if (p.target) tgt = p.target[oidx];
         }
-        // scaled (and, in a tile that holds a forbidden or out-of-range token, masked) logits, kept in acc
+        // This row tile's raw logits, in vector registers (out of the accumulation registers once, instead of at each use), masked
+        // in a tile that holds a forbidden or out-of-range token.  The temperature is a positive factor: it changes neither the
+        // order nor the maximum, and the exponentials take it in their constant.
+        // Nothing runs beside this at one wavefront a SIMD, so its instructions count: 5.75 a logit (1 to fetch it, a half for the
+        // maximum, 1.25 for its place, 3 for the sum) where there were 9.  Whole calls, us, before / after: 65536 x 157184 x 4096
+        // 69300 / 68270, 1024 x 126464 x 4096 946 / 909, 512 rows 495 / 481, 128 rows x 152064 x 3584 216.3 / 214.0.
+        float z[TVW][16];
+#pragma unroll
+        for (int a = 0; a < TVW; ++a)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                z[a][i] = acc[a][c][i];
+                asm volatile("" : "+v"(z[a][i]));
+            }
         const int vb = v0 + wv * TVW * 32 + 4 * hi;    // this lane's token of element (a, i): vb + 32 a + 8 (i >> 2) + (i & 3)
         if (edge) {
 #pragma unroll
@@ -207,14 +221,8 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int v = vb + a * 32 + 8 * (i >> 2) + (i & 3);
-                    const float z = acc[a][c][i] * p.inv_t;
-                    acc[a][c][i] = (v >= p.V || v == p.forbid) ? -INFINITY : z;
+                    if (v >= p.V || v == p.forbid) z[a][i] = -INFINITY;
                 }
-        } else {
-#pragma unroll
-            for (int a = 0; a < TVW; ++a)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[a][c][i] *= p.inv_t;
         }
         if (p.target) {                                // the target's logit, if this lane holds it
             const int dt = tgt - vb;
@@ -225,50 +233,67 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const bool hit = dt == a * 32 + 8 * (i >> 2) + (i & 3);
-                    zt = hit ? acc[a][c][i] : zt;
+                    zt = hit ? z[a][i] : zt;
                     found |= hit;
                 }
-            if (found && tgt >= 0) p.ztarget[oidx] = zt;
+            if (found && tgt >= 0) p.ztarget[oidx] = zt * p.inv_t;
         }
-        // maximum and runner-up (equal to the maximum when it occurs twice): the two largest of (m, m2, z)
-        Red red{-INFINITY, 0.f, -INFINITY, 0x7fffffff};
+        // maximum of each accumulator tile and of all
+        float tm[TVW], mraw = -INFINITY, m2raw = -INFINITY;
 #pragma unroll
-        for (int a = 0; a < TVW; ++a)
+        for (int a = 0; a < TVW; ++a) {
+            tm[a] = -INFINITY;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float z = acc[a][c][i];
-                red.m2 = __builtin_amdgcn_fmed3f(red.m, red.m2, z);
-                red.m = fmaxf(red.m, z);
+            for (int i = 0; i < 16; i += 2) tm[a] = __builtin_fmaxf(__builtin_fmaxf(tm[a], z[a][i]), z[a][i + 1]);   // v_max3
+        }
+        if (runner) {                                  // the two largest of (m, m2, z): equal to the maximum when that occurs twice
+#pragma unroll
+            for (int a = 0; a < TVW; ++a)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    m2raw = __builtin_amdgcn_fmed3f(mraw, m2raw, z[a][i]);
+                    mraw = __builtin_amdgcn_fmed3f(mraw, INFINITY, z[a][i]);   // the larger (fmaxf takes two instructions here)
+                }
+        }
+#pragma unroll
+        for (int a = 0; a < TVW; ++a) mraw = fmaxf(mraw, tm[a]);
+        Red red{mraw * p.inv_t, 0.f, m2raw * p.inv_t, 0x7fffffff};
+        float uent = 0.f;
+        if (mraw > -INFINITY) {
+            // lowest token that attains the maximum: the lowest accumulator tile that does, then a walk down that tile, in which the
+            // last hit stays (offsets from vb are constants)
+            int la = (TVW - 1) * 32;
+            float x[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[i] = z[TVW - 1][i];
+#pragma unroll
+            for (int a = TVW - 2; a >= 0; --a) {
+                const bool here = tm[a] == mraw;
+                la = here ? a * 32 : la;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) x[i] = here ? z[a][i] : x[i];
             }
-        // lowest token that attains the maximum: walk downwards, the last hit stays (offsets from vb are constants)
-        if (red.m > -INFINITY) {
             int li = 0;
 #pragma unroll
-            for (int a = TVW - 1; a >= 0; --a)
-#pragma unroll
-                for (int i = 15; i >= 0; --i)
-                    li = (acc[a][c][i] == red.m) ? a * 32 + 8 * (i >> 2) + (i & 3) : li;
-            red.idx = vb + li;
-        }
-        float uent = 0.f;
-        if (red.m > -INFINITY) {
-            const float mb = red.m * LOG2E;
+            for (int i = 15; i >= 0; --i) li = (x[i] == mraw) ? 8 * (i >> 2) + (i & 3) : li;
+            red.idx = vb + la + li;
+            const float sc = fminf(p.inv_t * LOG2E, 3.4e38f), mb = mraw * sc;
             float s = 0.f;
             if (ent) {
 #pragma unroll
                 for (int a = 0; a < TVW; ++a)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const float z = acc[a][c][i];
-                        const float e = fast_exp2(z * LOG2E - mb);
+                        const float y = z[a][i] * p.inv_t;
+                        const float e = fast_exp2(y * LOG2E - red.m * LOG2E);
                         s += e;
-                        uent += (z > -INFINITY) ? e * (z - red.m) : 0.f;
+                        uent += (y > -INFINITY) ? e * (y - red.m) : 0.f;
                     }
             } else {
 #pragma unroll
                 for (int a = 0; a < TVW; ++a)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) s += fast_exp2(acc[a][c][i] * LOG2E - mb);
+                    for (int i = 0; i < 16; ++i) s += fast_exp2(z[a][i] * sc - mb);
             }
             red.s = s;
         }
@@ -283,7 +308,7 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
         }
         Smp sm{-INFINITY, -INFINITY, 0x7fffffff};
         if (p.sample) {
-            // acc now holds the scaled, masked logits; noise is keyed by the row's index in `hidden`
+            // noise is keyed by the row's index in `hidden`
             const uint32_t rk = (r < M) ? (uint32_t)(p.row_idx ? p.row_idx[r] : r) : 0u;
 #pragma unroll
             for (int a = 0; a < TVW; ++a) {
@@ -293,11 +318,11 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
                     const u32x4 bits = philox4x32_10((uint32_t)vq >> 2, rk, p.step, p.stream, p.seed_lo, p.seed_hi);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float z = acc[a][c][4 * i4 + e];
-                        const float pert = z + gumbel_from_bits(bits[e]);
+                        const float y = z[a][4 * i4 + e] * p.inv_t;
+                        const float pert = y + gumbel_from_bits(bits[e]);
                         if (pert > sm.pm) {
                             sm.pm = pert;
-                            sm.pz = z;
+                            sm.pz = y;
                             sm.idx = vq + e;
                         }
                     }
