@@ -53,6 +53,7 @@ struct LmParams {
     int m_lo, m_hi;
     int alt_cap, alt_n_vt;   // reduction: row count <= alt_cap (> 0) -> alt_n_vt partials per row, second partials at alt_part2
     f32x4* alt_part2;
+    int* queue;   // paired ring only: one counter per XCD (16 words apart), null = one workgroup per tile (see lmhead_pair_kernel)
 };
 
 // Row count of this launch; false when the device's count belongs to the other shape queued for the same call.
@@ -172,12 +173,35 @@ __device__ __forceinline__ void lm_tile_of_block(int bid, int n_mc, int gm, int 
     group = super;
 }
 
-// Per hidden row (matrix column): reduce over this workgroup's vocabulary rows and write one partial.
-// Called after the main loop's final barrier, so the staging area can be reused.
-template <int WV, int WH, int TVW, int THW>
-__device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW][THW], unsigned char* smem, int v0, int m0,
-                                            int M, int vt, int wv, int wh, int n, int hi, int tid) {
-    constexpr int NT = 64 * WV * WH;
+// The same order as a dense list per XCD, for workgroups that take one tile after the other: list `xcd` holds the
+// lm_list_len() tiles (vt = xcd mod 8) x (row chunk); the last, incomplete group of vocabulary tiles makes narrower blocks.
+__device__ __forceinline__ int lm_list_len(int xcd, int n_vt, int n_mc) { return n_vt > xcd ? (n_vt - xcd + 7) / 8 * n_mc : 0; }
+__device__ __forceinline__ void lm_tile_of_slot(int xcd, int slot, int n_vt, int n_mc, int gm, int gv, int& vt, int& mc, int& group) {
+    const unsigned per_super = (unsigned)(gv * n_mc), super = (unsigned)slot / per_super, within = (unsigned)slot - super * per_super;
+    const unsigned per_blk = (unsigned)(min(gv, (n_vt - xcd + 7) / 8 - (int)super * gv) * gm);
+    const unsigned blk = within / per_blk, r = within - blk * per_blk, v_local = r / (unsigned)gm;
+    mc = (int)(blk * gm + (r - v_local * gm));
+    vt = (int)(super * gv + v_local) * 8 + xcd;
+    group = (int)super;
+}
+// Several row chunks: blocks of gm x gv workgroups for the 32 CUs of an XCD; gm is the largest divisor of the chunk count up to 8
+// (measured at V = 126464, Dh = 4096: +6 % at M >= 1024, +10..17 % at M = 512)
+__host__ __device__ inline void lm_blocking(int n_mc, int& gm, int& gv) {
+    gm = 1;
+    gv = 1;
+    if (n_mc >= 2) {
+        for (int c = 8; c >= 1; --c)
+            if (n_mc % c == 0) { gm = c; break; }
+        gv = 32 / gm > 8 ? 8 : 32 / gm;
+    }
+}
+
+// Per hidden row (matrix column): reduce over this wavefront's vocabulary rows, into LDS (`smem`: 2 * WV * MB * 16 bytes that no
+// wavefront reads any more); lm_store_partials, behind a barrier, merges the wavefronts and writes one partial a row.
+// SMP = false: the call does not sample (the noise is two thirds of this function's code)
+template <int WV, int WH, int TVW, int THW, bool SMP = true>
+__device__ __forceinline__ void lm_reduce_tile(const LmParams& p, f32x16 (&acc)[TVW][THW], unsigned char* smem, int v0, int m0,
+                                               int M, int wv, int wh, int n, int hi) {
     constexpr int MB = 32 * THW * WH;
     constexpr float LOG2E = 1.4426950408889634f;
     f32x4* redbuf = reinterpret_cast<f32x4*>(smem);  // [WV][MB] of (max, sumexp, runner-up, argmax bits)
@@ -188,7 +212,6 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
     constexpr int TVWG = 32 * TVW * WV;
     // does this workgroup's vocabulary tile hold a token that must be masked (past V, or the forbidden one)?
     const bool edge = (v0 + TVWG > p.V) || (p.forbid >= v0 && p.forbid < v0 + TVWG);
-    // (the loop above ended with a barrier: the staging area is free)
 #pragma unroll
     for (int c = 0; c < THW; ++c) {
         if (m0 + (wh * THW + c) * 32 >= M) continue;   // a row tile past the last row: nothing reads its partials
@@ -307,7 +330,7 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
             redbuf[wv * MB + col] = packed;
         }
         Smp sm{-INFINITY, -INFINITY, 0x7fffffff};
-        if (p.sample) {
+        if (SMP && p.sample) {
             // noise is keyed by the row's index in `hidden`
             const uint32_t rk = (r < M) ? (uint32_t)(p.row_idx ? p.row_idx[r] : r) : 0u;
 #pragma unroll
@@ -339,7 +362,15 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
             redbuf2[wv * MB + col] = packed;
         }
     }
-    __syncthreads();
+}
+
+template <int WV, int WH, int THW>
+__device__ __forceinline__ void lm_store_partials(const LmParams& p, unsigned char* smem, int m0, int M, int vt, int tid) {
+    constexpr int NT = 64 * WV * WH, MB = 32 * THW * WH;
+    const f32x4* redbuf = reinterpret_cast<const f32x4*>(smem);
+    const f32x4* redbuf2 = redbuf + WV * MB;
+    const bool ent = p.conf_mode == DLM_CONF_NEG_ENTROPY;
+    const bool second = p.sample || ent;
     for (int col = tid; col < MB; col += NT) {
         const int r = m0 + col;
         if (r >= M) continue;
@@ -367,6 +398,15 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
             p.part2[(int64_t)r * p.n_vt + vt] = out2;
         }
     }
+}
+
+// Called after the main loop's final barrier, so the staging area can be reused.
+template <int WV, int WH, int TVW, int THW>
+__device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW][THW], unsigned char* smem, int v0, int m0,
+                                            int M, int vt, int wv, int wh, int n, int hi, int tid) {
+    lm_reduce_tile<WV, WH, TVW, THW>(p, acc, smem, v0, m0, M, wv, wh, n, hi);
+    __syncthreads();
+    lm_store_partials<WV, WH, THW>(p, smem, m0, M, vt, tid);
 }
 
 // WV x WH wavefronts; each owns TVW x THW accumulator tiles of 32 (vocab) x 32 (hidden rows).
@@ -412,12 +452,15 @@ __global__ __launch_bounds__(64 * WV * WH, OCC) void lmhead_kernel(LmParams p) {
         wsrc[q] = p.w + (int64_t)v * p.w_stride + lc * 8;
     }
     const uint16_t* hsrc[HLD];
+    int hrow[HLD];
 #pragma unroll
-    for (int q = 0; q < HLD; ++q) {
-        const int r = min(m0 + lrow + q * RPP, M - 1);         // rows past M are clamped, never stored
-        const int64_t src = p.row_idx ? p.row_idx[r] : r;
-        hsrc[q] = p.hidden + src * p.h_stride + lc * 8;
+    for (int q = 0; q < HLD; ++q) hrow[q] = min(m0 + lrow + q * RPP, M - 1);   // rows past M are clamped, never stored
+    if (p.row_idx) {                                                           // (one trip to memory for all of them)
+#pragma unroll
+        for (int q = 0; q < HLD; ++q) hrow[q] = p.row_idx[hrow[q]];
     }
+#pragma unroll
+    for (int q = 0; q < HLD; ++q) hsrc[q] = p.hidden + hrow[q] * p.h_stride + lc * 8;
     u32x4 wreg[PD][WLD], hreg[PD][HLD];
 
     f32x16 acc[TVW][THW];
@@ -432,7 +475,7 @@ __global__ __launch_bounds__(64 * WV * WH, OCC) void lmhead_kernel(LmParams p) {
     // Every workgroup walks the Dh axis from a different starting chunk (and wraps).  Rows of W are a power
     // of two apart, so workgroups marching in step over the same columns would all hit the same few HBM
     // channels; the rotation spreads them (measured: 5.0 -> 6.2 TB/s on a pure read of W in this pattern).
-    const int kstart = (int)(((long)(p.gv > 1 ? kgroup : vt) * 11) % nk);
+    const int kstart = (int)((unsigned)(p.gv > 1 ? kgroup : vt) * 11u % (unsigned)nk);
 #define LM_CHUNK(kc) (((kc) + kstart) >= nk ? ((kc) + kstart - nk) : ((kc) + kstart))
 #define LM_GLOAD(slot, kc)                                                                               \
     {                                                                                                    \
@@ -637,7 +680,7 @@ __global__ __launch_bounds__(64 * WV) void lmhead_wdirect_kernel(LmParams p) {
             for (int i = 0; i < 16; ++i) acc[a][c][i] = 0.f;
 
     const int nk = p.Dh / KC;
-    const int kstart = (int)(((long)(p.gv > 1 ? kgroup : vt) * 11) % nk);
+    const int kstart = (int)((unsigned)(p.gv > 1 ? kgroup : vt) * 11u % (unsigned)nk);
 #define LM_CHUNK(kc) (((kc) + kstart) >= nk ? ((kc) + kstart - nk) : ((kc) + kstart))
 #define WD_GLOAD_W(slot, kc)                                                                             \
     {                                                                                                    \
@@ -774,7 +817,7 @@ __global__ __launch_bounds__(64 * WV * WH) void lmhead_dma_kernel(LmParams p) {
         }
     }
     const int nk = p.Dh / KCD;
-    const int kstart = (int)(((long)(p.gv > 1 ? kgroup : vt) * 11) % nk);
+    const int kstart = (int)((unsigned)(p.gv > 1 ? kgroup : vt) * 11u % (unsigned)nk);
 #define DMA_CHUNK(kc) (((kc) + kstart) >= nk ? ((kc) + kstart - nk) : ((kc) + kstart))
 #define DMA_ISSUE(stage, kc)                                                                             \
     {                                                                                                    \
@@ -923,60 +966,87 @@ __global__ __launch_bounds__(64 * WV * WH) void lmhead_dma_kernel(LmParams p) {
 // Five stages of 32 elements (the pair being multiplied, the pair in flight, and the stage just freed): pair
 // (k+4, k+5) is requested after the barrier of even stage k, into stages (k+4) % 5 and k % 5, and must have landed
 // by the barrier of stage k+3.
-template <int WV, int WH, int TVW, int THW>
+//
+// With a queue a workgroup multiplies one tile after the other: the requests of a tile's last two pairs of stages already
+// fetch the next tile's first two pairs, so the start of a tile (its addresses, row indices and first round trip to memory)
+// hides behind the tile before it, and the reduction of a finished tile (in the one stage that is free then) runs while those
+// requests are in flight.  A workgroup's first two tiles follow from its index, each later one is the next of its
+// XCD's list (a counter): handed out in order like the hardware's own dispatch, so that the workgroups of an XCD stay on
+// neighbouring tiles and share their panels through its L2 (a fixed stride drifts apart and was slower than one workgroup a tile).
+// The counter is asked at the start of a tile: asked behind it, the answer is not there in time (65536 rows: 69.3 instead of 66.5 ms).
+// One workgroup a tile / queue, ms: 8192 x 157184 x 4096 8.22 / 8.08, 65536 rows 68.5 / 66.4, 1024 x 126464 x 4096 0.918 / 0.897; on zeros,
+// where the power limit does not bind, 6.82 (before the cheaper reduction of a tile, too) / 6.27.  The loop itself runs at 1.42 PFLOP/s.
+template <int WV, int WH, int TVW, int THW, bool SMP>
 __global__ __launch_bounds__(64 * WV * WH) void lmhead_pair_kernel(LmParams p) {
     constexpr int NS = 5, KCD = 32, ROWB = 64;
     constexpr int NW = WV * WH;
     constexpr int TV = 32 * TVW * WV, MB = 32 * THW * WH;
     constexpr int STAGE = (TV + MB) * ROWB;
     constexpr int IPW = (TV + MB) / 16 / NW;          // 16-row groups per wavefront (two requests each per pair)
+    constexpr int RED = 2 * WV * MB * 16;             // both reduction buffers
+    constexpr bool QUEUE = RED + 16 <= STAGE;         // the shape can take its tiles from a queue: they and the next index fit one stage
     static_assert((TV + MB) / 16 % NW == 0, "rows must split evenly over the wavefronts");
     static_assert(NS * STAGE <= 160 * 1024, "five stages within the 160 KB of LDS");
-    static_assert(NS * STAGE >= 2 * WV * MB * 16, "both reduction buffers must fit in the ring");
+    static_assert(NS * STAGE >= RED, "both reduction buffers must fit in the ring");
     __shared__ __attribute__((aligned(1024))) unsigned char ring[NS * STAGE];
 
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wv = w % WV, wh = w / WV;
     const int n = lane & 31, hi = lane >> 5;
-    int vt, mc, kgroup;
-    lm_tile_of_block(blockIdx.x, p.n_mc, p.gm, p.gv, vt, mc, kgroup);
-    if (vt >= p.n_vt_l) return;
-    const int v0 = p.v_first + vt * TV, m0 = mc * MB;
-    vt += p.vt0;
     int M = p.M;
     if (!lm_rows(p, M)) return;
-    if (m0 >= M) return;
-
-    const uint16_t* src[IPW];
-#pragma unroll
-    for (int j = 0; j < IPW; ++j) {
-        const int row = (w * IPW + j) * 16 + (lane >> 2);
-        const int piece = (lane & 3) ^ ((row >> 2) & 3);
-        if (row < TV) {
-            const int v = min(v0 + row, p.V - 1);
-            src[j] = p.w + (int64_t)v * p.w_stride + piece * 8;
-        } else {
-            const int r = min(m0 + row - TV, M - 1);
-            const int64_t sr = p.row_idx ? p.row_idx[r] : r;
-            src[j] = p.hidden + sr * p.h_stride + piece * 8;
+    const bool queued = QUEUE && p.queue;
+    const int xcd = blockIdx.x & 7;
+    int vt, mc, kgroup;
+    int n_mc = p.n_mc, gm = p.gm, gv = p.gv, len = 0, ahead = 0;   // ahead: list index of the tile after this one
+    if (queued) {
+        const int live = (M + MB - 1) / MB;                        // row chunks that hold a row
+        if (live != n_mc) {
+            n_mc = live;
+            lm_blocking(n_mc, gm, gv);
         }
+        len = lm_list_len(xcd, p.n_vt_l, n_mc);
+        const int slot = blockIdx.x >> 3;
+        if (slot >= len) return;
+        lm_tile_of_slot(xcd, slot, p.n_vt_l, n_mc, gm, gv, vt, mc, kgroup);
+        ahead = slot + (int)(gridDim.x >> 3);
+    } else {
+        lm_tile_of_block(blockIdx.x, n_mc, gm, gv, vt, mc, kgroup);
+        if (vt >= p.n_vt_l || mc * MB >= M) return;
+    }
+    int v0 = p.v_first + vt * TV, m0 = mc * MB;
+
+    // source row of each of this wavefront's requests in the tile (v_first_, m_first_): a row of W, or of `hidden`
+#define PR_ROWS(dst, v_first_, m_first_)                                                                 \
+    {                                                                                                    \
+        _Pragma("unroll") for (int j = 0; j < IPW; ++j) dst[j] = min((m_first_) + max((w * IPW + j) * 16 + (lane >> 2) - TV, 0), M - 1); \
+        if (p.row_idx) {                                                                                 \
+            _Pragma("unroll") for (int j = 0; j < IPW; ++j) dst[j] = p.row_idx[dst[j]];                  \
+        }                                                                                                \
+        _Pragma("unroll") for (int j = 0; j < IPW; ++j)                                                  \
+            if ((w * IPW + j) * 16 < TV) dst[j] = min((v_first_) + (w * IPW + j) * 16 + (lane >> 2), p.V - 1); \
+    }
+#define PR_SOURCES(rows)                                                                                 \
+    {                                                                                                    \
+        _Pragma("unroll") for (int j = 0; j < IPW; ++j) {                                                \
+            const bool is_w = (w * IPW + j) * 16 < TV;                                                   \
+            const int piece = (lane & 3) ^ (((w * IPW + j) * 4 + (lane >> 4)) & 3);                      \
+            src[j] = (is_w ? p.w : p.hidden) + rows[j] * (is_w ? p.w_stride : p.h_stride) + piece * 8;   \
+        }                                                                                                \
+    }
+    const uint16_t* src[IPW];
+    {
+        int rows[IPW];
+        PR_ROWS(rows, v0, m0)
+        PR_SOURCES(rows)
     }
     const int nk = p.Dh / KCD;                        // even: Dh is a multiple of 64
     // rotated start as in the other shapes, kept even so that a pair stays one 128-byte line
-    const int kstart = ((int)(((long)(p.gv > 1 ? kgroup : vt) * 11) % nk)) & ~1;
+    int kstart = (int)((unsigned)(gv > 1 ? kgroup : vt) * 11u % (unsigned)nk) & ~1;
 #define PR_CHUNK(kc) (((kc) + kstart) >= nk ? ((kc) + kstart - nk) : ((kc) + kstart))
-    const int wsc = __builtin_amdgcn_readfirstlane(w);
 #define PR_ISSUE1(sbyte, j, eoff)                                                                        \
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + (eoff)),   \
-        (__attribute__((address_space(3))) void*)(ring + (sbyte) + (wsc * IPW + (j)) * 1024), 16, 0, 0)
-
-    f32x16 acc[TVW][THW];
-#pragma unroll
-    for (int a = 0; a < TVW; ++a)
-#pragma unroll
-        for (int c = 0; c < THW; ++c)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[a][c][i] = 0.f;
+        (__attribute__((address_space(3))) void*)(ring + (sbyte) + (w * IPW + (j)) * 1024), 16, 0, 0)
 
     const int sw = (n >> 2) & 3;
     const int off0 = n * ROWB + ((hi ^ sw) << 4);          // MFMA step 0: piece hi
@@ -996,99 +1066,174 @@ __global__ __launch_bounds__(64 * WV * WH) void lmhead_pair_kernel(LmParams p) {
     // launch are never multiplied): TVW * NL MFMAs on register set `half`; behind the first ones the fragment reads
     // of the other set (stage at rsb); part = 1 / 2: the first / second half of the pair's 2*IPW requests (chunk at
     // element offset ich into the stage at isb0, the following chunk into isb1), spread evenly over the MFMAs.
-    // NL = 0 (every row tile of this wavefront is past the end): only its share of the requests.
+    // NL = 0 (every row tile of this wavefront is past the end): only its share of the requests.  NL = -1: the count
+    // is nl, and the products of a row tile are jumped over as a group, with the rest behind the group.
 #define PR_HALF(half, rsb, part, isb0, isb1, ich, NL)                                                    \
-    {                                                                                                    \
-        constexpr int T_ = TVW * (NL), NF_ = TVW + (NL);                                                 \
-        if constexpr ((NL) == 0) {                                                                       \
-            if ((part) != 0) {                                                                           \
-                _Pragma("unroll") for (int j = 0; j < IPW; ++j) {                                        \
-                    const int jj = j + ((part) == 2 ? IPW : 0);                                          \
-                    if (jj & 1) PR_ISSUE1(isb1, jj >> 1, (ich) + KCD);                                   \
-                    else PR_ISSUE1(isb0, jj >> 1, (ich));                                                \
-                }                                                                                        \
-            }                                                                                            \
-        } else {                                                                                         \
-        _Pragma("unroll") for (int a = 0; a < TVW; ++a)                                                  \
-            _Pragma("unroll") for (int c = 0; c < (NL); ++c) {                                           \
-                const int i_ = a * (NL) + c;                                                             \
-                acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[half][a], bfr[half][c], acc[a][c], 0, 0, 0); \
-                _Pragma("unroll") for (int f = 0; f < NF_; ++f)                                          \
-                    if (f * T_ / (2 * NF_) == i_) PR_READ_ONE(1 - (half), rsb, f);                       \
-                if ((part) != 0) {                                                                       \
-                    _Pragma("unroll") for (int j = 0; j < IPW; ++j)                                      \
-                        if (j * T_ / IPW == i_) {                                                        \
-                            const int jj = j + ((part) == 2 ? IPW : 0);                                  \
-                            if (jj & 1) PR_ISSUE1(isb1, jj >> 1, (ich) + KCD);                           \
-                            else PR_ISSUE1(isb0, jj >> 1, (ich));                                        \
-                        }                                                                                \
-                }                                                                                        \
-                __builtin_amdgcn_sched_barrier(0);                                                       \
-            }                                                                                            \
+    if constexpr ((NL) >= 0) {                                                                           \
+        constexpr int T_ = TVW * ((NL) > 0 ? (NL) : 1), NF_ = TVW + (NL);                                \
+        _Pragma("unroll") for (int i_ = 0; i_ < T_; ++i_) {                                              \
+            if constexpr ((NL) > 0) PR_PRODUCT(half, i_ % TVW, i_ / TVW)                                 \
+            _Pragma("unroll") for (int f = 0; f < NF_; ++f)                                              \
+                if ((NL) > 0 && f * T_ / (2 * NF_) == i_) PR_READ_ONE(1 - (half), rsb, f);               \
+            PR_REQUESTS(part, isb0, isb1, ich, j * T_ / IPW == i_)                                       \
+            __builtin_amdgcn_sched_barrier(0);                                                           \
         }                                                                                                \
+    } else {                                                                                             \
+        _Pragma("unroll") for (int c = 0; c < THW; ++c) {                                                \
+            if (c < nl) {                                                                                \
+                _Pragma("unroll") for (int a = 0; a < TVW; ++a) PR_PRODUCT(half, a, c)                   \
+            }                                                                                            \
+            _Pragma("unroll") for (int f = 0; f < TVW + THW; ++f)                                        \
+                if (f * THW / (2 * (TVW + THW)) == c) PR_READ_ONE(1 - (half), rsb, f);                   \
+            PR_REQUESTS(part, isb0, isb1, ich, j * THW / IPW == c)                                       \
+            __builtin_amdgcn_sched_barrier(0);                                                           \
+        }                                                                                                \
+    }
+#define PR_PRODUCT(half, a, c)                                                                           \
+    acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[half][a], bfr[half][c], acc[a][c], 0, 0, 0);
+#define PR_REQUESTS(part, isb0, isb1, ich, now)                                                          \
+    if ((part) != 0) {                                                                                   \
+        _Pragma("unroll") for (int j = 0; j < IPW; ++j)                                                  \
+            if (now) {                                                                                   \
+                const int jj = j + ((part) == 2 ? IPW : 0);                                              \
+                if (jj & 1) PR_ISSUE1(isb1, jj >> 1, (ich) + KCD);                                       \
+                else PR_ISSUE1(isb0, jj >> 1, (ich));                                                    \
+            }                                                                                            \
     }
 #define PR_NEXT(x) (((x) + STAGE == NS * STAGE) ? 0 : (x) + STAGE)
-    // prologue: pairs (0,1) -> stages 0,1 and (2,3) -> stages 2,3 (a request past the end re-reads the last pair);
-    // then the loop over pairs of stages
-#define PR_MAIN(NL)                                                                                      \
+    // the accumulators stay in accumulation registers where the copies of the loop meet (as 256 vector registers they would push
+    // everything else into scratch memory)
+#define PR_HOLD                                                                                          \
+    _Pragma("unroll") for (int a = 0; a < TVW; ++a)                                                      \
+        _Pragma("unroll") for (int c = 0; c < THW; ++c) asm volatile("" : "+a"(acc[a][c]));
+    // One tile.  On entry the pair (0,1) is in the stages at sb, the pair (2,3) has been requested; on exit the same holds for the next
+    // tile, if there is one, and the stage in front of sb is free.  From the pair k + 4 = nk on the requests are the next tile's
+    // (without one they read the last pair again, into stages that nobody reads).
+#define PR_LOOP(NL)                                                                                      \
     {                                                                                                    \
-        _Pragma("unroll") for (int pr = 0; pr < 2; ++pr) {                                               \
-            const int e = PR_CHUNK(min(2 * pr, nk - 2)) * KCD;                                           \
-            _Pragma("unroll") for (int j = 0; j < IPW; ++j) {                                            \
-                PR_ISSUE1((2 * pr) * STAGE, j, e);                                                       \
-                PR_ISSUE1((2 * pr + 1) * STAGE, j, e + KCD);                                             \
+        int k = 0;                                                                                       \
+        _Pragma("unroll 1") for (int part = 0; part < 2; ++part) { /* the sources change outside of the loop */\
+            const int k_end = part == 0 ? nk - 4 : nk;                                                   \
+            int ahead_k = 4;                                                                             \
+            if (part == 1 && more) {                                                                     \
+                PR_SOURCES(nrows)                                                                        \
+                kstart = kstart_next;                                                                    \
+                ahead_k = 4 - nk;                                                                        \
+            }                                                                                            \
+            for (; k < k_end; k += 2) {                                                                  \
+                const int s1 = PR_NEXT(sb), s2 = PR_NEXT(s1), s3 = PR_NEXT(s2), s4 = PR_NEXT(s3);        \
+                const int ich = PR_CHUNK(min(k + ahead_k, nk - 2)) * KCD;                                \
+                /* even stage k */                                                                       \
+                PR_HALF(0, sb, 0, 0, 0, 0, NL);                                                          \
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                                       \
+                __builtin_amdgcn_s_barrier(); /* every wavefront has read stage k to the end: it is free */\
+                asm volatile("" ::: "memory");                                                           \
+                PR_HALF(1, s1, 1, s4, sb, ich, NL);                                                      \
+                /* odd stage k+1 */                                                                      \
+                PR_HALF(0, s1, 2, s4, sb, ich, NL);                                                      \
+                /* all but the pair just requested has landed: chunks k+2 and k+3 */                     \
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * IPW) : "memory");                \
+                __builtin_amdgcn_s_barrier();                                                            \
+                asm volatile("" ::: "memory");                                                           \
+                PR_HALF(1, s2, 0, 0, 0, 0, NL);                                                          \
+                sb = s2;                                                                                 \
             }                                                                                            \
         }                                                                                                \
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * IPW) : "memory");                                   \
-        __builtin_amdgcn_s_barrier();                                                                    \
-        asm volatile("" ::: "memory");                                                                   \
-        if constexpr ((NL) > 0) {                                                                        \
-            _Pragma("unroll") for (int f = 0; f < TVW + (NL); ++f) PR_READ_ONE(0, 0, f);                 \
-        }                                                                                                \
-        int sb = 0; /* byte offset of the stage of chunk k (k even at the loop top) */                   \
-        for (int k = 0; k < nk; k += 2) {                                                                \
-            const int s1 = PR_NEXT(sb), s2 = PR_NEXT(s1), s3 = PR_NEXT(s2), s4 = PR_NEXT(s3);            \
-            const int ich = PR_CHUNK(min(k + 4, nk - 2)) * KCD;                                          \
-            /* even stage k */                                                                           \
-            PR_HALF(0, sb, 0, 0, 0, 0, NL);                                                              \
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                                           \
-            __builtin_amdgcn_s_barrier(); /* every wavefront has read stage k to the end: it is free */  \
-            asm volatile("" ::: "memory");                                                               \
-            PR_HALF(1, s1, 1, s4, sb, ich, NL);                                                          \
-            /* odd stage k+1 */                                                                          \
-            PR_HALF(0, s1, 2, s4, sb, ich, NL);                                                          \
-            /* all but the pair just requested has landed: chunks k+2 and k+3 */                         \
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * IPW) : "memory");                    \
-            __builtin_amdgcn_s_barrier();                                                                \
-            asm volatile("" ::: "memory");                                                               \
-            PR_HALF(1, s2, 0, 0, 0, 0, NL);                                                              \
-            sb = s2;                                                                                     \
-        }                                                                                                \
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");                                      \
+        PR_HOLD                                                                                          \
     }
-    // Row tiles of this wavefront that hold a row of the launch: the loop exists once per count, so that the row
-    // count of a step that the host only knows an upper bound of (device-side M) costs what its rows cost.  Every
-    // copy runs the same barriers and the same requests.
-    const int nl = __builtin_amdgcn_readfirstlane(min(max((M - m0 - wh * THW * 32 + 31) >> 5, 0), THW));
 #define PR_CASE(k)                                                                                       \
     case k:                                                                                              \
-        if constexpr ((k) <= THW) { PR_MAIN(k) }                                                         \
+        if constexpr ((k) <= THW) PR_LOOP(k)                                                             \
         break;
-    switch (nl) {
-        PR_CASE(0) PR_CASE(1) PR_CASE(2) PR_CASE(3) PR_CASE(4) PR_CASE(5) PR_CASE(6)
-        default: break;
+    // prologue: pairs (0,1) -> stages 0,1 and (2,3) -> stages 2,3 (a request past the end re-reads the last pair)
+#pragma unroll
+    for (int pr = 0; pr < 2; ++pr) {
+        const int e = PR_CHUNK(min(2 * pr, nk - 2)) * KCD;
+#pragma unroll
+        for (int j = 0; j < IPW; ++j) {
+            PR_ISSUE1((2 * pr) * STAGE, j, e);
+            PR_ISSUE1((2 * pr + 1) * STAGE, j, e + KCD);
+        }
     }
-    static_assert(THW <= 6, "one copy of the loop per live-tile count");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * IPW) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    int sb = 0;   // byte offset of the stage of chunk k (k even at the loop top)
+    for (;;) {
+        f32x16 acc[TVW][THW];
+        const bool more = queued && ahead < len;
+        int nrows[IPW], kstart_next = 0, taken = 0;
+        int vt_next = 0, mc_next = 0;
+        if (more) {
+            lm_tile_of_slot(xcd, ahead, p.n_vt_l, n_mc, gm, gv, vt_next, mc_next, kgroup);
+            kstart_next = (int)((unsigned)(gv > 1 ? kgroup : vt_next) * 11u % (unsigned)nk) & ~1;
+            PR_ROWS(nrows, p.v_first + vt_next * TV, mc_next * MB)
+            if (tid == 0) taken = __hip_atomic_fetch_add(p.queue + 16 * xcd, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // Row tiles of this wavefront that hold a row of the launch, so that the row count of a step that the host only knows an
+        // upper bound of (device-side M) costs what its rows cost: the loop exists once per count, or, where a row tile has four
+        // products behind which the rest fits, once without jumps and once with (65536 rows 1.3 % faster than with five copies).
+        // Every copy runs the same barriers and the same requests.
+        const int nl = __builtin_amdgcn_readfirstlane(min(max((M - m0 - wh * THW * 32 + 31) >> 5, 0), THW));
+#pragma unroll
+        for (int a = 0; a < TVW; ++a)
+#pragma unroll
+            for (int c = 0; c < THW; ++c)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[a][c][i] = 0.f;
+#pragma unroll
+        for (int f = 0; f < TVW + THW; ++f) PR_READ_ONE(0, sb, f);
+        if constexpr (TVW >= 4) {
+            if (nl == THW) PR_LOOP(THW)
+            else PR_LOOP(-1)
+        } else {
+            switch (nl) {
+                PR_CASE(0) PR_CASE(1) PR_CASE(2) PR_CASE(3) PR_CASE(4) PR_CASE(5) PR_CASE(6)
+                default: break;
+            }
+            static_assert(THW <= 6, "one copy of the loop per live-tile count");
+        }
+        PR_HOLD
+        unsigned char* red = ring;
+        if constexpr (QUEUE) {
+            // the stage in front of sb was read to the end before the loop's last barrier, and nothing has been requested into it
+            red += sb == 0 ? (NS - 1) * STAGE : sb - STAGE;
+        } else {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+        // (what follows from the lane stays inside: computed ahead of the loop over the tiles it would fill the registers)
+        int lane_ = lane;
+        asm volatile("" : "+v"(lane_));
+        lm_reduce_tile<WV, WH, TVW, THW, SMP>(p, acc, red, v0, m0, M, wv, wh, lane_ & 31, lane_ >> 5);
+        if (more && tid == 0) *reinterpret_cast<int*>(red + RED) = taken;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        lm_store_partials<WV, WH, THW>(p, red, m0, M, p.vt0 + vt, w * 64 + lane_);
+        if (!more) break;
+        ahead = __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(red + RED)) + 2 * (int)(gridDim.x >> 3);
+        vt = vt_next;
+        v0 = p.v_first + vt * TV;
+        m0 = mc_next * MB;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no request into LDS may outlive its workgroup
 #undef PR_CASE
-#undef PR_MAIN
+#undef PR_LOOP
+#undef PR_HOLD
 #undef PR_CHUNK
 #undef PR_ISSUE1
 #undef PR_READ_ONE
 #undef PR_HALF
+#undef PR_PRODUCT
+#undef PR_REQUESTS
 #undef PR_NEXT
-    __syncthreads();
-    lm_epilogue<WV, WH, TVW, THW>(p, acc, ring, v0, m0, M, vt, wv, wh, n, hi, tid);
+#undef PR_ROWS
+#undef PR_SOURCES
 }
+
+__global__ void lmhead_queue_kernel(int* queue) { queue[threadIdx.x * 16] = 0; }
 
 // One workgroup per row: merge the per-vocabulary-tile partials (contiguous per row) in a fixed order: every thread
 // takes the tiles t = tid, tid + 256, ... (all loads issued before the first merge), then a fixed tree over the
@@ -1245,7 +1390,8 @@ static void launch_lma(dim3 grid, hipStream_t st, const LmParams& p) {
 #define LMX(WV, WH, TVW, THW, NS) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, -1, launch_lma<WV, WH, TVW, THW, NS, true>, nullptr}
 template <int WV, int WH, int TVW, int THW>
 static void launch_lmq(dim3 grid, hipStream_t st, const LmParams& p) {
-    hipLaunchKernelGGL((lmhead_pair_kernel<WV, WH, TVW, THW>), grid, dim3(64 * WV * WH), 0, st, p);
+    if (p.sample) hipLaunchKernelGGL((lmhead_pair_kernel<WV, WH, TVW, THW, true>), grid, dim3(64 * WV * WH), 0, st, p);
+    else hipLaunchKernelGGL((lmhead_pair_kernel<WV, WH, TVW, THW, false>), grid, dim3(64 * WV * WH), 0, st, p);
 }
 #define LMQ(WV, WH, TVW, THW) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, -1, launch_lmq<WV, WH, TVW, THW>, nullptr}
 #define LMV(WV, WH, TVW, THW, PD) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, -1, launch_lm<WV, WH, TVW, THW, PD>, launch_lm<WV, WH, TVW, THW, PD, 64, 1, false, true>}
@@ -1285,6 +1431,9 @@ static const LmVariant g_lm_variants[] = {
     /*27*/ LMQ(4, 2, 1, 4),     // 128 x 256, paired ring, 8 waves x (32 x 128)
     /*28*/ LMP(4, 2, 1, 4, 2),  // 128 x 256, register-staged, 8 waves
 };
+constexpr size_t LM_QUEUE_BYTES = 8 * 64;
+// entries that can take their tiles from a queue
+static bool lm_queued(int v) { return v == 20 || v == 22; }
 // entry -> its half-height form
 static int lm_half_of(int v) { return v == 2 ? 24 : v == 3 ? 25 : v == 4 ? 26 : v == 21 ? 27 : v == 5 ? 28 : -1; }
 #undef LMV
@@ -1345,25 +1494,6 @@ static int plan_capacity(int M) {
     return 0x7fffffff;
 }
 
-// Launches one kernel shape over n_vt_l vocabulary tiles that begin at row v_first (partials vt0 ...).
-static int launch_lm_tiles(const LmVariant& var, LmParams& p, int n_vt_l, int vt0, int v_first, hipStream_t st) {
-    p.n_vt_l = n_vt_l; p.vt0 = vt0; p.v_first = v_first;
-    // several row chunks: blocks of gm x gv workgroups for the 32 CUs of an XCD; gm is the largest divisor of the
-    // chunk count up to 8 (measured at V = 126464, Dh = 4096: +6 % at M >= 1024, +10..17 % at M = 512)
-    p.gm = 1; p.gv = 1;
-    if (p.n_mc >= 2) {
-        for (int c = 8; c >= 1; --c)
-            if (p.n_mc % c == 0) { p.gm = c; break; }
-        p.gv = 32 / p.gm > 8 ? 8 : 32 / p.gm;
-    }
-    if (g_lm_block_gv >= 0) { p.gv = g_lm_block_gv > 0 ? g_lm_block_gv : 1; if (g_lm_block_gv == 0) p.gm = 1; }
-    const int64_t n_vt8 = ((int64_t)(n_vt_l + 7) / 8 + p.gv - 1) / p.gv * p.gv;   // vocabulary tiles per XCD, padded to gv
-    const int64_t n_wg = n_vt8 * 8 * p.n_mc;
-    if (n_wg > 0x7fffffff) return fail(DLM_ERR_UNSUPPORTED, "lmhead: M * V too large for one launch");
-    ((p.n_mc == 1 && var.launch_nt && g_lm_nt) ? var.launch_nt : var.launch)(dim3((unsigned)n_wg), st, p);
-    return check_hip(hipGetLastError(), "lmhead_kernel launch");
-}
-
 static int device_cus() {
     static int cus[64];
     int dev = 0;
@@ -1375,13 +1505,37 @@ static int device_cus() {
     return cus[dev];
 }
 
+// Workgroups of a launch that takes its tiles from a queue: one per CU, the same number on every XCD.
+static int lm_queue_wgs() {
+    const int cus = (g_lm_cus > 0 ? g_lm_cus : device_cus()) & ~7;
+    return cus > 8 ? cus : 8;
+}
+
+// Launches one kernel shape over n_vt_l vocabulary tiles that begin at row v_first (partials vt0 ...).
+static int launch_lm_tiles(const LmVariant& var, LmParams& p, int n_vt_l, int vt0, int v_first, hipStream_t st) {
+    p.n_vt_l = n_vt_l; p.vt0 = vt0; p.v_first = v_first;
+    lm_blocking(p.n_mc, p.gm, p.gv);
+    if (g_lm_block_gv >= 0) { p.gv = g_lm_block_gv > 0 ? g_lm_block_gv : 1; if (g_lm_block_gv == 0) p.gm = 1; }
+    if (p.queue) {
+        hipLaunchKernelGGL(lmhead_queue_kernel, dim3(1), dim3(8), 0, st, p.queue);
+        var.launch(dim3((unsigned)lm_queue_wgs()), st, p);
+        return check_hip(hipGetLastError(), "lmhead_pair_kernel launch");
+    }
+    const int64_t n_vt8 = ((int64_t)(n_vt_l + 7) / 8 + p.gv - 1) / p.gv * p.gv;   // vocabulary tiles per XCD, padded to gv
+    const int64_t n_wg = n_vt8 * 8 * p.n_mc;
+    if (n_wg > 0x7fffffff) return fail(DLM_ERR_UNSUPPORTED, "lmhead: M * V too large for one launch");
+    ((p.n_mc == 1 && var.launch_nt && g_lm_nt) ? var.launch_nt : var.launch)(dim3((unsigned)n_wg), st, p);
+    return check_hip(hipGetLastError(), "lmhead_kernel launch");
+}
+
 // Fills the layout fields of p for one kernel shape (p.M = the rows this launch may hold, m_bound = the caller's
 // bound, which places the second partials) and launches it.
-// Tail rule: the shapes for 65 - 256 rows run one workgroup per CU, so a launch costs ceil(tiles / CUs) rounds of
-// equal length.  When the last round would occupy at most half of the CUs (V = 152064: 594 tiles = 2.32 rounds on 256
-// CUs, V = 157184: 614 = 2.40), the tiles of that round are launched at half height instead (a second launch of the
-// shape's 128-row form on twice as many tiles): 2.5 rounds' time instead of 3.
-static int launch_lm_shape(int v_idx, LmParams& p, int m_bound, hipStream_t st) {
+// Queue: the paired ring with several row chunks takes its tiles from one where there are more of them than CUs; ws_bytes (what the
+// call asks of its workspace, sized for 128-row tiles) leaves room for the counters behind the partials of its 256-row tiles.
+// Not with few chunks of which the last is nearly empty: a workgroup takes a tile one tile ahead, and with tiles of unequal length
+// that costs the end of the launch more than the start of the tiles (us with / without, V = 126464, Dh = 4096: 520 rows 597 / 591, 800
+// rows 811 / 784; but 512 rows 484 / 487, 896 rows 835 / 857, 1536 rows 1321 / 1364, 4100 rows 3477 / 3713).
+static int launch_lm_shape(int v_idx, LmParams& p, int m_bound, size_t ws_bytes, hipStream_t st) {
     const LmVariant& var = g_lm_variants[v_idx];
     const int n_full = (p.V + var.tv - 1) / var.tv;
     p.n_mc = (p.M + var.mb - 1) / var.mb;
@@ -1399,6 +1553,12 @@ static int launch_lm_shape(int v_idx, LmParams& p, int m_bound, hipStream_t st) 
     }
     p.n_vt = n_full;
     p.part2 = p.part + (size_t)p.n_vt * m_bound;
+    const bool second = p.sample || p.conf_mode == DLM_CONF_NEG_ENTROPY;
+    const size_t used = (size_t)(p.n_vt > p.alt_n_vt ? p.n_vt : p.alt_n_vt) * m_bound * sizeof(f32x4) * (second ? 2 : 1);
+    const int rest = p.M % var.mb;
+    const bool even = rest == 0 || 4 * rest > var.mb || p.n_mc > 8;
+    if (lm_queued(v_idx) && p.n_mc > 1 && p.Dh >= 128 && even && (int64_t)n_full * p.n_mc > lm_queue_wgs() && used + LM_QUEUE_BYTES <= ws_bytes)
+        p.queue = (int*)((char*)p.part + used);
     return launch_lm_tiles(var, p, n_full, 0, 0, st);
 }
 
@@ -1426,6 +1586,8 @@ static int lmhead_enqueue(const dlm_lmhead_args* a, void* workspace, void* strea
     p.step = a->sample_step; p.stream = a->sample_stream;
     p.m_lo = -1; p.m_hi = 0x7fffffff;
     p.alt_cap = 0; p.alt_n_vt = 0; p.alt_part2 = nullptr;
+    p.queue = nullptr;
+    const size_t ws_bytes = dlm_lmhead_workspace_bytes(a);
     hipStream_t st = (hipStream_t)stream;
 
     // The caller's bound M sizes the launch, the device's count says how many rows there are.  When the caller
@@ -1441,12 +1603,12 @@ static int lmhead_enqueue(const dlm_lmhead_args* a, void* workspace, void* strea
         LmParams q = p;
         q.M = cap;
         q.m_hi = cap;
-        rc = launch_lm_shape(v_try, q, a->M, st);
+        rc = launch_lm_shape(v_try, q, a->M, ws_bytes, st);
         if (rc != DLM_OK) return rc;
         p.m_lo = cap;
         p.alt_cap = cap; p.alt_n_vt = q.n_vt; p.alt_part2 = q.part2;
     }
-    rc = launch_lm_shape(v_safe, p, a->M, st);
+    rc = launch_lm_shape(v_safe, p, a->M, ws_bytes, st);
     if (rc != DLM_OK) return rc;
     // Many rows of which the device counts few: what a workgroup past the count loads before it ends is all that shows.  Whole call, us,
     // Dh = 256, with / without AHEAD: 65536 rows, V = 2048, 1 counted 36.3 / 27.7, 8192 counted 63.7 / 57.0, all 240 / 245; V = 60000, 1

@@ -431,3 +431,35 @@ def test_half_height_tail_launch(M, cus, V):
         compare(run_lm(h, w, forbid=V - 1, target=tgt), ref)
     finally:
         dlm.set_option("lmhead_cus", 0)
+
+
+@pytest.mark.parametrize("M,m_dev,Dh,V,cus", [
+    (257, None, 128, 2100, 8),      # shape of 192-row chunks, the shortest walk a queue takes, more lists than CUs
+    (300, 193, 192, 1100, 8),       # one row in the second chunk; 5 vocabulary tiles: three of the eight lists are empty
+    (384, 192, 128, 4000, 16),      # the device counts one chunk less than the bound
+    (470, None, 256, 2817, 8),      # 256-row chunks, a last vocabulary tile of one token
+    (580, 300, 128, 3000, 24),
+    (580, 256, 192, 3000, 8),
+    (700, 0, 128, 3000, 8),         # nothing counted
+    (700, 1, 128, 3000, 8),
+    (1700, 1400, 128, 2500, 8),     # seven chunks (blocks of seven), six of them counted
+    (2049, None, 128, 2600, 16),    # nine chunks, one row in the last; the last group of vocabulary tiles incomplete
+])
+def test_workgroups_that_take_their_tiles_from_a_queue(M, m_dev, Dh, V, cus):
+    """More tiles than workgroups, against the oracle, and (all rows counted) bit for bit what one workgroup a tile gives."""
+    R = M + 50
+    h, w = rnd(940 + M, (R, Dh)), rnd(941 + V, (V, Dh), Dh ** -0.25)
+    idx = np.random.default_rng(M).permutation(R)[:M].astype(np.int32)
+    kw = dict(row_idx=idx, M=M, m_dev=m_dev, forbid=V - 1, inv_t=0.9)
+    m = M if m_dev is None else m_dev
+    ref = oracle.lmhead(h, w, row_idx=idx[:m], forbid_token=V - 1, inv_temperature=0.9) if m else None
+    plain = run_lm(h, w, **kw)
+    dlm.set_option("lmhead_cus", cus)
+    try:
+        queued = [run_lm(h, w, **kw) for _ in range(2)]
+    finally:
+        dlm.set_option("lmhead_cus", 0)
+    for got in queued:
+        compare_prefix(got, ref, m)
+        if m_dev is None:
+            assert all(np.array_equal(got[k], plain[k], equal_nan=True) for k in plain)
