@@ -36,9 +36,8 @@ struct LmParams {
     float* ztarget;
     f32x4* part;  // [M][n_vt] of (max, sumexp, runner-up, argmax bits)
     int n_vt, n_mc;   // partials per row (all launches of the call together), row chunks
-    // One call may cover the vocabulary with two launches (full-height tiles, then half-height ones for the tail):
-    // a launch owns n_vt_l tiles that begin at vocabulary row v_first and fill the partials vt0 .. vt0 + n_vt_l - 1.
-    int n_vt_l, vt0, v_first;
+    int n_vt_l;   // full-height tiles of the launch
+    int n_half;   // half-height tiles behind them (lmhead_tail_kernel)
     int gm, gv;   // workgroup blocking per XCD: gm row chunks x gv vocabulary tiles run side by side
     // Gumbel-max sampling (sample != 0): a second partial per (tile, row) of
     // (perturbed max, logit of that token, its index bits, unused)
@@ -412,8 +411,11 @@ __device__ __forceinline__ void lm_epilogue(const LmParams& p, f32x16 (&acc)[TVW
 // WV x WH wavefronts; each owns TVW x THW accumulator tiles of 32 (vocab) x 32 (hidden rows).
 // PD = how many 64-element chunks of W / H are in flight in registers ahead of the one being multiplied.
 // NTW: W is fetched with non-temporal loads (see the launch table: for launches with one row chunk).
-template <int WV, int WH, int TVW, int THW, int PD, int KCH = 64, int OCC = 1, bool PIPE = false, bool NTW = false>
-__global__ __launch_bounds__(64 * WV * WH, OCC) void lmhead_kernel(LmParams p) {
+template <int WV, int WH, int TVW, int THW, int KCH>
+constexpr int lm_staged_lds() { return 2 * (32 * TVW * WV + 32 * THW * WH) * (KCH * 2 + 16); }
+// bid: index of the workgroup among those of its n_vt_l tiles, which begin at vocabulary row v_first and partial vt0
+template <int WV, int WH, int TVW, int THW, int PD, int KCH, bool PIPE, bool NTW>
+__device__ __forceinline__ void lm_staged_tile(const LmParams& p, unsigned char* smem, int bid, int n_vt_l, int vt0, int v_first) {
     constexpr int NT = 64 * WV * WH;
     constexpr int TV = 32 * TVW * WV;   // vocabulary rows per workgroup
     constexpr int MB = 32 * THW * WH;   // hidden rows per workgroup
@@ -426,16 +428,15 @@ __global__ __launch_bounds__(64 * WV * WH, OCC) void lmhead_kernel(LmParams p) {
     constexpr int STAGE = (TV + MB) * LP;
     constexpr int RED_BYTES = WV * MB * 16;
     static_assert(2 * STAGE >= 2 * RED_BYTES, "both reduction buffers must fit in the staging area");
-    __shared__ __attribute__((aligned(16))) unsigned char smem[2 * STAGE];
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int wv = w % WV, wh = w / WV;
     const int n = lane & 31, hi = lane >> 5;
     int vt, mc, kgroup;
-    lm_tile_of_block(blockIdx.x, p.n_mc, p.gm, p.gv, vt, mc, kgroup);
-    if (vt >= p.n_vt_l) return;
-    const int v0 = p.v_first + vt * TV;
-    vt += p.vt0;
+    lm_tile_of_block(bid, p.n_mc, p.gm, p.gv, vt, mc, kgroup);
+    if (vt >= n_vt_l) return;
+    const int v0 = v_first + vt * TV;
+    vt += vt0;
     const int m0 = mc * MB;
     int M = p.M;
     if (!lm_rows(p, M)) return;
@@ -623,6 +624,23 @@ __global__ __launch_bounds__(64 * WV * WH, OCC) void lmhead_kernel(LmParams p) {
     lm_epilogue<WV, WH, TVW, THW>(p, acc, smem, v0, m0, M, vt, wv, wh, n, hi, tid);
 }
 
+template <int WV, int WH, int TVW, int THW, int PD, int KCH = 64, int OCC = 1, bool PIPE = false, bool NTW = false>
+__global__ __launch_bounds__(64 * WV * WH, OCC) void lmhead_kernel(LmParams p) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[lm_staged_lds<WV, WH, TVW, THW, KCH>()];
+    lm_staged_tile<WV, WH, TVW, THW, PD, KCH, PIPE, NTW>(p, smem, blockIdx.x, p.n_vt_l, 0, 0);
+}
+
+// Two heights in one launch: full tiles in the first n_vt_l workgroups, then n_half tiles of half the height for the rest of the
+// vocabulary (see the tail rule below).  As a launch of their own the half tiles waited for the last full one.
+template <int WV, int WH, int TVW, int THW, int PD, bool NTW>
+__global__ __launch_bounds__(64 * WV * WH, 1) void lmhead_tail_kernel(LmParams p) {
+    static_assert(TVW % 2 == 0, "half the height is a whole number of accumulator tiles");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[lm_staged_lds<WV, WH, TVW, THW, 64>()];
+    const int bid = blockIdx.x;
+    if (bid < p.n_vt_l) lm_staged_tile<WV, WH, TVW, THW, PD, 64, true, NTW>(p, smem, bid, p.n_vt_l, 0, 0);
+    else lm_staged_tile<WV, WH, TVW / 2, THW, PD, 64, true, NTW>(p, smem, bid - p.n_vt_l, p.n_half, p.n_vt_l, p.n_vt_l * 32 * TVW * WV);
+}
+
 // Second kernel family: W fragments go straight from global memory into MFMA A-operand registers.
 // The wavefronts of a workgroup split only the vocabulary, so no W element is shared between them and
 // staging W in LDS would only add LDS traffic (the LDS port, not the MFMA pipe, limits the shared-W shapes
@@ -648,8 +666,7 @@ __global__ __launch_bounds__(64 * WV) void lmhead_wdirect_kernel(LmParams p) {
     int vt, mc, kgroup;
     lm_tile_of_block(blockIdx.x, p.n_mc, p.gm, p.gv, vt, mc, kgroup);
     if (vt >= p.n_vt_l) return;
-    const int v0 = p.v_first + vt * TV;
-    vt += p.vt0;
+    const int v0 = vt * TV;
     const int m0 = mc * MB;
     int M = p.M;
     if (!lm_rows(p, M)) return;
@@ -795,8 +812,7 @@ __global__ __launch_bounds__(64 * WV * WH) void lmhead_dma_kernel(LmParams p) {
     int vt, mc, kgroup;
     lm_tile_of_block(blockIdx.x, p.n_mc, p.gm, p.gv, vt, mc, kgroup);
     if (vt >= p.n_vt_l) return;
-    const int v0 = p.v_first + vt * TV, m0 = mc * MB;
-    vt += p.vt0;
+    const int v0 = vt * TV, m0 = mc * MB;
     int M = p.M;
     if (!lm_rows(p, M)) return;
     if (m0 >= M) return;
@@ -1014,7 +1030,7 @@ __global__ __launch_bounds__(64 * WV * WH) void lmhead_pair_kernel(LmParams p) {
         lm_tile_of_block(blockIdx.x, n_mc, gm, gv, vt, mc, kgroup);
         if (vt >= p.n_vt_l || mc * MB >= M) return;
     }
-    int v0 = p.v_first + vt * TV, m0 = mc * MB;
+    int v0 = vt * TV, m0 = mc * MB;
 
     // source row of each of this wavefront's requests in the tile (v_first_, m_first_): a row of W, or of `hidden`
 #define PR_ROWS(dst, v_first_, m_first_)                                                                 \
@@ -1167,7 +1183,7 @@ __global__ __launch_bounds__(64 * WV * WH) void lmhead_pair_kernel(LmParams p) {
         if (more) {
             lm_tile_of_slot(xcd, ahead, p.n_vt_l, n_mc, gm, gv, vt_next, mc_next, kgroup);
             kstart_next = (int)((unsigned)(gv > 1 ? kgroup : vt_next) * 11u % (unsigned)nk) & ~1;
-            PR_ROWS(nrows, p.v_first + vt_next * TV, mc_next * MB)
+            PR_ROWS(nrows, vt_next * TV, mc_next * MB)
             if (tid == 0) taken = __hip_atomic_fetch_add(p.queue + 16 * xcd, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // Row tiles of this wavefront that hold a row of the launch, so that the row count of a step that the host only knows an
@@ -1211,11 +1227,11 @@ __global__ __launch_bounds__(64 * WV * WH) void lmhead_pair_kernel(LmParams p) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        lm_store_partials<WV, WH, THW>(p, red, m0, M, p.vt0 + vt, w * 64 + lane_);
+        lm_store_partials<WV, WH, THW>(p, red, m0, M, vt, w * 64 + lane_);
         if (!more) break;
         ahead = __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(red + RED)) + 2 * (int)(gridDim.x >> 3);
         vt = vt_next;
-        v0 = p.v_first + vt * TV;
+        v0 = vt * TV;
         m0 = mc_next * MB;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no request into LDS may outlive its workgroup
@@ -1361,9 +1377,10 @@ __global__ __launch_bounds__(256) void lmhead_reduce_kernel(LmParams p) {
     }
 }
 
+int g_lm_nt = 1;                 // 1 = non-temporal W loads when there is one row chunk (default); 0 = never (tuning)
+
 struct LmVariant {
     int tv, mb, threads;
-    int half;   // table entry with the same rows and half the vocabulary tile height (for the tail of a launch), -1: none
     void (*launch)(dim3, hipStream_t, const LmParams&);
     // The same shape with W fetched by non-temporal loads, for launches with ONE row chunk, where every element of
     // W is used exactly once: W then streams through L2 without being kept.  Measured on one box, V = 126464,
@@ -1376,32 +1393,32 @@ template <int WV, int WH, int TVW, int THW, int PD, int KCH = 64, int OCC = 1, b
 static void launch_lm(dim3 grid, hipStream_t st, const LmParams& p) {
     hipLaunchKernelGGL((lmhead_kernel<WV, WH, TVW, THW, PD, KCH, OCC, PIPE, NTW>), grid, dim3(64 * WV * WH), 0, st, p);
 }
-#define LMP(WV, WH, TVW, THW, PD) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, -1, launch_lm<WV, WH, TVW, THW, PD, 64, 1, true>, launch_lm<WV, WH, TVW, THW, PD, 64, 1, true, true>}
+#define LMP(WV, WH, TVW, THW, PD) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, launch_lm<WV, WH, TVW, THW, PD, 64, 1, true>, launch_lm<WV, WH, TVW, THW, PD, 64, 1, true, true>}
 template <int WV, int TVW, int THW, int PDW>
 static void launch_lmd(dim3 grid, hipStream_t st, const LmParams& p) {
     hipLaunchKernelGGL((lmhead_wdirect_kernel<WV, TVW, THW, PDW>), grid, dim3(64 * WV), 0, st, p);
 }
-#define LMD(WV, TVW, THW, PDW) {32 * TVW * WV, 32 * THW, 64 * WV, -1, launch_lmd<WV, TVW, THW, PDW>, nullptr}
+#define LMD(WV, TVW, THW, PDW) {32 * TVW * WV, 32 * THW, 64 * WV, launch_lmd<WV, TVW, THW, PDW>, nullptr}
 template <int WV, int WH, int TVW, int THW, int NS, bool XB = false>
 static void launch_lma(dim3 grid, hipStream_t st, const LmParams& p) {
     hipLaunchKernelGGL((lmhead_dma_kernel<WV, WH, TVW, THW, NS, XB>), grid, dim3(64 * WV * WH), 0, st, p);
 }
-#define LMA(WV, WH, TVW, THW, NS) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, -1, launch_lma<WV, WH, TVW, THW, NS>, nullptr}
-#define LMX(WV, WH, TVW, THW, NS) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, -1, launch_lma<WV, WH, TVW, THW, NS, true>, nullptr}
+#define LMA(WV, WH, TVW, THW, NS) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, launch_lma<WV, WH, TVW, THW, NS>, nullptr}
+#define LMX(WV, WH, TVW, THW, NS) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, launch_lma<WV, WH, TVW, THW, NS, true>, nullptr}
 template <int WV, int WH, int TVW, int THW>
 static void launch_lmq(dim3 grid, hipStream_t st, const LmParams& p) {
     if (p.sample) hipLaunchKernelGGL((lmhead_pair_kernel<WV, WH, TVW, THW, true>), grid, dim3(64 * WV * WH), 0, st, p);
     else hipLaunchKernelGGL((lmhead_pair_kernel<WV, WH, TVW, THW, false>), grid, dim3(64 * WV * WH), 0, st, p);
 }
-#define LMQ(WV, WH, TVW, THW) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, -1, launch_lmq<WV, WH, TVW, THW>, nullptr}
-#define LMV(WV, WH, TVW, THW, PD) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, -1, launch_lm<WV, WH, TVW, THW, PD>, launch_lm<WV, WH, TVW, THW, PD, 64, 1, false, true>}
+#define LMQ(WV, WH, TVW, THW) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, launch_lmq<WV, WH, TVW, THW>, nullptr}
+#define LMV(WV, WH, TVW, THW, PD) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, launch_lm<WV, WH, TVW, THW, PD>, launch_lm<WV, WH, TVW, THW, PD, 64, 1, false, true>}
 static const LmVariant g_lm_variants[] = {
     // shapes the planner uses, by row count M (V = 126464, Dh = 4096 on MI355X, us per main-kernel launch in the
     // rollout, non-temporal W stream; entries 22, 20 above 256 rows):
     /*0*/ LMV(4, 1, 1, 1, 3),   // M <= 32   128 x 32 tile,  4 waves            ~161
     /*1*/ LMP(4, 1, 1, 2, 3),   // M <= 64   128 x 64,       4 waves            ~159
-    /*2*/ LMP(8, 1, 1, 3, 3),   // M <= 96   256 x 96,       8 waves            ~166
-    /*3*/ LMP(4, 2, 2, 2, 3),   // M <= 128  256 x 128,      8 waves            ~172
+    /*2*/ LMP(8, 1, 1, 3, 3),   // 256 x 96, 8 waves: as fast as entry 3 with up to 96 rows (tests, tuning)
+    /*3*/ LMP(4, 2, 2, 2, 3),   // M <= 128  256 x 128,      8 waves            ~166 - 180
     /*4*/ LMP(4, 2, 2, 3, 2),   // M <= 192  256 x 192,      8 waves            ~203
     /*5*/ LMP(4, 2, 2, 4, 2),   // M <= 256  256 x 256,      8 waves            ~245
     // alternatives kept for tests and tuning sweeps
@@ -1423,8 +1440,7 @@ static const LmVariant g_lm_variants[] = {
     /*21*/ LMQ(4, 2, 2, 4),     // same, 8 waves x (64 x 128): one 256-row chunk as fast as entry 5, with 1.47 x the HBM fetch
     /*22*/ LMQ(4, 1, 2, 6),     // 256 x 192, 4 waves x (64 x 192)
     /*23*/ LMQ(4, 1, 2, 4),     // 256 x 128, 4 waves x (64 x 128)
-    // half-height forms of entries 2, 3, 4, 21 and 5 (128 vocabulary rows): the tail of a launch whose tile count leaves
-    // at most half of the CUs busy in its last round (see launch_lm_shape)
+    // half-height forms (128 vocabulary rows)
     /*24*/ LMP(4, 1, 1, 3, 3),  // 128 x 96,  4 waves
     /*25*/ LMP(4, 2, 1, 2, 3),  // 128 x 128, 8 waves
     /*26*/ LMP(4, 2, 1, 3, 2),  // 128 x 192, 8 waves
@@ -1434,8 +1450,16 @@ static const LmVariant g_lm_variants[] = {
 constexpr size_t LM_QUEUE_BYTES = 8 * 64;
 // entries that can take their tiles from a queue
 static bool lm_queued(int v) { return v == 20 || v == 22; }
-// entry -> its half-height form
-static int lm_half_of(int v) { return v == 2 ? 24 : v == 3 ? 25 : v == 4 ? 26 : v == 21 ? 27 : v == 5 ? 28 : -1; }
+// The form of an entry that ends in half-height tiles, null where there is none.
+template <int WV, int WH, int TVW, int THW, int PD>
+static void launch_lmt(dim3 grid, hipStream_t st, const LmParams& p) {
+    if (g_lm_nt) hipLaunchKernelGGL((lmhead_tail_kernel<WV, WH, TVW, THW, PD, true>), grid, dim3(64 * WV * WH), 0, st, p);
+    else hipLaunchKernelGGL((lmhead_tail_kernel<WV, WH, TVW, THW, PD, false>), grid, dim3(64 * WV * WH), 0, st, p);
+}
+typedef void (*lm_launch_t)(dim3, hipStream_t, const LmParams&);
+static lm_launch_t lm_tail_of(int v) {
+    return v == 3 ? launch_lmt<4, 2, 2, 2, 3> : v == 4 ? launch_lmt<4, 2, 2, 3, 2> : v == 5 ? launch_lmt<4, 2, 2, 4, 2> : nullptr;
+}
 #undef LMV
 #undef LMA
 #undef LMX
@@ -1445,7 +1469,6 @@ static int lm_half_of(int v) { return v == 2 ? 24 : v == 3 ? 25 : v == 4 ? 26 : 
 constexpr int N_LM_VARIANTS = sizeof(g_lm_variants) / sizeof(g_lm_variants[0]);
 constexpr int LM_MIN_TV = 128;   // smallest vocabulary tile of any variant: sizes the workspace
 int g_lm_variant = -1;           // -1 = choose by M; otherwise force an entry of the table (dlm_set_option)
-int g_lm_nt = 1;                 // 1 = non-temporal W loads when there is one row chunk (default); 0 = never (tuning)
 int g_lm_block_gv = -1;          // -1 = automatic XCD blocking; 0 = none; n = n vocabulary tiles per block (tuning)
 int g_lm_cus = 0;                // CUs the tail rule assumes: 0 = the device's count; -1 = no half-height tail (tuning, tests)
 
@@ -1453,7 +1476,6 @@ static int plan_lmhead(int M) {
     if (g_lm_variant >= 0) return g_lm_variant;
     if (M <= 32) return 0;
     if (M <= 64) return 1;
-    if (M <= 96) return 2;
     if (M <= 128) return 3;
     if (M <= 192) return 4;
     if (M <= 256) return 5;         // one 256-row chunk, register-staged: as fast as the ring (entry 21), which fetches 1.3 - 1.5 x W here
@@ -1488,7 +1510,7 @@ using namespace dlm;
 
 // largest row count served by the shape plan_lmhead picks for M rows
 static int plan_capacity(int M) {
-    static const int caps[] = {32, 64, 96, 128, 192, 256, 384};
+    static const int caps[] = {32, 64, 128, 192, 256, 384};
     for (int c : caps)
         if (M <= c) return c;
     return 0x7fffffff;
@@ -1511,9 +1533,9 @@ static int lm_queue_wgs() {
     return cus > 8 ? cus : 8;
 }
 
-// Launches one kernel shape over n_vt_l vocabulary tiles that begin at row v_first (partials vt0 ...).
-static int launch_lm_tiles(const LmVariant& var, LmParams& p, int n_vt_l, int vt0, int v_first, hipStream_t st) {
-    p.n_vt_l = n_vt_l; p.vt0 = vt0; p.v_first = v_first;
+// Launches one kernel shape over n_vt_l vocabulary tiles.
+static int launch_lm_tiles(const LmVariant& var, LmParams& p, int n_vt_l, hipStream_t st) {
+    p.n_vt_l = n_vt_l; p.n_half = 0;
     lm_blocking(p.n_mc, p.gm, p.gv);
     if (g_lm_block_gv >= 0) { p.gv = g_lm_block_gv > 0 ? g_lm_block_gv : 1; if (g_lm_block_gv == 0) p.gm = 1; }
     if (p.queue) {
@@ -1535,21 +1557,26 @@ static int launch_lm_tiles(const LmVariant& var, LmParams& p, int n_vt_l, int vt
 // Not with few chunks of which the last is nearly empty: a workgroup takes a tile one tile ahead, and with tiles of unequal length
 // that costs the end of the launch more than the start of the tiles (us with / without, V = 126464, Dh = 4096: 520 rows 597 / 591, 800
 // rows 811 / 784; but 512 rows 484 / 487, 896 rows 835 / 857, 1536 rows 1321 / 1364, 4100 rows 3477 / 3713).
+// Tail rule: the shapes for 65 - 256 rows run one workgroup per CU, so a launch costs ceil(tiles / CUs) rounds of
+// equal length.  When the last round would occupy at most half of the CUs (V = 152064: 594 tiles = 2.32 rounds on 256
+// CUs, V = 157184: 614 = 2.40), the tiles of that round are cut in halves: 2.5 rounds' time instead of 3.  Both heights in one launch:
+// the half tiles start as the CUs come free.  us a call, V = 152064, Dh = 3584, halves as a launch of their own / in one launch: 80 rows 200 /
+// 196, 128 rows 216 / 213, 192 rows 258 / 254, 256 rows 314 / 310 (with three rounds 80 rows 232, 256 rows 343).
 static int launch_lm_shape(int v_idx, LmParams& p, int m_bound, size_t ws_bytes, hipStream_t st) {
     const LmVariant& var = g_lm_variants[v_idx];
     const int n_full = (p.V + var.tv - 1) / var.tv;
     p.n_mc = (p.M + var.mb - 1) / var.mb;
-    const int half = lm_half_of(v_idx);
+    const lm_launch_t tail_launch = lm_tail_of(v_idx);
     const int cus = g_lm_cus > 0 ? g_lm_cus : device_cus();
     const int tail = n_full % cus;
-    if (g_lm_cus >= 0 && half >= 0 && p.n_mc == 1 && n_full > cus && tail > 0 && 2 * tail <= cus) {
-        const int n_main = n_full - tail, v_split = n_main * var.tv;
-        const int n_half = (p.V - v_split + var.tv / 2 - 1) / (var.tv / 2);
-        p.n_vt = n_main + n_half;
+    if (g_lm_cus >= 0 && tail_launch && p.n_mc == 1 && n_full > cus && tail > 0 && 2 * tail <= cus) {
+        p.n_vt_l = n_full - tail;
+        p.n_half = (p.V - p.n_vt_l * var.tv + var.tv / 2 - 1) / (var.tv / 2);
+        p.n_vt = p.n_vt_l + p.n_half;
         p.part2 = p.part + (size_t)p.n_vt * m_bound;
-        int rc = launch_lm_tiles(var, p, n_main, 0, 0, st);
-        if (rc != DLM_OK) return rc;
-        return launch_lm_tiles(g_lm_variants[half], p, n_half, n_main, v_split, st);
+        p.gm = 1; p.gv = 1;
+        tail_launch(dim3((unsigned)p.n_vt), st, p);
+        return check_hip(hipGetLastError(), "lmhead_tail_kernel launch");
     }
     p.n_vt = n_full;
     p.part2 = p.part + (size_t)p.n_vt * m_bound;
@@ -1559,7 +1586,7 @@ static int launch_lm_shape(int v_idx, LmParams& p, int m_bound, size_t ws_bytes,
     const bool even = rest == 0 || 4 * rest > var.mb || p.n_mc > 8;
     if (lm_queued(v_idx) && p.n_mc > 1 && p.Dh >= 128 && even && (int64_t)n_full * p.n_mc > lm_queue_wgs() && used + LM_QUEUE_BYTES <= ws_bytes)
         p.queue = (int*)((char*)p.part + used);
-    return launch_lm_tiles(var, p, n_full, 0, 0, st);
+    return launch_lm_tiles(var, p, n_full, st);
 }
 
 extern "C" size_t dlm_lmhead_workspace_bytes(const dlm_lmhead_args* a) {
@@ -1587,6 +1614,7 @@ static int lmhead_enqueue(const dlm_lmhead_args* a, void* workspace, void* strea
     p.m_lo = -1; p.m_hi = 0x7fffffff;
     p.alt_cap = 0; p.alt_n_vt = 0; p.alt_part2 = nullptr;
     p.queue = nullptr;
+    p.n_half = 0;
     const size_t ws_bytes = dlm_lmhead_workspace_bytes(a);
     hipStream_t st = (hipStream_t)stream;
 
