@@ -60,10 +60,9 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
 
 // NTKV: K/V are fetched with non-temporal loads, for launches in which one workgroup is the only reader of its
 // (sequence, KV head): the rollout step streams 70 - 1000 MB of cache that nothing reads twice.
-// SWP: software-pipelined form of the 128-row shapes.  MFMA and vector-ALU instructions of DIFFERENT wavefronts of a
-// SIMD do not run side by side on this chip (a wavefront of MFMAs beside a wavefront of exponentials takes the sum of
-// their times: measured), those of ONE wavefront do; so each wavefront weaves the softmax of tile t between the score
-// MFMAs of tile t + 1 and between the first P V MFMAs of tile t, instead of running the three phases one after another.
+// SWP: software-pipelined form of the 128-row shapes: each wavefront weaves the softmax of tile t between the score MFMAs of tile
+// t + 1 and between the first P V MFMAs of tile t, instead of running the three phases one after another and leaving the
+// overlap to the other wavefronts of its SIMD (whose vector work does run beside its MFMAs).
 template <int D, int NWR, int NWK, int RTW, bool BC, int PF = 1, int OCC = 1, bool NTKV = false, bool SWP = false>
 __global__ __launch_bounds__(64 * NWR * NWK, OCC) void attn_kernel(AttnParams p) {
     static_assert(!SWP || (RTW == 1 && NWK == 1 && NWR > 1 && D == 128 && PF == 1), "the pipelined form exists for 128-row workgroups, d = 128");
@@ -319,6 +318,12 @@ __global__ __launch_bounds__(64 * NWR * NWK, OCC) void attn_kernel(AttnParams p)
 
     // One K/V tile: scores, (lazy) online softmax, P V.  A macro rather than a lambda: every array it
     // touches must stay in registers.
+    // Where a SIMD holds wavefronts of several workgroups, the further one is in its tile the higher its priority: of two that
+    // could issue, the one whose tile ends first goes first, and the wavefronts stay in different phases, products of
+    // one beside the softmax of another, instead of meeting at the matrix pipe.  Forward, us, without / with: 8 x 4096, 32 / 8 heads of 128,
+    // blocks of 4 1306 / 1278, full mask 2272 / 2222, 128 packed sequences 867 / 856, 16 x 1024, 14 / 2 heads of 64 69.8 / 66.2.  (Products alone or
+    // softmax alone raised: a third to two thirds of it.)
+#define ATTN_PRIO(level) if constexpr (NWR > 1) __builtin_amdgcn_s_setprio(level);
 #define ATTN_COMPUTE() /* uses the tile index `t` of the enclosing scope */                              \
     if (t < Tn) {                                                                                        \
         f32x16 S[RTW]; \
@@ -329,7 +334,7 @@ _Pragma("unroll") \
         /* K fragments are requested FD MFMA steps ahead of their use, so that the LDS round trip of one fragment \
            is covered by the MFMAs of the steps before it instead of sitting between two dependent MFMAs */ \
         { \
-            bf16x8 kfr[FD]; \
+            bf16x8 kfr[FD]; ATTN_PRIO(1) \
 _Pragma("unroll") \
             for (int c = 0; c < FD; ++c) kfr[c] = *reinterpret_cast<const bf16x8*>(Kl + n * KP + (16 * c + 8 * hi) * 2); \
 _Pragma("unroll") \
@@ -346,7 +351,7 @@ _Pragma("unroll") \
         const bool same = (sg == 0) ? same0 : ((sg == 1) ? same1 : same2); \
         const bool ragged = (lt * 32 + 32 > slen) || \
                             (BC && (spos0 + 31 >= qlim_min - hoff || (same && spos0 < qlim_max - p.bs))); \
-        bf16x8 pf[RTW][2]; \
+        bf16x8 pf[RTW][2]; ATTN_PRIO(2) \
 _Pragma("unroll") \
         for (int rt = 0; rt < RTW; ++rt) { \
             float mx = -INFINITY; \
@@ -397,7 +402,7 @@ _Pragma("unroll") \
             pf[rt][0] = as_bf16x8(lo); \
             pf[rt][1] = as_bf16x8(hi4); \
         } \
-        const int s16 = lane & 15, blk = (lane >> 4) & 1; \
+        const int s16 = lane & 15, blk = (lane >> 4) & 1; ATTN_PRIO(3) \
         /* step e = 2 * dt + j2 of the second product; its V^T fragment (two transposing reads) is requested FD steps ahead */ \
         { \
             union VFrag { s16x4 h[2]; bf16x8 v; }; \
@@ -420,7 +425,7 @@ _Pragma("unroll") \
                 } \
                 __builtin_amdgcn_sched_barrier(0); \
             } \
-        } \
+        } ATTN_PRIO(0) \
     }
 
     // tile of iteration `it` for this wave group: it * NWK + wk; it sits in register slot it % PF
@@ -640,6 +645,7 @@ _Pragma("unroll") \
 #undef ATTN_STORE
 #undef ATTN_TILE_SYNC
 #undef ATTN_COMPUTE
+#undef ATTN_PRIO
 #undef ATTN_PREFETCH
 #undef ATTN_LD
 #undef ATTN_TILE
