@@ -1552,7 +1552,8 @@ static int launch_lm_tiles(const LmVariant& var, LmParams& p, int n_vt_l, hipStr
 
 // Fills the layout fields of p for one kernel shape (p.M = the rows this launch may hold, m_bound = the caller's
 // bound, which places the second partials) and launches it.
-// Queue: the paired ring with several row chunks takes its tiles from one where there are more of them than CUs; ws_bytes (what the
+// Queue: the paired ring with several row chunks takes its tiles from one where there are two or more of them a CU (with fewer the launch
+// that clears the counters costs what the second tile saves: 9000 x 4096, 2100 rows, 1.3 tiles a CU, 186.6 against 183.3 us); ws_bytes (what the
 // call asks of its workspace, sized for 128-row tiles) leaves room for the counters behind the partials of its 256-row tiles.
 // Not with few chunks of which the last is nearly empty: a workgroup takes a tile one tile ahead, and with tiles of unequal length
 // that costs the end of the launch more than the start of the tiles (us with / without, V = 126464, Dh = 4096: 520 rows 597 / 591, 800
@@ -1584,7 +1585,7 @@ static int launch_lm_shape(int v_idx, LmParams& p, int m_bound, size_t ws_bytes,
     const size_t used = (size_t)(p.n_vt > p.alt_n_vt ? p.n_vt : p.alt_n_vt) * m_bound * sizeof(f32x4) * (second ? 2 : 1);
     const int rest = p.M % var.mb;
     const bool even = rest == 0 || 4 * rest > var.mb || p.n_mc > 8;
-    if (lm_queued(v_idx) && p.n_mc > 1 && p.Dh >= 128 && even && (int64_t)n_full * p.n_mc > lm_queue_wgs() && used + LM_QUEUE_BYTES <= ws_bytes)
+    if (lm_queued(v_idx) && p.n_mc > 1 && p.Dh >= 128 && even && (int64_t)n_full * p.n_mc >= 2 * lm_queue_wgs() && used + LM_QUEUE_BYTES <= ws_bytes)
         p.queue = (int*)((char*)p.part + used);
     return launch_lm_tiles(var, p, n_full, st);
 }

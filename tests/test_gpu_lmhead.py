@@ -435,10 +435,10 @@ def test_half_height_tail_launch(M, cus, V):
 
 @pytest.mark.parametrize("M,m_dev,Dh,V,cus", [
     (257, None, 128, 2100, 8),      # shape of 192-row chunks, the shortest walk a queue takes, more lists than CUs
-    (300, 193, 192, 1100, 8),       # one row in the second chunk; 5 vocabulary tiles: three of the eight lists are empty
+    (960, 300, 192, 1100, 8),       # two of four chunks counted; 5 vocabulary tiles: three of the eight lists are empty
     (384, 192, 128, 4000, 16),      # the device counts one chunk less than the bound
     (470, None, 256, 2817, 8),      # 256-row chunks, a last vocabulary tile of one token
-    (580, 300, 128, 3000, 24),
+    (580, 300, 128, 3000, 16),
     (580, 256, 192, 3000, 8),
     (700, 0, 128, 3000, 8),         # nothing counted
     (700, 1, 128, 3000, 8),
