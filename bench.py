@@ -158,8 +158,8 @@ def measure_peaks(torch, reps: int = 20) -> dict:
     ov = {}
     for mode, key in ((0, "all_mfma"), (1, "all_valu"), (2, "mfma_waves_beside_valu_waves"), (3, "both_in_each_wave")):
         ov[key] = round(timed(lambda: L.dlm_peak_overlap(mode, 256, 20000, fs.data_ptr(), st)) * 1e3, 3)
-    ov["note"] = ("ms for 20000 iterations, 8 wavefronts per CU; side by side across wavefronts would give max(all_mfma, all_valu) / 2 "
-                  "for the third figure, mutual exclusion their sum / 2")
+    ov["note"] = ("ms for 20000 iterations, 8 wavefronts per CU; a lone vector wavefront on a SIMD is bound by its own latency and "
+                  "takes longer than all_valu / 2, so the third figure beside the sum of the halves does not show exclusion")
     out["mfma_valu_overlap_ms"] = ov
     out["what"] = ("1 GiB device copy (read + write), 1 GiB one-pass read with ordinary / non-temporal loads, "
                    "register-only 32x32x16 bf16 MFMA loop on 2048 workgroups of 4 wavefronts with small constant operands and "

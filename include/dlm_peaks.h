@@ -40,8 +40,8 @@ int dlm_peak_mfma(int n_wg, int iters, const void *operands, float *sink, void *
  *   mode 0: all eight wavefronts matrix work;   mode 1: all eight vector work;
  *   mode 2: wavefronts 0-3 matrix, 4-7 vector (one of each kind per SIMD);
  *   mode 3: every wavefront both, each MFMA followed by four of the pairs in its own instruction stream.
- * If different wavefronts' MFMA and vector work overlapped, mode 2 would take the longer of half of mode 0 and half of
- * mode 1; if they exclude each other, the sum.  Mode 3 against modes 0 + 1 says the same for one wavefront's own stream.
+ * Mode 2 against the sum of half of mode 0 and half of mode 1 tells little by itself: a lone vector wavefront on a SIMD is bound
+ * by its own latency and takes longer than half of mode 1.  Mode 3 against modes 0 + 1 shows the overlap inside one wavefront.
  * sink: n_wg * 8 floats. */
 int dlm_peak_overlap(int mode, int n_wg, int iters, float *sink, void *stream);
 
