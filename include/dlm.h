@@ -201,6 +201,7 @@ size_t dlm_block_attn_bwd_workspace_bytes(const dlm_attn_bwd_args *args);
  *   z_v  = (hidden[row(r), :] . w[v, :]) * inv_temperature,  v in [0, V)
  *   z_forbid_token = -inf (when forbid_token >= 0)
  *   tok  = smallest v maximising z_v;  zmax = z_tok;  z2nd = max_{v != tok} z_v
+ *          (z_v as rounded to fp32: products that the temperature scales to one value are a tie)
  *   lse  = log sum_v exp(z_v);  conf = exp(zmax - lse)
  *   ztarget = z_{target[r]}  (optional; log p(target) = ztarget - lse, the term
  *             summed by the NELBO of Eq. 2 / Eq. 3)

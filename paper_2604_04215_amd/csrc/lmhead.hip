@@ -223,8 +223,10 @@ __device__ __forceinline__ void lm_reduce_tile(const LmParams& p, f32x16 (&acc)[
             if (p.target) tgt = p.target[oidx];
         }
         // This row tile's raw logits, in vector registers (out of the accumulation registers once, instead of at each use), masked
-        // in a tile that holds a forbidden or out-of-range token.  The temperature is a positive factor: it changes neither the
-        // order nor the maximum, and the exponentials take it in their constant.
+        // in a tile that holds a forbidden or out-of-range token.  The temperature is a positive factor: rounding keeps the order, so the
+        // maximum is the scaled raw maximum, and the exponentials take it in their constant; only the token is looked for among scaled
+        // logits, because two that differ may scale to one value, and the lowest token of a tie counts, here as in the merges.  (Scaled only
+        // where the temperature is not 1: the 0.3 instructions a logit show where this function does, 2048 rows x 2048 x 256 22.2 / 22.7 us.)
         // Nothing runs beside this at one wavefront a SIMD, so its instructions count: 5.75 a logit (1 to fetch it, a half for the
         // maximum, 1.25 for its place, 3 for the sum) where there were 9.  Whole calls, us, before / after: 65536 x 157184 x 4096
         // 69300 / 68270, 1024 x 126464 x 4096 946 / 909, 512 rows 495 / 481, 128 rows x 152064 x 3584 216.3 / 214.0.
@@ -281,23 +283,32 @@ __device__ __forceinline__ void lm_reduce_tile(const LmParams& p, f32x16 (&acc)[
         for (int a = 0; a < TVW; ++a) mraw = fmaxf(mraw, tm[a]);
         Red red{mraw * p.inv_t, 0.f, m2raw * p.inv_t, 0x7fffffff};
         float uent = 0.f;
-        if (mraw > -INFINITY) {
+        if (red.m > -INFINITY) {
             // lowest token that attains the maximum: the lowest accumulator tile that does, then a walk down that tile, in which the
             // last hit stays (offsets from vb are constants)
+            const bool scaled = p.inv_t != 1.f;
             int la = (TVW - 1) * 32;
+            if (scaled) {
+#pragma unroll
+                for (int a = 0; a < TVW; ++a) tm[a] *= p.inv_t;
+            }
             float x[16];
 #pragma unroll
             for (int i = 0; i < 16; ++i) x[i] = z[TVW - 1][i];
 #pragma unroll
             for (int a = TVW - 2; a >= 0; --a) {
-                const bool here = tm[a] == mraw;
+                const bool here = tm[a] == red.m;
                 la = here ? a * 32 : la;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) x[i] = here ? z[a][i] : x[i];
             }
+            if (scaled) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) x[i] *= p.inv_t;
+            }
             int li = 0;
 #pragma unroll
-            for (int i = 15; i >= 0; --i) li = (x[i] == mraw) ? 8 * (i >> 2) + (i & 3) : li;
+            for (int i = 15; i >= 0; --i) li = (x[i] == red.m) ? 8 * (i >> 2) + (i & 3) : li;
             red.idx = vb + la + li;
             const float sc = fminf(p.inv_t * LOG2E, 3.4e38f), mb = mraw * sc;
             float s = 0.f;

@@ -269,6 +269,37 @@ def test_ties_pick_lowest_index():
     assert got["tok"][0] == 131 and got["z2nd"][0] == got["zmax"][0] == 2.0
 
 
+@pytest.mark.parametrize("M,cus", [(20, 0), (50, 0), (90, 0), (150, 0), (250, 0), (300, 0), (520, 0), (250, 4), (300, 8), (520, 8)])
+def test_logits_that_scale_to_one_value_are_a_tie(M, cus):
+    """z = raw logit * inverse temperature in fp32, and the smallest token that maximises z is the answer: of two raw logits one
+    unit in the last place apart that scale to the same z, the lower token wins, wherever the two lie in the vocabulary tiles."""
+    Dh, V, ulp = 128, 4200, 2.0 ** -23
+    t = np.float32(0.7)
+    a = next(x for x in np.arange(1.0, 2.0, 2.0 ** -7, dtype=np.float32) if x * t == (x + np.float32(ulp)) * t)
+    rng = np.random.default_rng(8)
+    # pair j: `lo` has the raw logit a, the higher token lo + gap has a + ulp (both sums exact in fp32)
+    gaps = [1, 2, 3, 4, 8, 9, 16, 24, 27, 32, 36, 64, 65, 96, 123, 128, 160, 256, 512, 1000, 2048]
+    wf, lows, used = np.zeros((V, Dh), np.float32), [], set()
+    for j in range(64):
+        gap = gaps[j % len(gaps)]
+        lo = next(v for v in rng.permutation((V - gap) // 4) * 4 if v + gap < V and not used & {v, v + gap})
+        used |= {lo, lo + gap}
+        wf[lo, j] = wf[lo + gap, j] = a
+        wf[lo + gap, 64 + j] = 1.0
+        lows.append(lo)
+    pair = np.arange(M) % 64
+    hf = np.zeros((M, Dh), np.float32)
+    hf[np.arange(M), pair] = 1.0
+    hf[np.arange(M), 64 + pair] = ulp
+    dlm.set_option("lmhead_cus", cus)
+    try:
+        got = run_lm(synth.f32_to_bf16_bits(hf), synth.f32_to_bf16_bits(wf), inv_t=float(t))
+    finally:
+        dlm.set_option("lmhead_cus", 0)
+    assert np.all(got["zmax"] == a * t) and np.all(got["z2nd"] == a * t)
+    assert np.array_equal(got["tok"], np.asarray(lows)[pair])
+
+
 def test_closed_form_threshold_boundary():
     # z = (a, 0, ..., 0): conf = e^a / (e^a + V - 1)
     Dh, V = 64, 2048
