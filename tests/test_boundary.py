@@ -152,6 +152,16 @@ def test_lmhead_validation():
     assert dlm.lmhead_workspace_bytes(256, 126464) >= 256 * 16 * (126464 // 256)
 
 
+@pytest.mark.parametrize("M,V", [(1 << 27, 1 << 22), (1 << 26, 1 << 21), (2000000000, 157184)])
+def test_lmhead_refuses_more_tiles_than_one_launch_counts(M, V):
+    """More (vocabulary tile, row chunk) pairs than 2^31 - 1 are refused before anything is launched, also by the shapes whose
+    workgroups take them from a queue and count them in 32 bits."""
+    L = dlm.lib()
+    need = L.dlm_lmhead_workspace_bytes(C.byref(_lm(M=M, V=V)))
+    assert L.dlm_lmhead_confidence(C.byref(_lm(M=M, V=V, workspace=0x2000, workspace_bytes=need)), None) == dlm.DLM_ERR_UNSUPPORTED
+    assert "too large" in dlm.last_error()
+
+
 def _cm(**kw):
     a = dlm.CommitArgs()
     a.struct_size = C.sizeof(dlm.CommitArgs)
