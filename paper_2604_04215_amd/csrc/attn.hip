@@ -63,7 +63,8 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
 // SWP: software-pipelined form of the 128-row shapes: each wavefront weaves the softmax of tile t between the score MFMAs of tile
 // t + 1 and between the first P V MFMAs of tile t, instead of running the three phases one after another and leaving the
 // overlap to the other wavefronts of its SIMD (whose vector work does run beside its MFMAs).
-template <int D, int NWR, int NWK, int RTW, bool BC, int PF = 1, int OCC = 1, bool NTKV = false, bool SWP = false>
+// PRIO: issue priority by phase (see ATTN_PRIO), for deep launches (see attn_deep).
+template <int D, int NWR, int NWK, int RTW, bool BC, int PF = 1, int OCC = 1, bool NTKV = false, bool SWP = false, bool PRIO = false>
 __global__ __launch_bounds__(64 * NWR * NWK, OCC) void attn_kernel(AttnParams p) {
     static_assert(!SWP || (RTW == 1 && NWK == 1 && NWR > 1 && D == 128 && PF == 1), "the pipelined form exists for 128-row workgroups, d = 128");
     static_assert(NWR == 1 || NWK <= 2, "row-split workgroups have at most two key groups");
@@ -318,12 +319,10 @@ __global__ __launch_bounds__(64 * NWR * NWK, OCC) void attn_kernel(AttnParams p)
 
     // One K/V tile: scores, (lazy) online softmax, P V.  A macro rather than a lambda: every array it
     // touches must stay in registers.
-    // Where a SIMD holds wavefronts of several workgroups, the further one is in its tile the higher its priority: of two that
-    // could issue, the one whose tile ends first goes first, and the wavefronts stay in different phases, products of
-    // one beside the softmax of another, instead of meeting at the matrix pipe.  Forward, us, without / with: 8 x 4096, 32 / 8 heads of 128,
-    // blocks of 4 1306 / 1278, full mask 2272 / 2222, 128 packed sequences 867 / 856, 16 x 1024, 14 / 2 heads of 64 69.8 / 66.2.  (Products alone or
-    // softmax alone raised: a third to two thirds of it.)
-#define ATTN_PRIO(level) if constexpr (NWR > 1) __builtin_amdgcn_s_setprio(level);
+    // PRIO: of the wavefronts that three workgroups put on a SIMD, the further one is in its tile the higher its priority: of two that
+    // could issue, the one whose tile ends first goes first, and they stay in different phases, products of one beside the
+    // softmax of another, instead of meeting at the matrix pipe.  (Products alone or softmax alone raised: a third to two thirds of the gain.)
+#define ATTN_PRIO(level) if constexpr (PRIO) __builtin_amdgcn_s_setprio(level);
 #define ATTN_COMPUTE() /* uses the tile index `t` of the enclosing scope */                              \
     if (t < Tn) {                                                                                        \
         f32x16 S[RTW]; \
@@ -942,6 +941,19 @@ static int plan_nsplit(const dlm_attn_args* a) {
     return n < 1 ? 1 : (int)n;
 }
 
+// Are issue priorities by phase worth it?  In launches of three and more rounds of workgroups (three a CU on 256 CUs) whose rows see 24 and
+// more key tiles.  With fewer rounds the workgroups that were held back are what the end of the launch waits for, with few tiles the phases have
+// no time to part.  Us without / with: 8 x 4096 tokens, 32 / 8 heads of 128, blocks of 4 1251 / 1218, full mask 2265 / 2213; but 3040 rows x 8192 keys
+// (760 workgroups) 505 / 552, 2 x 3872, 16 / 2 heads (968) 149 / 158, 128 x 64, 32 heads (4096 workgroups of two key tiles) 52 / 57, and at two
+// workgroups a CU 4 x 1024, 14 / 2 heads of 64 30.7 / 32.1.
+// A packed batch is judged by its tokens, not by the bound that the grid is made for, and its rows see more than the mean length, as
+// the long sequences hold most of them.
+static bool attn_deep(const AttnParams& p) {
+    const int64_t rows = p.cu ? (int64_t)p.Hkv * p.g * p.total : (int64_t)p.B * p.Hkv * p.R;
+    const int64_t keys = p.cu ? p.total / p.B : (int64_t)p.seg[0].len + p.seg[1].len + p.seg[2].len;
+    return rows >= 3 * 768 * 128 && keys >= (p.cu ? 512 : 768);
+}
+
 template <int D, bool BC>
 static int launch_attn(const AttnParams& p, hipStream_t st) {
     const int64_t BH = (int64_t)p.B * p.Hkv;
@@ -1006,6 +1018,7 @@ static int launch_attn(const AttnParams& p, hipStream_t st) {
         }
         if (variant == 4) hipLaunchKernelGGL((attn_kernel<D, 4, 1, 1, BC, 2, 2>), grid, dim3(256), 0, st, q);
         else if (variant == 5) hipLaunchKernelGGL((attn_kernel<D, 4, 1, 1, BC, 2, 3>), grid, dim3(256), 0, st, q);
+        else if (variant == 6 && attn_deep(p)) hipLaunchKernelGGL((attn_kernel<D, 4, 1, 1, BC, 1, 3, false, false, true>), grid, dim3(256), 0, st, q);
         else if (variant == 6) hipLaunchKernelGGL((attn_kernel<D, 4, 1, 1, BC, 1, 3>), grid, dim3(256), 0, st, q);
         else hipLaunchKernelGGL((attn_kernel<D, 4, 1, 1, BC, 1, 4>), grid, dim3(256), 0, st, q);
         return check_hip(hipGetLastError(), "attn_kernel launch");

@@ -381,3 +381,31 @@ def test_two_key_groups_per_workgroup_edge_cases(variant):
     run_case(B=2, Lq=70, Hq=6, Hkv=2, d=64, P=333, Lb=70, S=11, variant=variant, seed=63)
     run_case(B=1, Lq=200, Hq=2, Hkv=1, d=128, P=0, Lb=200, S=0, mode="block_causal", bs=4, q_pos0=0, variant=variant, seed=64)
     run_case(B=2, Lq=4, Hq=2, Hkv=2, d=128, P=5, Lb=0, S=0, plen=[0, 5], variant=variant, seed=65)
+
+
+@pytest.mark.parametrize("d,bs,packed", [(64, 0, False), (64, 4, False), (128, 0, False), (128, 32, False), (64, 4, True), (128, 0, True)])
+def test_launches_deep_enough_for_issue_priorities(d, bs, packed):
+    """3 * 768 * 128 and more rows with 768 and more keys (packed: a mean length of 512) run the kernel with issue priorities: bit for bit
+    what two launches of half the batch give, which are too small for it."""
+    H, B, Lq, Lk = 4, 568, 130, 768
+    mode = dict(mask_mode=dlm.MASK_BLOCK_CAUSAL, block_size=bs) if bs else {}
+    g = torch.Generator(device=DEV).manual_seed(d + bs)
+    rn = lambda *shape: torch.randn(shape, generator=g, device=DEV).bfloat16()
+    if packed:
+        lens = np.where(np.arange(148) % 2, 417, 607)
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        T, half = int(cu[-1]), int(cu[74])
+        assert H * T >= 3 * 768 * 128 > H * half and T // 148 == 512
+        q, k, v = rn(T, H, d), rn(T, H, d), rn(T, H, d)
+        run = lambda q, k, v, o, c: dlm.varlen_attn(q, k, v, o, dev(c), 607, **mode)
+        parts = [(slice(0, half), cu[:75]), (slice(half, T), cu[74:] - cu[74])]
+        whole = cu
+    else:
+        q, k, v = rn(B, Lq, H, d), rn(B, H, Lk, d), rn(B, H, Lk, d)
+        run = lambda q, k, v, o, c: dlm.block_attn(q, o, block=(k, v, 0), q_pos0=Lk - Lq, **mode)
+        parts, whole = [(slice(0, B // 2), None), (slice(B // 2, B), None)], None
+    out, ref = torch.zeros_like(q), torch.zeros_like(q)
+    run(q, k, v, out, whole)
+    for part, c in parts:
+        run(q[part], k[part], v[part], ref[part], c)
+    assert out.any() and torch.equal(out.view(torch.int16), ref.view(torch.int16))
