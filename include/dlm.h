@@ -410,11 +410,13 @@ int dlm_kv_refresh(const dlm_kv_seg *src, int32_t B, int32_t Hkv, int32_t d,
  *   "lmhead_variant" -1 = pick the LM-head kernel shape (workgroup tile, wavefront layout, prefetch depth) from M
  *                   (default); >= 0 forces one entry of the library's shape table.
  *   "lmhead_block"  -1 = automatic blocking of LM-head workgroups per XCD (default); 0 = none (row chunks of one
- *                   vocabulary tile side by side); 1..8 = that many vocabulary tiles per block.
+ *                   vocabulary tile side by side); 1..8 = that many vocabulary tiles per block.  0..8 also give every
+ *                   tile a workgroup of its own: no launch takes its tiles from a queue.
  *   "lmhead_nt"     1 = when a launch has one row chunk (every element of W used once) fetch W with non-temporal
  *                   loads (default); 0 = never.
- *   "lmhead_cus"    0 = the half-height tail rule of the LM head assumes the device's CU count (default); n > 0 = assume n
- *                   (tests: makes a small vocabulary take the two-launch path); -1 = no half-height tail.
+ *   "lmhead_cus"    CU count that the LM head's half-height tail and its queue of tiles assume (the rules of both, and the
+ *                   number of workgroups that share a queue): 0 = the device's (default); n > 0 = n (tests: makes
+ *                   small vocabularies take both); -1 = the device's, and no half-height tail (the queue stays).
  *   "attn_nt"       1 = non-temporal K/V loads when one workgroup is the only reader of its (sequence, KV head)
  *                   (g*Lq <= 32; default); 0 = never.
  *   "kv_copy_unroll" 16-byte pieces per thread of the copy kernel (1, 2, 4 or 8), plus 16 when K and V are copied by

@@ -1480,8 +1480,8 @@ static lm_launch_t lm_tail_of(int v) {
 constexpr int N_LM_VARIANTS = sizeof(g_lm_variants) / sizeof(g_lm_variants[0]);
 constexpr int LM_MIN_TV = 128;   // smallest vocabulary tile of any variant: sizes the workspace
 int g_lm_variant = -1;           // -1 = choose by M; otherwise force an entry of the table (dlm_set_option)
-int g_lm_block_gv = -1;          // -1 = automatic XCD blocking; 0 = none; n = n vocabulary tiles per block (tuning)
-int g_lm_cus = 0;                // CUs the tail rule assumes: 0 = the device's count; -1 = no half-height tail (tuning, tests)
+int g_lm_block_gv = -1;          // -1 = automatic XCD blocking; 0 = none; n = n vocabulary tiles per block, both without a queue (tuning)
+int g_lm_cus = 0;                // CUs the tail and the queue rule assume: 0 = the device's count; -1 = that and no half-height tail (tuning, tests)
 
 static int plan_lmhead(int M) {
     if (g_lm_variant >= 0) return g_lm_variant;
@@ -1596,7 +1596,7 @@ static int launch_lm_shape(int v_idx, LmParams& p, int m_bound, size_t ws_bytes,
     const size_t used = (size_t)(p.n_vt > p.alt_n_vt ? p.n_vt : p.alt_n_vt) * m_bound * sizeof(f32x4) * (second ? 2 : 1);
     const int rest = p.M % var.mb;
     const bool even = rest == 0 || 4 * rest > var.mb || p.n_mc > 8;
-    if (lm_queued(v_idx) && p.n_mc > 1 && p.Dh >= 128 && even && (int64_t)n_full * p.n_mc >= 2 * lm_queue_wgs() && used + LM_QUEUE_BYTES <= ws_bytes)
+    if (lm_queued(v_idx) && g_lm_block_gv < 0 && p.n_mc > 1 && p.Dh >= 128 && even && (int64_t)n_full * p.n_mc >= 2 * lm_queue_wgs() && used + LM_QUEUE_BYTES <= ws_bytes)
         p.queue = (int*)((char*)p.part + used);
     return launch_lm_tiles(var, p, n_full, st);
 }

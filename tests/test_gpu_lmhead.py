@@ -494,3 +494,20 @@ def test_workgroups_that_take_their_tiles_from_a_queue(M, m_dev, Dh, V, cus):
         compare_prefix(got, ref, m)
         if m_dev is None:
             assert all(np.array_equal(got[k], plain[k], equal_nan=True) for k in plain)
+
+
+@pytest.mark.parametrize("m_dev", [None, 900, 600])
+def test_every_value_of_the_blocking_option(m_dev):
+    """Blocks of workgroups per XCD change the order of the tiles and where a tile's walk over Dh starts, and the values >= 0 also
+    switch the queue off.  The device's count leaves every chunk, all but one and half of them.  Against the oracle: 128 products summed in
+    fp32 in any order stay within 128 * 2^-24 * sum |h w| < 128 * 2^-24 * 128 = 1e-3 of the exact sum, below Z_TOL."""
+    h, w = rnd(1700, (1100, 128)), rnd(1701, (3000, 128), 128 ** -0.25)
+    ref = oracle.lmhead(h[:m_dev], w, forbid_token=7)
+    dlm.set_option("lmhead_cus", 8)
+    try:
+        for block in (-1, 0, 1, 4, 8):
+            dlm.set_option("lmhead_block", block)
+            compare_prefix(run_lm(h, w, m_dev=m_dev, forbid=7), ref, m_dev or 1100)
+    finally:
+        dlm.set_option("lmhead_block", -1)
+        dlm.set_option("lmhead_cus", 0)
