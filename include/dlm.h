@@ -219,8 +219,8 @@ size_t dlm_block_attn_bwd_workspace_bytes(const dlm_attn_bwd_args *args);
  *           The kernel shape is chosen on the host from M, which a caller that polls the device late only
  *           knows as an upper bound.  When M_expected falls in a smaller shape's range, the call queues that
  *           shape guarded by "*m_dev fits it" and the shape for M guarded by the opposite, so a right
- *           guess runs the better shape and a wrong one costs an empty launch.  Results depend on it only
- *           through the summation order of the shape that ran (rounding).
+ *           guess runs the better shape, and either way one of the two launches is empty.  Results depend on it
+ *           only through the summation order of the shape that ran (rounding).
  *   w       bf16 [V, Dh], row stride w_stride_row
  *   out_scatter  0: outputs are indexed by r; 1: by row(r) (dense per-position arrays)
  *   conf, tok    required; lse, zmax, z2nd, target+ztarget optional.  `target` is
@@ -280,7 +280,7 @@ size_t dlm_lmhead_workspace_bytes(const dlm_lmhead_args *args);
  * 512 rows when sampling), else DLM_ERR_WORKSPACE and nothing is enqueued.
  * All calls on one GPU share the one array: calls that overlap in time on the same GPU (different streams or
  * threads) race; calls on one stream are ordered and safe.  Nothing in the array needs clearing between calls:
- * every partial a call reads was written by that call. */
+ * every partial a call reads was written by that call, and the counters that hand out its tiles it clears itself. */
 #define DLM_LMHEAD_STATIC_SCRATCH_BYTES (32u << 20)
 int dlm_lmhead_confidence_static(const dlm_lmhead_args *args, void *stream);
 size_t dlm_lmhead_static_scratch_bytes(void);

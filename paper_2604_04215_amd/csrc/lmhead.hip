@@ -53,10 +53,13 @@ struct LmParams {
     int alt_cap, alt_n_vt;   // reduction: row count <= alt_cap (> 0) -> alt_n_vt partials per row, second partials at alt_part2
     f32x4* alt_part2;
     int* queue;   // paired ring only: one counter per XCD (16 words apart), null = one workgroup per tile (see lmhead_pair_kernel)
+    int* clear;   // the counters of the shape queued behind this one for the same call, null = none
 };
 
 // Row count of this launch; false when the device's count belongs to the other shape queued for the same call.
+// (Clears the other shape's counters in passing.)
 __device__ __forceinline__ bool lm_rows(const LmParams& p, int& M) {
+    if (p.clear && blockIdx.x == 0 && threadIdx.x < 8) p.clear[threadIdx.x * 16] = 0;
     if (p.m_dev) {
         const int md = max(*p.m_dev, 0);
         if (md <= p.m_lo || md > p.m_hi) return false;
@@ -1539,66 +1542,68 @@ static int device_cus() {
 }
 
 // Workgroups of a launch that takes its tiles from a queue: one per CU, the same number on every XCD.
-static int lm_queue_wgs() {
-    const int cus = (g_lm_cus > 0 ? g_lm_cus : device_cus()) & ~7;
-    return cus > 8 ? cus : 8;
-}
-
-// Launches one kernel shape over n_vt_l vocabulary tiles.
-static int launch_lm_tiles(const LmVariant& var, LmParams& p, int n_vt_l, hipStream_t st) {
-    p.n_vt_l = n_vt_l; p.n_half = 0;
-    lm_blocking(p.n_mc, p.gm, p.gv);
-    if (g_lm_block_gv >= 0) { p.gv = g_lm_block_gv > 0 ? g_lm_block_gv : 1; if (g_lm_block_gv == 0) p.gm = 1; }
-    const int64_t n_vt8 = ((int64_t)(n_vt_l + 7) / 8 + p.gv - 1) / p.gv * p.gv;   // vocabulary tiles per XCD, padded to gv
-    const int64_t n_wg = n_vt8 * 8 * p.n_mc;
-    if (n_wg > 0x7fffffff) return fail(DLM_ERR_UNSUPPORTED, "lmhead: M * V too large for one launch");
-    if (p.queue) {
-        hipLaunchKernelGGL(lmhead_queue_kernel, dim3(1), dim3(8), 0, st, p.queue);
-        var.launch(dim3((unsigned)lm_queue_wgs()), st, p);
-        return check_hip(hipGetLastError(), "lmhead_pair_kernel launch");
-    }
-    ((p.n_mc == 1 && var.launch_nt && g_lm_nt) ? var.launch_nt : var.launch)(dim3((unsigned)n_wg), st, p);
-    return check_hip(hipGetLastError(), "lmhead_kernel launch");
-}
+static int lm_queue_wgs(int cus) { return cus >= 16 ? cus & ~7 : 8; }
 
 // Fills the layout fields of p for one kernel shape (p.M = the rows this launch may hold, m_bound = the caller's
-// bound, which places the second partials) and launches it.
+// bound, which places the second partials).
 // Queue: the paired ring with several row chunks takes its tiles from one where there are two or more of them a CU (with fewer the launch
 // that clears the counters costs what the second tile saves: 9000 x 4096, 2100 rows, 1.3 tiles a CU, 186.6 against 183.3 us); ws_bytes (what the
-// call asks of its workspace, sized for 128-row tiles) leaves room for the counters behind the partials of its 256-row tiles.
+// call asks of its workspace, sized for 128-row tiles) leaves room for the counters behind the partials of its 256-row tiles.  They lie at the
+// end, in one place for both shapes of a call with a guess: only one of the two runs, and the first launch clears them.
 // Not with few chunks of which the last is nearly empty: a workgroup takes a tile one tile ahead, and with tiles of unequal length
 // that costs the end of the launch more than the start of the tiles (us with / without, V = 126464, Dh = 4096: 520 rows 597 / 591, 800
-// rows 811 / 784; but 512 rows 484 / 487, 896 rows 835 / 857, 1536 rows 1321 / 1364, 4100 rows 3477 / 3713).
+// rows 811 / 784; but 512 rows 484 / 487, 896 rows 835 / 857, 1536 rows 1321 / 1364, 4100 rows 3477 / 3713).  The rule sees the caller's
+// bound: 800 rows counted on the device under a bound of 1024 take the queue, 811 us, where a workgroup a tile takes 823 for the chunk that
+// is not there.
 // Tail rule: the shapes for 65 - 256 rows run one workgroup per CU, so a launch costs ceil(tiles / CUs) rounds of
 // equal length.  When the last round would occupy at most half of the CUs (V = 152064: 594 tiles = 2.32 rounds on 256
 // CUs, V = 157184: 614 = 2.40), the tiles of that round are cut in halves: 2.5 rounds' time instead of 3.  Both heights in one launch:
 // the half tiles start as the CUs come free.  us a call, V = 152064, Dh = 3584, halves as a launch of their own / in one launch: 80 rows 200 /
 // 196, 128 rows 216 / 213, 192 rows 258 / 254, 256 rows 314 / 310 (with three rounds 80 rows 232, 256 rows 343).
-static int launch_lm_shape(int v_idx, LmParams& p, int m_bound, size_t ws_bytes, hipStream_t st) {
+static void plan_lm_shape(int v_idx, LmParams& p, int m_bound, size_t ws_bytes, int cus) {
     const LmVariant& var = g_lm_variants[v_idx];
     const int n_full = (p.V + var.tv - 1) / var.tv;
     p.n_mc = (p.M + var.mb - 1) / var.mb;
-    const lm_launch_t tail_launch = lm_tail_of(v_idx);
-    const int cus = g_lm_cus > 0 ? g_lm_cus : device_cus();
     const int tail = n_full % cus;
-    if (g_lm_cus >= 0 && tail_launch && p.n_mc == 1 && n_full > cus && tail > 0 && 2 * tail <= cus) {
+    p.n_vt_l = p.n_vt = n_full;
+    p.n_half = 0;
+    p.gm = 1; p.gv = 1;
+    if (g_lm_cus >= 0 && lm_tail_of(v_idx) && p.n_mc == 1 && n_full > cus && tail > 0 && 2 * tail <= cus) {
         p.n_vt_l = n_full - tail;
         p.n_half = (p.V - p.n_vt_l * var.tv + var.tv / 2 - 1) / (var.tv / 2);
         p.n_vt = p.n_vt_l + p.n_half;
         p.part2 = p.part + (size_t)p.n_vt * m_bound;
-        p.gm = 1; p.gv = 1;
-        tail_launch(dim3((unsigned)p.n_vt), st, p);
-        return check_hip(hipGetLastError(), "lmhead_tail_kernel launch");
+        return;
     }
-    p.n_vt = n_full;
     p.part2 = p.part + (size_t)p.n_vt * m_bound;
+    lm_blocking(p.n_mc, p.gm, p.gv);
+    if (g_lm_block_gv >= 0) { p.gv = g_lm_block_gv > 0 ? g_lm_block_gv : 1; if (g_lm_block_gv == 0) p.gm = 1; }
     const bool second = p.sample || p.conf_mode == DLM_CONF_NEG_ENTROPY;
     const size_t used = (size_t)(p.n_vt > p.alt_n_vt ? p.n_vt : p.alt_n_vt) * m_bound * sizeof(f32x4) * (second ? 2 : 1);
     const int rest = p.M % var.mb;
     const bool even = rest == 0 || 4 * rest > var.mb || p.n_mc > 8;
-    if (lm_queued(v_idx) && g_lm_block_gv < 0 && p.n_mc > 1 && p.Dh >= 128 && even && (int64_t)n_full * p.n_mc >= 2 * lm_queue_wgs() && used + LM_QUEUE_BYTES <= ws_bytes)
-        p.queue = (int*)((char*)p.part + used);
-    return launch_lm_tiles(var, p, n_full, st);
+    if (lm_queued(v_idx) && g_lm_block_gv < 0 && p.n_mc > 1 && p.Dh >= 128 && even && (int64_t)n_full * p.n_mc >= 2 * lm_queue_wgs(cus) &&
+        used + LM_QUEUE_BYTES <= ws_bytes)
+        p.queue = (int*)((char*)p.part + ws_bytes - LM_QUEUE_BYTES);
+}
+
+// Launches a planned shape; clear = its counters have not been cleared by the launch in front of it.
+static int launch_lm_shape(int v_idx, const LmParams& p, bool clear, int cus, hipStream_t st) {
+    const LmVariant& var = g_lm_variants[v_idx];
+    if (p.n_half) {
+        lm_tail_of(v_idx)(dim3((unsigned)p.n_vt), st, p);
+        return check_hip(hipGetLastError(), "lmhead_tail_kernel launch");
+    }
+    const int64_t n_vt8 = ((int64_t)(p.n_vt_l + 7) / 8 + p.gv - 1) / p.gv * p.gv;   // vocabulary tiles per XCD, padded to gv
+    const int64_t n_wg = n_vt8 * 8 * p.n_mc;
+    if (n_wg > 0x7fffffff) return fail(DLM_ERR_UNSUPPORTED, "lmhead: M * V too large for one launch");
+    if (p.queue) {
+        if (clear) hipLaunchKernelGGL(lmhead_queue_kernel, dim3(1), dim3(8), 0, st, p.queue);
+        var.launch(dim3((unsigned)lm_queue_wgs(cus)), st, p);
+        return check_hip(hipGetLastError(), "lmhead_pair_kernel launch");
+    }
+    ((p.n_mc == 1 && var.launch_nt && g_lm_nt) ? var.launch_nt : var.launch)(dim3((unsigned)n_wg), st, p);
+    return check_hip(hipGetLastError(), "lmhead_kernel launch");
 }
 
 extern "C" size_t dlm_lmhead_workspace_bytes(const dlm_lmhead_args* a) {
@@ -1626,8 +1631,9 @@ static int lmhead_enqueue(const dlm_lmhead_args* a, void* workspace, void* strea
     p.m_lo = -1; p.m_hi = 0x7fffffff;
     p.alt_cap = 0; p.alt_n_vt = 0; p.alt_part2 = nullptr;
     p.queue = nullptr;
-    p.n_half = 0;
+    p.clear = nullptr;
     const size_t ws_bytes = dlm_lmhead_workspace_bytes(a);
+    const int cus = g_lm_cus > 0 ? g_lm_cus : device_cus();
     hipStream_t st = (hipStream_t)stream;
 
     // The caller's bound M sizes the launch, the device's count says how many rows there are.  When the caller
@@ -1639,16 +1645,22 @@ static int lmhead_enqueue(const dlm_lmhead_args* a, void* workspace, void* strea
         cap = plan_capacity(a->M_expected);
         if (cap < a->M) v_try = plan_lmhead(cap);
     }
-    if (v_try != v_safe) {
-        LmParams q = p;
+    const bool guess = v_try != v_safe;
+    LmParams q = p;
+    if (guess) {
         q.M = cap;
         q.m_hi = cap;
-        rc = launch_lm_shape(v_try, q, a->M, ws_bytes, st);
-        if (rc != DLM_OK) return rc;
+        plan_lm_shape(v_try, q, a->M, ws_bytes, cus);
         p.m_lo = cap;
         p.alt_cap = cap; p.alt_n_vt = q.n_vt; p.alt_part2 = q.part2;
     }
-    rc = launch_lm_shape(v_safe, p, a->M, ws_bytes, st);
+    plan_lm_shape(v_safe, p, a->M, ws_bytes, cus);
+    if (guess) {
+        if (!q.queue) q.clear = p.queue;   // (with a queue of its own it has the same counters)
+        rc = launch_lm_shape(v_try, q, true, cus, st);
+        if (rc != DLM_OK) return rc;
+    }
+    rc = launch_lm_shape(v_safe, p, !guess, cus, st);
     if (rc != DLM_OK) return rc;
     // Many rows of which the device counts few: what a workgroup past the count loads before it ends is all that shows.  Whole call, us,
     // Dh = 256, with / without AHEAD: 65536 rows, V = 2048, 1 counted 36.3 / 27.7, 8192 counted 63.7 / 57.0, all 240 / 245; V = 60000, 1
