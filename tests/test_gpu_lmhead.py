@@ -511,3 +511,62 @@ def test_every_value_of_the_blocking_option(m_dev):
     finally:
         dlm.set_option("lmhead_block", -1)
         dlm.set_option("lmhead_cus", 0)
+
+
+@pytest.mark.parametrize("kind", ["plain", "static", "strided", "margin", "entropy", "sampled", "sampled_entropy", "target_scatter"])
+@pytest.mark.parametrize("M,Dh,V,cus,counted", [
+    (300, 128, 2100, 8, (300,)),                        # 192-row chunks, the shortest walk a queue takes
+    (580, 192, 2817, 8, (580, 300)),                    # 256-row chunks, all counted and two of three; a last vocabulary tile of one token
+    (580, 128, 3000, 16, (200, 385, 384)),              # guess 300: both shapes queued for the call have a queue, the first runs, then the second
+    (580, 128, 3000, 8, (100, 140)),                    # guess 100: the one-chunk shape clears the counters of the other
+])
+def test_every_form_of_a_call_through_a_queue(kind, M, Dh, V, cus, counted):
+    """The forms that the tiles of a queue take their own way: the noise's kernel, the second partials (behind which the counters lie) and
+    the runner-up in the free stage of the ring, targets stored between two tiles, other strides, the library's own scratch, two
+    queued shapes.  The counters start with what the workspace held: 0x5A bytes at first, then what the last call left."""
+    from oracle import sampling
+    guess = {200: 300, 385: 300, 384: 300, 100: 100, 140: 100}.get(counted[0], 0)
+    R = M + 37
+    h, w = rnd(1800 + M, (R, Dh)), rnd(1801 + V, (V, Dh), Dh ** -0.25)
+    idx = np.random.default_rng(M).permutation(R)[:M].astype(np.int32)
+    pad = 24 if kind == "strided" else 0
+    hd, wd = torch.zeros((R, Dh + pad), dtype=torch.bfloat16, device=DEV), torch.zeros((V, Dh + 2 * pad), dtype=torch.bfloat16, device=DEV)
+    hd[:, :Dh], wd[:, :Dh] = bf16_dev(h), bf16_dev(w)
+    sample, ent, scatter = "sampled" in kind, "entropy" in kind, kind == "target_scatter"
+    mode = dlm.CONF_NEG_ENTROPY if ent else dlm.CONF_MARGIN if kind == "margin" else dlm.CONF_TOKEN_PROB
+    tgt = np.random.default_rng(V).integers(0, V - 1, size=R).astype(np.int32)
+    ref = oracle.lmhead(h, w, row_idx=idx, forbid_token=V - 1, inv_temperature=0.8, target=tgt[idx])
+    smp = sampling.lmhead_sampled(h, w, seed=77, step=5, stream=2, row_idx=idx, forbid_token=V - 1, inv_temperature=0.8) if sample else None
+    want = smp["conf"] if sample and not ent else ref["neg_entropy"] if ent else ref["margin"] if kind == "margin" else ref["conf"]
+    top, second = (smp["pmax"], smp["p2nd"]) if sample else (ref["zmax"], ref["z2nd"])
+    want_tok = smp["tok"] if sample else ref["tok"]
+    gw = GuardedWorkspace(dlm.lmhead_workspace_bytes(M, V, sample=sample, conf_mode=mode))
+    gw.ws.fill_(0x5A)
+    n_out = R if scatter else M
+    dlm.set_option("lmhead_cus", cus)
+    try:
+        for m in counted:
+            f = lambda: torch.full((n_out,), float("nan"), dtype=torch.float32, device=DEV)
+            conf, lse, zt, tok = f(), f(), f(), torch.full((n_out,), -7, dtype=torch.int32, device=DEV)
+            kw = dict(M=M, row_idx=dev(idx), m_dev=None if m == M else dev(np.asarray([m], np.int32)), M_expected=guess, forbid_token=V - 1,
+                      inv_temperature=0.8, lse=lse, conf_mode=mode, out_scatter=scatter)
+            if sample:
+                kw.update(sample_seed=77, sample_step=5, sample_stream=2)
+            if scatter:
+                kw.update(target=dev(tgt), ztarget=zt)
+            kw.update(static_scratch=True) if kind == "static" else kw.update(workspace=gw.ws)
+            dlm.lmhead_confidence(hd[:, :Dh], wd[:, :Dh], conf, tok, **kw)
+            gw.check()
+            at = idx[:m] if scatter else np.arange(m)
+            conf, lse, zt, tok = conf.cpu().numpy(), lse.cpu().numpy(), zt.cpu().numpy(), tok.cpu().numpy()
+            clear = (top - second)[:m] >= MARGIN
+            assert clear.mean() > 0.9 and np.array_equal(tok[at][clear], want_tok[:m][clear])
+            same = tok[at] == want_tok[:m] if sample and not ent else np.ones(m, bool)
+            assert np.abs(conf[at][same].astype(np.float64) - want[:m][same]).max() <= (Z_TOL if ent else CONF_TOL)
+            assert np.abs(lse[at] - ref["lse"][:m]).max() <= Z_TOL
+            if scatter:
+                assert np.abs(zt[at] - ref["zt"][:m]).max() <= Z_TOL
+            rest = np.setdiff1d(np.arange(n_out), at)
+            assert np.all(np.isnan(conf[rest])) and np.all(tok[rest] == -7) and np.all(np.isnan(zt[rest]))
+    finally:
+        dlm.set_option("lmhead_cus", 0)
