@@ -7,11 +7,12 @@
 //     holds 16 vocabulary entries of ONE hidden row per accumulator tile, so the
 //     per-row reductions over the vocabulary are in-register, plus one exchange with
 //     lane^32 and one small LDS merge across the wavefronts of the workgroup.
-//   * A workgroup owns TV vocabulary rows and up to MB hidden rows and streams its
-//     W panel exactly once from HBM over the Dh axis in 64-element chunks, LDS
-//     double-buffered with register prefetch; the (small) H panel is re-read from
-//     L2 by every workgroup.
-//   * Each workgroup writes one partial (max, sumexp, argmax, runner-up) per row;
+//   * A tile is TV vocabulary rows and up to MB hidden rows; its workgroup streams its
+//     W panel over the Dh axis in 64-element chunks, LDS double-buffered with register
+//     prefetch (up to 256 rows: one row chunk, W comes from HBM exactly once), or both
+//     panels straight to LDS (more rows, where a workgroup takes one tile after the
+//     other); the (small) H panel is re-read from L2 for every tile.
+//   * A tile gives one partial (max, sumexp, argmax, runner-up) per row;
 //     a second kernel merges the V/TV partials per row in a fixed order
 //     (deterministic; ties resolve to the lowest vocabulary index).
 #include "common.hpp"
@@ -1419,12 +1420,13 @@ static void launch_lma(dim3 grid, hipStream_t st, const LmParams& p) {
 }
 #define LMA(WV, WH, TVW, THW, NS) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, launch_lma<WV, WH, TVW, THW, NS>, nullptr}
 #define LMX(WV, WH, TVW, THW, NS) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, launch_lma<WV, WH, TVW, THW, NS, true>, nullptr}
-template <int WV, int WH, int TVW, int THW>
+// GREEDY: calls that do not sample have a kernel of their own (the planner's shapes)
+template <int WV, int WH, int TVW, int THW, bool GREEDY>
 static void launch_lmq(dim3 grid, hipStream_t st, const LmParams& p) {
-    if (p.sample) hipLaunchKernelGGL((lmhead_pair_kernel<WV, WH, TVW, THW, true>), grid, dim3(64 * WV * WH), 0, st, p);
-    else hipLaunchKernelGGL((lmhead_pair_kernel<WV, WH, TVW, THW, false>), grid, dim3(64 * WV * WH), 0, st, p);
+    if (!GREEDY || p.sample) hipLaunchKernelGGL((lmhead_pair_kernel<WV, WH, TVW, THW, true>), grid, dim3(64 * WV * WH), 0, st, p);
+    else hipLaunchKernelGGL((lmhead_pair_kernel<WV, WH, TVW, THW, !GREEDY>), grid, dim3(64 * WV * WH), 0, st, p);
 }
-#define LMQ(WV, WH, TVW, THW) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, launch_lmq<WV, WH, TVW, THW>, nullptr}
+#define LMQ(WV, WH, TVW, THW, GREEDY) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, launch_lmq<WV, WH, TVW, THW, GREEDY>, nullptr}
 #define LMV(WV, WH, TVW, THW, PD) {32 * TVW * WV, 32 * THW * WH, 64 * WV * WH, launch_lm<WV, WH, TVW, THW, PD>, launch_lm<WV, WH, TVW, THW, PD, 64, 1, false, true>}
 static const LmVariant g_lm_variants[] = {
     // shapes the planner uses, by row count M (V = 126464, Dh = 4096 on MI355X, us per main-kernel launch in the
@@ -1450,15 +1452,15 @@ static const LmVariant g_lm_variants[] = {
     /*17*/ LMA(4, 4, 2, 2, 3),  // same, 3 stages      (both within 3 % of entry 5 from M = 224 to 8192)
     /*18*/ LMX(2, 2, 4, 4, 4),  // entry 10 with the operand fragments read one MFMA step ahead, across the barrier
     /*19*/ LMX(4, 2, 2, 4, 4),  // entry 13 likewise
-    /*20*/ LMQ(2, 2, 4, 4),     // paired, evenly spread requests, 5 stages: 256 x 256, 4 waves x (128 x 128)
-    /*21*/ LMQ(4, 2, 2, 4),     // same, 8 waves x (64 x 128): one 256-row chunk as fast as entry 5, with 1.47 x the HBM fetch
-    /*22*/ LMQ(4, 1, 2, 6),     // 256 x 192, 4 waves x (64 x 192)
-    /*23*/ LMQ(4, 1, 2, 4),     // 256 x 128, 4 waves x (64 x 128)
-    // half-height forms (128 vocabulary rows)
+    /*20*/ LMQ(2, 2, 4, 4, true),  // paired, evenly spread requests, 5 stages: 256 x 256, 4 waves x (128 x 128)
+    /*21*/ LMQ(4, 2, 2, 4, false),  // same, 8 waves x (64 x 128): one 256-row chunk as fast as entry 5, with 1.47 x the HBM fetch
+    /*22*/ LMQ(4, 1, 2, 6, true),  // 256 x 192, 4 waves x (64 x 192)
+    /*23*/ LMQ(4, 1, 2, 4, false),  // 256 x 128, 4 waves x (64 x 128)
+    // 128 vocabulary rows (forced only, as entry 2: the half-height tiles of a tail are part of lmhead_tail_kernel)
     /*24*/ LMP(4, 1, 1, 3, 3),  // 128 x 96,  4 waves
     /*25*/ LMP(4, 2, 1, 2, 3),  // 128 x 128, 8 waves
     /*26*/ LMP(4, 2, 1, 3, 2),  // 128 x 192, 8 waves
-    /*27*/ LMQ(4, 2, 1, 4),     // 128 x 256, paired ring, 8 waves x (32 x 128)
+    /*27*/ LMQ(4, 2, 1, 4, false),  // 128 x 256, paired ring, 8 waves x (32 x 128)
     /*28*/ LMP(4, 2, 1, 4, 2),  // 128 x 256, register-staged, 8 waves
 };
 constexpr size_t LM_QUEUE_BYTES = 8 * 64;
