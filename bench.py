@@ -153,13 +153,14 @@ def measure_peaks(torch, reps: int = 20) -> dict:
     ops = torch.randn(16 * 64 * 8, device=dev).bfloat16()          # N(0,1) operand fragments
     t = timed(lambda: L.dlm_peak_mfma(n_wg, iters, ops.data_ptr(), fs.data_ptr(), st))
     out["mfma_bf16_tflops_normal_data"] = round(n_wg * 4 * iters * 8 * 32768 / t / 1e12, 1)
-    # do MFMA and vector-ALU work overlap on a SIMD: across wavefronts (mode 2) / inside one wavefront's stream (mode 3)?
+    # do MFMA and vector-ALU work overlap on a SIMD: across wavefronts (mode 2 against 4 and 5) / inside one wavefront's stream (mode 3)?
     L.dlm_peak_overlap.argtypes = [C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p]
     ov = {}
-    for mode, key in ((0, "all_mfma"), (1, "all_valu"), (2, "mfma_waves_beside_valu_waves"), (3, "both_in_each_wave")):
+    for mode, key in ((0, "all_mfma"), (1, "all_valu"), (2, "mfma_waves_beside_valu_waves"), (3, "both_in_each_wave"),
+                      (4, "mfma_waves_alone"), (5, "valu_waves_alone")):
         ov[key] = round(timed(lambda: L.dlm_peak_overlap(mode, 256, 20000, fs.data_ptr(), st)) * 1e3, 3)
-    ov["note"] = ("ms for 20000 iterations, 8 wavefronts per CU; a lone vector wavefront on a SIMD is bound by its own latency and "
-                  "takes longer than all_valu / 2, so the third figure beside the sum of the halves does not show exclusion")
+    ov["note"] = ("ms for 20000 iterations, 8 wavefronts per CU; the third figure against the larger of the last two and their sum: "
+                  "side by side across wavefronts, or in turn; the fourth against the first two: inside one wavefront")
     out["mfma_valu_overlap_ms"] = ov
     out["what"] = ("1 GiB device copy (read + write), 1 GiB one-pass read with ordinary / non-temporal loads, "
                    "register-only 32x32x16 bf16 MFMA loop on 2048 workgroups of 4 wavefronts with small constant operands and "

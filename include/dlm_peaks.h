@@ -39,9 +39,10 @@ int dlm_peak_mfma(int n_wg, int iters, const void *operands, float *sink, void *
  * (fused multiply-add, exponential) pairs on 16 independent values.
  *   mode 0: all eight wavefronts matrix work;   mode 1: all eight vector work;
  *   mode 2: wavefronts 0-3 matrix, 4-7 vector (one of each kind per SIMD);
- *   mode 3: every wavefront both, each MFMA followed by four of the pairs in its own instruction stream.
- * Mode 2 against the sum of half of mode 0 and half of mode 1 tells little by itself: a lone vector wavefront on a SIMD is bound
- * by its own latency and takes longer than half of mode 1.  Mode 3 against modes 0 + 1 shows the overlap inside one wavefront.
+ *   mode 3: every wavefront both, each MFMA followed by four of the pairs in its own instruction stream;
+ *   mode 4: wavefronts 0-3 matrix, 4-7 idle;   mode 5: wavefronts 4-7 vector, 0-3 idle.
+ * Mode 2 against modes 4 and 5 shows the overlap of different wavefronts (the longer of the two, or their sum), mode 3 against
+ * modes 0 + 1 that inside one wavefront.  (Half of mode 1 is no yardstick for mode 2: a lone vector wavefront is bound by its latency.)
  * sink: n_wg * 8 floats. */
 int dlm_peak_overlap(int mode, int n_wg, int iters, float *sink, void *stream);
 

@@ -93,8 +93,9 @@ __global__ __launch_bounds__(512) void overlap_kernel(int iters, float* __restri
     float x[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) x[i] = 0.001f * (float)(lane + i);
-    const bool do_m = MODE == 0 || (MODE == 2 && w < 4);
-    const bool do_v = MODE == 1 || (MODE == 2 && w >= 4);
+    const bool do_m = MODE == 0 || ((MODE == 2 || MODE == 4) && w < 4);
+    const bool do_v = MODE == 1 || ((MODE == 2 || MODE == 5) && w >= 4);
+    if (MODE != 3 && !do_m && !do_v) iters = 0;
     for (int it = 0; it < iters; ++it) {
         if (MODE == 3) {
 #pragma unroll
@@ -163,14 +164,16 @@ extern "C" int dlm_peak_mfma(int n_wg, int iters, const void* operands, float* s
 }
 
 extern "C" int dlm_peak_overlap(int mode, int n_wg, int iters, float* sink, void* stream) {
-    if (mode < 0 || mode > 3 || n_wg <= 0 || iters <= 0 || !sink) return -1;
+    if (mode < 0 || mode > 5 || n_wg <= 0 || iters <= 0 || !sink) return -1;
     const dim3 grid((unsigned)n_wg), blk(512);
     hipStream_t st = (hipStream_t)stream;
     switch (mode) {
         case 0: hipLaunchKernelGGL(overlap_kernel<0>, grid, blk, 0, st, iters, sink); break;
         case 1: hipLaunchKernelGGL(overlap_kernel<1>, grid, blk, 0, st, iters, sink); break;
         case 2: hipLaunchKernelGGL(overlap_kernel<2>, grid, blk, 0, st, iters, sink); break;
-        default: hipLaunchKernelGGL(overlap_kernel<3>, grid, blk, 0, st, iters, sink); break;
+        case 3: hipLaunchKernelGGL(overlap_kernel<3>, grid, blk, 0, st, iters, sink); break;
+        case 4: hipLaunchKernelGGL(overlap_kernel<4>, grid, blk, 0, st, iters, sink); break;
+        default: hipLaunchKernelGGL(overlap_kernel<5>, grid, blk, 0, st, iters, sink); break;
     }
     return launched();
 }
