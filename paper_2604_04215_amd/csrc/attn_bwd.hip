@@ -417,7 +417,7 @@ __device__ __forceinline__ void bw_mfma_zero(f32x16& c, bf16x8 a, bf16x8 b) {
 // fragment twice.  That takes the whole register file (one wavefront per SIMD), so nothing may wait in turn:
 //   * S is formed once for dV and dK (two passes, one for each, formed it twice: 5 products instead of 4);
 //   * the exponentials sit between the MFMAs of dP and of the first half of dV, dS between those of the second half of
-//     dV and the first of dK (vector and matrix instructions of one wavefront overlap, of different ones do not);
+//     dV and the first of dK (there is one wavefront a SIMD: only its own vector and matrix instructions can overlap);
 //   * tiles go from memory to LDS without registers (global_load_lds) through a ring of four, two tiles ahead, and the
 //     next tile's first fragments are read before this tile's last MFMAs: the barrier sits between;
 //   * one wavefront issues one instruction at a time: 3.9 vector and 2.3 scalar instructions per MFMA, after 7.5 and 1.7 with

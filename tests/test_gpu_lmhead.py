@@ -437,8 +437,8 @@ def test_expected_row_count_with_sampling_and_entropy_partials():
 @pytest.mark.parametrize("M,cus,V", [(70, 8, 2600), (100, 8, 2400), (128, 4, 1500), (150, 8, 2561), (192, 8, 2300), (230, 8, 2500),
                                      (256, 6, 2047), (96, 8, 2305)])
 def test_half_height_tail_launch(M, cus, V):
-    """A vocabulary whose tile count leaves the last round of workgroups at most half full is covered by two launches:
-    full-height tiles, then half-height ones for the tail.  The assumed CU count is lowered so that a small problem
+    """A vocabulary whose tile count leaves the last round of workgroups at most half full is covered by full-height tiles and, in the
+    same launch, half-height ones for the tail.  The assumed CU count is lowered so that a small problem
     takes that path (e.g. 2600 rows = 11 tiles of 256 on 8 'CUs': 8 full tiles + 5 half tiles, the last one ragged);
     every output against the oracle, with a forbidden token in the tail and targets on both sides of the seam."""
     Dh = 128
@@ -450,7 +450,7 @@ def test_half_height_tail_launch(M, cus, V):
     try:
         got = run_lm(h, w, forbid=V - 1, target=tgt)
         compare(got, ref)
-        # device-side row count below the bound, and the two-shape queue on top of the two-launch tail
+        # device-side row count below the bound, and two queued shapes on top of the tail
         m_dev = max(1, M - 37)
         got = run_lm(h, w, forbid=V - 1, m_dev=m_dev, M_expected=max(1, int(0.8 * M)))
         compare_prefix(got, ref, m_dev)
