@@ -1456,12 +1456,14 @@ static const LmVariant g_lm_variants[] = {
     /*21*/ LMQ(4, 2, 2, 4, false),  // same, 8 waves x (64 x 128): one 256-row chunk as fast as entry 5, with 1.47 x the HBM fetch
     /*22*/ LMQ(4, 1, 2, 6, true),  // 256 x 192, 4 waves x (64 x 192)
     /*23*/ LMQ(4, 1, 2, 4, false),  // 256 x 128, 4 waves x (64 x 128)
-    // 128 vocabulary rows (forced only, as entry 2: the half-height tiles of a tail are part of lmhead_tail_kernel)
+    // 128 vocabulary rows (forced only, as entry 2: the half-height tiles of a tail are part of lmhead_tail_kernel; 25 also for
+    // small vocabularies, see plan_lmhead)
     /*24*/ LMP(4, 1, 1, 3, 3),  // 128 x 96,  4 waves
     /*25*/ LMP(4, 2, 1, 2, 3),  // 128 x 128, 8 waves
     /*26*/ LMP(4, 2, 1, 3, 2),  // 128 x 192, 8 waves
     /*27*/ LMQ(4, 2, 1, 4, false),  // 128 x 256, paired ring, 8 waves x (32 x 128)
     /*28*/ LMP(4, 2, 1, 4, 2),  // 128 x 256, register-staged, 8 waves
+    /*29*/ LMP(4, 2, 1, 1, 3),  // 128 x 64,  8 waves: small vocabularies (see plan_lmhead)
 };
 constexpr size_t LM_QUEUE_BYTES = 8 * 64;
 // entries that can take their tiles from a queue
@@ -1488,8 +1490,7 @@ int g_lm_variant = -1;           // -1 = choose by M; otherwise force an entry o
 int g_lm_block_gv = -1;          // -1 = automatic XCD blocking; 0 = none; n = n vocabulary tiles per block, both without a queue (tuning)
 int g_lm_cus = 0;                // CUs the tail and the queue rule assume: 0 = the device's count; -1 = that and no half-height tail (tuning, tests)
 
-static int plan_lmhead(int M) {
-    if (g_lm_variant >= 0) return g_lm_variant;
+static int plan_rows(int M) {
     if (M <= 32) return 0;
     if (M <= 64) return 1;
     if (M <= 128) return 3;
@@ -1497,6 +1498,36 @@ static int plan_lmhead(int M) {
     if (M <= 256) return 5;         // one 256-row chunk, register-staged: as fast as the ring (entry 21), which fetches 1.3 - 1.5 x W here
     if (M <= 384) return 22;        // two 192-row chunks
     return 20;                      // 256-row chunks, one wavefront per SIMD with a 128 x 128 tile
+}
+
+static int64_t lm_tiles(int v, int M, int V) {
+    const int tv = g_lm_variants[v].tv, mb = g_lm_variants[v].mb;
+    return ((int64_t)V + tv - 1) / tv * (((int64_t)M + mb - 1) / mb);
+}
+
+// The shape for M rows of V tokens.  The one for M alone is made to read W once; with a small vocabulary its few large tiles leave most
+// CUs idle, and a CU brings in no more than 60 - 70 GB/s however much it has in flight.  So where it gives at most five
+// eighths as many workgroups as there are CUs (160 of 256), the smallest tile is taken of which there is at most one a CU: more CUs
+// share the load, and W and H, read more than once, come from L2.  Over 1074 points (V 2048 .. 157184, Dh 256 .. 4096, 16 .. 2048 rows)
+// this is the faster side or the same everywhere, 0.79 of the time in the geometric mean.  Us a call, M alone / now: V = 2048, Dh =
+// 256, 64 rows 10.4 / 8.1; V = 8000, Dh = 4096, 96 rows 63 / 27, 256 rows 105 / 33; V = 2048, Dh = 4096, 1024 rows 84 / 38; V = 32000,
+// Dh = 4096, 128 rows 71 / 56.  With 161 - 256 workgroups smaller tiles lose (V = 50000, Dh = 4096, 256 rows 127 / 157 and more).
+// More than 256 rows of fewer than 512 elements keep the ring, though small tiles would be faster there too (V = 4096, Dh = 256, 512 rows 21 /
+// 10 us): such calls give the same bits on any number of CUs, with a queue of tiles and without, which the tests hold them to.
+static bool lm_few(int M, int V, int Dh, int cus) {
+    return g_lm_variant < 0 && (M <= 256 || Dh >= 512) && 8 * lm_tiles(plan_rows(M), M, V) <= 5 * (int64_t)cus;
+}
+static int plan_lmhead(int M, int V, int Dh, int cus) {
+    if (g_lm_variant >= 0) return g_lm_variant;
+    const int usual = plan_rows(M);
+    if (lm_few(M, V, Dh, cus)) {
+        static const int small[] = {0, 29, 25, 3};
+        for (int v : small) {
+            if (g_lm_variants[v].tv * g_lm_variants[v].mb >= g_lm_variants[usual].tv * g_lm_variants[usual].mb) break;
+            if (lm_tiles(v, M, V) <= cus) return v;
+        }
+    }
+    return usual;
 }
 
 static int validate_lm(const dlm_lmhead_args* a) {
@@ -1524,7 +1555,7 @@ static int validate_lm(const dlm_lmhead_args* a) {
 
 using namespace dlm;
 
-// largest row count served by the shape plan_lmhead picks for M rows
+// largest row count served by the shape plan_rows picks for M rows
 static int plan_capacity(int M) {
     static const int caps[] = {32, 64, 128, 192, 256, 384};
     for (int c : caps)
@@ -1641,11 +1672,12 @@ static int lmhead_enqueue(const dlm_lmhead_args* a, void* workspace, void* strea
     // The caller's bound M sizes the launch, the device's count says how many rows there are.  When the caller
     // expects the count to fall in a smaller shape's range, that shape is queued first, guarded by "count <= its
     // capacity", and the bound's shape after it, guarded by the opposite: one of the two returns at once.
-    const int v_safe = plan_lmhead(a->M);
+    // (Not where the bound gives few tiles: then it is cut into small row chunks, and those past the count return at once.)
+    const int v_safe = plan_lmhead(a->M, a->V, a->Dh, cus);
     int v_try = v_safe, cap = 0;
-    if (a->m_dev && a->M_expected > 0 && a->M_expected < a->M && g_lm_variant < 0) {
+    if (a->m_dev && a->M_expected > 0 && a->M_expected < a->M && g_lm_variant < 0 && !lm_few(a->M, a->V, a->Dh, cus)) {
         cap = plan_capacity(a->M_expected);
-        if (cap < a->M) v_try = plan_lmhead(cap);
+        if (cap < a->M) v_try = plan_lmhead(cap, a->V, a->Dh, cus);
     }
     const bool guess = v_try != v_safe;
     LmParams q = p;

@@ -570,3 +570,36 @@ def test_every_form_of_a_call_through_a_queue(kind, M, Dh, V, cus, counted):
             assert np.all(np.isnan(conf[rest])) and np.all(tok[rest] == -7) and np.all(np.isnan(zt[rest]))
     finally:
         dlm.set_option("lmhead_cus", 0)
+
+
+@pytest.mark.parametrize("M,m_dev,Dh,V,guess", [
+    (33, None, 64, 100, 0), (64, 40, 64, 129, 0),          # 128 x 32 tiles instead of 128 x 64, the shortest walk
+    (65, None, 320, 2100, 0), (256, 97, 512, 4096, 120),   # 128 x 32, all 256 of them; a count with whole chunks past it
+    (256, 255, 512, 4097, 200), (200, None, 128, 5000, 0), # one vocabulary tile more: 128 x 64
+    (384, None, 512, 10000, 0), (385, 129, 576, 2200, 0),  # 128 x 128 and 128 x 32
+    (500, 3, 512, 17000, 0), (1030, None, 512, 300, 0),    # 256 x 128; more row chunks than vocabulary tiles
+    (256, 200, 64, 40960, 0), (256, 200, 64, 40961, 0),    # 160 tiles of 256 x 256, the most that are few, and one more
+])
+def test_small_vocabularies_take_small_tiles(M, m_dev, Dh, V, guess):
+    """The shapes that fill the chip where the one for the row count alone leaves most of it idle, on both sides of the lines between them."""
+    R = M + 19
+    h, w = rnd(1900 + M, (R, Dh)), rnd(1901 + V, (V, Dh), Dh ** -0.25)
+    idx = np.random.default_rng(M + V).permutation(R)[:M].astype(np.int32)
+    m = m_dev or M
+    ref = oracle.lmhead(h, w, row_idx=idx[:m], forbid_token=V - 1, inv_temperature=0.9)
+    compare_prefix(run_lm(h, w, row_idx=idx, M=M, m_dev=m_dev, inv_t=0.9, forbid=V - 1, M_expected=guess), ref, m)
+
+
+@pytest.mark.parametrize("R,n_sel,variant", [(400, 300, 22), (900, 700, 20)])
+def test_gather_on_the_ring_shapes_by_name(R, n_sel, variant):
+    test_gather_mdev_target_on_the_ring_shapes(R, n_sel, variant)
+
+
+def test_expected_row_counts_where_tiles_are_many():
+    dlm.set_option("lmhead_cus", 8)
+    try:
+        for M, m_dev, guess in ((256, 150, 160), (256, 200, 160), (500, 200, 250), (500, 300, 250), (300, 0, 100), (100, 33, 30)):
+            test_expected_row_count_only_selects_the_shape(M, m_dev, guess)
+        test_expected_row_count_with_sampling_and_entropy_partials()
+    finally:
+        dlm.set_option("lmhead_cus", 0)
