@@ -403,7 +403,8 @@ int dlm_kv_refresh(const dlm_kv_seg *src, int32_t B, int32_t Hkv, int32_t d,
  *                   13, 14 = 128-row workgroups of 8 wavefronts in two key groups, combined through LDS (prefetch depth 1, 2;
  *                       13 is chosen when there is at most one 128-row workgroup per CU);
  *                   15 = software-pipelined 128-row workgroups (d = 128; softmax of one key tile woven between the MFMAs
- *                       of the next).
+ *                       of the next);
+ *                   16 = 11 with eight wavefronts (chosen up to one such workgroup per CU).
  *   "attn_split"    0 = the library decides whether several workgroups share the keys of a row tile (default: only with at
  *                   most 128 workgroups and at least 32 key tiles, and only when the call brings the workspace);
  *                   1 = never; 2..16 = that many (lowered to keep four key tiles per workgroup).

@@ -48,6 +48,7 @@ struct AttnParams {
     // [T * split / nsplit, T * (split + 1) / nsplit) and stores its unnormalised accumulators and its (running
     // maximum, sum) instead of the output; attn_merge_kernel combines the nsplit partials of every row.
     int nsplit;
+    int rows32;       // the split was planned for 32-row workgroups
     float* part_o;    // [nsplit][B * Hkv * R][d]
     float* part_ml;   // [nsplit][B * Hkv * R][2]  (maximum in log2 units, sum of exponentials relative to it)
 };
@@ -429,7 +430,7 @@ _Pragma("unroll") \
 
     // tile of iteration `it` for this wave group: it * NWK + wk; it sits in register slot it % PF
     if (n_it > 0) {
-        const int rot0 = DB ? 0 : (int)(((unsigned)b * (unsigned)p.Hkv + (unsigned)kvh) * 5u % (unsigned)n_it);
+        const int rot0 = NTKV ? (int)(((unsigned)b * (unsigned)p.Hkv + (unsigned)kvh) * 5u % (unsigned)n_it) : 0;
 #pragma unroll
         for (int s = 0; s < PF; ++s)
             if (s < n_it) ATTN_PREFETCH(s, ((s + rot0 >= n_it) ? s + rot0 - n_it : s + rot0) * NWK + wk);
@@ -615,8 +616,9 @@ _Pragma("unroll") \
     } else {
         // Each (sequence, KV head) starts its walk over the key tiles at a different tile and wraps: the K/V
         // blocks of different heads are a large power-of-two-ish stride apart, so workgroups that all begin at
-        // tile 0 hit the same few HBM channels together.  Softmax is order-independent up to rounding.
-        const int rot = (n_it > 0) ? (int)(((unsigned)b * (unsigned)p.Hkv + (unsigned)kvh) * 5u % (unsigned)n_it) : 0;
+        // tile 0 hit the same few HBM channels together.  Softmax is order-independent up to rounding.  (Where K and V are streamed
+        // past L2: in the shapes with several row tiles it gains nothing, and without it equal sequences give equal bits.)
+        const int rot = (NTKV && n_it > 0) ? (int)(((unsigned)b * (unsigned)p.Hkv + (unsigned)kvh) * 5u % (unsigned)n_it) : 0;
 #define ATTN_KS_TILE(i) ((((i) + rot) >= n_it ? (i) + rot - n_it : (i) + rot) * NWK + wk)
         int it = 0;
         const int n_steady = (n_it - PF > 0) ? ((n_it - PF) / PF) * PF : 0;
@@ -893,28 +895,54 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
 
 int g_attn_split = 0;    // 0 = choose the key split across workgroups from the shape; 1 = never; 2..16 = force (dlm_set_option "attn_split")
 int g_attn_nt = 1;       // 1 = non-temporal K/V loads in the one-workgroup-per-KV-head shape (default); 0 = never (tuning)
-int g_attn_variant = 0;  // 0 = choose by shape; 1..3 force a kernel shape (dlm_set_option "attn_variant")
+int g_attn_variant = 0;  // 0 = choose by shape; 1..16 force a kernel shape (dlm_set_option "attn_variant")
 int g_attn_remap = 7;    // XCD-grouped grids: bit 0 forward and dQ, bit 1 longest key range first, bit 2 dK / dV (dlm_set_option "attn_remap")
 
 // The kernel shape the planner picks for a problem (0 = "automatic" resolved).  Measured on MI355X (us, GPU time):
 //   g * Lq <= 32 (every rollout step): one key-split workgroup per (sequence, KV head); sized for two per CU it is
 //     8 - 10 % faster than sized for one even when only one is resident (c2 22.4 -> 19.7, c3 72 -> 66, c5a 173 -> 162);
 //   more rows: 128-row workgroups; with at most one of them per CU, eight wavefronts in two key groups (two wavefronts
-//     per SIMD from one workgroup: c4 39.1 -> 32.2), otherwise two or three four-wavefront workgroups per CU.
-static int plan_variant(const AttnParams& p) {
+//     per SIMD from one workgroup: c4 39.1 -> 32.2), otherwise two or three four-wavefront workgroups per CU;
+//   where 32-row workgroups (K/V re-read per row tile, through one L2) are at most one per CU, a wavefront's walk over its key tiles is
+//     all the time there is, about 2 us a tile of d = 128 and 1 of d = 64, so eight wavefronts share the keys of 32 rows.  Us, before
+//     (128 rows, or four wavefronts) / now: 8 x 28/4 heads x 500 keys 14.1 / 11.8, 20 x 16/2 x 8062 120 / 69, 4 x 14/2 of 64 x 833 13.2 / 9.2,
+//     1 x 3756 tokens, 4 heads of 64, blocks of 32 (472 workgroups) 71 / 30.  At d = 64 three workgroups of four wavefronts fit a CU: up
+//     to 512 they lead with fewer than 48 tiles (6 x 348 tokens, 4 heads 12.1 / 8.7; with 640 workgroups 8.7 / 8.4, with 752 7.6 / 10.2);
+//   g * Lq <= 32 likewise: 24 x 4 heads of 64 x 500 keys 9.1 / 8.0, 2 x 32/8 of 128 x 1024 17.6 / 15.3; at d = 128 only where the keys are
+//     not split across workgroups, with which the two are even;
+//   under a block-causal mask over whole sequences, whose workgroups differ in length, the eight wavefronts of two key groups also where there are up to two
+//     workgroups per CU (a packed batch: of its tokens) and 16 key tiles: the longest ends sooner.  Us, four / eight wavefronts: 2 x 600 tokens,
+//     32/8 heads 28.1 / 21.4 (16 tiles 28.8 / 27.1, 13 in a packed batch 21.5 / 23.1), 1 x 2000, 32/8 77.8 / 60.1; at d = 64, two such
+//     workgroups a CU, up to 850 with 38 tiles: 10 x 2000, 4 heads 86.9 / 63.7 (1008 with 112 144 / 151).  Not where the rows are a
+//     block at the end, all workgroups equally long: 60 x 32 rows x 2291 keys, 28/4 heads 105 / 124;
+//   513 - 767 workgroups of d = 128 (not of a packed batch, of which fewer have rows) at three a CU, in one round: 3 x 800 tokens, 28/4 heads
+//     58.6 / 46.4.
+// Workgroups of the fullest XCD (32 CUs) of a grid that set_remap makes of nx tiles for each of n_groups
+static int64_t xcd_load(int64_t n_groups, int64_t nx) {
+    GridRemap m;
+    return set_remap(m, n_groups, (int)nx, false) / 8;
+}
+// tiles: key tiles of a (sequence, KV head), the most one can have
+static int plan_variant(const AttnParams& p, int d, bool bc, int64_t tiles) {
+    if (g_attn_variant != 0) return g_attn_variant;
     const int64_t BH = (int64_t)p.B * p.Hkv;
-    int variant = g_attn_variant;
-    if (variant == 0) {
-        const int64_t wgs128 = BH * ((p.R + 127) / 128) * (p.nsplit > 1 ? p.nsplit : 1);
-        if (p.R <= 32) variant = 12;          // waves split the keys, merge on chip
-        // far too few 128-row workgroups for 256 CUs (and no workspace to split the keys across workgroups with):
-        // 32-row key-split tiles (K/V re-read per row tile, through one L2)
-        else if (wgs128 <= 64 || (wgs128 <= 128 && p.R <= 64)) variant = 11;
-        else if (wgs128 <= 256) variant = 13; // one 128-row workgroup per CU at most: eight wavefronts, two key groups
-        else if (wgs128 >= 768) variant = 6;  // 128-row workgroups, three resident per CU (softmax of one overlaps MFMA of another)
-        else variant = 4;                     // 128-row workgroups, two resident per CU, deeper prefetch
+    const int ns = p.nsplit > 1 ? p.nsplit : 1;
+    const int64_t wgs128 = BH * ((p.R + 127) / 128) * ns, wgs32 = BH * ((p.R + 31) / 32) * ns;
+    if (p.R <= 32)                          // waves split the keys, merge on chip
+        return (d == 64 ? wgs32 <= 256 && tiles >= 12 * ns : ns == 1 && wgs32 <= 160 && tiles >= 16) ? 10 : 12;
+    if (ns == 1 || p.rows32) {
+        if (wgs32 <= 256) return tiles >= 6 && xcd_load(BH, wgs32 / BH) <= 32 ? 16 : 11;
+        if (d == 64 && wgs32 <= 512) return tiles >= 48 ? 16 : 11;
     }
-    return variant;
+    if (wgs128 <= 256) return 13;           // one 128-row workgroup per CU at most: eight wavefronts, two key groups
+    const int64_t live = p.cu ? ((int64_t)p.total * p.g / 128 + p.B / 2) * p.Hkv : wgs128;
+    if (bc && ns == 1 && 2 * (int64_t)p.Lq + 64 >= 32 * tiles && ((live <= 512 && tiles >= 16) || (d == 64 && live <= 850 && tiles >= 38))) return 13;
+    if (wgs128 >= (d == 128 && !p.cu ? 513 : 768)) return 6;   // 128-row workgroups, three resident per CU (softmax of one overlaps MFMA of another)
+    return 4;                               // 128-row workgroups, two resident per CU, deeper prefetch
+}
+
+static int64_t key_tiles(const dlm_attn_args* a) {
+    return ((int64_t)a->prefix.len + 31) / 32 + ((int64_t)a->block.len + 31) / 32 + ((int64_t)a->suffix.len + 31) / 32;
 }
 
 // How many workgroups share the keys of one row tile.  A split costs a second launch (the merge) and (d + 2) * 4 bytes
@@ -929,7 +957,7 @@ static int plan_nsplit(const dlm_attn_args* a) {
     if (a->cu_seqlens || g_attn_split == 1) return 1;
     const int g = a->Hq / a->Hkv;
     const int64_t R = (int64_t)g * a->Lq, BH = (int64_t)a->B * a->Hkv;
-    const int64_t tiles = ((int64_t)a->prefix.len + 31) / 32 + ((int64_t)a->block.len + 31) / 32 + ((int64_t)a->suffix.len + 31) / 32;
+    const int64_t tiles = key_tiles(a);
     int64_t n = 1;
     if (g_attn_split >= 2) n = g_attn_split;
     else if (g_attn_variant == 0) {
@@ -939,6 +967,25 @@ static int plan_nsplit(const dlm_attn_args* a) {
     if (n > 16) n = 16;
     if (n > tiles / 4) n = tiles / 4;         // at least four key tiles per workgroup
     return n < 1 ? 1 : (int)n;
+}
+
+// How many of the n_max splits that the workspace has room for a call takes, and whether for 32-row workgroups (p.rows32).  Those read K and V
+// once for every 32 rows: about 1.1 ns a key tile of d = 128 (14.6 TB/s from L2), on top of some 12 us; 128-row ones take 18 and 0.55 a
+// tile and split.  Us, 128 / 32 rows: 1 x 32/8 heads of 128 x 8192 keys 26.3 / 21.5, 4 x 28/4 x 2048 24.9 / 20.6, x 4096 26.3 / 29.1.  Fewer, longer
+// splits where the tiles are few, as the merge costs more with each: 1 x 4 heads of 64 x 2048 keys, 16 / 8 splits 13.8 / 10.4;
+// 24 x 4 heads of 64 x 1024 keys, 2 / none 12.4 / 10.4.
+static int plan_use_nsplit(AttnParams& p, int d, int64_t tiles, int n_max) {
+    p.rows32 = 0;
+    if (n_max <= 1 || g_attn_split >= 2 || g_attn_variant != 0) return n_max;
+    const int64_t BH = (int64_t)p.B * p.Hkv, n32 = BH * ((p.R + 31) / 32);
+    if (p.R <= 32) return d == 64 && tiles < 48 ? 1 : (int)(tiles / 8 < n_max ? tiles / 8 : n_max);
+    if (n32 > 256 || n32 * tiles * 1120 * d / 128 >= 6000000 + tiles * 550000 / n_max) return n_max;
+    p.rows32 = 1;
+    int64_t n = 256 / n32 < tiles / 8 ? 256 / n32 : tiles / 8;
+    if (tiles < 48 && (d == 64 || n32 > 64)) n = 1;
+    if (n > n_max) n = n_max;
+    while (n > 1 && xcd_load(BH, n32 / BH * n) > 32) --n;
+    return (int)n;
 }
 
 // Are issue priorities by phase worth it?  In launches of three and more rounds of workgroups (three a CU on 256 CUs) whose rows see 24 and
@@ -955,16 +1002,17 @@ static bool attn_deep(const AttnParams& p) {
 }
 
 template <int D, bool BC>
-static int launch_attn(const AttnParams& p, hipStream_t st) {
+static int launch_attn(const AttnParams& p, int64_t tiles, hipStream_t st) {
     const int64_t BH = (int64_t)p.B * p.Hkv;
     const int ns = p.nsplit > 1 ? p.nsplit : 1;
-    int variant = plan_variant(p);
-    if (variant == 0 + 11 || (variant == 1 && p.R > 32)) {
+    int variant = plan_variant(p, D, BC, tiles);
+    if (variant == 11 || variant == 16 || (variant == 1 && p.R > 32)) {
         // 32-row workgroups whose wavefronts split the keys, several row tiles per (sequence, KV head), XCD-grouped
         AttnParams q = p;
         const int64_t n_wg = set_remap(q.remap, BH, (p.R + 31) / 32 * ns, BC && (g_attn_remap & 2));
         if (n_wg > 0) {
-            hipLaunchKernelGGL((attn_kernel<D, 1, 4, 1, BC, 1>), dim3((unsigned)n_wg), dim3(256), 0, st, q);
+            if (variant == 16) hipLaunchKernelGGL((attn_kernel<D, 1, 8, 1, BC, 1>), dim3((unsigned)n_wg), dim3(512), 0, st, q);
+            else hipLaunchKernelGGL((attn_kernel<D, 1, 4, 1, BC, 1>), dim3((unsigned)n_wg), dim3(256), 0, st, q);
             return check_hip(hipGetLastError(), "attn_kernel launch");
         }
         variant = 2;
@@ -1096,7 +1144,7 @@ using namespace dlm;
 extern "C" int dlm_set_option(const char* name, int value) {
     if (!name) return fail(DLM_ERR_INVALID_ARG, "set_option: null name");
     if (!strcmp(name, "attn_variant")) {
-        if (value < 0 || value > 15) return fail(DLM_ERR_INVALID_ARG, "set_option: attn_variant must be 0..15");
+        if (value < 0 || value > 16) return fail(DLM_ERR_INVALID_ARG, "set_option: attn_variant must be 0..16");
         g_attn_variant = value;
         return DLM_OK;
     }
@@ -1159,19 +1207,20 @@ extern "C" int dlm_block_attn(const dlm_attn_args* a, void* stream) {
     p.seq_active = a->seq_active;
     p.remap = no_remap();
     // The key split across workgroups is taken only when the caller brought the workspace it needs.
-    p.nsplit = 1; p.part_o = nullptr; p.part_ml = nullptr;
-    const int ns = plan_nsplit(a);
-    const size_t need = split_workspace_bytes(a, ns);
-    if (ns > 1 && a->workspace && a->workspace_bytes >= need && aligned16(a->workspace)) {
+    p.nsplit = 1; p.rows32 = 0; p.part_o = nullptr; p.part_ml = nullptr;
+    const int64_t tiles = key_tiles(a);
+    const int n_max = plan_nsplit(a);
+    const size_t need = split_workspace_bytes(a, n_max);
+    if (n_max > 1 && a->workspace && a->workspace_bytes >= need && aligned16(a->workspace)) {
         const size_t rows_total = (size_t)a->B * a->Hq * a->Lq;
-        p.nsplit = ns;
+        p.nsplit = plan_use_nsplit(p, a->d, tiles, n_max);
         p.part_o = (float*)a->workspace;
-        p.part_ml = p.part_o + (size_t)ns * rows_total * a->d;
+        p.part_ml = p.part_o + (size_t)p.nsplit * rows_total * a->d;
     }
     hipStream_t st = (hipStream_t)stream;
     const bool bc = a->mask_mode == DLM_MASK_BLOCK_CAUSAL;
-    if (a->d == 128) rc = bc ? launch_attn<128, true>(p, st) : launch_attn<128, false>(p, st);
-    else rc = bc ? launch_attn<64, true>(p, st) : launch_attn<64, false>(p, st);
+    if (a->d == 128) rc = bc ? launch_attn<128, true>(p, tiles, st) : launch_attn<128, false>(p, tiles, st);
+    else rc = bc ? launch_attn<64, true>(p, tiles, st) : launch_attn<64, false>(p, tiles, st);
     if (rc != DLM_OK || p.nsplit <= 1) return rc;
     const int64_t rows_total = (int64_t)a->B * a->Hq * a->Lq;
     if (a->d == 128) hipLaunchKernelGGL(attn_merge_kernel<128>, dim3((unsigned)((rows_total + 7) / 8)), dim3(256), 0, st, p);

@@ -409,3 +409,32 @@ def test_launches_deep_enough_for_issue_priorities(d, bs, packed):
     for part, c in parts:
         run(q[part], k[part], v[part], ref[part], c)
     assert out.any() and torch.equal(out.view(torch.int16), ref.view(torch.int16))
+
+
+@pytest.mark.parametrize("d,Lq,Hq,Hkv,P,S,split,kw", [
+    (64, 1, 33, 1, 0, 0, 0, {}),                              # one key: seven of the eight wavefronts have no tile
+    (128, 33, 2, 2, 190, 7, 0, {}),                           # 9 tiles over three segments, a row tile of one row
+    (64, 40, 7, 1, 225, 0, 0, dict(mode="block_causal", bs=8)),
+    (128, 20, 8, 2, 250, 0, 0, dict(plen=[250, 31])),         # a sequence whose prefix is one tile
+    (128, 32, 8, 2, 1500, 0, 5, {}),                          # splits of nine and ten tiles
+    (64, 32, 14, 2, 1030, 0, 16, dict(mode="block_causal", bs=32)),
+])
+def test_eight_wavefronts_that_share_the_keys_of_32_rows(d, Lq, Hq, Hkv, P, S, split, kw):
+    run_case(B=2, Lq=Lq, Hq=Hq, Hkv=Hkv, d=d, P=P, Lb=Lq, S=S, seed=60 + P, variant=16, split=split, **kw)
+
+
+@pytest.mark.parametrize("B,Lq,Hq,Hkv,d,P,kw", [
+    (1, 32, 4, 4, 64, 2016, {}), (24, 16, 4, 4, 64, 1000, {}), (24, 16, 4, 4, 64, 2016, {}),   # up to 32 rows: splits of 8 tiles, none, 2
+    (1, 32, 32, 8, 128, 1000, {}), (2, 32, 28, 4, 128, 1100, {}), (4, 32, 28, 4, 128, 1100, {}),   # splits of 32-row workgroups, none
+    (6, 32, 14, 2, 64, 2100, dict(mode="block_causal", bs=32)),   # as many splits as the fullest XCD has CUs for
+    (8, 32, 28, 4, 128, 2900, {}), (8, 32, 28, 4, 128, 2000, {}),   # more tiles than 32-row workgroups are worth, and fewer
+])
+def test_splits_that_a_call_takes_of_those_it_has_room_for(B, Lq, Hq, Hkv, d, P, kw):
+    """Calls with a workspace for the most splits: how many of them are taken, and the rows of a workgroup, follow from the shape."""
+    run_case(B=B, Lq=Lq, Hq=Hq, Hkv=Hkv, d=d, P=P, Lb=Lq, S=0, seed=70 + B, split=0, **kw)
+
+
+@pytest.mark.parametrize("B,L,Hq,Hkv,d,bs", [(1, 1008, 16, 2, 128, 16), (2, 500, 14, 2, 64, 4), (3, 800, 28, 4, 128, 0), (1, 900, 4, 4, 64, 0),
+                                             (1, 2050, 4, 4, 64, 8), (6, 348, 4, 4, 64, 32)])
+def test_full_sequences_on_both_sides_of_the_lines_between_shapes(B, L, Hq, Hkv, d, bs):
+    run_case(B=B, Lq=L, Hq=Hq, Hkv=Hkv, d=d, P=0, Lb=L, S=0, seed=80 + L, **(dict(mode="block_causal", bs=bs, q_pos0=0) if bs else {}))
