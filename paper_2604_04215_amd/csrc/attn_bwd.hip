@@ -408,6 +408,18 @@ __device__ __forceinline__ void bw_mfma_zero(f32x16& c, bf16x8 a, bf16x8 b) {
     asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
 }
 
+// Is a workgroup ever given two slabs (`pair`)?  Never with one wavefront (one slab in all) or with 2 x 2 of them (too few slabs for it):
+// without the second pass nothing has to be kept over the first.
+template <bool BC, int NWK, int NWR>
+constexpr bool dkv_pairs() { return BC && NWK * NWR != 1 && !(NWK == 2 && NWR == 2); }
+
+// the lane number, formed where it stands (asm: what follows from it is not moved away or kept in registers in its place)
+__device__ __forceinline__ int bw_lane() {
+    int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
 // dK and dV of one segment in one pass.  A wavefront owns 64 keys (two MFMA column tiles, K and V fragments and both
 // accumulators in registers) and walks 32-row tiles of (query, head in group) rows; NWK wavefronts side by side share
 // the tiles through LDS, NWR groups of them take every NWR-th tile and are summed through LDS at the end.
@@ -421,14 +433,17 @@ __device__ __forceinline__ void bw_mfma_zero(f32x16& c, bf16x8 a, bf16x8 b) {
 //   * tiles go from memory to LDS without registers (global_load_lds) through a ring of four, two tiles ahead, and the
 //     next tile's first fragments are read before this tile's last MFMAs: the barrier sits between;
 //   * one wavefront issues one instruction at a time: 3.9 vector and 2.3 scalar instructions per MFMA, after 7.5 and 1.7 with
-//     LDS addresses, row divisions and statistics formed per read (2.6 -> 1.9 ms below).  At d = 128 the compiler still spills: 18
-//     or 50 vector registers outside the tile loop (with the full mask one of them comes back once a tile), and 52 - 65 scalars to
-//     lanes of vector registers, some 20 of which the loop reads back a tile, most for request paths the launch does not take.
+//     LDS addresses, row divisions and statistics formed per read (2.6 -> 1.9 ms below).  At d = 128 the compiler still spills 40 - 70
+//     scalars to lanes of vector registers, some 20 of which the loop reads back a tile, most for request paths the launch does not take;
+//   * nothing covers what a workgroup does before its first product, so K, V and the first tiles travel together: no vector register is
+//     spilled in the shapes that large launches take (with 18 or 50 of them kept on the stack from the start of the kernel on, every reload
+//     waited for all requests before it: five trips to memory one after another, 1.72 -> 1.63 ms on the packed batch below).
 // Measured (8 x 4096 tokens, 32 / 8 heads of 128, blocks of 4): 1.86 - 1.95 ms = 1.17 PFLOP/s of products, two passes with 32
-// keys a wavefront 4.28 ms; 128 packed sequences of 64 k tokens, 32 heads: 1.73 ms, before 2.86.  MFMA pipes busy 0.52 at
+// keys a wavefront 4.28 ms; 128 packed sequences of 64 k tokens, 32 heads: 1.63 ms, two passes 2.86.  MFMA pipes busy 0.52 at
 // 2.2 GHz: with all loads, waits and vector work taken out the loop still runs at 1.35 PFLOP/s, the power limit on such data.
 template <int D, bool BC, int NWK, int NWR>
 __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdParams p, int sidx, int n_slabs, int pair, GridRemap rm) {
+    constexpr bool PAIR = dkv_pairs<BC, NWK, NWR>();   // a workgroup may take two slabs
     constexpr int NS = D == 128 && NWK * NWR == 1 ? 2 : 4;   // ring stages: four such rings fit a CU, one a SIMD
     constexpr int FD = D == 128 ? 2 : 4;               // fragments read ahead (at d = 128 all that registers allow)
     constexpr int AHEAD = NWK == 1 ? NS - 1 : 2;       // tiles requested ahead: a ring that is the wavefront's own needs no slack
@@ -447,10 +462,9 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     static_assert(IPW >= 1, "at least one request per wavefront");
     __shared__ __attribute__((aligned(1024))) unsigned char smem[BODY + NWK * NWR * NS * 256];
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wk = w % NWK, wr = w / NWK;
-    const int n = lane & 31, hi = lane >> 5;
     int b = blockIdx.z, kvh = blockIdx.y, bx = blockIdx.x;
     if (rm.nx > 0) {
         int grp;
@@ -491,21 +505,10 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     const int mul_g = (65536 + g - 1) / g;
     const uint16_t* const qb = p.q + q_off + (int64_t)(kvh * g) * p.q_sh;
     const uint16_t* const gb = p.dout + do_off + (int64_t)(kvh * g) * p.do_sh;
-    // statistics: lanes 0..31 fetch LSE, lanes 32..63 delta of the tile's rows
-    const float* const stp = (hi ? p.delta : p.lse) + stat_index(p, b, kvh * g, 0, s0);
     const int st_h = p.cu ? p.total : p.Lq;            // statistics of the next head
     const int stat_base = BODY + w * NS * 256;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-    // lane parts of the LDS addresses: row reads (row n, piece 2 c + hi) and transposing reads (row 16 j + 8 q + 4 hi + s16 / 4,
-    // piece 4 dt + 2 blk + ...); the step-dependent part is an exclusive-or above bit 5 or 6
-    constexpr int RSH = D == 128 ? 6 : 5, RDIV = D == 128 ? 2 : 1;
-    const int row_base = n / RPI * BW_GP + n % RPI * P + hi * 16;
-    const int row_x = bw_swz<D>(n) >> 1 << 5 & (D == 128 ? 0xc0 : 0x60);
-    const int s16 = lane & 15, blk = (lane >> 4) & 1;
-    const int tr_base = (D == 128 ? hi * BW_GP + (s16 >> 2) * P : (4 * hi + (s16 >> 2)) * P) +
-                        (((2 * blk + ((s16 & 3) >> 1)) ^ (D == 128 ? 0 : 2 * hi)) << 4) + 8 * (s16 & 1);
-    const int tr_x = (D == 128 ? s16 >> 2 : s16 >> 3) << 6;
     // requests with 32-bit offsets from a wave-uniform query: strides of less than 2^24 bytes, all of a group's heads within 2^30
     const bool small = p.q_st >= 0 && p.q_sh >= 0 && p.do_st >= 0 && p.do_sh >= 0 && p.q_st < (1 << 23) && p.q_sh < (1 << 23) &&
                        p.do_st < (1 << 23) && p.do_sh < (1 << 23) && g * p.q_sh < (1 << 29) && g * p.do_sh < (1 << 29);
@@ -515,17 +518,15 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     const bool regular = small && (32 % g) == 0 && p.q_st == p.do_st && p.q_sh == p.do_sh;
     const int gsh = 31 - __builtin_clz(g);
     const int qst2 = (int)p.q_st * 2, qsh2 = (int)p.q_sh * 2;
-    const uint32_t voff = regular ? __umul24((lane / C8) >> gsh, qst2) + __umul24((lane / C8) & (g - 1), qsh2) + ((lane % C8) ^ bw_swz<D>(lane / C8)) * 16 : 0;
-    const float* const sptr = stp + (int64_t)(n & (g - 1)) * st_h + (n >> gsh);
 
     // Under a block-causal mask the work of a key slab shrinks with its index (later keys are seen by fewer rows).
     // pair != 0: a workgroup takes slab x and then slab n_slabs - 1 - x, so every workgroup does the same amount
     // of work and the workgroups of one (sequence, KV head) stay in step on the same Q / dO tiles (L2 reuse).
     // pair == 0: one slab per workgroup; every second group of 8 slabs is taken in reverse so that the 8 XCDs,
     // which get workgroups round-robin, receive equal sums.
-    for (int pass = 0; pass < (pair ? 2 : 1); ++pass) {
+    for (int pass = 0; pass < (PAIR && pair ? 2 : 1); ++pass) {
     int slab = bx;
-    if (pair) {
+    if (PAIR && pair) {
         slab = pass ? n_slabs - 1 - bx : bx;
         if (pass && slab <= bx) break;
     } else {
@@ -535,6 +536,11 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     const int j0 = slab * KS;                         // first key of this pass inside the segment
     if (j0 >= slen) continue;
     const int jw = j0 + wk * 64;                      // first key of this wavefront (past the end: nothing to multiply)
+
+    // What depends on the lane is formed anew here, not kept in registers from one pass to the next (they were spilled, and every reload
+    // waited for the requests in flight)
+    const int lane = bw_lane();
+    const int n = lane & 31, hi = lane >> 5;
 
     // ---- this lane's two keys: K and V fragments (B operands).  A key past the end repeats the last one; its column
     // of the accumulators is never stored. --------------------------------------------------------------------------
@@ -551,6 +557,19 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
             vf[s][c] = bw_as_bf16x8(*reinterpret_cast<const u32x4*>(sv + ko + 16 * c + 8 * hi));
         }
     }
+    // lane parts of the LDS addresses: row reads (row n, piece 2 c + hi) and transposing reads (row 16 j + 8 q + 4 hi + s16 / 4,
+    // piece 4 dt + 2 blk + ...); the step-dependent part is an exclusive-or above bit 5 or 6
+    constexpr int RSH = D == 128 ? 6 : 5, RDIV = D == 128 ? 2 : 1;
+    const int row_base = n / RPI * BW_GP + n % RPI * P + hi * 16;
+    const int row_x = bw_swz<D>(n) >> 1 << 5 & (D == 128 ? 0xc0 : 0x60);
+    const int s16 = lane & 15, blk = (lane >> 4) & 1;
+    const int tr_base = (D == 128 ? hi * BW_GP + (s16 >> 2) * P : (4 * hi + (s16 >> 2)) * P) +
+                        (((2 * blk + ((s16 & 3) >> 1)) ^ (D == 128 ? 0 : 2 * hi)) << 4) + 8 * (s16 & 1);
+    const int tr_x = (D == 128 ? s16 >> 2 : s16 >> 3) << 6;
+    // statistics: lanes 0..31 fetch LSE, lanes 32..63 delta of the tile's rows
+    const float* const stp = (hi ? p.delta : p.lse) + stat_index(p, b, kvh * g, 0, s0);
+    const uint32_t voff = regular ? __umul24((lane / C8) >> gsh, qst2) + __umul24((lane / C8) & (g - 1), qsh2) + ((lane % C8) ^ bw_swz<D>(lane / C8)) * 16 : 0;
+    const float* const sptr = stp + (int64_t)(n & (g - 1)) * st_h + (n >> gsh);
     // ---- rows that can see some key of this workgroup: tiles [rt_begin, rt_end) -----------------------------
     int rt_begin = 0, rt_end = (R + 31) >> 5;
     if (BC) {
@@ -574,7 +593,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     // The second slab of a pair is walked upwards: its range begins where the first slab's walk ended (slab x ends
     // after n - x steps, slab n - 1 - x begins at tile n - 1 - x), so at any time all the workgroups of the group
     // that are in their second pass are on one tile again, whatever their x.
-    const bool up = pair && pass;
+    const bool up = PAIR && pair && pass;
     int rt = up ? rt_begin + wr : rt_end - 1 - wr;    // this wavefront's tile
     const int rt_step = up ? NWR : -NWR;
 
@@ -608,8 +627,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
             if (whole) {                                                                                 \
                 bw_load_lds16_pair<IMG>(qt, gt, voff, ((q_ * RPI) >> gsh) * qst2 + ((q_ * RPI) & (g - 1)) * qsh2, dst_); \
             } else {                                                                                     \
-            unsigned lo_ = lane;                                                                         \
-            asm volatile("" : "+v"(lo_));                                                                \
+            const unsigned lo_ = bw_lane();                                                              \
             const int c16 = ((int)(lo_ % C8) ^ bw_swz<D>(lo_ / C8)) * 16;                                \
             BW_ROW(q_ * RPI + (int)(lo_ / C8), i_, h_)                                                   \
             if (small) {                                                                                 \
@@ -626,8 +644,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
         } else if (whole) {                                                                              \
             bw_load_lds4(sptr + i0, lds0 + stat_base + ist * 256);                                       \
         } else {                                                                                         \
-            unsigned lo_ = lane;                                                                         \
-            asm volatile("" : "+v"(lo_));                                                                \
+            const unsigned lo_ = bw_lane();                                                              \
             BW_ROW((int)(lo_ & 31), i_, h_)                                                              \
             bw_load_lds4(stp + (int64_t)h_ * st_h + i_, lds0 + stat_base + ist * 256);              \
         }                                                                                                \
@@ -723,8 +740,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // one wavefront's LDS operations complete in order
             }
             if (rt * 32 < r_clear_lo || rt * 32 + 32 > r_clear_hi) {
-                int lo = lane;
-                asm volatile("" : "+v"(lo));          // formed here, on these few tiles, not kept in registers over the loop
+                const int lo = bw_lane();             // formed here, on these few tiles, not kept in registers over the loop
                 const int rbase = rt * 32 + 4 * (lo >> 5);
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
@@ -818,8 +834,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     __syncthreads();
 
-    int le = lane;
-    asm volatile("" : "+v"(le));                      // its offsets are formed here, not kept over the loop
+    const int le = bw_lane();                         // its offsets are formed here, not kept over the loop
     const int ne = le & 31, he = le >> 5;
     // ---- sum over the row groups, register for register --------------------------------------------------------------
     if (NWR > 1) {
@@ -1039,50 +1054,57 @@ __global__ __launch_bounds__(128, 1) void attn_bwd_dq64_kernel(BwdParams p, Grid
     }
 
     // ---- this lane's two query rows: Q and dO fragments (B operands), LSE and delta ---------------------------
+    // Everything is requested before anything is used: one round trip, which nothing else on the SIMD covers (before: a row tile at a
+    // time and its LSE behind it, four trips, 10.0 of a workgroup's 38 us on 64 k packed tokens; now 7.8, of which 3.1 are the address unit's
+    // for 98 requests that touch 32 rows each).  A row past the end repeats the last one: it gets no probability and is not stored.
     bf16x8 qf[2][D / 16], dof[2][D / 16];
     float nlse2[2], ndelta[2];            // -LSE in log2 units (-inf: no probability at all), -delta
     int qlim[2];
     int qlim_min = 0x7fffffff, qlim_max = 0;
+    u32x4 of[2][D / 16];
+    int64_t si[2];
+    float lse[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-        const int r = r0 + w * 64 + s * 32 + n;
-        const bool valid = r < R;
-        const int qi = valid ? r / p.g : 0;
-        const int h = kvh * p.g + (valid ? r - qi * p.g : 0);
+        const int r = min(r0 + w * 64 + s * 32 + n, R - 1);
+        const int qi = r / p.g;
+        const int h = kvh * p.g + r - qi * p.g;
         const uint16_t* qp = p.q + q_off + qi * p.q_st + (int64_t)h * p.q_sh;
         const uint16_t* dp = p.dout + do_off + qi * p.do_st + (int64_t)h * p.do_sh;
         const uint16_t* op = p.o + o_off + qi * p.o_st + (int64_t)h * p.o_sh;
-        float acc = 0.f;
+        si[s] = stat_index(p, b, h, qi, s0);
+        lse[s] = p.lse[si[s]];
 #pragma unroll
         for (int c = 0; c < D / 16; ++c) {
-            u32x4 a = {0, 0, 0, 0}, d = {0, 0, 0, 0}, o = {0, 0, 0, 0};
-            if (valid) {
-                a = *reinterpret_cast<const u32x4*>(qp + 16 * c + 8 * hi);
-                d = *reinterpret_cast<const u32x4*>(dp + 16 * c + 8 * hi);
-                o = *reinterpret_cast<const u32x4*>(op + 16 * c + 8 * hi);
-            }
-            qf[s][c] = bw_as_bf16x8(a);
-            dof[s][c] = bw_as_bf16x8(d);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc += bf16_bits_to_f32(o[e] & 0xffffu) * bf16_bits_to_f32(d[e] & 0xffffu);
-                acc += bf16_bits_to_f32(o[e] >> 16) * bf16_bits_to_f32(d[e] >> 16);
-            }
-        }
-        acc += shfl_xor(acc, 32);
-        ndelta[s] = -acc;
-        nlse2[s] = -INFINITY;
-        if (valid) {
-            const int64_t si = stat_index(p, b, h, qi, s0);
-            const float l = p.lse[si];
-            if (l > -INFINITY) nlse2[s] = l * -1.4426950408889634f;
-            if (hi == 0) p.delta[si] = -acc;
+            qf[s][c] = bw_as_bf16x8(*reinterpret_cast<const u32x4*>(qp + 16 * c + 8 * hi));
+            dof[s][c] = bw_as_bf16x8(*reinterpret_cast<const u32x4*>(dp + 16 * c + 8 * hi));
+            of[s][c] = *reinterpret_cast<const u32x4*>(op + 16 * c + 8 * hi);
         }
         qlim[s] = BC ? ((p.q_pos0 + qi) / p.bs + 1) * p.bs : 0;
         if (BC) {
             qlim_min = min(qlim_min, qlim[s]);
             qlim_max = max(qlim_max, qlim[s]);
         }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        float acc = 0.f;
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) {
+            union { bf16x8 b; u32x4 u; } d;
+            d.b = dof[s][c];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc += bf16_bits_to_f32(of[s][c][e] & 0xffffu) * bf16_bits_to_f32(d.u[e] & 0xffffu);
+                acc += bf16_bits_to_f32(of[s][c][e] >> 16) * bf16_bits_to_f32(d.u[e] >> 16);
+            }
+        }
+        acc += shfl_xor(acc, 32);
+        ndelta[s] = -acc;
+        const bool valid = r0 + w * 64 + s * 32 + n < R;
+        nlse2[s] = valid && lse[s] > -INFINITY ? lse[s] * -1.4426950408889634f : -INFINITY;
+        if (valid && hi == 0) p.delta[si[s]] = -acc;
     }
     if (BC) {
 #pragma unroll
@@ -1269,7 +1291,7 @@ static int launch_dkv(const BwdParams& p, int s, hipStream_t st) {
     const int n_slabs = (p.seg[s].len + 64 * NWK - 1) / (64 * NWK);
     // equal-work pairing where the mask makes slabs unequal (not for "own block only": every slab sees one block's rows) and
     // half as many workgroups still fill the chip
-    const int pair = (BC && p.seg[s].rule != DLM_SEG_SAME_BLOCK && n_slabs >= 4 && (int64_t)n_slabs * p.B * p.Hkv >= 1024) ? 1 : 0;
+    const int pair = (dkv_pairs<BC, NWK, NWR>() && p.seg[s].rule != DLM_SEG_SAME_BLOCK && n_slabs >= 4 && (int64_t)n_slabs * p.B * p.Hkv >= 1024) ? 1 : 0;
     dim3 grid(pair ? (n_slabs + 1) / 2 : n_slabs, p.Hkv, p.B);
     GridRemap rm = no_remap();
     if ((g_attn_remap & 4) && grid.x >= 2) {
