@@ -164,6 +164,7 @@ __global__ __launch_bounds__(1024) void commit_fused_kernel(CommitParams p, int3
                                                             int32_t* host_total, int32_t* host_max, CopyParams cp) {
     __shared__ uint8_t newmask[FUSED_MAX_POS];
     __shared__ int wave_tot[16], wave_max[16];
+    fetch_args<sizeof(CommitParams) + 4 * sizeof(void*) + sizeof(CopyParams)>();
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if (blockIdx.x > 0) {
         // DLM_WB_WHILE_ACTIVE: workgroups 1.. copy the block's K/V of one (sequence, KV head) each.  They read
@@ -190,20 +191,24 @@ __global__ __launch_bounds__(1024) void commit_fused_kernel(CommitParams p, int3
         const int64_t base = (int64_t)b * p.n_pos;
         uint8_t* mrow = p.mask + b * p.mask_stride_b;
         float cf[CH];
+        int tk[CH];
         bool masked[CH], chosen[CH];
         int cnt = 0;
+        // mask, confidence and token of every position in one trip (confidences only of masked positions, then tokens only of
+        // chosen ones, were three, one after another: with the arguments in one trip 4.26 -> 3.87 us for 1 x 32 positions)
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const int i = lane + 64 * c;
-            masked[c] = (i < p.group_len) && (mrow[i] != 0);
+            const int i = min(lane + 64 * c, p.group_len - 1);
+            masked[c] = mrow[i] != 0;
+            cf[c] = p.conf[base + i];
+            tk[c] = p.tok[base + i];
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            masked[c] = masked[c] && lane + 64 * c < p.group_len;
             chosen[c] = false;
-            float v = -INFINITY;
-            if (masked[c]) {
-                v = p.conf[base + i];
-                if (!(v == v)) v = -INFINITY;
-                ++cnt;
-            }
-            cf[c] = v;
+            if (!masked[c] || !(cf[c] == cf[c])) cf[c] = -INFINITY;
+            cnt += masked[c] ? 1 : 0;
         }
         cnt = wave_sum(cnt);
         int ncom = 0;
@@ -241,7 +246,7 @@ __global__ __launch_bounds__(1024) void commit_fused_kernel(CommitParams p, int3
             const int i = lane + 64 * c;
             if (i < p.group_len) {
                 if (chosen[c]) {
-                    p.x[b * p.x_stride_b + p.x_pos0 + i] = p.tok[base + i];
+                    p.x[b * p.x_stride_b + p.x_pos0 + i] = tk[c];
                     mrow[i] = 0;
                     if (p.commit_step) p.commit_step[base + i] = (int16_t)p.step;
                     ++ncom;

@@ -453,12 +453,21 @@ __device__ __forceinline__ void lm_staged_tile(const LmParams& p, unsigned char*
     const int v0 = v_first + vt * TV;
     vt += vt0;
     const int m0 = mc * MB;
+    if (m0 >= p.M) return;
+    const int lrow = tid / TPR, lc = tid % TPR;
+    // the list's rows (M of them by the caller's bound) travel with the device's count, not behind it
+    int hrow[HLD];
+#pragma unroll
+    for (int q = 0; q < HLD; ++q) hrow[q] = min(m0 + lrow + q * RPP, p.M - 1);
+    if (p.row_idx) {
+#pragma unroll
+        for (int q = 0; q < HLD; ++q) hrow[q] = p.row_idx[hrow[q]];
+    }
     int M = p.M;
     if (!lm_rows(p, M)) return;
     if (m0 >= M) return;
 
     // ---- global -> register staging addresses --------------------------------
-    const int lrow = tid / TPR, lc = tid % TPR;
 #define W_ON(q) ((TV % RPP == 0) || (lrow + (q) * RPP < TV))   // a ragged last pass leaves some threads idle
 #define H_ON(q) ((MB % RPP == 0) || (lrow + (q) * RPP < MB))
     const uint16_t* wsrc[WLD];
@@ -467,16 +476,9 @@ __device__ __forceinline__ void lm_staged_tile(const LmParams& p, unsigned char*
         const int v = min(v0 + lrow + q * RPP, p.V - 1);       // rows past V are clamped, masked in the epilogue
         wsrc[q] = p.w + (int64_t)v * p.w_stride + lc * 8;
     }
-    const uint16_t* hsrc[HLD];
-    int hrow[HLD];
+    const uint16_t* hsrc[HLD];   // of rows past M the first of all is read (what the list holds there counts for nothing), never stored
 #pragma unroll
-    for (int q = 0; q < HLD; ++q) hrow[q] = min(m0 + lrow + q * RPP, M - 1);   // rows past M are clamped, never stored
-    if (p.row_idx) {                                                           // (one trip to memory for all of them)
-#pragma unroll
-        for (int q = 0; q < HLD; ++q) hrow[q] = p.row_idx[hrow[q]];
-    }
-#pragma unroll
-    for (int q = 0; q < HLD; ++q) hsrc[q] = p.hidden + hrow[q] * p.h_stride + lc * 8;
+    for (int q = 0; q < HLD; ++q) hsrc[q] = p.hidden + (m0 + lrow + q * RPP < M ? hrow[q] : 0) * p.h_stride + lc * 8;
     u32x4 wreg[PD][WLD], hreg[PD][HLD];
 
     f32x16 acc[TVW][THW];
@@ -641,6 +643,7 @@ __device__ __forceinline__ void lm_staged_tile(const LmParams& p, unsigned char*
 
 template <int WV, int WH, int TVW, int THW, int PD, int KCH = 64, int OCC = 1, bool PIPE = false, bool NTW = false>
 __global__ __launch_bounds__(64 * WV * WH, OCC) void lmhead_kernel(LmParams p) {
+    fetch_args<sizeof(LmParams)>();
     __shared__ __attribute__((aligned(16))) unsigned char smem[lm_staged_lds<WV, WH, TVW, THW, KCH>()];
     lm_staged_tile<WV, WH, TVW, THW, PD, KCH, PIPE, NTW>(p, smem, blockIdx.x, p.n_vt_l, 0, 0);
 }
@@ -650,6 +653,7 @@ __global__ __launch_bounds__(64 * WV * WH, OCC) void lmhead_kernel(LmParams p) {
 template <int WV, int WH, int TVW, int THW, int PD, bool NTW>
 __global__ __launch_bounds__(64 * WV * WH, 1) void lmhead_tail_kernel(LmParams p) {
     static_assert(TVW % 2 == 0, "half the height is a whole number of accumulator tiles");
+    fetch_args<sizeof(LmParams)>();
     __shared__ __attribute__((aligned(16))) unsigned char smem[lm_staged_lds<WV, WH, TVW, THW, 64>()];
     const int bid = blockIdx.x;
     if (bid < p.n_vt_l) lm_staged_tile<WV, WH, TVW, THW, PD, 64, true, NTW>(p, smem, bid, p.n_vt_l, 0, 0);
