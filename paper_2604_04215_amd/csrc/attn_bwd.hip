@@ -408,16 +408,23 @@ __device__ __forceinline__ void bw_mfma_zero(f32x16& c, bf16x8 a, bf16x8 b) {
     asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
 }
 
-// Is a workgroup ever given two slabs (`pair`)?  Never with one wavefront (one slab in all) or with 2 x 2 of them (too few slabs for it):
-// without the second pass nothing has to be kept over the first.
+// Is a workgroup ever given two slabs (`pair`)?  Only with two wavefronts side by side: one has one slab in all, and where wavefronts share a slab's rows
+// there are hardly slabs enough for it.  Without the second pass nothing has to be kept over the first (8 x 2048 tokens, blocks of 32, 4 heads of 64, forward
+// and backward: 521 -> 494 us).
 template <bool BC, int NWK, int NWR>
-constexpr bool dkv_pairs() { return BC && NWK * NWR != 1 && !(NWK == 2 && NWR == 2); }
+constexpr bool dkv_pairs() { return BC && NWK == 2 && NWR == 1; }
 
 // the lane number, formed where it stands (asm: what follows from it is not moved away or kept in registers in its place)
 __device__ __forceinline__ int bw_lane() {
     int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
     asm volatile("" : "+v"(l));
     return l;
+}
+
+// Strides of Q and dO of less than 2^24 bytes, all of a group's heads within 2^30: requests can take 32-bit offsets
+__host__ __device__ __forceinline__ bool small_strides(const BwdParams& p) {
+    return p.q_st >= 0 && p.q_sh >= 0 && p.do_st >= 0 && p.do_sh >= 0 && p.q_st < (1 << 23) && p.q_sh < (1 << 23) &&
+           p.do_st < (1 << 23) && p.do_sh < (1 << 23) && p.g * p.q_sh < (1 << 29) && p.g * p.do_sh < (1 << 29);
 }
 
 // dK and dV of one segment in one pass.  A wavefront owns 64 keys (two MFMA column tiles, K and V fragments and both
@@ -433,18 +440,19 @@ __device__ __forceinline__ int bw_lane() {
 //   * tiles go from memory to LDS without registers (global_load_lds) through a ring of four, two tiles ahead, and the
 //     next tile's first fragments are read before this tile's last MFMAs: the barrier sits between;
 //   * one wavefront issues one instruction at a time: 3.9 vector and 2.3 scalar instructions per MFMA, after 7.5 and 1.7 with
-//     LDS addresses, row divisions and statistics formed per read (2.6 -> 1.9 ms below).  At d = 128 the compiler still spills 40 - 70
-//     scalars to lanes of vector registers, some 20 of which the loop reads back a tile, most for request paths the launch does not take;
+//     LDS addresses, row divisions and statistics formed per read (2.6 -> 1.9 ms below).  The compiler still spills 30 - 70 scalars
+//     to lanes of vector registers, the more the more request paths a kernel has (ALIKE), some of which come back every tile;
 //   * nothing covers what a workgroup does before its first product, so K, V and the first tiles travel together: no vector register is
 //     spilled in the shapes that large launches take (with 18 or 50 of them kept on the stack from the start of the kernel on, every reload
 //     waited for all requests before it: five trips to memory one after another, 1.72 -> 1.63 ms on the packed batch below).
 // Measured (8 x 4096 tokens, 32 / 8 heads of 128, blocks of 4): 1.86 - 1.95 ms = 1.17 PFLOP/s of products, two passes with 32
 // keys a wavefront 4.28 ms; 128 packed sequences of 64 k tokens, 32 heads: 1.63 ms, two passes 2.86.  MFMA pipes busy 0.52 at
 // 2.2 GHz: with all loads, waits and vector work taken out the loop still runs at 1.35 PFLOP/s, the power limit on such data.
-template <int D, bool BC, int NWK, int NWR>
+template <int D, bool BC, int NWK, int NWR, bool ALIKE>
 __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdParams p, int sidx, int n_slabs, int pair, GridRemap rm) {
     constexpr bool PAIR = dkv_pairs<BC, NWK, NWR>();   // a workgroup may take two slabs
     constexpr int NS = D == 128 && NWK * NWR == 1 ? 2 : 4;   // ring stages: four such rings fit a CU, one a SIMD
+    constexpr bool BY_HEAD = ALIKE;
     constexpr int FD = D == 128 ? 2 : 4;               // fragments read ahead (at d = 128 all that registers allow)
     constexpr int AHEAD = NWK == 1 ? NS - 1 : 2;       // tiles requested ahead: a ring that is the wavefront's own needs no slack
     constexpr int P = D * 2, C8 = D / 8;
@@ -484,12 +492,11 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     const int64_t sst = (sidx == 0) ? p.seg[0].st : ((sidx == 1) ? p.seg[1].st : p.seg[2].st);
     const int srule = (sidx == 0) ? p.seg[0].rule : ((sidx == 1) ? p.seg[1].rule : p.seg[2].rule);
 
-    int R = p.R, s0 = 0, Lq = p.Lq;
+    int s0 = 0, Lq = p.Lq;
     int64_t q_off = b * p.q_sb, do_off = b * p.do_sb, kv_off = b * ssb;
     if (p.cu) {
         s0 = min(max(p.cu[b], 0), p.total);
         const int sl = max(min(min(p.cu[b + 1], p.total) - s0, p.Lq), 0);
-        R = p.g * sl;
         Lq = sl;
         slen = min(slen, sl);
         q_off = s0 * p.q_st;
@@ -498,24 +505,32 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     }
     const int hoff = (BC && srule == DLM_SEG_EARLIER_BLOCKS) ? p.bs : 0;
     const bool same = BC && srule == DLM_SEG_SAME_BLOCK;
-    const int g = p.g;
+    // requests with 32-bit offsets from a wave-uniform query
+    const bool small = ALIKE || small_strides(p);
+    const bool alike = ALIKE || (small && p.q_st == p.do_st && p.q_sh == p.do_sh);
+    const int64_t do_st = ALIKE ? p.q_st : p.do_st, do_sh = ALIKE ? p.q_sh : p.do_sh;
+    // Rows in order of (query, head), or (by_head) the queries of one head after another, each head cut into tiles of its own: where the heads do not
+    // divide a tile, the place of a row in it changes from tile to tile, and forming it costs some 30 vector instructions a request (see
+    // `regular`).  With the heads apart a tile is 32 queries of one head whatever their number.  Where that makes at most an eighth more
+    // tiles (a head's last tile is partly empty).  Forward and backward, us, before / with it and ALIKE: 64 packed sequences of 48 - 900 tokens, 14/2
+    // heads of 64 504 / 471, 4 x 777 tokens, block diffusion 301 / 262; 28/4 heads of 128, 1425 / 1325.
+    const bool by_head = BY_HEAD && (32 % p.g) != 0 && 8 * p.g * ((Lq + 31) >> 5) <= 9 * ((p.g * Lq + 31) >> 5);
+    const int g = by_head ? 1 : p.g;                   // heads that the rows of a tile run over
+    const int R = g * Lq;
     // Row r of the group is query r / g, head r % g.  Inside a tile that starts at (query i0, head h0) row l is on query i0 + 1 + u / g
     // rounded down, u = h0 + l - g: on i0 where u < 0, and otherwise u < 31, where u * ceil(2^16 / g) / 2^16 rounds down to the same (the
     // excess is below 31 / 2^16, u / g at least 1 / 31 short of the next whole number, or g > 31 and both are 0).
     const int mul_g = (65536 + g - 1) / g;
-    const uint16_t* const qb = p.q + q_off + (int64_t)(kvh * g) * p.q_sh;
-    const uint16_t* const gb = p.dout + do_off + (int64_t)(kvh * g) * p.do_sh;
+    const uint16_t* const qb = p.q + q_off + (int64_t)(kvh * p.g) * p.q_sh;
+    const uint16_t* const gb = p.dout + do_off + (int64_t)(kvh * p.g) * p.do_sh;
     const int st_h = p.cu ? p.total : p.Lq;            // statistics of the next head
     const int stat_base = BODY + w * NS * 256;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-    // requests with 32-bit offsets from a wave-uniform query: strides of less than 2^24 bytes, all of a group's heads within 2^30
-    const bool small = p.q_st >= 0 && p.q_sh >= 0 && p.do_st >= 0 && p.do_sh >= 0 && p.q_st < (1 << 23) && p.q_sh < (1 << 23) &&
-                       p.do_st < (1 << 23) && p.do_sh < (1 << 23) && g * p.q_sh < (1 << 29) && g * p.do_sh < (1 << 29);
-    // The usual case: 1, 2, 4 .. 32 heads a group and Q and dO laid out alike.  A tile then holds whole queries, so row l of any
+    // The usual case: 1, 2, 4 .. 32 heads a tile and Q and dO laid out alike.  A tile then holds whole queries, so row l of any
     // tile is at the same place relative to its first row: one lane offset, and a wave-uniform step from request to request.
     // (Per row this is 1 vector instruction for both operands instead of some 20.)
-    const bool regular = small && (32 % g) == 0 && p.q_st == p.do_st && p.q_sh == p.do_sh;
+    const bool regular = alike && (32 % g) == 0;
     const int gsh = 31 - __builtin_clz(g);
     const int qst2 = (int)p.q_st * 2, qsh2 = (int)p.q_sh * 2;
 
@@ -524,6 +539,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     // of work and the workgroups of one (sequence, KV head) stay in step on the same Q / dO tiles (L2 reuse).
     // pair == 0: one slab per workgroup; every second group of 8 slabs is taken in reverse so that the 8 XCDs,
     // which get workgroups round-robin, receive equal sums.
+#pragma clang loop unroll(disable)
     for (int pass = 0; pass < (PAIR && pair ? 2 : 1); ++pass) {
     int slab = bx;
     if (PAIR && pair) {
@@ -567,7 +583,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
                         (((2 * blk + ((s16 & 3) >> 1)) ^ (D == 128 ? 0 : 2 * hi)) << 4) + 8 * (s16 & 1);
     const int tr_x = (D == 128 ? s16 >> 2 : s16 >> 3) << 6;
     // statistics: lanes 0..31 fetch LSE, lanes 32..63 delta of the tile's rows
-    const float* const stp = (hi ? p.delta : p.lse) + stat_index(p, b, kvh * g, 0, s0);
+    const float* const stp = (hi ? p.delta : p.lse) + stat_index(p, b, kvh * p.g, 0, s0);
     const uint32_t voff = regular ? __umul24((lane / C8) >> gsh, qst2) + __umul24((lane / C8) & (g - 1), qsh2) + ((lane % C8) ^ bw_swz<D>(lane / C8)) * 16 : 0;
     const float* const sptr = stp + (int64_t)(n & (g - 1)) * st_h + (n >> gsh);
     // ---- rows that can see some key of this workgroup: tiles [rt_begin, rt_end) -----------------------------
@@ -586,7 +602,8 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
         r_first = min(max((kw_first + hoff) / p.bs * p.bs - p.q_pos0, 0), Lq) * g;
     }
     const int n_rt = rt_end - rt_begin;
-    const int n_it = (n_rt + NWR - 1) / NWR;
+    const int n_tiles = by_head ? n_rt * p.g : n_rt;
+    const int n_it = (n_tiles + NWR - 1) / NWR;
 
     // Row tiles are walked from the last one down: under a block-causal mask the workgroups of one (sequence,
     // KV head) differ in where their range BEGINS, so this way they all start on the same tile and stay in step.
@@ -594,7 +611,8 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     // after n - x steps, slab n - 1 - x begins at tile n - 1 - x), so at any time all the workgroups of the group
     // that are in their second pass are on one tile again, whatever their x.
     const bool up = PAIR && pair && pass;
-    int rt = up ? rt_begin + wr : rt_end - 1 - wr;    // this wavefront's tile
+    int rt = up ? rt_begin + wr : rt_end - 1 - wr;    // this wavefront's tile (by_head: of one head, over and over)
+#define BW_WRAP() if (BY_HEAD && by_head && n_rt > 0) { while (rt < rt_begin) rt += n_rt; while (rt >= rt_end) rt -= n_rt; }
     const int rt_step = up ? NWR : -NWR;
 
     // next tile to request: first row = query i0, head h0 (kept without divisions); queries are clamped to the sequence,
@@ -611,6 +629,23 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     const int qpt = regular ? 32 >> gsh : 0;
     const uint16_t *qt = qb + (regular ? i0 * p.q_st : 0), *gt = gb + (regular ? i0 * p.q_st : 0);
     const int64_t dqt = regular ? (up ? di : -di) * p.q_st : 0;
+    // by_head: head that the request cursor is on (requests past the end stay on the last one), its part of the statistics' address; after a head's last
+    // tile the cursor goes back to the first tile's place, a head further
+    int hd = 0;
+    int64_t hstat = 0;
+#define BW_NEXT_HEAD()                                                                                   \
+    if (BY_HEAD && by_head && n_rt > 0) {                                                                \
+        while (i0 < rt_begin * 32 || i0 >= rt_end * 32) {                                                \
+            const int back_ = i0 < rt_begin * 32 ? n_rt * 32 : -n_rt * 32;                               \
+            const int64_t dh_ = hd + 1 < p.g ? p.q_sh : 0;                                               \
+            i0 += back_;                                                                                 \
+            qt += back_ * p.q_st + dh_;                                                                  \
+            gt += back_ * p.q_st + dh_;                                                                  \
+            if (hd + 1 < p.g) { ++hd; hstat += st_h; }                                                   \
+        }                                                                                                \
+    }
+    BW_NEXT_HEAD()
+    BW_WRAP()
     bool whole = regular && i0 >= 0 && i0 + qpt <= Lq;
 #define BW_ROW(l, i_, h_)                                                                                \
     const int u_ = h0 - g + (l);                                                                         \
@@ -624,7 +659,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
         if ((x) < IPW) {                                                                                 \
             const int q_ = wk * IPW + (x);                                                               \
             const uint32_t dst_ = lds0 + (wr * NS + ist) * STAGE + q_ * BW_GP;                           \
-            if (whole) {                                                                                 \
+            if (whole) {                                                                               \
                 bw_load_lds16_pair<IMG>(qt, gt, voff, ((q_ * RPI) >> gsh) * qst2 + ((q_ * RPI) & (g - 1)) * qsh2, dst_); \
             } else {                                                                                     \
             const unsigned lo_ = bw_lane();                                                              \
@@ -633,20 +668,20 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
             if (small) {                                                                                 \
                 const int ic_ = min(max(i0, 0), Lq - 1);                                                 \
                 const uint32_t oq_ = __umul24(i_ - ic_, (int)p.q_st * 2) + __umul24(h_, (int)p.q_sh * 2) + c16;   \
-                const uint32_t og_ = __umul24(i_ - ic_, (int)p.do_st * 2) + __umul24(h_, (int)p.do_sh * 2) + c16; \
-                bw_load_lds16(qb + ic_ * p.q_st, oq_, dst_);                                             \
-                bw_load_lds16(gb + ic_ * p.do_st, og_, dst_ + IMG);                                      \
+                const uint32_t og_ = ALIKE ? oq_ : __umul24(i_ - ic_, (int)do_st * 2) + __umul24(h_, (int)do_sh * 2) + c16; \
+                bw_load_lds16(qb + ic_ * p.q_st + hd * p.q_sh, oq_, dst_);                               \
+                bw_load_lds16(gb + ic_ * do_st + hd * do_sh, og_, dst_ + IMG);                       \
             } else {                                                                                     \
                 bw_load_lds16(qb + bw_offset(i_, p.q_st) + bw_offset(h_, p.q_sh) + c16 / 2, dst_);       \
-                bw_load_lds16(gb + bw_offset(i_, p.do_st) + bw_offset(h_, p.do_sh) + c16 / 2, dst_ + IMG); \
+                bw_load_lds16(gb + bw_offset(i_, do_st) + bw_offset(h_, do_sh) + c16 / 2, dst_ + IMG); \
             }                                                                                            \
             }                                                                                            \
-        } else if (whole) {                                                                              \
-            bw_load_lds4(sptr + i0, lds0 + stat_base + ist * 256);                                       \
+        } else if (whole) {                                                                            \
+            bw_load_lds4(sptr + i0 + hstat, lds0 + stat_base + ist * 256);                               \
         } else {                                                                                         \
             const unsigned lo_ = bw_lane();                                                              \
             BW_ROW((int)(lo_ & 31), i_, h_)                                                              \
-            bw_load_lds4(stp + (int64_t)h_ * st_h + i_, lds0 + stat_base + ist * 256);              \
+            bw_load_lds4(stp + hstat + (int64_t)h_ * st_h + i_, lds0 + stat_base + ist * 256);           \
         }                                                                                                \
     }
 #define BW_ADVANCE()                                                                                     \
@@ -656,6 +691,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
         else { i0 -= di; h0 -= dh; if (h0 < 0) { h0 += g; --i0; } }                                      \
         qt += dqt;                                                                                       \
         gt += dqt;                                                                                       \
+        BW_NEXT_HEAD()                                                                                   \
         whole = regular && i0 >= 0 && i0 + qpt <= Lq;                                                    \
     }
     // fragment of step s (0 .. 4 * PH - 1): Q rows, dO rows, dO^T, Q^T; the transposed ones in the order keys 0..15, 16..31
@@ -676,14 +712,6 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
         }                                                                                                \
     }
 
-    f32x16 av[2][D / 32], ak[2][D / 32];   // dV^T, dK^T: lane = key, registers = 16 of the 32 head-dim entries of tile dt
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) av[s][dt][i] = ak[s][dt][i] = 0.f;
-
     Frag fr[FD];
     int st = 0;                                       // ring stage of this iteration's tile
     if (n_it > 0) {
@@ -694,6 +722,13 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
             BW_ADVANCE();
         }
     }
+    f32x16 av[2][D / 32], ak[2][D / 32];   // dV^T, dK^T: lane = key, registers = 16 of the 32 head-dim entries of tile dt
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) av[s][dt][i] = ak[s][dt][i] = 0.f;
     // K, V and the first tiles: a full wait, after which the compiler counts no load of its own inside the loop
     __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
     if (n_it > 0) {
@@ -710,7 +745,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
         const int sb = (wr * NS + st) * STAGE;
         const int stn = st + 1 == NS ? 0 : st + 1;
         const int sbn = (wr * NS + stn) * STAGE;
-        const bool work = jw < slen && it * NWR + wr < n_rt && rt * 32 + 32 > r_first;
+        const bool work = jw < slen && it * NWR + wr < n_tiles && rt * 32 + 32 > r_first;
         int ra[4], ta[D / 32];                        // LDS addresses of the row and the transposing reads
         if (work) {
             BW_ROW_ADDR(ra, sb)
@@ -823,7 +858,10 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
         BW_ADVANCE();
         st = stn;
         rt += rt_step;
+        BW_WRAP()
     }
+#undef BW_WRAP
+#undef BW_NEXT_HEAD
 #undef BW_READ
 #undef BW_ROW_ADDR
 #undef BW_TR_ADDR
@@ -1288,6 +1326,10 @@ __global__ __launch_bounds__(128, 1) void attn_bwd_dq64_kernel(BwdParams p, Grid
 
 template <int D, bool BC, int NWK, int NWR>
 static int launch_dkv(const BwdParams& p, int s, hipStream_t st) {
+    // Q and dO laid out alike, the usual case: a kernel without the other request paths (scalars kept in lanes of vector registers 46 -> 31 at d =
+    // 128, 57 -> 31 - 42 at d = 64; forward and backward, 4 x 777 tokens, block diffusion, 4 heads of 64: 165 -> 148 us).  Not with d = 128 under a
+    // block-causal mask, where the compiler then spills 48 vector registers.
+    const bool alike = !(D == 128 && BC) && small_strides(p) && p.q_st == p.do_st && p.q_sh == p.do_sh;
     const int n_slabs = (p.seg[s].len + 64 * NWK - 1) / (64 * NWK);
     // equal-work pairing where the mask makes slabs unequal (not for "own block only": every slab sees one block's rows) and
     // half as many workgroups still fill the chip
@@ -1299,7 +1341,8 @@ static int launch_dkv(const BwdParams& p, int s, hipStream_t st) {
         if (n_wg > 0) grid = dim3((unsigned)n_wg);
         else rm = no_remap();
     }
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, BC, NWK, NWR>), grid, dim3(64 * NWK * NWR), 0, st, p, s, n_slabs, pair, rm);
+    if (alike) hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, BC, NWK, NWR, !(D == 128 && BC)>), grid, dim3(64 * NWK * NWR), 0, st, p, s, n_slabs, pair, rm);
+    else hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, BC, NWK, NWR, false>), grid, dim3(64 * NWK * NWR), 0, st, p, s, n_slabs, pair, rm);
     return check_hip(hipGetLastError(), "attn_bwd_dkv_kernel launch");
 }
 

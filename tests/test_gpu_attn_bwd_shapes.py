@@ -173,6 +173,18 @@ def test_rows_that_see_no_key(size, d):
     check_copies(q, segs, d_out, batches(388, 4, 1)[size], mode="block_causal", bs=4)
 
 
+@pytest.mark.parametrize("size", [0, 1], ids=["row-split", "key-split"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L,Hq,Hkv,lens,bs", [(64, 5, 1, None, 0), (96, 3, 1, None, 4), (255, 14, 2, None, 32), (257, 7, 1, None, 0), (320, 6, 2, None, 7),
+                                              (96, 7, 1, (70, 96, 40), 0), (256, 7, 1, (256, 256, 0), 4)])
+def test_heads_apart(size, d, L, Hq, Hkv, lens, bs):
+    """Heads that do not divide a 32-row tile and rows that fill theirs: dK / dV takes the heads one after another (257 rows: too many tiles for it), with as
+    few as one tile a head for four wavefronts (late keys of a causal mask) and an own-block segment's range in the middle."""
+    rules = ("earlier", "same", "causal") if lens and bs else None
+    q, segs, d_out = make(1, L, Hq, Hkv, d, lens or (0, L, 0), seed=3800 + L, **(dict(pos=(0, 0, 0), rules=rules) if rules else {}))
+    check_copies(q, segs, d_out, batches(L, Hq, Hkv)[size], **(dict(mode="block_causal", bs=bs) if bs else {}))
+
+
 class Backwards:
     """The tokens of x [B, L, H, d] as the binding sees a tensor, last one first in memory: a negative token stride."""
     def __init__(self, x):
