@@ -86,7 +86,7 @@ __global__ __launch_bounds__(64 * NWR * NWK, OCC) void attn_kernel(AttnParams p)
     constexpr int SMEM = (NBUF * NWK * TILE_BYTES > MERGE_BYTES) ? NBUF * NWK * TILE_BYTES : MERGE_BYTES;
     __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
 
-    fetch_args<sizeof(AttnParams)>();
+    if constexpr (OCC < 3) fetch_args<sizeof(AttnParams)>();   // (three workgroups a CU: launches of many, whose arguments are there after the first; 28/4 heads, 64 sequences 319 / 315)
     const int tid = threadIdx.x, lane = tid & 63;
     // wave-uniform by construction: kept in scalar registers so that the per-tile bookkeeping derived from the key
     // group index stays scalar too

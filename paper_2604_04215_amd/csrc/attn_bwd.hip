@@ -166,33 +166,25 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(BwdParams p, GridRe
               sp2 = __builtin_amdgcn_readfirstlane(p.seg[2].pos0);
 
     // ---- this lane's query row: Q and dO fragments (B operands), LSE and delta ----------------------------
-    const int r = r0 + w * 32 + n;
-    const bool valid = r < R;
-    const int qi = valid ? r / p.g : 0;
-    const int hg = valid ? r - qi * p.g : 0;
+    // All requested at once and unconditionally (a row past the end repeats the last one, gets no probability and is not stored): behind branches each
+    // piece, and then LSE and delta, was a trip of its own.  Forward and backward, us: 4 x 777 tokens, block diffusion, 14/2 heads of 64 262 / 254.
+    const bool valid = r0 + w * 32 + n < R;
+    const int r = min(r0 + w * 32 + n, R - 1);
+    const int qi = r / p.g;
+    const int hg = r - qi * p.g;
     const int h = kvh * p.g + hg;
     bf16x8 qf[D / 16], dof[D / 16];
-    {
-        const uint16_t* qp = p.q + q_off + qi * p.q_st + (int64_t)h * p.q_sh;
-        const uint16_t* dp = p.dout + do_off + qi * p.do_st + (int64_t)h * p.do_sh;
+    const uint16_t* qp = p.q + q_off + qi * p.q_st + (int64_t)h * p.q_sh;
+    const uint16_t* dp = p.dout + do_off + qi * p.do_st + (int64_t)h * p.do_sh;
 #pragma unroll
-        for (int c = 0; c < D / 16; ++c) {
-            u32x4 a = {0, 0, 0, 0}, d = {0, 0, 0, 0};
-            if (valid) {
-                a = *reinterpret_cast<const u32x4*>(qp + 16 * c + 8 * hi);
-                d = *reinterpret_cast<const u32x4*>(dp + 16 * c + 8 * hi);
-            }
-            qf[c] = bw_as_bf16x8(a);
-            dof[c] = bw_as_bf16x8(d);
-        }
+    for (int c = 0; c < D / 16; ++c) {
+        qf[c] = bw_as_bf16x8(*reinterpret_cast<const u32x4*>(qp + 16 * c + 8 * hi));
+        dof[c] = bw_as_bf16x8(*reinterpret_cast<const u32x4*>(dp + 16 * c + 8 * hi));
     }
-    float lse2 = INFINITY, delta = 0.f;   // +inf: every probability of an absent row (or one that saw no key) is 0
-    if (valid) {
-        const int64_t si = stat_index(p, b, h, qi, s0);
-        const float l = p.lse[si];
-        if (l > -INFINITY) lse2 = l * 1.4426950408889634f;
-        delta = -p.delta[si];
-    }
+    const int64_t si = stat_index(p, b, h, qi, s0);
+    const float row_lse = p.lse[si], delta = -p.delta[si];
+    // +inf: every probability of an absent row (or one that saw no key) is 0
+    const float lse2 = valid && row_lse > -INFINITY ? row_lse * 1.4426950408889634f : INFINITY;
     const int qlim = BC ? ((p.q_pos0 + qi) / p.bs + 1) * p.bs : 0;
     int qlim_min = 0x7fffffff, qlim_max = 0;
     if (BC) {
