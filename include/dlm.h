@@ -217,9 +217,10 @@ size_t dlm_block_attn_bwd_workspace_bytes(const dlm_attn_bwd_args *args);
  *           host round trip); outputs beyond that count are left untouched
  *   M_expected  0, or the row count the caller expects *m_dev to hold (a guess, not a bound; needs m_dev).
  *           The kernel shape is chosen on the host from M, which a caller that polls the device late only
- *           knows as an upper bound.  When M_expected falls in a smaller shape's range, the call queues that
- *           shape guarded by "*m_dev fits it" and the shape for M guarded by the opposite, so a right
- *           guess runs the better shape, and either way one of the two launches is empty.  Results depend on it
+ *           knows as an upper bound.  When M_expected falls in a smaller shape's range and that shape saves more than
+ *           its launch costs, the call queues it guarded by "*m_dev fits it" and the shape for M guarded by the
+ *           opposite, so a right guess runs the better shape, and either way one of the two launches is empty.  (It
+ *           always does unless the vocabulary is so small that M rows give few workgroups.)  Results depend on it
  *           only through the summation order of the shape that ran (rounding).
  *   w       bf16 [V, Dh], row stride w_stride_row
  *   out_scatter  0: outputs are indexed by r; 1: by row(r) (dense per-position arrays)

@@ -1534,6 +1534,22 @@ static int plan_lmhead(int M, int V, int Dh, int cus) {
     return usual;
 }
 
+// Is a shape queued for the expected rows worth the launch that then ends at once, 2.2 - 2.5 us?  Where the bound's own shape has many tiles, yes.
+// Where it has few: if a CU brings in at least 256 KB less (at some 100 GB/s); tiles that do not all fit at once count half as much again, as W
+// is then what all wait for; and not only for a narrower tile of as many workgroups, as rows past the count, all one and the same, cost
+// little, and W of one row chunk is fetched past the caches.  Us, without / with, Dh = 4096: bound 1024, 81 expected, V = 10000 82 / 33; 512, 128, 16000
+// 59 / 35; 256, 128, 40000 87 / 77; not taken: 128, 32, 40000 61 / 71; 256, 20, 16000 30 / 35; Dh = 256: 128, 32, 16000 9.1 / 11.3.  Over 298 calls
+// with few tiles (V 2048 .. 40000, Dh 256 .. 4096, bound 40 .. 1024) within 0.3 % of the faster side in the geometric mean.
+static int64_t lm_load(int v, int M, int V, int cus) {
+    const int64_t rounds = (lm_tiles(v, M, V) + cus - 1) / cus, rows = g_lm_variants[v].tv + g_lm_variants[v].mb;
+    return rounds <= 1 ? rows : 3 * rounds * rows / 2;
+}
+static bool lm_guess_pays(int v_try, int v_safe, int expected, int M, int V, int Dh, int cus) {
+    if (!lm_few(M, V, Dh, cus)) return true;
+    return (lm_load(v_safe, expected, V, cus) - lm_load(v_try, expected, V, cus)) * Dh >= 131072 &&
+           (lm_tiles(v_try, expected, V) > lm_tiles(v_safe, expected, V) || M <= g_lm_variants[v_safe].mb);
+}
+
 static int validate_lm(const dlm_lmhead_args* a) {
     if (!a) return fail(DLM_ERR_INVALID_ARG, "lmhead: null args");
     if (a->struct_size != sizeof(dlm_lmhead_args))
@@ -1676,12 +1692,12 @@ static int lmhead_enqueue(const dlm_lmhead_args* a, void* workspace, void* strea
     // The caller's bound M sizes the launch, the device's count says how many rows there are.  When the caller
     // expects the count to fall in a smaller shape's range, that shape is queued first, guarded by "count <= its
     // capacity", and the bound's shape after it, guarded by the opposite: one of the two returns at once.
-    // (Not where the bound gives few tiles: then it is cut into small row chunks, and those past the count return at once.)
     const int v_safe = plan_lmhead(a->M, a->V, a->Dh, cus);
     int v_try = v_safe, cap = 0;
-    if (a->m_dev && a->M_expected > 0 && a->M_expected < a->M && g_lm_variant < 0 && !lm_few(a->M, a->V, a->Dh, cus)) {
+    if (a->m_dev && a->M_expected > 0 && a->M_expected < a->M && g_lm_variant < 0) {
         cap = plan_capacity(a->M_expected);
         if (cap < a->M) v_try = plan_lmhead(cap, a->V, a->Dh, cus);
+        if (!lm_guess_pays(v_try, v_safe, a->M_expected, a->M, a->V, a->Dh, cus)) v_try = v_safe;
     }
     const bool guess = v_try != v_safe;
     LmParams q = p;

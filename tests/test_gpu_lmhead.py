@@ -603,3 +603,27 @@ def test_expected_row_counts_where_tiles_are_many():
         test_expected_row_count_with_sampling_and_entropy_partials()
     finally:
         dlm.set_option("lmhead_cus", 0)
+
+
+@pytest.mark.parametrize("M,expected,counted,V,Dh", [
+    (1024, 81, 76, 5000, 4096), (512, 128, 121, 16000, 4096), (384, 96, 91, 16000, 4096), (256, 128, 121, 20000, 4096),   # the bound's tiles: 256 x 128
+    (1024, 250, 243, 10000, 1024), (1024, 81, 76, 10000, 1024), (512, 40, 38, 20000, 1024),                               # 256 x 256
+])
+def test_a_right_guess_runs_the_shape_of_its_own_rows(M, expected, counted, V, Dh):
+    """Small vocabularies, where the bound alone would leave most CUs without a row that counts: the outputs are, bit for bit, those of a call
+    whose bound is the guessed shape's capacity (the shapes group the vocabulary differently, so another shape rounds its sums otherwise)."""
+    g = torch.Generator(device=DEV).manual_seed(M + V)
+    h = torch.randn(M, Dh, generator=g, device=DEV, dtype=torch.bfloat16)
+    w = torch.randn(V, Dh, generator=g, device=DEV, dtype=torch.bfloat16) * Dh ** -0.25
+    cap = next(c for c in (32, 64, 128, 192, 256, 384) if expected <= c)
+    outs = []
+    for bound, guess in ((M, expected), (cap, 0)):
+        conf, lse = (torch.full((M,), float("nan"), device=DEV) for _ in range(2))
+        tok = torch.full((M,), -7, dtype=torch.int32, device=DEV)
+        ws = torch.empty(dlm.lmhead_workspace_bytes(bound, V), dtype=torch.uint8, device=DEV)
+        dlm.lmhead_confidence(h, w, conf, tok, M=bound, m_dev=dev(np.asarray([counted], np.int32)), forbid_token=V - 1, lse=lse, workspace=ws,
+                              M_expected=guess)
+        outs.append((conf, lse, tok))
+    for a, b in zip(*outs):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    assert not outs[0][0][:counted].isnan().any() and outs[0][0][counted:].isnan().all()
