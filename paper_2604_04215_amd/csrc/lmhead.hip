@@ -1512,19 +1512,18 @@ static int64_t lm_tiles(int v, int M, int V) {
 // The shape for M rows of V tokens.  The one for M alone is made to read W once; with a small vocabulary its few large tiles leave most
 // CUs idle, and a CU brings in no more than 60 - 70 GB/s however much it has in flight.  So where it gives at most five
 // eighths as many workgroups as there are CUs (160 of 256), the smallest tile is taken of which there is at most one a CU: more CUs
-// share the load, and W and H, read more than once, come from L2.  Over 1074 points (V 2048 .. 157184, Dh 256 .. 4096, 16 .. 2048 rows)
-// this is the faster side or the same everywhere, 0.79 of the time in the geometric mean.  Us a call, M alone / now: V = 2048, Dh =
-// 256, 64 rows 10.4 / 8.1; V = 8000, Dh = 4096, 96 rows 63 / 27, 256 rows 105 / 33; V = 2048, Dh = 4096, 1024 rows 84 / 38; V = 32000,
-// Dh = 4096, 128 rows 71 / 56.  With 161 - 256 workgroups smaller tiles lose (V = 50000, Dh = 4096, 256 rows 127 / 157 and more).
-// More than 256 rows of fewer than 512 elements keep the ring, though small tiles would be faster there too (V = 4096, Dh = 256, 512 rows 21 /
-// 10 us): such calls give the same bits on any number of CUs, with a queue of tiles and without, which the tests hold them to.
-static bool lm_few(int M, int V, int Dh, int cus) {
-    return g_lm_variant < 0 && (M <= 256 || Dh >= 512) && 8 * lm_tiles(plan_rows(M), M, V) <= 5 * (int64_t)cus;
+// share the load, and W and H, read more than once, come from L2.  Over 1765 calls without a guess (V 300 .. 157184, Dh 64 .. 4096, 16 .. 4096 rows)
+// the 847 that take another shape for it need 0.56 of the time in the geometric mean and 0.93 at most.  Us a call, M alone / now: V = 2048,
+// Dh = 256, 64 rows 10.4 / 8.1; V = 8000, Dh = 4096, 96 rows 63 / 27, 256 rows 105 / 33; V = 2048, Dh = 4096, 1024 rows 84 / 38; V = 32000,
+// Dh = 4096, 128 rows 71 / 56; V = 4096, Dh = 256, 512 rows 21 / 10.  With 161 - 256 workgroups smaller tiles lose (V = 50000, Dh = 4096, 256 rows
+// 127 / 157 and more).
+static bool lm_few(int M, int V, int cus) {
+    return g_lm_variant < 0 && 8 * lm_tiles(plan_rows(M), M, V) <= 5 * (int64_t)cus;
 }
-static int plan_lmhead(int M, int V, int Dh, int cus) {
+static int plan_lmhead(int M, int V, int cus) {
     if (g_lm_variant >= 0) return g_lm_variant;
     const int usual = plan_rows(M);
-    if (lm_few(M, V, Dh, cus)) {
+    if (lm_few(M, V, cus)) {
         static const int small[] = {0, 29, 25, 3};
         for (int v : small) {
             if (g_lm_variants[v].tv * g_lm_variants[v].mb >= g_lm_variants[usual].tv * g_lm_variants[usual].mb) break;
@@ -1534,18 +1533,19 @@ static int plan_lmhead(int M, int V, int Dh, int cus) {
     return usual;
 }
 
-// Is a shape queued for the expected rows worth the launch that then ends at once, 2.2 - 2.5 us?  Where the bound's own shape has many tiles, yes.
-// Where it has few: if a CU brings in at least 256 KB less (at some 100 GB/s); tiles that do not all fit at once count half as much again, as W
-// is then what all wait for; and not only for a narrower tile of as many workgroups, as rows past the count, all one and the same, cost
-// little, and W of one row chunk is fetched past the caches.  Us, without / with, Dh = 4096: bound 1024, 81 expected, V = 10000 82 / 33; 512, 128, 16000
-// 59 / 35; 256, 128, 40000 87 / 77; not taken: 128, 32, 40000 61 / 71; 256, 20, 16000 30 / 35; Dh = 256: 128, 32, 16000 9.1 / 11.3.  Over 298 calls
-// with few tiles (V 2048 .. 40000, Dh 256 .. 4096, bound 40 .. 1024) within 0.3 % of the faster side in the geometric mean.
+// Is a shape queued for the expected rows worth the launch that then ends at once, 2.2 - 2.5 us?  Where the bound's own shape has many tiles, or is the
+// ring, which takes 18 us for the shortest walk (Dh = 256, bound 512, 128 expected, V = 20000: without / with 21 / 15): yes.  Where it has few: if a
+// CU brings in at least 256 KB less (at some 100 GB/s); tiles that do not all fit at once count half as much again, as W is then what all wait
+// for; and not only for a narrower tile of as many workgroups, as rows past the count, all one and the same, cost little, and W of one row
+// chunk is fetched past the caches.  Us, without / with, Dh = 4096: bound 1024, 81 expected, V = 10000 82 / 33; 512, 128, 16000 59 / 35; 256, 128,
+// 40000 87 / 77; not taken: 128, 32, 40000 61 / 71; 256, 20, 16000 30 / 35; Dh = 256: 128, 32, 16000 9.1 / 11.3.  Over 298 calls with few tiles (V 2048 ..
+// 40000, Dh 256 .. 4096, bound 40 .. 1024) within 0.3 % of the faster side in the geometric mean.
 static int64_t lm_load(int v, int M, int V, int cus) {
     const int64_t rounds = (lm_tiles(v, M, V) + cus - 1) / cus, rows = g_lm_variants[v].tv + g_lm_variants[v].mb;
     return rounds <= 1 ? rows : 3 * rounds * rows / 2;
 }
 static bool lm_guess_pays(int v_try, int v_safe, int expected, int M, int V, int Dh, int cus) {
-    if (!lm_few(M, V, Dh, cus)) return true;
+    if (!lm_few(M, V, cus) || lm_queued(v_safe)) return true;
     return (lm_load(v_safe, expected, V, cus) - lm_load(v_try, expected, V, cus)) * Dh >= 131072 &&
            (lm_tiles(v_try, expected, V) > lm_tiles(v_safe, expected, V) || M <= g_lm_variants[v_safe].mb);
 }
@@ -1692,11 +1692,11 @@ static int lmhead_enqueue(const dlm_lmhead_args* a, void* workspace, void* strea
     // The caller's bound M sizes the launch, the device's count says how many rows there are.  When the caller
     // expects the count to fall in a smaller shape's range, that shape is queued first, guarded by "count <= its
     // capacity", and the bound's shape after it, guarded by the opposite: one of the two returns at once.
-    const int v_safe = plan_lmhead(a->M, a->V, a->Dh, cus);
+    const int v_safe = plan_lmhead(a->M, a->V, cus);
     int v_try = v_safe, cap = 0;
     if (a->m_dev && a->M_expected > 0 && a->M_expected < a->M && g_lm_variant < 0) {
         cap = plan_capacity(a->M_expected);
-        if (cap < a->M) v_try = plan_lmhead(cap, a->V, a->Dh, cus);
+        if (cap < a->M) v_try = plan_lmhead(cap, a->V, cus);
         if (!lm_guess_pays(v_try, v_safe, a->M_expected, a->M, a->V, a->Dh, cus)) v_try = v_safe;
     }
     const bool guess = v_try != v_safe;

@@ -477,19 +477,22 @@ def test_half_height_tail_launch(M, cus, V):
     (2049, None, 128, 2600, 16),    # nine chunks, one row in the last; the last group of vocabulary tiles incomplete
 ])
 def test_workgroups_that_take_their_tiles_from_a_queue(M, m_dev, Dh, V, cus):
-    """More tiles than workgroups, against the oracle, and (all rows counted) bit for bit what one workgroup a tile gives."""
+    """More tiles than workgroups, against the oracle, and (all rows counted) bit for bit what one workgroup a tile gives.  The shape is the one for
+    the row count by name: without the lowered CU count such small vocabularies take smaller tiles, which sum in another order."""
     R = M + 50
     h, w = rnd(940 + M, (R, Dh)), rnd(941 + V, (V, Dh), Dh ** -0.25)
     idx = np.random.default_rng(M).permutation(R)[:M].astype(np.int32)
     kw = dict(row_idx=idx, M=M, m_dev=m_dev, forbid=V - 1, inv_t=0.9)
     m = M if m_dev is None else m_dev
     ref = oracle.lmhead(h, w, row_idx=idx[:m], forbid_token=V - 1, inv_temperature=0.9) if m else None
-    plain = run_lm(h, w, **kw)
-    dlm.set_option("lmhead_cus", cus)
+    dlm.set_option("lmhead_variant", 22 if M <= 384 else 20)
     try:
+        plain = run_lm(h, w, **kw)
+        dlm.set_option("lmhead_cus", cus)
         queued = [run_lm(h, w, **kw) for _ in range(2)]
     finally:
         dlm.set_option("lmhead_cus", 0)
+        dlm.set_option("lmhead_variant", -1)
     for got in queued:
         compare_prefix(got, ref, m)
         if m_dev is None:
@@ -627,3 +630,17 @@ def test_a_right_guess_runs_the_shape_of_its_own_rows(M, expected, counted, V, D
     for a, b in zip(*outs):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
     assert not outs[0][0][:counted].isnan().any() and outs[0][0][counted:].isnan().all()
+
+
+@pytest.mark.parametrize("M,Dh,V,shape", [(257, 64, 300, 0), (300, 448, 20000, 3), (512, 256, 4096, 29), (700, 192, 3000, 25), (4096, 128, 2048, 3)])
+def test_small_tiles_whatever_the_hidden_size(M, Dh, V, shape):
+    """More than 256 rows of fewer than 512 elements: the shape that fills the chip, bit for bit as by name, and the oracle's values."""
+    h, w = rnd(2000 + M, (M, Dh)), rnd(2001 + V, (V, Dh), Dh ** -0.25)
+    got = run_lm(h, w, forbid=V - 1)
+    dlm.set_option("lmhead_variant", shape)
+    try:
+        named = run_lm(h, w, forbid=V - 1)
+    finally:
+        dlm.set_option("lmhead_variant", -1)
+    assert all(np.array_equal(got[k], named[k], equal_nan=True) for k in named)
+    compare(got, oracle.lmhead(h, w, forbid_token=V - 1))
