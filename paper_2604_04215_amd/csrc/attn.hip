@@ -911,17 +911,31 @@ int g_attn_remap = 7;    // XCD-grouped grids: bit 0 forward and dQ, bit 1 longe
 //     to 512 they lead with fewer than 48 tiles (6 x 348 tokens, 4 heads 12.1 / 8.7; with 640 workgroups 8.7 / 8.4, with 752 7.6 / 10.2);
 //   g * Lq <= 32 likewise: 24 x 4 heads of 64 x 500 keys 9.1 / 8.0, 2 x 32/8 of 128 x 1024 17.6 / 15.3; at d = 128 only where the keys are
 //     not split across workgroups, with which the two are even;
-//   under a block-causal mask over whole sequences, whose workgroups differ in length, the eight wavefronts of two key groups also where there are up to two
-//     workgroups per CU (a packed batch: of its tokens) and 16 key tiles: the longest ends sooner.  Us, four / eight wavefronts: 2 x 600 tokens,
-//     32/8 heads 28.1 / 21.4 (16 tiles 28.8 / 27.1, 13 in a packed batch 21.5 / 23.1), 1 x 2000, 32/8 77.8 / 60.1; at d = 64, two such
-//     workgroups a CU, up to 850 with 38 tiles: 10 x 2000, 4 heads 86.9 / 63.7 (1008 with 112 144 / 151).  Not where the rows are a
-//     block at the end, all workgroups equally long: 60 x 32 rows x 2291 keys, 28/4 heads 105 / 124;
+//   under a block-causal mask over whole sequences, whose workgroups differ in length, the eight wavefronts of two key groups also where there are more
+//     than one such workgroup a CU, as long as a CU is given little more than the longest takes (see two_groups_pay);
 //   513 - 767 workgroups of d = 128 (not of a packed batch, of which fewer have rows) at three a CU, in one round: 3 x 800 tokens, 28/4 heads
 //     58.6 / 46.4.
 // Workgroups of the fullest XCD (32 CUs) of a grid that set_remap makes of nx tiles for each of n_groups
 static int64_t xcd_load(int64_t n_groups, int64_t nx) {
     GridRemap m;
     return set_remap(m, n_groups, (int)nx, false) / 8;
+}
+// Is it the longest workgroup that a block-causal launch over whole sequences waits for?  Eight wavefronts take it through its keys in 0.65 of the
+// time of four, but fewer of them fit a CU, so it is worth it while a CU's share of the work, with six tiles for the start and end of a workgroup, is at most
+// 1.3 (d = 128, one workgroup a CU) or 1.8 (d = 64, two) of the longest.  A row tile sees half the keys in the mean (of a packed batch: of lengths
+// spread evenly up to the longest, which is a guess and which the XCDs may share unevenly: 0.6 and 1.2).  Us, four / eight wavefronts: 1 x 3000 tokens, 16/2
+// heads of 128 109 / 70, 2 x 600, 32/8 27.8 / 20.9, 10 x 2000, 4 heads of 64 86 / 62; left out by the line: 4 x 500, 32 heads of 128 30.1 / 36.1, 16
+// packed of 1 - 533, 16/2 heads 24.6 / 35.0, 16 x 1500, 4 heads of 64 57 / 64.  Of 1588 launches of 257 - 1100 workgroups none is slower by more than 3 % for it.
+static bool two_groups_pay(const AttnParams& p, int d, int64_t tiles, int64_t n_wg, int64_t nx) {
+    if (tiles < 12) return false;
+    const double longest = (double)tiles;
+    double wgs = (double)n_wg, mean = longest * (double)(nx + 1) / (2.0 * (double)nx);
+    if (p.cu) {
+        const double m = (double)p.total / p.B, hi = p.Lq, lo = 2 * m > hi ? 2 * m - hi : 0;
+        wgs = ((double)p.total * p.g / 128 + p.B / 2) * p.Hkv;
+        mean = (lo * lo + lo * hi + hi * hi) / (3 * 64 * m) + 2.0 / p.g;
+    }
+    return wgs * (mean + 6) <= (d == 64 ? (p.cu ? 1.2 : 1.8) : (p.cu ? 0.6 : 1.3)) * 256 * longest;
 }
 // tiles: key tiles of a (sequence, KV head), the most one can have
 static int plan_variant(const AttnParams& p, int d, bool bc, int64_t tiles) {
@@ -936,8 +950,8 @@ static int plan_variant(const AttnParams& p, int d, bool bc, int64_t tiles) {
         if (d == 64 && wgs32 <= 512) return tiles >= 48 ? 16 : 11;
     }
     if (wgs128 <= 256) return 13;           // one 128-row workgroup per CU at most: eight wavefronts, two key groups
-    const int64_t live = p.cu ? ((int64_t)p.total * p.g / 128 + p.B / 2) * p.Hkv : wgs128;
-    if (bc && ns == 1 && 2 * (int64_t)p.Lq + 64 >= 32 * tiles && ((live <= 512 && tiles >= 16) || (d == 64 && live <= 850 && tiles >= 38))) return 13;
+    const bool whole = bc && ns == 1 && 2 * (int64_t)p.Lq + 64 >= 32 * tiles;   // not a block at the end, where all workgroups are equally long
+    if (whole && two_groups_pay(p, d, tiles, wgs128, (p.R + 127) / 128)) return 13;
     if (wgs128 >= (d == 128 && !p.cu ? 513 : 768)) return 6;   // 128-row workgroups, three resident per CU (softmax of one overlaps MFMA of another)
     return 4;                               // 128-row workgroups, two resident per CU, deeper prefetch
 }

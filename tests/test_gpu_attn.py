@@ -438,3 +438,42 @@ def test_splits_that_a_call_takes_of_those_it_has_room_for(B, Lq, Hq, Hkv, d, P,
                                              (1, 2050, 4, 4, 64, 8), (6, 348, 4, 4, 64, 32)])
 def test_full_sequences_on_both_sides_of_the_lines_between_shapes(B, L, Hq, Hkv, d, bs):
     run_case(B=B, Lq=L, Hq=Hq, Hkv=Hkv, d=d, P=0, Lb=L, S=0, seed=80 + L, **(dict(mode="block_causal", bs=bs, q_pos0=0) if bs else {}))
+
+
+def planned_and_named(call, out, **named):
+    """A call as planned and with its shape (and split) by name: the same kernel, so the same bits."""
+    call()
+    planned = out.clone()
+    out.zero_()
+    for name, value in named.items():
+        dlm.set_option(name, value)
+    try:
+        call()
+    finally:
+        for name in named:
+            dlm.set_option(name, 0)
+    assert planned.any() and torch.equal(planned.view(torch.int16), out.view(torch.int16))
+
+
+def normal(seed, *shape):
+    return torch.randn(shape, generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV, dtype=torch.bfloat16)
+
+
+@pytest.mark.parametrize("B,L,Hq,Hkv,d,variant", [
+    (4, 500, 32, 32, 128, 4), (2, 1000, 32, 32, 128, 4), (16, 1500, 4, 4, 64, 6),   # a CU would get too much of them one after another
+    (1, 1500, 16, 2, 128, 13), (2, 600, 32, 8, 128, 13), (10, 1300, 4, 4, 64, 13),   # the longest is what the launch waits for
+    (-16, 533, 16, 2, 128, 6), (-8, 1000, 16, 2, 128, 6), (-4, 1600, 16, 2, 64, 13),   # packed: lengths from 1 to L
+])
+def test_eight_wavefronts_under_a_causal_mask_where_the_longest_decides(B, L, Hq, Hkv, d, variant):
+    mask = dict(mask_mode=dlm.MASK_BLOCK_CAUSAL, block_size=32)
+    if B > 0:
+        q, k, v = normal(1, B, L, Hq, d), normal(2, B, Hkv, L, d), normal(3, B, Hkv, L, d)
+        out = torch.zeros_like(q)
+        planned_and_named(lambda: dlm.block_attn(q, out, block=(k, v, 0), **mask), out, attn_variant=variant)
+    else:
+        lens = np.linspace(1, L, -B).astype(np.int32)
+        cu = dev(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32))
+        T = int(lens.sum())
+        q, k, v = normal(1, T, Hq, d), normal(2, T, Hkv, d), normal(3, T, Hkv, d)
+        out = torch.zeros_like(q)
+        planned_and_named(lambda: dlm.varlen_attn(q, k, v, out, cu, L, **mask), out, attn_variant=variant)
