@@ -914,7 +914,9 @@ int g_attn_remap = 7;    // XCD-grouped grids: bit 0 forward and dQ, bit 1 longe
 //   under a block-causal mask over whole sequences, whose workgroups differ in length, the eight wavefronts of two key groups also where there are more
 //     than one such workgroup a CU, as long as a CU is given little more than the longest takes (see two_groups_pay);
 //   513 - 767 workgroups of d = 128 (not of a packed batch, of which fewer have rows) at three a CU, in one round: 3 x 800 tokens, 28/4 heads
-//     58.6 / 46.4.
+//     58.6 / 46.4, 44 shapes 0.78 - 0.89 of the time at two.  Under a block-causal mask over whole sequences only up to 12 row tiles a KV head: with
+//     more the second round that two a CU leave is of short ones, and all three at once wait for the longest (6 x 2000 tokens, 8/2 heads, 63 row
+//     tiles 88 / 108, 4 x 1300, 16/8, 21 of them 57 / 65; but 12 x 420, 16/8, 7 of them 34.6 / 27.9).
 // Workgroups of the fullest XCD (32 CUs) of a grid that set_remap makes of nx tiles for each of n_groups
 static int64_t xcd_load(int64_t n_groups, int64_t nx) {
     GridRemap m;
@@ -952,7 +954,7 @@ static int plan_variant(const AttnParams& p, int d, bool bc, int64_t tiles) {
     if (wgs128 <= 256) return 13;           // one 128-row workgroup per CU at most: eight wavefronts, two key groups
     const bool whole = bc && ns == 1 && 2 * (int64_t)p.Lq + 64 >= 32 * tiles;   // not a block at the end, where all workgroups are equally long
     if (whole && two_groups_pay(p, d, tiles, wgs128, (p.R + 127) / 128)) return 13;
-    if (wgs128 >= (d == 128 && !p.cu ? 513 : 768)) return 6;   // 128-row workgroups, three resident per CU (softmax of one overlaps MFMA of another)
+    if (wgs128 >= (d == 128 && !p.cu && !(whole && p.R > 12 * 128) ? 513 : 768)) return 6;   // 128-row workgroups, three resident per CU (softmax of one overlaps MFMA of another)
     return 4;                               // 128-row workgroups, two resident per CU, deeper prefetch
 }
 

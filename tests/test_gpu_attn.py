@@ -1,4 +1,9 @@
 """dlm_block_attn against the oracle, element by element (GPU)."""
+import json
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -477,3 +482,34 @@ def test_eight_wavefronts_under_a_causal_mask_where_the_longest_decides(B, L, Hq
         q, k, v = normal(1, T, Hq, d), normal(2, T, Hkv, d), normal(3, T, Hkv, d)
         out = torch.zeros_like(q)
         planned_and_named(lambda: dlm.varlen_attn(q, k, v, out, cu, L, **mask), out, attn_variant=variant)
+
+
+KERNEL_NAMES = """
+import json, sys
+import torch
+from torch.profiler import ProfilerActivity, profile
+from paper_2604_04215_amd import binding as dlm
+for B, L, Hq, Hkv, bs in json.loads(sys.argv[1]):
+    q, k = (torch.ones(B, *s, 128, device="cuda:0", dtype=torch.bfloat16) for s in ((L, Hq), (Hkv, L)))
+    out = torch.zeros_like(q)
+    call = lambda: dlm.block_attn(q, out, block=(k, k, 0), mask_mode=dlm.MASK_BLOCK_CAUSAL if bs else dlm.MASK_FULL, block_size=bs)
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    print("NAME", next(e.name for e in prof.events() if "attn_kernel<" in e.name), flush=True)
+"""
+
+
+def test_workgroups_a_cu_for_less_than_768():
+    """Two or three workgroups a CU give the same bits: the shape is read from the kernel's name (in a process of its own, which a profiler follows)."""
+    cases = [(6, 2000, 8, 2, 4, 2), (4, 1300, 16, 8, 4, 2), (4, 2600, 8, 8, 32, 2),   # causal, more than 12 row tiles of 128: two
+             (12, 420, 16, 8, 4, 3), (16, 640, 8, 4, 32, 3), (3, 800, 28, 4, 0, 3), (3, 3000, 8, 2, 0, 3)]   # few row tiles, no mask: three
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    run = subprocess.run([sys.executable, "-c", KERNEL_NAMES, json.dumps([c[:5] for c in cases])], cwd=root, capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0, run.stderr[-2000:]
+    names = [line for line in run.stdout.splitlines() if line.startswith("NAME")]
+    for name, case in zip(names, cases, strict=True):
+        row_waves, key_waves, tiles, causal, _, a_cu = name.split("attn_kernel<128, ")[1].split(">")[0].split(", ")[:6]
+        assert (row_waves, key_waves, tiles, causal, a_cu) == ("4", "1", "1", "true" if case[4] else "false", str(case[5])), (case, name)
