@@ -986,22 +986,28 @@ static int plan_nsplit(const dlm_attn_args* a) {
     return n < 1 ? 1 : (int)n;
 }
 
-// How many of the n_max splits that the workspace has room for a call takes, and whether for 32-row workgroups (p.rows32).  Those read K and V
-// once for every 32 rows: about 1.1 ns a key tile of d = 128 (14.6 TB/s from L2), on top of some 12 us; 128-row ones take 18 and 0.55 a
-// tile and split.  Us, 128 / 32 rows: 1 x 32/8 heads of 128 x 8192 keys 26.3 / 21.5, 4 x 28/4 x 2048 24.9 / 20.6, x 4096 26.3 / 29.1.  Fewer, longer
-// splits where the tiles are few, as the merge costs more with each: 1 x 4 heads of 64 x 2048 keys, 16 / 8 splits 13.8 / 10.4;
-// 24 x 4 heads of 64 x 1024 keys, 2 / none 12.4 / 10.4.
+// How many of the n_max splits that the workspace has room for a call takes, and whether for 32-row workgroups (p.rows32).  Those read K and V once for
+// every 32 rows, and their eight wavefronts walk the keys of a split in steps of eight tiles; the 128-row ones read them once for 128 rows, in as many
+// splits as fill the chip.  Estimated in ns from some 6000 calls of 1000 - 12000 keys, each to 10 % for four in five (ends and merge, a step, a tile
+// from L2): 4 % is the most that the choice lost in them.  Us, 128 / 32 rows: 1 x 32/8 heads of 128 x 8192 keys 26.3 / 21.5, 4 x 28/4 x 2048 24.9 / 20.6,
+// x 4096 26.3 / 29.1; heads of 64, where 160 workgroups without a split are too few for long keys: 20 x 14/2, 16 rows x 8000 30 / 42, 5 x 16/2, 64 x
+// 12000 39 / 61.  Fewer, longer splits where the tiles are few, as the merge costs more with each: 1 x 4 heads of 64 x 2048 keys, 16 / 8 splits
+// 13.8 / 10.4; 24 x 4 heads of 64 x 1024 keys, 2 / none 12.4 / 10.4.
 static int plan_use_nsplit(AttnParams& p, int d, int64_t tiles, int n_max) {
     p.rows32 = 0;
     if (n_max <= 1 || g_attn_split >= 2 || g_attn_variant != 0) return n_max;
-    const int64_t BH = (int64_t)p.B * p.Hkv, n32 = BH * ((p.R + 31) / 32);
+    const int64_t BH = (int64_t)p.B * p.Hkv, n32 = BH * ((p.R + 31) / 32), n128 = BH * ((p.R + 127) / 128);
     if (p.R <= 32) return d == 64 && tiles < 48 ? 1 : (int)(tiles / 8 < n_max ? tiles / 8 : n_max);
-    if (n32 > 256 || n32 * tiles * 1120 * d / 128 >= 6000000 + tiles * 550000 / n_max) return n_max;
-    p.rows32 = 1;
+    if (n32 > 256) return n_max;
     int64_t n = 256 / n32 < tiles / 8 ? 256 / n32 : tiles / 8;
     if (tiles < 48 && (d == 64 || n32 > 64)) n = 1;
     if (n > n_max) n = n_max;
     while (n > 1 && xcd_load(BH, n32 / BH * n) > 32) --n;
+    const int64_t steps = (tiles + 8 * n - 1) / (8 * n), ends32 = n > 1 ? 5200 : 0;
+    const int64_t t32 = ends32 + (d == 64 ? 4800 + 1000 * steps + 86 * n32 * tiles / 1000 : 6200 + 1460 * steps + 420 * n32 * tiles / 1000);
+    const int64_t t128 = 210 * n_max + (d == 64 ? 11200 + 1500 * n128 * tiles / 1000 : 14200 + 2300 * n128 * tiles / 1000);
+    if (t32 >= t128) return n_max;
+    p.rows32 = 1;
     return (int)n;
 }
 

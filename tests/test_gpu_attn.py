@@ -513,3 +513,15 @@ def test_workgroups_a_cu_for_less_than_768():
     for name, case in zip(names, cases, strict=True):
         row_waves, key_waves, tiles, causal, _, a_cu = name.split("attn_kernel<128, ")[1].split(">")[0].split(", ")[:6]
         assert (row_waves, key_waves, tiles, causal, a_cu) == ("4", "1", "1", "true" if case[4] else "false", str(case[5])), (case, name)
+
+
+@pytest.mark.parametrize("B,Lb,Hq,Hkv,d,P,variant,split", [
+    (20, 16, 14, 2, 64, 8000, 13, 6), (5, 64, 16, 2, 64, 12000, 13, 6), (20, 48, 4, 4, 128, 8000, 13, 3),   # too few 32-row workgroups for keys that long
+    (4, 32, 14, 2, 64, 4000, 16, 4), (4, 32, 8, 2, 128, 2000, 16, 8), (1, 32, 32, 8, 128, 8000, 16, 8),     # but enough here
+])
+def test_rows_of_a_split(B, Lb, Hq, Hkv, d, P, variant, split):
+    q, k, v = normal(1, B, Lb, Hq, d), normal(2, B, Hkv, P + Lb, d), normal(3, B, Hkv, P + Lb, d)
+    segs = dict(prefix=(k[:, :, :P], v[:, :, :P], 0), block=(k[:, :, P:], v[:, :, P:], P))
+    ws = torch.empty(16 * B * Lb * Hq * (d + 2) * 4, dtype=torch.uint8, device=DEV)
+    out = torch.zeros_like(q)
+    planned_and_named(lambda: dlm.block_attn(q, out, workspace=ws, **segs), out, attn_variant=variant, attn_split=split)
