@@ -992,14 +992,16 @@ static int plan_nsplit(const dlm_attn_args* a) {
 // from L2): 4 % is the most that the choice lost in them.  Us, 128 / 32 rows: 1 x 32/8 heads of 128 x 8192 keys 26.3 / 21.5, 4 x 28/4 x 2048 24.9 / 20.6,
 // x 4096 26.3 / 29.1; heads of 64, where 160 workgroups without a split are too few for long keys: 20 x 14/2, 16 rows x 8000 30 / 42, 5 x 16/2, 64 x
 // 12000 39 / 61.  Fewer, longer splits where the tiles are few, as the merge costs more with each: 1 x 4 heads of 64 x 2048 keys, 16 / 8 splits
-// 13.8 / 10.4; 24 x 4 heads of 64 x 1024 keys, 2 / none 12.4 / 10.4.
+// 13.8 / 10.4; 24 x 4 heads of 64 x 1024 keys, 2 / none 12.4 / 10.4.  Of at most eight tiles, two steps of four wavefronts: 1 x 1 head of 128 x
+// 4000 keys, 15 / 16 splits 14.9 / 13.8, 2 x 16/2, 4 rows x 3000, 11 / 12 splits 15.5 / 14.2.
 static int plan_use_nsplit(AttnParams& p, int d, int64_t tiles, int n_max) {
     p.rows32 = 0;
     if (n_max <= 1 || g_attn_split >= 2 || g_attn_variant != 0) return n_max;
     const int64_t BH = (int64_t)p.B * p.Hkv, n32 = BH * ((p.R + 31) / 32), n128 = BH * ((p.R + 127) / 128);
-    if (p.R <= 32) return d == 64 && tiles < 48 ? 1 : (int)(tiles / 8 < n_max ? tiles / 8 : n_max);
+    const int64_t eights = (tiles + 7) / 8;
+    if (p.R <= 32) return d == 64 && (tiles < 40 || (tiles < 48 && n_max < 4)) ? 1 : (int)(eights < n_max ? eights : n_max);
     if (n32 > 256) return n_max;
-    int64_t n = 256 / n32 < tiles / 8 ? 256 / n32 : tiles / 8;
+    int64_t n = 256 / n32 < eights ? 256 / n32 : eights;
     if (tiles < 48 && (d == 64 || n32 > 64)) n = 1;
     if (n > n_max) n = n_max;
     while (n > 1 && xcd_load(BH, n32 / BH * n) > 32) --n;

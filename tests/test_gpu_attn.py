@@ -518,6 +518,7 @@ def test_workgroups_a_cu_for_less_than_768():
 @pytest.mark.parametrize("B,Lb,Hq,Hkv,d,P,variant,split", [
     (20, 16, 14, 2, 64, 8000, 13, 6), (5, 64, 16, 2, 64, 12000, 13, 6), (20, 48, 4, 4, 128, 8000, 13, 3),   # too few 32-row workgroups for keys that long
     (4, 32, 14, 2, 64, 4000, 16, 4), (4, 32, 8, 2, 128, 2000, 16, 8), (1, 32, 32, 8, 128, 8000, 16, 8),     # but enough here
+    (1, 4, 4, 4, 128, 4000, 12, 16), (2, 4, 14, 2, 64, 3000, 12, 12), (8, 4, 4, 4, 64, 1300, 12, 6), (1, 16, 28, 4, 128, 4000, 16, 16),   # no split of nine tiles
 ])
 def test_rows_of_a_split(B, Lb, Hq, Hkv, d, P, variant, split):
     q, k, v = normal(1, B, Lb, Hq, d), normal(2, B, Hkv, P + Lb, d), normal(3, B, Hkv, P + Lb, d)
