@@ -908,7 +908,9 @@ int g_attn_remap = 7;    // XCD-grouped grids: bit 0 forward and dQ, bit 1 longe
 //     all the time there is, about 2 us a tile of d = 128 and 1 of d = 64, so eight wavefronts share the keys of 32 rows.  Us, before
 //     (128 rows, or four wavefronts) / now: 8 x 28/4 heads x 500 keys 14.1 / 11.8, 20 x 16/2 x 8062 120 / 69, 4 x 14/2 of 64 x 833 13.2 / 9.2,
 //     1 x 3756 tokens, 4 heads of 64, blocks of 32 (472 workgroups) 71 / 30.  At d = 64 three workgroups of four wavefronts fit a CU: up
-//     to 512 they lead with fewer than 48 tiles (6 x 348 tokens, 4 heads 12.1 / 8.7; with 640 workgroups 8.7 / 8.4, with 752 7.6 / 10.2);
+//     to 512 they lead with 4 - 47 tiles (6 x 348 tokens, 4 heads 12.1 / 8.7; with 640 workgroups 8.7 / 8.4, with 752 7.6 / 10.2; 32 x 48 tokens, 8/4
+//     heads, two tiles 5.3 / 5.9).  Not where the grid's grouping gives an XCD more than 32 of them and one fits a CU: 5 x 100 tokens, 16/2 heads of
+//     128, 250 workgroups, 35 on the fullest XCD 9.0 / 11.7;
 //   g * Lq <= 32 likewise: 24 x 4 heads of 64 x 500 keys 9.1 / 8.0, 2 x 32/8 of 128 x 1024 17.6 / 15.3; at d = 128 only where the keys are
 //     not split across workgroups, with which the two are even;
 //   under a block-causal mask over whole sequences, whose workgroups differ in length, the eight wavefronts of two key groups also where there are more
@@ -948,8 +950,9 @@ static int plan_variant(const AttnParams& p, int d, bool bc, int64_t tiles) {
     if (p.R <= 32)                          // waves split the keys, merge on chip
         return (d == 64 ? wgs32 <= 256 && tiles >= 12 * ns : ns == 1 && wgs32 <= 160 && tiles >= 16) ? 10 : 12;
     if (ns == 1 || p.rows32) {
-        if (wgs32 <= 256) return tiles >= 6 && xcd_load(BH, wgs32 / BH) <= 32 ? 16 : 11;
-        if (d == 64 && wgs32 <= 512) return tiles >= 48 ? 16 : 11;
+        const bool even = wgs32 <= 256 && xcd_load(BH, wgs32 / BH) <= 32;   // no CU is dealt two
+        if (wgs32 <= 256 && (even || d == 64 || wgs128 <= 64)) return even && tiles >= 6 ? 16 : 11;
+        if (d == 64 && wgs32 <= 512 && tiles >= 4) return tiles >= 48 ? 16 : 11;
     }
     if (wgs128 <= 256) return 13;           // one 128-row workgroup per CU at most: eight wavefronts, two key groups
     const bool whole = bc && ns == 1 && 2 * (int64_t)p.Lq + 64 >= 32 * tiles;   // not a block at the end, where all workgroups are equally long
@@ -1005,6 +1008,7 @@ static int plan_use_nsplit(AttnParams& p, int d, int64_t tiles, int n_max) {
     if (tiles < 48 && (d == 64 || n32 > 64)) n = 1;
     if (n > n_max) n = n_max;
     while (n > 1 && xcd_load(BH, n32 / BH * n) > 32) --n;
+    if (d == 128 && xcd_load(BH, n32 / BH * n) > 32) return n_max;
     const int64_t steps = (tiles + 8 * n - 1) / (8 * n), ends32 = n > 1 ? 5200 : 0;
     const int64_t t32 = ends32 + (d == 64 ? 4800 + 1000 * steps + 86 * n32 * tiles / 1000 : 6200 + 1460 * steps + 420 * n32 * tiles / 1000);
     const int64_t t128 = 210 * n_max + (d == 64 ? 11200 + 1500 * n128 * tiles / 1000 : 14200 + 2300 * n128 * tiles / 1000);

@@ -526,3 +526,13 @@ def test_rows_of_a_split(B, Lb, Hq, Hkv, d, P, variant, split):
     ws = torch.empty(16 * B * Lb * Hq * (d + 2) * 4, dtype=torch.uint8, device=DEV)
     out = torch.zeros_like(q)
     planned_and_named(lambda: dlm.block_attn(q, out, workspace=ws, **segs), out, attn_variant=variant, attn_split=split)
+
+
+@pytest.mark.parametrize("B,L,Hq,Hkv,d,variant", [
+    (32, 48, 8, 4, 64, 13), (5, 48, 32, 32, 64, 13), (3, 100, 28, 4, 64, 11),   # 257 - 512 of 32 rows: two key tiles, four
+    (5, 100, 16, 2, 128, 13), (5, 100, 8, 1, 128, 11),                          # 35 of them on the fullest XCD, 20
+])
+def test_short_sequences_on_few_rows(B, L, Hq, Hkv, d, variant):
+    q, k, v = normal(1, B, L, Hq, d), normal(2, B, Hkv, L, d), normal(3, B, Hkv, L, d)
+    out = torch.zeros_like(q)
+    planned_and_named(lambda: dlm.block_attn(q, out, block=(k, v, 0)), out, attn_variant=variant)
