@@ -139,7 +139,8 @@ def test_around_the_fewest_rows_of_a_row_split(L, Hq, Hkv, d, bs):
 
 @pytest.mark.parametrize("B", [16, 32], ids=["row-split", "key-split"])
 def test_paired_slabs(B):
-    """33 slabs of 64 keys (17 of 128), 1024 of them and more: the launch pairs the slabs of a block-causal segment."""
+    """33 slabs of 64 keys (17 of 128), 1024 of them and more: the launch of two wavefronts side by side (32 sequences) pairs the slabs of a block-causal
+    segment; the row-split one (16) has as many and does not."""
     q, segs, d_out = make(1, 2100, 2, 2, 64, (0, 2100, 0), seed=3600)
     check_copies(q, segs, d_out, B, mode="block_causal", bs=32)
 
@@ -178,11 +179,20 @@ def test_rows_that_see_no_key(size, d):
 @pytest.mark.parametrize("L,Hq,Hkv,lens,bs", [(64, 5, 1, None, 0), (96, 3, 1, None, 4), (255, 14, 2, None, 32), (257, 7, 1, None, 0), (320, 6, 2, None, 7),
                                               (96, 7, 1, (70, 96, 40), 0), (256, 7, 1, (256, 256, 0), 4)])
 def test_heads_apart(size, d, L, Hq, Hkv, lens, bs):
-    """Heads that do not divide a 32-row tile and rows that fill theirs: dK / dV takes the heads one after another (257 rows: too many tiles for it), with as
-    few as one tile a head for four wavefronts (late keys of a causal mask) and an own-block segment's range in the middle."""
+    """Heads that do not divide a 32-row tile and rows that fill theirs: dK / dV takes the heads one after another (257 rows: too many tiles for it; d = 128 with
+    a causal mask: the kernel without that walk, on the same rows), with as few as one tile a head for four wavefronts (late keys of a causal mask) and an
+    own-block segment's range in the middle."""
     rules = ("earlier", "same", "causal") if lens and bs else None
     q, segs, d_out = make(1, L, Hq, Hkv, d, lens or (0, L, 0), seed=3800 + L, **(dict(pos=(0, 0, 0), rules=rules) if rules else {}))
     check_copies(q, segs, d_out, batches(L, Hq, Hkv)[size], **(dict(mode="block_causal", bs=bs) if bs else {}))
+
+
+@pytest.mark.parametrize("L,Hq,Hkv,bs,rules", [(512, 7, 1, 4, None), (640, 7, 1, 32, None), (639, 6, 2, 8, None), (512, 7, 1, 4, ("earlier", "same", "causal"))])
+def test_heads_apart_on_paired_slabs(L, Hq, Hkv, bs, rules):
+    """4 and 5 slabs of 128 keys, 1024 of them and more, of heads of 64 that do not divide a tile: the second slab of a pair is walked upwards, head after
+    head, from where its causal range begins (an odd number of slabs: the middle one has no partner)."""
+    q, segs, d_out = make(1, L, Hq, Hkv, 64, (L, L, 0) if rules else (0, L, 0), seed=3850 + L, **(dict(pos=(0, 0, 0), rules=rules) if rules else {}))
+    check_copies(q, segs, d_out, 1024 // ((L + 127) // 128 * Hkv) + 1, mode="block_causal", bs=bs)
 
 
 class Backwards:
@@ -234,12 +244,12 @@ PACKED = (400, 1, 65, 0, 129, 63, 257, 33)
 
 
 @pytest.mark.parametrize("groups", [10, 19], ids=["single", "paired"])
-@pytest.mark.parametrize("g,bs", [(2, 0), (7, 0), (2, 4), (7, 32)])
-def test_packed(groups, g, bs):
+@pytest.mark.parametrize("g,bs,d", [(2, 0, 128), (7, 0, 128), (2, 4, 128), (7, 32, 128), (7, 32, 64), (3, 4, 64)])
+def test_packed(groups, g, bs, d):
     """Unequal sequences, many enough for the 64-row dQ and the key-split dK / dV kernels (80 of them: 1120 workgroups of 128 rows, 640
     slabs) and, under the block-causal mask, for paired slabs (152: 1216).  The lengths come in groups of 8, the same 8
-    sequences each time and in another order."""
-    Hkv, d = 2, 128
+    sequences each time and in another order.  At d = 64 7 and 3 heads are taken one after another in the sequences whose tiles they fill."""
+    Hkv = 2
     Hq = g * Hkv
     starts = np.concatenate([[0], np.cumsum(PACKED)])
     n = int(starts[-1])

@@ -83,7 +83,7 @@ def test_shapes_vs_oracle(M, Dh, V):
     assert np.all(got["tok"] != V - 1)
 
 
-@pytest.mark.parametrize("variant", range(29))
+@pytest.mark.parametrize("variant", range(30))
 def test_every_kernel_shape(variant):
     # each entry of the library's shape table on a problem with several row chunks and ragged tails
     M, Dh, V = 300, 192, 1100
@@ -339,7 +339,7 @@ def test_full_vocabulary_sampled_rows():
     assert np.allclose(got["conf"], np.exp(got["zmax"] - got["lse"]), atol=1e-5)
 
 
-@pytest.mark.parametrize("variant", [-1, 0, 3, 5, 7, 10, 16, 20, 21])
+@pytest.mark.parametrize("variant", [-1, 0, 3, 5, 7, 10, 16, 20, 21, 22, 25, 29])
 @pytest.mark.parametrize("mode", ["margin", "neg_entropy"])
 def test_alternative_confidence_scores(mode, variant):
     """conf = p(top-1) - p(top-2) or sum_v p_v log p_v instead of the token probability; every other output unchanged."""
@@ -582,6 +582,8 @@ def test_every_form_of_a_call_through_a_queue(kind, M, Dh, V, cus, counted):
     (384, None, 512, 10000, 0), (385, 129, 576, 2200, 0),  # 128 x 128 and 128 x 32
     (500, 3, 512, 17000, 0), (1030, None, 512, 300, 0),    # 256 x 128; more row chunks than vocabulary tiles
     (256, 200, 64, 40960, 0), (256, 200, 64, 40961, 0),    # 160 tiles of 256 x 256, the most that are few, and one more
+    (256, 90, 64, 40960, 100), (256, 110, 4096, 33000, 120), (256, 200, 4096, 33000, 120),   # the bound's shape stays the large one: a guess that is not
+    (512, 100, 512, 17000, 120), (1024, 200, 1024, 5000, 80),                                # worth it, one that is, right and wrong
 ])
 def test_small_vocabularies_take_small_tiles(M, m_dev, Dh, V, guess):
     """The shapes that fill the chip where the one for the row count alone leaves most of it idle, on both sides of the lines between them."""
@@ -644,3 +646,10 @@ def test_small_tiles_whatever_the_hidden_size(M, Dh, V, shape):
         dlm.set_option("lmhead_variant", -1)
     assert all(np.array_equal(got[k], named[k], equal_nan=True) for k in named)
     compare(got, oracle.lmhead(h, w, forbid_token=V - 1))
+
+
+@pytest.mark.parametrize("kind", ["plain", "static", "strided", "margin", "entropy", "sampled", "sampled_entropy", "target_scatter"])
+@pytest.mark.parametrize("M,Dh,V,counted", [(90, 128, 2049, (90, 33)), (512, 256, 4096, (512, 300)), (700, 192, 3000, (700, 40))])
+def test_every_form_of_a_call_of_a_small_vocabulary(kind, M, Dh, V, counted):
+    """Tiles of 128 x 32, 128 x 64 and 128 x 128, all rows counted and with whole chunks past the count."""
+    test_every_form_of_a_call_through_a_queue(kind, M, Dh, V, 0, counted)
