@@ -48,7 +48,6 @@ struct AttnParams {
     // [T * split / nsplit, T * (split + 1) / nsplit) and stores its unnormalised accumulators and its (running
     // maximum, sum) instead of the output; attn_merge_kernel combines the nsplit partials of every row.
     int nsplit;
-    int rows32;       // the split was planned for 32-row workgroups
     float* part_o;    // [nsplit][B * Hkv * R][d]
     float* part_ml;   // [nsplit][B * Hkv * R][2]  (maximum in log2 units, sum of exponentials relative to it)
 };
@@ -899,6 +898,30 @@ int g_attn_nt = 1;       // 1 = non-temporal K/V loads in the one-workgroup-per-
 int g_attn_variant = 0;  // 0 = choose by shape; 1..16 force a kernel shape (dlm_set_option "attn_variant")
 int g_attn_remap = 7;    // XCD-grouped grids: bit 0 forward and dQ, bit 1 longest key range first, bit 2 dK / dV (dlm_set_option "attn_remap")
 
+// Workgroups of the fullest XCD (32 CUs) of a grid that set_remap makes of nx tiles for each of n_groups
+static int64_t xcd_load(int64_t n_groups, int64_t nx) {
+    GridRemap m;
+    return set_remap(m, n_groups, (int)nx, false) / 8;
+}
+
+// Is it the longest workgroup that a block-causal launch over whole sequences waits for?  Eight wavefronts take it through its keys in 0.65 of the
+// time of four, but fewer of them fit a CU, so it is worth it while a CU's share of the work, with six tiles for the start and end of a workgroup, is at most
+// 1.3 (d = 128, one workgroup a CU) or 1.8 (d = 64, two) of the longest.  A row tile sees half the keys in the mean (of a packed batch: of lengths
+// spread evenly up to the longest, which is a guess and which the XCDs may share unevenly: 0.6 and 1.2).  Us, four / eight wavefronts: 1 x 3000 tokens, 16/2
+// heads of 128 109 / 70, 2 x 600, 32/8 27.8 / 20.9, 10 x 2000, 4 heads of 64 86 / 62; left out by the line: 4 x 500, 32 heads of 128 30.1 / 36.1, 16
+// packed of 1 - 533, 16/2 heads 24.6 / 35.0, 16 x 1500, 4 heads of 64 57 / 64.  Of 1588 launches of 257 - 1100 workgroups none is slower by more than 3 % for it.
+static bool two_groups_pay(const AttnParams& p, int d, int64_t tiles, int64_t n_wg, int64_t nx) {
+    if (tiles < 12) return false;
+    const double longest = (double)tiles;
+    double wgs = (double)n_wg, mean = longest * (double)(nx + 1) / (2.0 * (double)nx);
+    if (p.cu) {
+        const double m = (double)p.total / p.B, hi = p.Lq, lo = 2 * m > hi ? 2 * m - hi : 0;
+        wgs = ((double)p.total * p.g / 128 + p.B / 2) * p.Hkv;
+        mean = (lo * lo + lo * hi + hi * hi) / (3 * 64 * m) + 2.0 / p.g;
+    }
+    return wgs * (mean + 6) <= (d == 64 ? (p.cu ? 1.2 : 1.8) : (p.cu ? 0.6 : 1.3)) * 256 * longest;
+}
+
 // The kernel shape the planner picks for a problem (0 = "automatic" resolved).  Measured on MI355X (us, GPU time):
 //   g * Lq <= 32 (every rollout step): one key-split workgroup per (sequence, KV head); sized for two per CU it is
 //     8 - 10 % faster than sized for one even when only one is resident (c2 22.4 -> 19.7, c3 72 -> 66, c5a 173 -> 162);
@@ -919,37 +942,15 @@ int g_attn_remap = 7;    // XCD-grouped grids: bit 0 forward and dQ, bit 1 longe
 //     58.6 / 46.4, 44 shapes 0.78 - 0.89 of the time at two.  Under a block-causal mask over whole sequences only up to 12 row tiles a KV head: with
 //     more the second round that two a CU leave is of short ones, and all three at once wait for the longest (6 x 2000 tokens, 8/2 heads, 63 row
 //     tiles 88 / 108, 4 x 1300, 16/8, 21 of them 57 / 65; but 12 x 420, 16/8, 7 of them 34.6 / 27.9).
-// Workgroups of the fullest XCD (32 CUs) of a grid that set_remap makes of nx tiles for each of n_groups
-static int64_t xcd_load(int64_t n_groups, int64_t nx) {
-    GridRemap m;
-    return set_remap(m, n_groups, (int)nx, false) / 8;
-}
-// Is it the longest workgroup that a block-causal launch over whole sequences waits for?  Eight wavefronts take it through its keys in 0.65 of the
-// time of four, but fewer of them fit a CU, so it is worth it while a CU's share of the work, with six tiles for the start and end of a workgroup, is at most
-// 1.3 (d = 128, one workgroup a CU) or 1.8 (d = 64, two) of the longest.  A row tile sees half the keys in the mean (of a packed batch: of lengths
-// spread evenly up to the longest, which is a guess and which the XCDs may share unevenly: 0.6 and 1.2).  Us, four / eight wavefronts: 1 x 3000 tokens, 16/2
-// heads of 128 109 / 70, 2 x 600, 32/8 27.8 / 20.9, 10 x 2000, 4 heads of 64 86 / 62; left out by the line: 4 x 500, 32 heads of 128 30.1 / 36.1, 16
-// packed of 1 - 533, 16/2 heads 24.6 / 35.0, 16 x 1500, 4 heads of 64 57 / 64.  Of 1588 launches of 257 - 1100 workgroups none is slower by more than 3 % for it.
-static bool two_groups_pay(const AttnParams& p, int d, int64_t tiles, int64_t n_wg, int64_t nx) {
-    if (tiles < 12) return false;
-    const double longest = (double)tiles;
-    double wgs = (double)n_wg, mean = longest * (double)(nx + 1) / (2.0 * (double)nx);
-    if (p.cu) {
-        const double m = (double)p.total / p.B, hi = p.Lq, lo = 2 * m > hi ? 2 * m - hi : 0;
-        wgs = ((double)p.total * p.g / 128 + p.B / 2) * p.Hkv;
-        mean = (lo * lo + lo * hi + hi * hi) / (3 * 64 * m) + 2.0 / p.g;
-    }
-    return wgs * (mean + 6) <= (d == 64 ? (p.cu ? 1.2 : 1.8) : (p.cu ? 0.6 : 1.3)) * 256 * longest;
-}
 // tiles: key tiles of a (sequence, KV head), the most one can have
-static int plan_variant(const AttnParams& p, int d, bool bc, int64_t tiles) {
+static int plan_variant(const AttnParams& p, int d, bool bc, int64_t tiles, bool rows32) {
     if (g_attn_variant != 0) return g_attn_variant;
     const int64_t BH = (int64_t)p.B * p.Hkv;
     const int ns = p.nsplit > 1 ? p.nsplit : 1;
     const int64_t wgs128 = BH * ((p.R + 127) / 128) * ns, wgs32 = BH * ((p.R + 31) / 32) * ns;
     if (p.R <= 32)                          // waves split the keys, merge on chip
         return (d == 64 ? wgs32 <= 256 && tiles >= 12 * ns : ns == 1 && wgs32 <= 160 && tiles >= 16) ? 10 : 12;
-    if (ns == 1 || p.rows32) {
+    if (ns == 1 || rows32) {
         const bool even = wgs32 <= 256 && xcd_load(BH, wgs32 / BH) <= 32;   // no CU is dealt two
         if (wgs32 <= 256 && (even || d == 64 || wgs128 <= 64)) return even && tiles >= 6 ? 16 : 11;
         if (d == 64 && wgs32 <= 512 && tiles >= 4) return tiles >= 48 ? 16 : 11;
@@ -989,7 +990,7 @@ static int plan_nsplit(const dlm_attn_args* a) {
     return n < 1 ? 1 : (int)n;
 }
 
-// How many of the n_max splits that the workspace has room for a call takes, and whether for 32-row workgroups (p.rows32).  Those read K and V once for
+// How many of the n_max splits that the workspace has room for a call takes, and whether for 32-row workgroups (rows32).  Those read K and V once for
 // every 32 rows, and their eight wavefronts walk the keys of a split in steps of eight tiles; the 128-row ones read them once for 128 rows, in as many
 // splits as fill the chip.  Estimated in ns from some 6000 calls of 1000 - 12000 keys, each to 10 % for four in five (ends and merge, a step, a tile
 // from L2): 4 % is the most that the choice lost in them.  Us, 128 / 32 rows: 1 x 32/8 heads of 128 x 8192 keys 26.3 / 21.5, 4 x 28/4 x 2048 24.9 / 20.6,
@@ -997,8 +998,7 @@ static int plan_nsplit(const dlm_attn_args* a) {
 // 12000 39 / 61.  Fewer, longer splits where the tiles are few, as the merge costs more with each: 1 x 4 heads of 64 x 2048 keys, 16 / 8 splits
 // 13.8 / 10.4; 24 x 4 heads of 64 x 1024 keys, 2 / none 12.4 / 10.4.  Of at most eight tiles, two steps of four wavefronts: 1 x 1 head of 128 x
 // 4000 keys, 15 / 16 splits 14.9 / 13.8, 2 x 16/2, 4 rows x 3000, 11 / 12 splits 15.5 / 14.2.
-static int plan_use_nsplit(AttnParams& p, int d, int64_t tiles, int n_max) {
-    p.rows32 = 0;
+static int plan_use_nsplit(const AttnParams& p, int d, int64_t tiles, int n_max, bool& rows32) {
     if (n_max <= 1 || g_attn_split >= 2 || g_attn_variant != 0) return n_max;
     const int64_t BH = (int64_t)p.B * p.Hkv, n32 = BH * ((p.R + 31) / 32), n128 = BH * ((p.R + 127) / 128);
     const int64_t eights = (tiles + 7) / 8;
@@ -1013,7 +1013,7 @@ static int plan_use_nsplit(AttnParams& p, int d, int64_t tiles, int n_max) {
     const int64_t t32 = ends32 + (d == 64 ? 4800 + 1000 * steps + 86 * n32 * tiles / 1000 : 6200 + 1460 * steps + 420 * n32 * tiles / 1000);
     const int64_t t128 = 210 * n_max + (d == 64 ? 11200 + 1500 * n128 * tiles / 1000 : 14200 + 2300 * n128 * tiles / 1000);
     if (t32 >= t128) return n_max;
-    p.rows32 = 1;
+    rows32 = true;
     return (int)n;
 }
 
@@ -1031,10 +1031,10 @@ static bool attn_deep(const AttnParams& p) {
 }
 
 template <int D, bool BC>
-static int launch_attn(const AttnParams& p, int64_t tiles, hipStream_t st) {
+static int launch_attn(const AttnParams& p, int64_t tiles, bool rows32, hipStream_t st) {
     const int64_t BH = (int64_t)p.B * p.Hkv;
     const int ns = p.nsplit > 1 ? p.nsplit : 1;
-    int variant = plan_variant(p, D, BC, tiles);
+    int variant = plan_variant(p, D, BC, tiles, rows32);
     if (variant == 11 || variant == 16 || (variant == 1 && p.R > 32)) {
         // 32-row workgroups whose wavefronts split the keys, several row tiles per (sequence, KV head), XCD-grouped
         AttnParams q = p;
@@ -1236,20 +1236,21 @@ extern "C" int dlm_block_attn(const dlm_attn_args* a, void* stream) {
     p.seq_active = a->seq_active;
     p.remap = no_remap();
     // The key split across workgroups is taken only when the caller brought the workspace it needs.
-    p.nsplit = 1; p.rows32 = 0; p.part_o = nullptr; p.part_ml = nullptr;
+    p.nsplit = 1; p.part_o = nullptr; p.part_ml = nullptr;
     const int64_t tiles = key_tiles(a);
     const int n_max = plan_nsplit(a);
+    bool rows32 = false;   // the split was planned for 32-row workgroups
     const size_t need = split_workspace_bytes(a, n_max);
     if (n_max > 1 && a->workspace && a->workspace_bytes >= need && aligned16(a->workspace)) {
         const size_t rows_total = (size_t)a->B * a->Hq * a->Lq;
-        p.nsplit = plan_use_nsplit(p, a->d, tiles, n_max);
+        p.nsplit = plan_use_nsplit(p, a->d, tiles, n_max, rows32);
         p.part_o = (float*)a->workspace;
         p.part_ml = p.part_o + (size_t)p.nsplit * rows_total * a->d;
     }
     hipStream_t st = (hipStream_t)stream;
     const bool bc = a->mask_mode == DLM_MASK_BLOCK_CAUSAL;
-    if (a->d == 128) rc = bc ? launch_attn<128, true>(p, tiles, st) : launch_attn<128, false>(p, tiles, st);
-    else rc = bc ? launch_attn<64, true>(p, tiles, st) : launch_attn<64, false>(p, tiles, st);
+    if (a->d == 128) rc = bc ? launch_attn<128, true>(p, tiles, rows32, st) : launch_attn<128, false>(p, tiles, rows32, st);
+    else rc = bc ? launch_attn<64, true>(p, tiles, rows32, st) : launch_attn<64, false>(p, tiles, rows32, st);
     if (rc != DLM_OK || p.nsplit <= 1) return rc;
     const int64_t rows_total = (int64_t)a->B * a->Hq * a->Lq;
     if (a->d == 128) hipLaunchKernelGGL(attn_merge_kernel<128>, dim3((unsigned)((rows_total + 7) / 8)), dim3(256), 0, st, p);

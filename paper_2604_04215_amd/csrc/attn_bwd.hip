@@ -444,7 +444,6 @@ template <int D, bool BC, int NWK, int NWR, bool ALIKE>
 __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdParams p, int sidx, int n_slabs, int pair, GridRemap rm) {
     constexpr bool PAIR = dkv_pairs<BC, NWK, NWR>();   // a workgroup may take two slabs
     constexpr int NS = D == 128 && NWK * NWR == 1 ? 2 : 4;   // ring stages: four such rings fit a CU, one a SIMD
-    constexpr bool BY_HEAD = ALIKE;
     constexpr int FD = D == 128 ? 2 : 4;               // fragments read ahead (at d = 128 all that registers allow)
     constexpr int AHEAD = NWK == 1 ? NS - 1 : 2;       // tiles requested ahead: a ring that is the wavefront's own needs no slack
     constexpr int P = D * 2, C8 = D / 8;
@@ -506,7 +505,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     // `regular`).  With the heads apart a tile is 32 queries of one head whatever their number.  Where that makes at most an eighth more
     // tiles (a head's last tile is partly empty).  Forward and backward, us, before / with it and ALIKE: 64 packed sequences of 48 - 900 tokens, 14/2
     // heads of 64 504 / 471, 4 x 777 tokens, block diffusion 301 / 262; 28/4 heads of 128, 1425 / 1325.
-    const bool by_head = BY_HEAD && (32 % p.g) != 0 && 8 * p.g * ((Lq + 31) >> 5) <= 9 * ((p.g * Lq + 31) >> 5);
+    const bool by_head = ALIKE && (32 % p.g) != 0 && 8 * p.g * ((Lq + 31) >> 5) <= 9 * ((p.g * Lq + 31) >> 5);
     const int g = by_head ? 1 : p.g;                   // heads that the rows of a tile run over
     const int R = g * Lq;
     // Row r of the group is query r / g, head r % g.  Inside a tile that starts at (query i0, head h0) row l is on query i0 + 1 + u / g
@@ -604,7 +603,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     // that are in their second pass are on one tile again, whatever their x.
     const bool up = PAIR && pair && pass;
     int rt = up ? rt_begin + wr : rt_end - 1 - wr;    // this wavefront's tile (by_head: of one head, over and over)
-#define BW_WRAP() if (BY_HEAD && by_head && n_rt > 0) { while (rt < rt_begin) rt += n_rt; while (rt >= rt_end) rt -= n_rt; }
+#define BW_WRAP() if (ALIKE && by_head && n_rt > 0) { while (rt < rt_begin) rt += n_rt; while (rt >= rt_end) rt -= n_rt; }
     const int rt_step = up ? NWR : -NWR;
 
     // next tile to request: first row = query i0, head h0 (kept without divisions); queries are clamped to the sequence,
@@ -626,7 +625,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
     int hd = 0;
     int64_t hstat = 0;
 #define BW_NEXT_HEAD()                                                                                   \
-    if (BY_HEAD && by_head && n_rt > 0) {                                                                \
+    if (ALIKE && by_head && n_rt > 0) {                                                                \
         while (i0 < rt_begin * 32 || i0 >= rt_end * 32) {                                                \
             const int back_ = i0 < rt_begin * 32 ? n_rt * 32 : -n_rt * 32;                               \
             const int64_t dh_ = hd + 1 < p.g ? p.q_sh : 0;                                               \
@@ -651,7 +650,7 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
         if ((x) < IPW) {                                                                                 \
             const int q_ = wk * IPW + (x);                                                               \
             const uint32_t dst_ = lds0 + (wr * NS + ist) * STAGE + q_ * BW_GP;                           \
-            if (whole) {                                                                               \
+            if (whole) {                                                                                 \
                 bw_load_lds16_pair<IMG>(qt, gt, voff, ((q_ * RPI) >> gsh) * qst2 + ((q_ * RPI) & (g - 1)) * qsh2, dst_); \
             } else {                                                                                     \
             const unsigned lo_ = bw_lane();                                                              \
@@ -662,13 +661,13 @@ __global__ __launch_bounds__(64 * NWK * NWR, 1) void attn_bwd_dkv_kernel(BwdPara
                 const uint32_t oq_ = __umul24(i_ - ic_, (int)p.q_st * 2) + __umul24(h_, (int)p.q_sh * 2) + c16;   \
                 const uint32_t og_ = ALIKE ? oq_ : __umul24(i_ - ic_, (int)do_st * 2) + __umul24(h_, (int)do_sh * 2) + c16; \
                 bw_load_lds16(qb + ic_ * p.q_st + hd * p.q_sh, oq_, dst_);                               \
-                bw_load_lds16(gb + ic_ * do_st + hd * do_sh, og_, dst_ + IMG);                       \
+                bw_load_lds16(gb + ic_ * do_st + hd * do_sh, og_, dst_ + IMG);                           \
             } else {                                                                                     \
                 bw_load_lds16(qb + bw_offset(i_, p.q_st) + bw_offset(h_, p.q_sh) + c16 / 2, dst_);       \
                 bw_load_lds16(gb + bw_offset(i_, do_st) + bw_offset(h_, do_sh) + c16 / 2, dst_ + IMG); \
             }                                                                                            \
             }                                                                                            \
-        } else if (whole) {                                                                            \
+        } else if (whole) {                                                                              \
             bw_load_lds4(sptr + i0 + hstat, lds0 + stat_base + ist * 256);                               \
         } else {                                                                                         \
             const unsigned lo_ = bw_lane();                                                              \

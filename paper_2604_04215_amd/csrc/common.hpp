@@ -59,8 +59,8 @@ inline int64_t set_remap(GridRemap& m, int64_t n_groups, int nx, bool rev) {
 // ---- device helpers ---------------------------------------------------------
 // Brings a kernel's arguments (the first BYTES of them) into the scalar cache in one trip to memory.  The compiler reads them a few at a time, where
 // they are first needed, and in a kernel of a few microseconds each such wait is a trip of its own: attention of 1 x 4 heads of 64 x 288 keys 6.70 -> 6.36
-// us.  (One asm block, with the wait in it: the
-// values themselves are dropped, the reads that follow find the lines.)
+// us.  (One asm block with the wait in it: nothing is in flight behind it.  The values themselves are not wanted, the reads that follow find the
+// lines.)
 template <int BYTES>
 __device__ __forceinline__ void fetch_args() {
     static_assert(BYTES > 192 && BYTES <= 384, "four to six lines");
@@ -78,6 +78,7 @@ __device__ __forceinline__ void fetch_args() {
         asm volatile("s_load_dword %0, %1, 0x0\n\ts_load_dword %0, %1, 0x40\n\ts_load_dword %0, %1, 0x80\n\ts_load_dword %0, %1, 0xc0\n\t"
                      "s_load_dword %0, %1, %2\n\ts_waitcnt lgkmcnt(0)"
                      : "=&s"(t) : "s"(a), "n"((BYTES - 4) & ~3));
+    asm volatile("" : : "s"(t));
 }
 
 // fp32 -> bf16, round to nearest even (the hardware conversion of gfx950)
