@@ -106,8 +106,9 @@ typedef struct dlm_kv_seg {
  * workspace: optional.  dlm_block_attn_workspace_bytes(args) is non-zero for shapes that leave most of the chip idle with
  *           one workgroup per row tile (few sequences x KV heads, long context): given that many bytes (16-byte aligned),
  *           the call lets several workgroups share the keys of a row tile (fp32 partial results in the workspace, merged
- *           in a fixed order by a second launch: deterministic).  Without it, or with a smaller buffer, the call runs
- *           unsplit; results then differ by the rounding of another summation order only.
+ *           in a fixed order by a second launch: deterministic).  The call may take fewer parts than that many, and a buffer
+ *           for those is enough; without one, or with a smaller one, it runs unsplit; results then differ by the
+ *           rounding of another summation order only.
  *   seq_active  optional device int32 [B]: sequence b is skipped (its rows of out and lse are left as they
  *           are) when seq_active[b] == 0.  For denoising steps in which some sequences of the batch have no
  *           masked position left: nothing reads their attention output (the LM head runs on masked rows

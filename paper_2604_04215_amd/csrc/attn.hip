@@ -966,10 +966,10 @@ static int64_t key_tiles(const dlm_attn_args* a) {
     return ((int64_t)a->prefix.len + 31) / 32 + ((int64_t)a->block.len + 31) / 32 + ((int64_t)a->suffix.len + 31) / 32;
 }
 
-// How many workgroups share the keys of one row tile.  A split costs a second launch (the merge) and (d + 2) * 4 bytes
-// written and read again per row and split, so it pays only where the unsplit launch leaves most of the chip idle: at
-// most 128 workgroups (half the CUs) and at least 32 key tiles.  Then the count brings the launch to about one
-// workgroup per CU with at least four key tiles each.  Measured (us): 1 x 32 heads x 8192 keys 114 -> 33 (8 splits);
+// How many workgroups share the keys of one row tile at most (plan_use_nsplit may take fewer; the workspace is sized for this many, which only grows
+// with the keys).  A split costs a second launch (the merge) and (d + 2) * 4 bytes written and read again per row and split, so
+// it pays only where the unsplit launch leaves most of the chip idle: at most 128 workgroups (half the CUs) and at least 32 key tiles.  Then the count
+// brings the launch to about one workgroup per CU with at least four key tiles each.  Measured (us): 1 x 32 heads x 8192 keys 114 -> 33 (8 splits);
 // 1 x 32/8 heads x 16384 keys 318 -> 43 (16); 8 x 28/4 heads x 4096 keys 88 -> 40 (4); 4 x 32 heads x 2048 keys 33 -> 30 (2).
 // With 256 or more workgroups every split measured slower (c2 19.7 -> 28.4, c3 66 -> 81, c4 32 -> 50, c5a 162 -> 180):
 // those launches already keep the memory system busy and the partials and the second launch are pure cost.
@@ -990,7 +990,7 @@ static int plan_nsplit(const dlm_attn_args* a) {
     return n < 1 ? 1 : (int)n;
 }
 
-// How many of the n_max splits that the workspace has room for a call takes, and whether for 32-row workgroups (rows32).  Those read K and V once for
+// How many of the n_max splits that the workspace is sized for a call takes, and whether for 32-row workgroups (rows32).  Those read K and V once for
 // every 32 rows, and their eight wavefronts walk the keys of a split in steps of eight tiles; the 128-row ones read them once for 128 rows, in as many
 // splits as fill the chip.  Estimated in ns from some 6000 calls of 1000 - 12000 keys, each to 10 % for four in five (ends and merge, a step, a tile
 // from L2): 4 % is the most that the choice lost in them.  Us, 128 / 32 rows: 1 x 32/8 heads of 128 x 8192 keys 26.3 / 21.5, 4 x 28/4 x 2048 24.9 / 20.6,
@@ -1235,17 +1235,16 @@ extern "C" int dlm_block_attn(const dlm_attn_args* a, void* stream) {
     p.cu = a->cu_seqlens; p.total = a->total_tokens;
     p.seq_active = a->seq_active;
     p.remap = no_remap();
-    // The key split across workgroups is taken only when the caller brought the workspace it needs.
+    // The key split across workgroups is taken only when the caller brought the workspace that its own number of splits needs.
     p.nsplit = 1; p.part_o = nullptr; p.part_ml = nullptr;
     const int64_t tiles = key_tiles(a);
-    const int n_max = plan_nsplit(a);
-    bool rows32 = false;   // the split was planned for 32-row workgroups
-    const size_t need = split_workspace_bytes(a, n_max);
-    if (n_max > 1 && a->workspace && a->workspace_bytes >= need && aligned16(a->workspace)) {
+    bool rows32 = false;   // the split is planned for 32-row workgroups
+    const int n = plan_use_nsplit(p, a->d, tiles, plan_nsplit(a), rows32);
+    if (n > 1 && a->workspace && a->workspace_bytes >= split_workspace_bytes(a, n) && aligned16(a->workspace)) {
         const size_t rows_total = (size_t)a->B * a->Hq * a->Lq;
-        p.nsplit = plan_use_nsplit(p, a->d, tiles, n_max, rows32);
+        p.nsplit = n;
         p.part_o = (float*)a->workspace;
-        p.part_ml = p.part_o + (size_t)p.nsplit * rows_total * a->d;
+        p.part_ml = p.part_o + (size_t)n * rows_total * a->d;
     }
     hipStream_t st = (hipStream_t)stream;
     const bool bc = a->mask_mode == DLM_MASK_BLOCK_CAUSAL;

@@ -528,6 +528,24 @@ def test_rows_of_a_split(B, Lb, Hq, Hkv, d, P, variant, split):
     planned_and_named(lambda: dlm.block_attn(q, out, workspace=ws, **segs), out, attn_variant=variant, attn_split=split)
 
 
+@pytest.mark.parametrize("B,Lq,Hq,Hkv,d,L,most,used", [(1, 32, 4, 4, 64, 2048, 16, 8), (2, 32, 28, 4, 128, 1132, 9, 4), (1, 16, 28, 4, 128, 2000, 15, 8)])
+def test_a_workspace_for_the_splits_that_a_call_takes(B, Lq, Hq, Hkv, d, L, most, used):
+    """dlm_block_attn_workspace_bytes covers every number of splits; a buffer for those that the call takes is enough, 16 bytes less are not."""
+    q, k, v = normal(1, B, Lq, Hq, d), normal(2, B, Hkv, L, d), normal(3, B, Hkv, L, d)
+    segs, split = dict(block=(k, v, 0)), B * Lq * Hq * (d + 2) * 4
+    assert dlm.block_attn_workspace_bytes(q, **segs) == most * split
+    outs = []
+    for size in (most * split, used * split, used * split - 16, 0):
+        gw = GuardedWorkspace(size) if size else None
+        out = torch.zeros_like(q)
+        dlm.block_attn(q, out, workspace=gw and gw.ws, **segs)
+        torch.cuda.synchronize()
+        if gw:
+            gw.check()
+        outs.append(out.view(torch.int16))
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[2], outs[3]) and not torch.equal(outs[0], outs[2])
+
+
 @pytest.mark.parametrize("B,L,Hq,Hkv,d,variant", [
     (32, 48, 8, 4, 64, 13), (5, 48, 32, 32, 64, 13), (3, 100, 28, 4, 64, 11),   # 257 - 512 of 32 rows: two key tiles, four
     (5, 100, 16, 2, 128, 13), (5, 100, 8, 1, 128, 11),                          # 35 of them on the fullest XCD, 20
