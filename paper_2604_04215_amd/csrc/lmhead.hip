@@ -1632,7 +1632,9 @@ static void plan_lm_shape(int v_idx, LmParams& p, int m_bound, size_t ws_bytes, 
     lm_blocking(p.n_mc, p.gm, p.gv);
     if (g_lm_block_gv >= 0) { p.gv = g_lm_block_gv > 0 ? g_lm_block_gv : 1; if (g_lm_block_gv == 0) p.gm = 1; }
     const bool second = p.sample || p.conf_mode == DLM_CONF_NEG_ENTROPY;
-    const size_t used = (size_t)(p.n_vt > p.alt_n_vt ? p.n_vt : p.alt_n_vt) * m_bound * sizeof(f32x4) * (second ? 2 : 1);
+    // (the partials of the guessed shape are those of at most alt_cap rows, the second ones placed by the bound)
+    const size_t own = (size_t)p.n_vt * m_bound * (second ? 2 : 1), alt = (size_t)p.alt_n_vt * (p.alt_cap + (second ? (size_t)m_bound : 0));
+    const size_t used = (own > alt ? own : alt) * sizeof(f32x4);
     const int rest = p.M % var.mb;
     const bool even = rest == 0 || 4 * rest > var.mb || p.n_mc > 8;
     if (lm_queued(v_idx) && g_lm_block_gv < 0 && p.n_mc > 1 && p.Dh >= 128 && even && (int64_t)n_full * p.n_mc >= 2 * lm_queue_wgs(cus) &&

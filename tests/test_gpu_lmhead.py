@@ -653,3 +653,28 @@ def test_small_tiles_whatever_the_hidden_size(M, Dh, V, shape):
 def test_every_form_of_a_call_of_a_small_vocabulary(kind, M, Dh, V, counted):
     """Tiles of 128 x 32, 128 x 64 and 128 x 128, all rows counted and with whole chunks past the count."""
     test_every_form_of_a_call_through_a_queue(kind, M, Dh, V, 0, counted)
+
+
+@pytest.mark.parametrize("sample", [False, True])
+@pytest.mark.parametrize("counted", [90, 2200])
+def test_a_guess_of_narrow_tiles_leaves_the_bound_its_queue(counted, sample):
+    """The guess's tiles of 128 tokens make as many partials a row as the workspace has room for, but of its own rows alone: the counters of the
+    bound's queue (one in each of the last eight lines) still fit behind them.  Either launch gives what its shape gives without the other."""
+    M, Dh, V, expected = 2300, 128, 16000, 100
+    g = torch.Generator(device=DEV).manual_seed(71)
+    h = torch.randn(M, Dh, generator=g, device=DEV, dtype=torch.bfloat16)
+    w = torch.randn(V, Dh, generator=g, device=DEV, dtype=torch.bfloat16) * Dh ** -0.25
+    ws = torch.full((dlm.lmhead_workspace_bytes(M, V, sample=sample),), 0xFF, dtype=torch.uint8, device=DEV)
+    outs = []
+    for bound, guess in ((M, expected), (M, 0) if counted > 128 else (128, 0)):
+        conf, lse = (torch.full((M,), float("nan"), device=DEV) for _ in range(2))
+        tok = torch.full((M,), -7, dtype=torch.int32, device=DEV)
+        dlm.lmhead_confidence(h, w, conf, tok, M=bound, m_dev=dev(np.asarray([counted], np.int32)), lse=lse, workspace=ws, M_expected=guess,
+                              **(dict(sample_seed=5, sample_step=1) if sample else {}))
+        if guess:
+            drawn = ws[-512:].view(torch.int32)[::16].cpu()
+            assert (drawn >= 0).all() and (counted <= 128 or (drawn > 0).all()), drawn
+        outs.append((conf, lse, tok))
+    for a, b in zip(*outs):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    assert not outs[0][0][:counted].isnan().any() and outs[0][0][counted:].isnan().all()
