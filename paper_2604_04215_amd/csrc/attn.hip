@@ -901,64 +901,106 @@ int g_attn_remap = 7;    // XCD-grouped grids: bit 0 forward and dQ, bit 1 longe
 // Workgroups of the fullest XCD (32 CUs) of a grid that set_remap makes of nx tiles for each of n_groups
 static int64_t xcd_load(int64_t n_groups, int64_t nx) {
     GridRemap m;
-    return set_remap(m, n_groups, (int)nx, false) / 8;
+    const int64_t n_wg = set_remap(m, n_groups, (int)nx, false);
+    return n_wg > 0 ? n_wg / 8 : (int64_t)1 << 31;   // (0: more than a launch holds)
+}
+
+// What a launch of few workgroups takes, ns: ns workgroups share the keys of each of nx row tiles of BH (sequence, KV head), in the kernel shape `variant`.
+// Start and end of a workgroup, its steps over the keys (a tile for each of its wavefronts), a tile of keys wherever it is read, the merge of a split; above one
+// workgroup a CU on the fullest XCD they share it (d = 64) or take turns.  No less than memory takes at 6.8 TB/s for keys that are read once
+// for every XCD their row tiles are on.  Fitted to 5000 calls of 1000 - 12000 keys, each in every shape with up to 16 splits: within 5 % for nine in
+// ten that are one workgroup a CU, 8 % above that.
+static int64_t attn_ns(int variant, int d, int64_t BH, int64_t nx, int64_t tiles, int64_t ns, int64_t R) {
+    static const struct { int variant, waves, cost[2][2][3]; } shapes[] = {   // [d == 128][above one a CU]: start, step, tile (ps)
+        {12, 4, {{{3400, 970, 300}, {3400, 970, 300}}, {{4400, 1400, 620}, {4400, 1400, 620}}}},
+        {10, 8, {{{3900, 1190, 340}, {3900, 1190, 340}}, {{4500, 2100, 990}, {4500, 2100, 990}}}},
+        {16, 8, {{{4400, 1150, 110}, {7700, 2050, 150}}, {{6100, 1830, 160}, {11100, 3200, 220}}}},
+        {11, 4, {{{3300, 1220, 160}, {4500, 1370, 80}}, {{4850, 1710, 150}, {9000, 3370, 130}}}},
+        {13, 2, {{{4900, 843, 60}, {8700, 1290, 0}}, {{6400, 1100, 25}, {12300, 2100, 100}}}},
+    };
+    const auto* s = shapes;
+    while (s->variant != variant) ++s;
+    GridRemap m;
+    const bool wide = d == 128, above = R > 32 && set_remap(m, BH, (int)(nx * ns), false) > 256;
+    int64_t copies = 1;
+    if (R > 32)
+        while (copies < m.sp && copies < nx && copies * ns % m.sp) ++copies;   // row tiles r and r + copies of a split are on one XCD
+    const int* c = s->cost[wide][above];
+    const int64_t run = c[0] + c[1] * ((tiles + s->waves * ns - 1) / (s->waves * ns)) + c[2] * BH * nx * tiles / 1000;
+    const int64_t mem = 4000 + BH * tiles * copies * (wide ? 2400 : 1200) / 1000;
+    const int64_t merge = ns == 1 ? 0 : wide ? 2800 + 210 * ns + 270 * BH * R * ns / 1000 : 2500 + 240 * ns + 130 * BH * R * ns / 1000;
+    return (run > mem ? run : mem) + merge;
 }
 
 // Is it the longest workgroup that a block-causal launch over whole sequences waits for?  Eight wavefronts take it through its keys in 0.65 of the
-// time of four, but fewer of them fit a CU, so it is worth it while a CU's share of the work, with six tiles for the start and end of a workgroup, is at most
-// 1.3 (d = 128, one workgroup a CU) or 1.8 (d = 64, two) of the longest.  A row tile sees half the keys in the mean (of a packed batch: of lengths
-// spread evenly up to the longest, which is a guess and which the XCDs may share unevenly: 0.6 and 1.2).  Us, four / eight wavefronts: 1 x 3000 tokens, 16/2
-// heads of 128 109 / 70, 2 x 600, 32/8 27.8 / 20.9, 10 x 2000, 4 heads of 64 86 / 62; left out by the line: 4 x 500, 32 heads of 128 30.1 / 36.1, 16
-// packed of 1 - 533, 16/2 heads 24.6 / 35.0, 16 x 1500, 4 heads of 64 57 / 64.  Of 1588 launches of 257 - 1100 workgroups none is slower by more than 3 % for it.
-static bool two_groups_pay(const AttnParams& p, int d, int64_t tiles, int64_t n_wg, int64_t nx) {
-    if (tiles < 12) return false;
+// time of four, but fewer of them fit a CU, so it is worth it while the fullest XCD's share of the work a CU, with six tiles for the start and end of a
+// workgroup, is at most 1.25 (d = 128, one workgroup a CU) or 2.0 (d = 64, two) of the longest.  A row tile sees half the keys in the mean (of a
+// packed batch: of lengths spread evenly up to the longest, a guess, and over all XCDs: 0.85 and 1.6).  Us, four / eight wavefronts: 1 x 3000 tokens, 16/2
+// heads of 128 109 / 70, 2 x 600, 32/8 27.8 / 20.9, 10 x 2000, 4 heads of 64 86 / 62, 6 packed of up to 1250, 5162 in all, 8/2 heads 53 / 36; left out: 4 x 500, 32
+// heads of 128 30.1 / 36.1, 16 packed of 1 - 533, 16/2 heads 24.6 / 35.0.
+static bool two_groups_pay(const AttnParams& p, int d, int64_t tiles, int64_t nx) {
+    if (tiles <= 12) return false;
     const double longest = (double)tiles;
-    double wgs = (double)n_wg, mean = longest * (double)(nx + 1) / (2.0 * (double)nx);
+    double wgs = 8.0 * (double)xcd_load((int64_t)p.B * p.Hkv, nx), mean = longest * (double)(nx + 1) / (2.0 * (double)nx);
     if (p.cu) {
         const double m = (double)p.total / p.B, hi = p.Lq, lo = 2 * m > hi ? 2 * m - hi : 0;
         wgs = ((double)p.total * p.g / 128 + p.B / 2) * p.Hkv;
         mean = (lo * lo + lo * hi + hi * hi) / (3 * 64 * m) + 2.0 / p.g;
     }
-    return wgs * (mean + 6) <= (d == 64 ? (p.cu ? 1.2 : 1.8) : (p.cu ? 0.6 : 1.3)) * 256 * longest;
+    return wgs * (mean + 6) <= (d == 64 ? (p.cu ? 1.6 : 2.0) : (p.cu ? 0.85 : 1.25)) * 256 * longest;
 }
 
-// The kernel shape the planner picks for a problem (0 = "automatic" resolved).  Measured on MI355X (us, GPU time):
+// The kernel shape the planner picks for a problem.  Measured on MI355X (us, GPU time; profiles/attention_forward_few_workgroups_ab.md):
 //   g * Lq <= 32 (every rollout step): one key-split workgroup per (sequence, KV head); sized for two per CU it is
-//     8 - 10 % faster than sized for one even when only one is resident (c2 22.4 -> 19.7, c3 72 -> 66, c5a 173 -> 162);
-//   more rows: 128-row workgroups; with at most one of them per CU, eight wavefronts in two key groups (two wavefronts
-//     per SIMD from one workgroup: c4 39.1 -> 32.2), otherwise two or three four-wavefront workgroups per CU;
-//   where 32-row workgroups (K/V re-read per row tile, through one L2) are at most one per CU, a wavefront's walk over its key tiles is
-//     all the time there is, about 2 us a tile of d = 128 and 1 of d = 64, so eight wavefronts share the keys of 32 rows.  Us, before
-//     (128 rows, or four wavefronts) / now: 8 x 28/4 heads x 500 keys 14.1 / 11.8, 20 x 16/2 x 8062 120 / 69, 4 x 14/2 of 64 x 833 13.2 / 9.2,
-//     1 x 3756 tokens, 4 heads of 64, blocks of 32 (472 workgroups) 71 / 30.  At d = 64 three workgroups of four wavefronts fit a CU: up
-//     to 512 they lead with 4 - 47 tiles (6 x 348 tokens, 4 heads 12.1 / 8.7; with 640 workgroups 8.7 / 8.4, with 752 7.6 / 10.2; 32 x 48 tokens, 8/4
-//     heads, two tiles 5.3 / 5.9).  Not where the grid's grouping gives an XCD more than 32 of them and one fits a CU: 5 x 100 tokens, 16/2 heads of
-//     128, 250 workgroups, 35 on the fullest XCD 9.0 / 11.7;
-//   g * Lq <= 32 likewise: 24 x 4 heads of 64 x 500 keys 9.1 / 8.0, 2 x 32/8 of 128 x 1024 17.6 / 15.3; at d = 128 only where the keys are
-//     not split across workgroups, with which the two are even;
-//   under a block-causal mask over whole sequences, whose workgroups differ in length, the eight wavefronts of two key groups also where there are more
-//     than one such workgroup a CU, as long as a CU is given little more than the longest takes (see two_groups_pay);
-//   513 - 767 workgroups of d = 128 (not of a packed batch, of which fewer have rows) at three a CU, in one round: 3 x 800 tokens, 28/4 heads
-//     58.6 / 46.4, 44 shapes 0.78 - 0.89 of the time at two.  Under a block-causal mask over whole sequences only up to 12 row tiles a KV head: with
-//     more the second round that two a CU leave is of short ones, and all three at once wait for the longest (6 x 2000 tokens, 8/2 heads, 63 row
-//     tiles 88 / 108, 4 x 1300, 16/8, 21 of them 57 / 65; but 12 x 420, 16/8, 7 of them 34.6 / 27.9).
+//     8 - 10 % faster than sized for one even when only one is resident (c2 22.4 -> 19.7, c3 72 -> 66, c5a 173 -> 162); with few of them
+//     and keys enough eight wavefronts: 24 x 4 heads of 64 x 500 keys 9.1 / 8.0, 2 x 32/8 of 128 x 1024 17.6 / 15.3;
+//   where 32-row workgroups (K/V re-read per row tile, through one L2) are at most one per CU on every XCD, a wavefront's walk over its key tiles is all the
+//     time there is, about 2 us a tile of d = 128 and 1 of d = 64, so eight wavefronts share the keys of 32 rows from 6 tiles on, four below: 0.4 - 0.9 of the
+//     time of 128 rows (8 x 28/4 heads x 500 keys 14.1 / 11.8);
+//   at d = 64, where three workgroups of four wavefronts fit a CU, also up to two a CU (from 3 tiles on: 6 x 348 tokens, 4 heads 12.1 / 8.7; two tiles 5.3 /
+//     5.9; above two a CU 1.04 - 1.18 of the time of 128 rows), but where 128-row workgroups are at most one a CU and read keys for fewer XCDs only
+//     if attn_ns agrees (63 x 16 rows, 16/2 heads, 305 keys 9.6 / 12.0).  At d = 128 one fits a CU: 5 x 100 tokens, 16/2 heads, 35 on the fullest XCD 9.0 / 11.7;
+//     in a packed batch most are empty, and they are taken where those of its tokens fill 20 of an XCD's 32 CUs (11 x 71 tokens, 8/2 heads 8.9 / 6.7; at 25, 19 x
+//     69, 4/4 8.9 / 12.8), or with 16 tiles and up to 35 on an XCD (11 of up to 620 tokens, 1 head 19.9 / 15.0);
+//   under a block-causal mask over whole sequences, whose workgroups differ in length, from 24 tiles on up to 256 workgroups of 32 rows (d = 64: from 16
+//     on up to 512) however they are spread (0.7 of the time), and eight wavefronts on 128 rows as long as a CU is given little more than the longest
+//     takes (two_groups_pay);
+//   otherwise 128-row workgroups; with at most one of them per CU, eight wavefronts in two key groups (two wavefronts per SIMD from one workgroup:
+//     c4 39.1 -> 32.2), otherwise two or three four-wavefront workgroups per CU: three from 768 on and, at d = 128 (not of a packed batch, of which fewer have
+//     rows), above two a CU on the fullest XCD, 0.80 - 0.88 of the time up to three (3 x 800 tokens, 28/4 heads 58.6 / 46.4).  Under a block-causal mask over
+//     whole sequences of 25 - 64 key tiles and more than 12 row tiles two up to there: the second round is of short ones, and all three at once wait for the
+//     longest (6 x 2000 tokens, 8/2 heads 88 / 108, 4 x 1300, 16/8 57 / 65; but 12 x 420, 16/8 34.6 / 27.9).
 // tiles: key tiles of a (sequence, KV head), the most one can have
-static int plan_variant(const AttnParams& p, int d, bool bc, int64_t tiles, bool rows32) {
+static int plan_variant(const AttnParams& p, int d, bool bc, int64_t tiles) {
     if (g_attn_variant != 0) return g_attn_variant;
-    const int64_t BH = (int64_t)p.B * p.Hkv;
+    const int64_t BH = (int64_t)p.B * p.Hkv, nx32 = (p.R + 31) / 32, nx128 = (p.R + 127) / 128;
     const int ns = p.nsplit > 1 ? p.nsplit : 1;
-    const int64_t wgs128 = BH * ((p.R + 127) / 128) * ns, wgs32 = BH * ((p.R + 31) / 32) * ns;
+    const int64_t wgs32 = BH * nx32 * ns, wgs128 = BH * nx128 * ns;
     if (p.R <= 32)                          // waves split the keys, merge on chip
         return (d == 64 ? wgs32 <= 256 && tiles >= 12 * ns : ns == 1 && wgs32 <= 160 && tiles >= 16) ? 10 : 12;
-    if (ns == 1 || rows32) {
-        const bool even = wgs32 <= 256 && xcd_load(BH, wgs32 / BH) <= 32;   // no CU is dealt two
-        if (wgs32 <= 256 && (even || d == 64 || wgs128 <= 64)) return even && tiles >= 6 ? 16 : 11;
-        if (d == 64 && wgs32 <= 512 && tiles >= 4) return tiles >= 48 ? 16 : 11;
+    const bool whole = bc && ns == 1 && 2 * (int64_t)p.Lq + 64 >= 32 * tiles;   // not a block at the end, where all workgroups are equally long
+    if (ns == 1 && wgs32 <= 512) {
+        const int64_t load = xcd_load(BH, nx32);
+        if (load <= 32) return tiles >= 6 ? 16 : 11;
+        const bool two = d == 64 && load <= 64 && tiles >= 3;
+        if (p.cu) {
+            const int64_t live = ((int64_t)p.total * p.g / 32 + p.B / 2) * p.Hkv;
+            if (two) return tiles >= 48 ? 16 : 11;
+            if (d == 128 && wgs32 <= 256 && (load * live <= 20 * wgs32 || (load <= 35 && tiles >= 16))) return 11;
+        } else if (whole) {
+            if (two || (d == 64 ? tiles >= 16 : tiles >= 24 && wgs32 <= 256)) return tiles >= 24 ? 16 : 11;
+        } else if (two) {
+            const int v = tiles >= 48 ? 16 : 11;
+            if (wgs128 > 256 || attn_ns(v, d, BH, nx32, tiles, 1, p.R) < attn_ns(13, d, BH, nx128, tiles, 1, p.R)) return v;
+        }
     }
     if (wgs128 <= 256) return 13;           // one 128-row workgroup per CU at most: eight wavefronts, two key groups
-    const bool whole = bc && ns == 1 && 2 * (int64_t)p.Lq + 64 >= 32 * tiles;   // not a block at the end, where all workgroups are equally long
-    if (whole && two_groups_pay(p, d, tiles, wgs128, (p.R + 127) / 128)) return 13;
-    if (wgs128 >= (d == 128 && !p.cu && !(whole && p.R > 12 * 128) ? 513 : 768)) return 6;   // 128-row workgroups, three resident per CU (softmax of one overlaps MFMA of another)
+    if (whole && two_groups_pay(p, d, tiles, nx128)) return 13;
+    if (wgs128 >= 768) return 6;            // 128-row workgroups, three resident per CU (softmax of one overlaps MFMA of another)
+    if (d == 128 && !p.cu && ns == 1) {
+        const int64_t load = xcd_load(BH, nx128);
+        if (load > 64 && !(whole && nx128 > 12 && tiles > 24 && tiles <= 64 && load <= 96)) return 6;
+    }
     return 4;                               // 128-row workgroups, two resident per CU, deeper prefetch
 }
 
@@ -990,31 +1032,40 @@ static int plan_nsplit(const dlm_attn_args* a) {
     return n < 1 ? 1 : (int)n;
 }
 
-// How many of the n_max splits that the workspace is sized for a call takes, and whether for 32-row workgroups (rows32).  Those read K and V once for
-// every 32 rows, and their eight wavefronts walk the keys of a split in steps of eight tiles; the 128-row ones read them once for 128 rows, in as many
-// splits as fill the chip.  Estimated in ns from some 6000 calls of 1000 - 12000 keys, each to 10 % for four in five (ends and merge, a step, a tile
-// from L2): 4 % is the most that the choice lost in them.  Us, 128 / 32 rows: 1 x 32/8 heads of 128 x 8192 keys 26.3 / 21.5, 4 x 28/4 x 2048 24.9 / 20.6,
-// x 4096 26.3 / 29.1; heads of 64, where 160 workgroups without a split are too few for long keys: 20 x 14/2, 16 rows x 8000 30 / 42, 5 x 16/2, 64 x
-// 12000 39 / 61.  Fewer, longer splits where the tiles are few, as the merge costs more with each: 1 x 4 heads of 64 x 2048 keys, 16 / 8 splits
-// 13.8 / 10.4; 24 x 4 heads of 64 x 1024 keys, 2 / none 12.4 / 10.4.  Of at most eight tiles, two steps of four wavefronts: 1 x 1 head of 128 x
-// 4000 keys, 15 / 16 splits 14.9 / 13.8, 2 x 16/2, 4 rows x 3000, 11 / 12 splits 15.5 / 14.2.
-static int plan_use_nsplit(const AttnParams& p, int d, int64_t tiles, int n_max, bool& rows32) {
-    if (n_max <= 1 || g_attn_split >= 2 || g_attn_variant != 0) return n_max;
-    const int64_t BH = (int64_t)p.B * p.Hkv, n32 = BH * ((p.R + 31) / 32), n128 = BH * ((p.R + 127) / 128);
-    const int64_t eights = (tiles + 7) / 8;
-    if (p.R <= 32) return d == 64 && (tiles < 40 || (tiles < 48 && n_max < 4)) ? 1 : (int)(eights < n_max ? eights : n_max);
-    if (n32 > 256) return n_max;
-    int64_t n = 256 / n32 < eights ? 256 / n32 : eights;
-    if (tiles < 48 && (d == 64 || n32 > 64)) n = 1;
-    if (n > n_max) n = n_max;
-    while (n > 1 && xcd_load(BH, n32 / BH * n) > 32) --n;
-    if (d == 128 && xcd_load(BH, n32 / BH * n) > 32) return n_max;
-    const int64_t steps = (tiles + 8 * n - 1) / (8 * n), ends32 = n > 1 ? 5200 : 0;
-    const int64_t t32 = ends32 + (d == 64 ? 4800 + 1000 * steps + 86 * n32 * tiles / 1000 : 6200 + 1460 * steps + 420 * n32 * tiles / 1000);
-    const int64_t t128 = 210 * n_max + (d == 64 ? 11200 + 1500 * n128 * tiles / 1000 : 14200 + 2300 * n128 * tiles / 1000);
-    if (t32 >= t128) return n_max;
-    rows32 = true;
-    return (int)n;
+// The shape of a call whose keys the workspace lets n_max > 1 workgroups share, and how many do (n; 1: none): the least by attn_ns of
+//   up to 32 rows: no split, splits of at most eight tiles (two steps of four wavefronts), all n_max;
+//   128-row workgroups in n_max splits, and in as many as leave no CU two of them (not where a causal mask makes most of them short: 6 x 2674 tokens, 1
+//     head of 128, 2 splits / 1 45 / 63);
+//   32-row workgroups in as many splits of at least eight tiles as leave no CU two of them, and in one.
+// Us, 128 / 32 rows: 1 x 32/8 heads of 128 x 8192 keys 26.3 / 21.5, 4 x 28/4 x 2048 24.9 / 20.6, x 4096 26.3 / 29.1; 7 x 32 rows, 16/2 x 2269 keys
+// 32.3 / 21.7; 31 x 8 rows, 16/2 x 7971, keys that 32-row workgroups read on two XCDs 49 / 80; heads of 64, 160 workgroups too few for long keys: 20 x 14/2, 16 rows x
+// 8000 30 / 42.  Fewer, longer splits where the tiles are few, as the merge costs more with each: 1 x 4 heads of 64 x 2048 keys, 16 / 8 splits
+// 13.8 / 10.4; 24 x 4 heads of 64 x 1024 keys, 2 / none 12.4 / 10.4; but 1 x 1 row, 32/8 heads of 128 x 1012 keys, 4 / 8 splits 10.9 / 9.7.
+static int plan_split(const AttnParams& p, int d, bool bc, int64_t tiles, int n_max, int& n) {
+    const int64_t BH = (int64_t)p.B * p.Hkv, eights = (tiles + 7) / 8 < n_max ? (tiles + 7) / 8 : n_max;
+    int64_t best = 0;
+    int variant = 0;
+    const auto consider = [&](int v, int64_t nx, int64_t ns) {
+        const int64_t t = attn_ns(v, d, BH, nx, tiles, ns, p.R);
+        if (variant == 0 || t < best) { best = t; variant = v; n = (int)ns; }
+    };
+    if (p.R <= 32) {
+        for (const int64_t ns : {(int64_t)1, eights, (int64_t)n_max})
+            consider((d == 64 ? BH * ns <= 256 && tiles >= 12 * ns : ns == 1) ? 10 : 12, 1, ns);
+        return variant;
+    }
+    const int64_t nx32 = (p.R + 31) / 32, nx128 = (p.R + 127) / 128, wgs32 = BH * nx32;
+    int64_t ns = n_max;
+    while (ns > 1 && !(bc && nx128 > 2) && xcd_load(BH, nx128 * ns) > 32) --ns;
+    consider(13, nx128, ns);
+    if (ns < n_max) consider(13, nx128, n_max);
+    if (wgs32 > (d == 64 ? 512 : 256)) return variant;
+    ns = 256 / wgs32 < eights ? 256 / wgs32 : eights;
+    while (ns > 1 && xcd_load(BH, nx32 * ns) > 32) --ns;
+    if (ns > 1) consider(16, nx32, ns);
+    if (xcd_load(BH, nx32) <= 32) consider(16, nx32, 1);
+    else if (d == 64) consider(tiles >= 48 ? 16 : 11, nx32, 1);
+    return variant;
 }
 
 // Are issue priorities by phase worth it?  In launches of three and more rounds of workgroups (three a CU on 256 CUs) whose rows see 24 and
@@ -1031,10 +1082,9 @@ static bool attn_deep(const AttnParams& p) {
 }
 
 template <int D, bool BC>
-static int launch_attn(const AttnParams& p, int64_t tiles, bool rows32, hipStream_t st) {
+static int launch_attn(const AttnParams& p, int variant, hipStream_t st) {
     const int64_t BH = (int64_t)p.B * p.Hkv;
     const int ns = p.nsplit > 1 ? p.nsplit : 1;
-    int variant = plan_variant(p, D, BC, tiles, rows32);
     if (variant == 11 || variant == 16 || (variant == 1 && p.R > 32)) {
         // 32-row workgroups whose wavefronts split the keys, several row tiles per (sequence, KV head), XCD-grouped
         AttnParams q = p;
@@ -1237,19 +1287,22 @@ extern "C" int dlm_block_attn(const dlm_attn_args* a, void* stream) {
     p.remap = no_remap();
     // The key split across workgroups is taken only when the caller brought the workspace that its own number of splits needs.
     p.nsplit = 1; p.part_o = nullptr; p.part_ml = nullptr;
-    const int64_t tiles = key_tiles(a);
-    bool rows32 = false;   // the split is planned for 32-row workgroups
-    const int n = plan_use_nsplit(p, a->d, tiles, plan_nsplit(a), rows32);
-    if (n > 1 && a->workspace && a->workspace_bytes >= split_workspace_bytes(a, n) && aligned16(a->workspace)) {
-        const size_t rows_total = (size_t)a->B * a->Hq * a->Lq;
-        p.nsplit = n;
-        p.part_o = (float*)a->workspace;
-        p.part_ml = p.part_o + (size_t)n * rows_total * a->d;
-    }
-    hipStream_t st = (hipStream_t)stream;
     const bool bc = a->mask_mode == DLM_MASK_BLOCK_CAUSAL;
-    if (a->d == 128) rc = bc ? launch_attn<128, true>(p, tiles, rows32, st) : launch_attn<128, false>(p, tiles, rows32, st);
-    else rc = bc ? launch_attn<64, true>(p, tiles, rows32, st) : launch_attn<64, false>(p, tiles, rows32, st);
+    const int64_t tiles = key_tiles(a);
+    const int n_max = plan_nsplit(a);
+    int n = n_max, variant = 0;
+    if (n_max > 1 && g_attn_split < 2 && g_attn_variant == 0) variant = plan_split(p, a->d, bc, tiles, n_max, n);
+    if (n > 1) {
+        if (a->workspace && a->workspace_bytes >= split_workspace_bytes(a, n) && aligned16(a->workspace)) {
+            p.nsplit = n;
+            p.part_o = (float*)a->workspace;
+            p.part_ml = p.part_o + (size_t)n * a->B * a->Hq * a->Lq * a->d;
+        } else variant = 0;
+    }
+    if (variant == 0) variant = plan_variant(p, a->d, bc, tiles);
+    hipStream_t st = (hipStream_t)stream;
+    if (a->d == 128) rc = bc ? launch_attn<128, true>(p, variant, st) : launch_attn<128, false>(p, variant, st);
+    else rc = bc ? launch_attn<64, true>(p, variant, st) : launch_attn<64, false>(p, variant, st);
     if (rc != DLM_OK || p.nsplit <= 1) return rc;
     const int64_t rows_total = (int64_t)a->B * a->Hq * a->Lq;
     if (a->d == 128) hipLaunchKernelGGL(attn_merge_kernel<128>, dim3((unsigned)((rows_total + 7) / 8)), dim3(256), 0, st, p);

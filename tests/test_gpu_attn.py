@@ -467,7 +467,7 @@ def normal(seed, *shape):
 @pytest.mark.parametrize("B,L,Hq,Hkv,d,variant", [
     (4, 500, 32, 32, 128, 4), (2, 1000, 32, 32, 128, 4), (16, 1500, 4, 4, 64, 6),   # a CU would get too much of them one after another
     (1, 1500, 16, 2, 128, 13), (2, 600, 32, 8, 128, 13), (10, 1300, 4, 4, 64, 13),   # the longest is what the launch waits for
-    (-16, 533, 16, 2, 128, 6), (-8, 1000, 16, 2, 128, 6), (-4, 1600, 16, 2, 64, 13),   # packed: lengths from 1 to L
+    (-16, 533, 16, 2, 128, 6), (-8, 1000, 16, 2, 128, 6), (-4, 1600, 16, 2, 64, 13), (-6, 1250, 8, 2, 128, 13), (-11, 620, 1, 1, 128, 11),   # packed: lengths from 1 to L
 ])
 def test_eight_wavefronts_under_a_causal_mask_where_the_longest_decides(B, L, Hq, Hkv, d, variant):
     mask = dict(mask_mode=dlm.MASK_BLOCK_CAUSAL, block_size=32)
@@ -504,8 +504,9 @@ for B, L, Hq, Hkv, bs in json.loads(sys.argv[1]):
 
 def test_workgroups_a_cu_for_less_than_768():
     """Two or three workgroups a CU give the same bits: the shape is read from the kernel's name (in a process of its own, which a profiler follows)."""
-    cases = [(6, 2000, 8, 2, 4, 2), (4, 1300, 16, 8, 4, 2), (4, 2600, 8, 8, 32, 2),   # causal, more than 12 row tiles of 128: two
-             (12, 420, 16, 8, 4, 3), (16, 640, 8, 4, 32, 3), (3, 800, 28, 4, 0, 3), (3, 3000, 8, 2, 0, 3)]   # few row tiles, no mask: three
+    cases = [(6, 2000, 8, 2, 4, 2), (4, 1300, 16, 8, 4, 2),                             # causal, 25 - 64 key tiles: two
+             (12, 420, 16, 8, 4, 3), (16, 640, 8, 4, 32, 3), (19, 264, 16, 2, 32, 3), (4, 2600, 8, 8, 32, 3),   # fewer, more: three
+             (3, 800, 28, 4, 0, 3), (3, 3000, 8, 2, 0, 3)]                              # and without a mask
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     run = subprocess.run([sys.executable, "-c", KERNEL_NAMES, json.dumps([c[:5] for c in cases])], cwd=root, capture_output=True, text=True, timeout=100)
     assert run.returncode == 0, run.stderr[-2000:]
@@ -517,8 +518,10 @@ def test_workgroups_a_cu_for_less_than_768():
 
 @pytest.mark.parametrize("B,Lb,Hq,Hkv,d,P,variant,split", [
     (20, 16, 14, 2, 64, 8000, 13, 6), (5, 64, 16, 2, 64, 12000, 13, 6), (20, 48, 4, 4, 128, 8000, 13, 3),   # too few 32-row workgroups for keys that long
-    (4, 32, 14, 2, 64, 4000, 16, 4), (4, 32, 8, 2, 128, 2000, 16, 8), (1, 32, 32, 8, 128, 8000, 16, 8),     # but enough here
+    (18, 64, 7, 1, 64, 3891, 13, 3), (25, 64, 4, 4, 128, 4577, 13, 2), (31, 8, 16, 2, 128, 7963, 13, 4),    # more than one a CU; keys read on two XCDs
+    (4, 32, 14, 2, 64, 4000, 16, 4), (4, 32, 8, 2, 128, 2000, 16, 8), (1, 32, 32, 8, 128, 8000, 16, 8), (7, 32, 16, 2, 128, 2237, 16, 2),   # but enough here
     (1, 4, 4, 4, 128, 4000, 12, 16), (2, 4, 14, 2, 64, 3000, 12, 12), (8, 4, 4, 4, 64, 1300, 12, 6), (1, 16, 28, 4, 128, 4000, 16, 16),   # no split of nine tiles
+    (40, 16, 16, 2, 64, 289, 11, 1), (63, 16, 16, 2, 64, 289, 13, 1),   # two 32-row workgroups a CU; and keys read on four XCDs for them
 ])
 def test_rows_of_a_split(B, Lb, Hq, Hkv, d, P, variant, split):
     q, k, v = normal(1, B, Lb, Hq, d), normal(2, B, Hkv, P + Lb, d), normal(3, B, Hkv, P + Lb, d)
@@ -528,7 +531,7 @@ def test_rows_of_a_split(B, Lb, Hq, Hkv, d, P, variant, split):
     planned_and_named(lambda: dlm.block_attn(q, out, workspace=ws, **segs), out, attn_variant=variant, attn_split=split)
 
 
-@pytest.mark.parametrize("B,Lq,Hq,Hkv,d,L,most,used", [(1, 32, 4, 4, 64, 2048, 16, 8), (2, 32, 28, 4, 128, 1132, 9, 4), (1, 16, 28, 4, 128, 2000, 15, 8)])
+@pytest.mark.parametrize("B,Lq,Hq,Hkv,d,L,most,used", [(1, 32, 4, 4, 64, 2048, 16, 8), (4, 32, 8, 2, 128, 2000, 15, 8), (1, 16, 28, 4, 128, 2000, 15, 8)])
 def test_a_workspace_for_the_splits_that_a_call_takes(B, Lq, Hq, Hkv, d, L, most, used):
     """dlm_block_attn_workspace_bytes covers every number of splits; a buffer for those that the call takes is enough, 16 bytes less are not."""
     q, k, v = normal(1, B, Lq, Hq, d), normal(2, B, Hkv, L, d), normal(3, B, Hkv, L, d)
@@ -547,7 +550,8 @@ def test_a_workspace_for_the_splits_that_a_call_takes(B, Lq, Hq, Hkv, d, L, most
 
 
 @pytest.mark.parametrize("B,L,Hq,Hkv,d,variant", [
-    (32, 48, 8, 4, 64, 13), (5, 48, 32, 32, 64, 13), (3, 100, 28, 4, 64, 11),   # 257 - 512 of 32 rows: two key tiles, four
+    (32, 48, 8, 4, 64, 13), (5, 48, 32, 32, 64, 13), (7, 75, 16, 2, 64, 11), (3, 100, 28, 4, 64, 11),   # 257 - 512 of 32 rows: two key tiles, three, four
+    (17, 132, 7, 1, 64, 13), (10, 112, 14, 2, 64, 13),                          # more than two of them a CU on the fullest XCD
     (5, 100, 16, 2, 128, 13), (5, 100, 8, 1, 128, 11),                          # 35 of them on the fullest XCD, 20
 ])
 def test_short_sequences_on_few_rows(B, L, Hq, Hkv, d, variant):
