@@ -396,30 +396,35 @@ int dlm_kv_refresh(const dlm_kv_seg *src, int32_t B, int32_t Hkv, int32_t d,
  * dlm_lmhead_confidence_static); every default is the planner's choice, and every setting computes the same function.
  *   "attn_variant"  0 = pick the attention kernel shape from the problem shape (default);
  *                   1 = 32-row workgroups whose wavefronts split the keys (needs g*Lq <= 32, otherwise falls back to 2),
- *                       sized for one workgroup per CU; 12 = the same sized for two (the planner's choice for g*Lq <= 32);
+ *                       sized for one workgroup per CU; 12 = the same sized for two (chosen for g*Lq <= 32, see 10);
  *                   2 = 128-row; 3 = 256-row workgroups (one per CU);
  *                   4..7 = 128-row workgroups sized for 2, 3, 3, 4 resident workgroups per CU;
- *                   8..10 = key-split alternatives (deeper prefetch, 8 wavefronts) for g*Lq <= 32;
+ *                   8..10 = key-split alternatives (deeper prefetch, 8 wavefronts) for g*Lq <= 32 (10, eight wavefronts, is
+ *                       chosen where at most 256 workgroups, at d = 128 160 and no split, have enough keys for them);
  *                   11 = 32-row key-split workgroups for any row count, the row tiles of one (sequence, KV head) grouped
- *                       on one XCD (chosen when 128-row workgroups would leave most CUs idle and no workspace is given);
+ *                       on one XCD (chosen where 32-row workgroups are at most one per CU, at d = 64 two, and have few keys);
  *                   13, 14 = 128-row workgroups of 8 wavefronts in two key groups, combined through LDS (prefetch depth 1, 2;
- *                       13 is chosen when there is at most one 128-row workgroup per CU);
+ *                       13 is chosen when there is at most one 128-row workgroup per CU but too many of 32 rows for 11 and
+ *                       16, and, under a block-causal mask over whole sequences, where the longest workgroup decides);
  *                   15 = software-pipelined 128-row workgroups (d = 128; softmax of one key tile woven between the MFMAs
  *                       of the next);
- *                   16 = 11 with eight wavefronts (chosen up to one such workgroup per CU).
+ *                   16 = 11 with eight wavefronts (chosen up to one such workgroup per CU, at d = 64 and many keys two).
  *   "attn_split"    0 = the library decides whether several workgroups share the keys of a row tile (default: only with at
- *                   most 128 workgroups and at least 32 key tiles, and only when the call brings the workspace);
+ *                   most 128 workgroups and at least 32 key tiles, into as many as give every CU a workgroup or into
+ *                   fewer and longer ones, and only when the call brings the workspace for those);
  *                   1 = never; 2..16 = that many (lowered to keep four key tiles per workgroup).
  *   "lmhead_variant" -1 = pick the LM-head kernel shape (workgroup tile, wavefront layout, prefetch depth) from M
+ *                   and, with a vocabulary so small that M's own shape leaves CUs idle, from V and the CU count
  *                   (default); >= 0 forces one entry of the library's shape table.
  *   "lmhead_block"  -1 = automatic blocking of LM-head workgroups per XCD (default); 0 = none (row chunks of one
  *                   vocabulary tile side by side); 1..8 = that many vocabulary tiles per block.  0..8 also give every
  *                   tile a workgroup of its own: no launch takes its tiles from a queue.
  *   "lmhead_nt"     1 = when a launch has one row chunk (every element of W used once) fetch W with non-temporal
  *                   loads (default); 0 = never.
- *   "lmhead_cus"    CU count that the LM head's half-height tail and its queue of tiles assume (the rules of both, and the
- *                   number of workgroups that share a queue): 0 = the device's (default); n > 0 = n (tests: makes
- *                   small vocabularies take both); -1 = the device's, and no half-height tail (the queue stays).
+ *   "lmhead_cus"    CU count that the LM head's half-height tail, its queue of tiles and its shapes for small vocabularies
+ *                   assume (their rules, and the number of workgroups that share a queue): 0 = the device's (default);
+ *                   n > 0 = n (tests: makes small vocabularies take tail and queue); -1 = the device's, and no half-height
+ *                   tail (the queue stays).
  *   "attn_nt"       1 = non-temporal K/V loads when one workgroup is the only reader of its (sequence, KV head)
  *                   (g*Lq <= 32; default); 0 = never.
  *   "kv_copy_unroll" 16-byte pieces per thread of the copy kernel (1, 2, 4 or 8), plus 16 when K and V are copied by

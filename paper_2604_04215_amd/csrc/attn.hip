@@ -908,8 +908,8 @@ static int64_t xcd_load(int64_t n_groups, int64_t nx) {
 // What a launch of few workgroups takes, ns: ns workgroups share the keys of each of nx row tiles of BH (sequence, KV head), in the kernel shape `variant`.
 // Start and end of a workgroup, its steps over the keys (a tile for each of its wavefronts), a tile of keys wherever it is read, the merge of a split; above one
 // workgroup a CU on the fullest XCD they share it (d = 64) or take turns.  No less than memory takes at 6.8 TB/s for keys that are read once
-// for every XCD their row tiles are on.  Fitted to 5000 calls of 1000 - 12000 keys, each in every shape with up to 16 splits: within 5 % for nine in
-// ten that are one workgroup a CU, 8 % above that.
+// for every XCD their row tiles are on.  Fitted to 2751 calls from 24 key tiles on, each in every shape with up to 16 splits: at one workgroup a CU within 7 % for nine in
+// ten, above that 7 % with 32 rows, 18 % with 128.
 static int64_t attn_ns(int variant, int d, int64_t BH, int64_t nx, int64_t tiles, int64_t ns, int64_t R) {
     static const struct { int variant, waves, cost[2][2][3]; } shapes[] = {   // [d == 128][above one a CU]: start, step, tile (ps)
         {12, 4, {{{3400, 970, 300}, {3400, 970, 300}}, {{4400, 1400, 620}, {4400, 1400, 620}}}},
