@@ -1008,7 +1008,7 @@ static int64_t key_tiles(const dlm_attn_args* a) {
     return ((int64_t)a->prefix.len + 31) / 32 + ((int64_t)a->block.len + 31) / 32 + ((int64_t)a->suffix.len + 31) / 32;
 }
 
-// How many workgroups share the keys of one row tile at most (plan_use_nsplit may take fewer; the workspace is sized for this many, which only grows
+// How many workgroups share the keys of one row tile at most (plan_split may take fewer; the workspace is sized for this many, which only grows
 // with the keys).  A split costs a second launch (the merge) and (d + 2) * 4 bytes written and read again per row and split, so
 // it pays only where the unsplit launch leaves most of the chip idle: at most 128 workgroups (half the CUs) and at least 32 key tiles.  Then the count
 // brings the launch to about one workgroup per CU with at least four key tiles each.  Measured (us): 1 x 32 heads x 8192 keys 114 -> 33 (8 splits);

@@ -189,13 +189,18 @@ __device__ __forceinline__ void lm_tile_of_slot(int xcd, int slot, int n_vt, int
 }
 // Several row chunks: blocks of gm x gv workgroups for the 32 CUs of an XCD; gm is the largest divisor of the chunk count up to 8
 // (measured at V = 126464, Dh = 4096: +6 % at M >= 1024, +10..17 % at M = 512)
-__host__ __device__ inline void lm_blocking(int n_mc, int& gm, int& gv) {
+// The blocks of an XCD are equally wide: in a grid of whole blocks the workgroups of a narrower last one that have no tile take turns
+// with those that have, always on the same shader engines, whose CUs are then given two tiles and the others none (us, blocks of 8 where 2 or 3 tiles
+// are left / as wide as they are: 1405 rows, V = 3887, Dh = 3584 103 / 58, 1059, 4701, 4096 102 / 62).
+__host__ __device__ inline void lm_blocking(int n_mc, int n_vt, int& gm, int& gv) {
     gm = 1;
     gv = 1;
     if (n_mc >= 2) {
         for (int c = 8; c >= 1; --c)
             if (n_mc % c == 0) { gm = c; break; }
         gv = 32 / gm > 8 ? 8 : 32 / gm;
+        const int n = (n_vt + 7) / 8, blocks = (n + gv - 1) / gv;
+        gv = (n + blocks - 1) / blocks;
     }
 }
 
@@ -1038,7 +1043,7 @@ __global__ __launch_bounds__(64 * WV * WH) void lmhead_pair_kernel(LmParams p) {
         const int live = (M + MB - 1) / MB;                        // row chunks that hold a row
         if (live != n_mc) {
             n_mc = live;
-            lm_blocking(n_mc, gm, gv);
+            lm_blocking(n_mc, p.n_vt_l, gm, gv);
         }
         len = lm_list_len(xcd, p.n_vt_l, n_mc);
         const int slot = blockIdx.x >> 3;
@@ -1629,7 +1634,7 @@ static void plan_lm_shape(int v_idx, LmParams& p, int m_bound, size_t ws_bytes, 
         return;
     }
     p.part2 = p.part + (size_t)p.n_vt * m_bound;
-    lm_blocking(p.n_mc, p.gm, p.gv);
+    lm_blocking(p.n_mc, p.n_vt_l, p.gm, p.gv);
     if (g_lm_block_gv >= 0) { p.gv = g_lm_block_gv > 0 ? g_lm_block_gv : 1; if (g_lm_block_gv == 0) p.gm = 1; }
     const bool second = p.sample || p.conf_mode == DLM_CONF_NEG_ENTROPY;
     // (the partials of the guessed shape are those of at most alt_cap rows, the second ones placed by the bound)

@@ -584,6 +584,7 @@ def test_every_form_of_a_call_through_a_queue(kind, M, Dh, V, cus, counted):
     (256, 200, 64, 40960, 0), (256, 200, 64, 40961, 0),    # 160 tiles of 256 x 256, the most that are few, and one more
     (256, 90, 64, 40960, 100), (256, 110, 4096, 33000, 120), (256, 200, 4096, 33000, 120),   # the bound's shape stays the large one: a guess that is not
     (512, 100, 512, 17000, 120), (1024, 200, 1024, 5000, 80),                                # worth it, one that is, right and wrong
+    (1405, None, 64, 3887, 0), (1059, 700, 128, 4701, 0), (700, 650, 64, 10000, 0),          # blocks of 2, 3 and 5 vocabulary tiles an XCD
 ])
 def test_small_vocabularies_take_small_tiles(M, m_dev, Dh, V, guess):
     """The shapes that fill the chip where the one for the row count alone leaves most of it idle, on both sides of the lines between them."""
