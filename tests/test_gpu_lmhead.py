@@ -635,7 +635,8 @@ def test_a_right_guess_runs_the_shape_of_its_own_rows(M, expected, counted, V, D
     assert not outs[0][0][:counted].isnan().any() and outs[0][0][counted:].isnan().all()
 
 
-@pytest.mark.parametrize("M,Dh,V,shape", [(257, 64, 300, 0), (300, 448, 20000, 3), (512, 256, 4096, 29), (700, 192, 3000, 25), (4096, 128, 2048, 3)])
+@pytest.mark.parametrize("M,Dh,V,shape", [(257, 64, 300, 0), (300, 448, 20000, 3), (512, 256, 4096, 29), (700, 192, 3000, 25), (4096, 128, 2048, 3),
+                                          (1503, 64, 5318, 20), (372, 64, 2365, 29), (716, 64, 2383, 25)])   # 36 of a smaller tile on an XCD
 def test_small_tiles_whatever_the_hidden_size(M, Dh, V, shape):
     """More than 256 rows of fewer than 512 elements: the shape that fills the chip, bit for bit as by name, and the oracle's values."""
     h, w = rnd(2000 + M, (M, Dh)), rnd(2001 + V, (V, Dh), Dh ** -0.25)
