@@ -1523,13 +1523,13 @@ static int64_t lm_fullest_xcd(int v, int M, int V) {
 // The shape for M rows of V tokens.  The one for M alone is made to read W once; with a small vocabulary its few large tiles leave most
 // CUs idle, and a CU brings in no more than 60 - 70 GB/s however much it has in flight.  So where it gives at most five
 // eighths as many workgroups as there are CUs (160 of 256), the smallest tile is taken of which there is at most one a CU: more CUs
-// share the load, and W and H, read more than once, come from L2.  No XCD may hold more than one for each of its CUs (28 of the expected rows where the others' row
-// chunks stand empty between them): V = 5318, Dh = 4096, 1503 rows, 252 tiles but 36 on an XCD, ring / 256 x 128 91 / 127; 2365, 4096, 372 rows, 36 of 128 x
-// 32, 128 x 64 / 128 x 32 31 / 38; 10634, 2048, 578 of 681 expected, 30 on an XCD 51 / 60; 12575, 2048, 509 of 599, 28, sampled 75 / 48.  Over 1765 calls without a guess (V 300 .. 157184, Dh 64 .. 4096, 16 .. 4096 rows)
-// the 847 that take another shape for it need 0.56 of the time in the geometric mean and 0.93 at most.  Us a call, M alone / now: V = 2048,
-// Dh = 256, 64 rows 10.4 / 8.1; V = 8000, Dh = 4096, 96 rows 63 / 27, 256 rows 105 / 33; V = 2048, Dh = 4096, 1024 rows 84 / 38; V = 32000,
-// Dh = 4096, 128 rows 71 / 56; V = 4096, Dh = 256, 512 rows 21 / 10.  With 161 - 256 workgroups smaller tiles lose (V = 50000, Dh = 4096, 256 rows
-// 127 / 157 and more).
+// share the load, and W and H, read more than once, come from L2.  No XCD may hold more than one for each of its CUs (28 of the expected
+// rows where the others' row chunks stand empty between them): V = 5318, Dh = 4096, 1503 rows, 252 tiles but 36 on an XCD, ring / 256 x 128 91 / 127;
+// 2365, 4096, 372 rows, 36 of 128 x 32, 128 x 64 / 128 x 32 31 / 38; 10634, 2048, 578 of 681 expected, 30 on an XCD 51 / 60; 12575, 2048, 509 of 599,
+// 28, sampled 75 / 48.  Over 1765 calls without a guess (V 300 .. 157184, Dh 64 .. 4096, 16 .. 4096 rows) the 847 that took another shape for it needed
+// 0.56 of the time in the geometric mean and 0.93 at most.  Us a call, M alone / now: V = 2048, Dh = 256, 64 rows 10.4 / 8.1; V = 8000,
+// Dh = 4096, 96 rows 63 / 27, 256 rows 105 / 33; V = 2048, Dh = 4096, 1024 rows 84 / 38; V = 32000, Dh = 4096, 128 rows 71 / 56; V = 4096,
+// Dh = 256, 512 rows 21 / 10.  With 161 - 256 workgroups smaller tiles lose (V = 50000, Dh = 4096, 256 rows 127 / 157 and more).
 static bool lm_few(int M, int V, int cus) {
     return g_lm_variant < 0 && 8 * lm_tiles(plan_rows(M), M, V) <= 5 * (int64_t)cus;
 }
@@ -1552,9 +1552,10 @@ static int plan_lmhead(int M, int V, int cus, int expected) {
 // ring, which takes 18 us for the shortest walk (Dh = 256, bound 512, 128 expected, V = 20000: without / with 21 / 15): yes.  Where it has few: if a
 // CU brings in at least 256 KB less (at some 100 GB/s); tiles that do not all fit at once count half as much again, as W is then what all wait
 // for; and not only for a narrower tile of as many workgroups, as rows past the count, all one and the same, cost little, and W of one row
-// chunk is fetched past the caches.  Calls that sample count the noise of a large tile (0.4 ns a logit): V = 5609, Dh = 256, bound 764, 191 expected 22.6 / 14.4.  Us, without / with, Dh = 4096: bound 1024, 81 expected, V = 10000 82 / 33; 512, 128, 16000 59 / 35; 256, 128,
-// 40000 87 / 77; not taken: 128, 32, 40000 61 / 71; 256, 20, 16000 30 / 35; Dh = 256: 128, 32, 16000 9.1 / 11.3.  Over 298 calls with few tiles (V 2048 ..
-// 40000, Dh 256 .. 4096, bound 40 .. 1024) within 0.3 % of the faster side in the geometric mean.
+// chunk is fetched past the caches.  Calls that sample count the noise of a large tile (0.4 ns a logit): V = 5609, Dh = 256, bound 764, 191 expected
+// 22.6 / 14.4.  Us, without / with, Dh = 4096: bound 1024, 81 expected, V = 10000 82 / 33; 512, 128, 16000 59 / 35; 256, 128, 40000 87 / 77; not taken:
+// 128, 32, 40000 61 / 71; 256, 20, 16000 30 / 35; Dh = 256: 128, 32, 16000 9.1 / 11.3.  Over 298 calls with few tiles (V 2048 .. 40000, Dh 256 .. 4096,
+// bound 40 .. 1024) within 0.3 % of the faster side in the geometric mean.
 static int64_t lm_load(int v, int M, int V, int cus) {
     const int64_t rounds = (lm_tiles(v, M, V) + cus - 1) / cus, rows = g_lm_variants[v].tv + g_lm_variants[v].mb;
     return rounds <= 1 ? rows : 3 * rounds * rows / 2;
